@@ -572,6 +572,16 @@ static int lut_ws_reserve(pq_ctx *ctx, size_t bytes) {
     return PQ_OK;
 }
 
+bool lut_ws_try(pq_ctx *ctx, size_t bytes) {
+    if (bytes <= ctx->lut_ws_bytes) return true;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone && lut_ws_reserve(ctx, bytes) == PQ_OK;
+}
+
 // Launch of the 128 x 128 form: two blocks per compute unit (a multiple of 8 blocks, one share per die).
 // Sub-vectors of 64 dimensions and more take the pass that converts the operands first, if every
 // operand row serves 8 tiles and more (the pass costs about as much as one of them) and the copies

@@ -46,6 +46,9 @@ int fail(pq_ctx *ctx, int code, const char *fmt, ...);
 int hip_fail(pq_ctx *ctx, hipError_t e, const char *what);
 // Make the workspace at least `bytes` large; returns PQ_OK or an error already recorded.
 int ws_reserve(pq_ctx *ctx, size_t bytes);
+// Make the context's buffer for converted operands (lut_ws) at least `bytes` large; false if that is not possible now
+// (out of memory, or the stream is being captured and the buffer would have to grow), for callers with another way.
+bool lut_ws_try(pq_ctx *ctx, size_t bytes);
 
 #define PQ_HIP(ctx, call)                                                \
     do {                                                                 \

@@ -509,6 +509,35 @@ def test_encode_ties_and_exact_hits(ctx):
     assert host(ctx.pq_encode(dev(x[:0]), dev(cb))).shape == (0, 8)
 
 
+@pytest.mark.parametrize("ds,m,k,n", [(1, 8, 256, 1), (2, 8, 256, 65), (7, 4, 255, 511), (8, 16, 16, 513), (15, 6, 16, 1000),
+                                      (16, 8, 256, 263_001), (17, 3, 33, 130), (30, 32, 16, 3001), (32, 2, 256, 64), (33, 5, 241, 700),
+                                      (60, 16, 256, 2049), (64, 2, 17, 129), (65, 2, 40, 200)])
+def test_encode_edges_of_tiles(ctx, ds, m, k, n):
+    """Ragged numbers of vectors, dimensions and centroids, every alignment of a sub-vector, and vectors that the ranking
+    on 16-bit halves cannot settle: not finite, far larger or smaller than the codebook, exactly between two centroids."""
+    r = np.random.default_rng(ds * 100 + k)
+    fmt = orc.CODES_U4_PACKED if k == 16 else orc.CODES_U8
+    for scale in (1.0, 1e-30, 1e25):
+        cb = ((r.random((m, k, ds)) - 0.3) * scale).astype(np.float32)
+        x = ((r.random((n, m, ds)) - 0.3) * scale).astype(np.float32)
+        x[n // 3] = np.nan
+        x[n // 2, 0, 0] = np.inf
+        x[n // 4] *= np.float32(1e5)
+        x[n // 5] *= np.float32(1e-9)
+        x[n // 6] = (cb[:, 0] + cb[:, k - 1]) / 2
+        if k > 2:
+            cb[:, k // 2] = cb[:, 1]
+        x = x.reshape(n, m * ds)
+        with np.errstate(invalid="ignore", over="ignore"):
+            ref = orc.pq_encode(x, cb)
+        ref = orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref
+        for shift in (0, 1):   # vectors that start on 16 bytes or only on 4
+            buf = torch.empty(n * m * ds + 4, device="cuda")
+            xd = buf[shift:shift + n * m * ds].view(n, m * ds)
+            xd.copy_(torch.from_numpy(x))
+            assert np.array_equal(host(ctx.pq_encode(xd, dev(cb), fmt)), ref), (scale, shift)
+
+
 # ----------------------------------------------------------------------------- full size (bench configuration)
 FULL_N, FULL_NQ = 25_000_000, 1000
 SAMPLE_Q = [0, 1, 7, 8, 123, 500, 640, 777, 998, 999]
