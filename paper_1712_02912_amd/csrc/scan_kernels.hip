@@ -462,6 +462,12 @@ int launch_scan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const void
         return w16::launch_scan_tuned(ctx, m == 8 ? 0 : 1, codes, n, luts, nq, topk, out_val, out_ids);
     if (!general && cf == PQ_CODES_U4_PACKED && lf == PQ_LUT_U8 && k == 16 && m == 16)
         return w16::launch_scan_tuned(ctx, 2, codes, n, luts, nq, topk, out_val, out_ids);
+    // 32 tables: 1 M codes, 100 queries, top-1000: scan 10.5 -> 0.26 ms, two-pass call 10.8 -> 0.54; with the fixed scratch of the call that allocates nothing,
+    // requests that do not fit there go on to the general kernel, which may need less
+    if (!general && cf == PQ_CODES_U4_PACKED && lf == PQ_LUT_U8 && k == 16 && m == 32) {
+        const int rc = w16::launch_scan_tuned(ctx, 7, codes, n, luts, nq, topk, out_val, out_ids);
+        if (!(rc == PQ_ENOMEM && ctx->ws_fixed)) return rc;
+    }
     if ((int64_t)m * k <= 8192)
         return run_generic(ctx, codes, n, cf, luts, lf == PQ_LUT_U8, nq, m, k, topk, out_val, out_ids);
     return fail(ctx, PQ_EUNSUPPORTED, "scan: no kernel for m=%d k=%d code_fmt=%d lut_fmt=%d", m, k, cf, lf);

@@ -3,6 +3,7 @@
 //   F32_M16 : 16 float tables of 256 entries, 16-byte codes, 4 queries per block
 //   U4_M16  : 16 tables of 16 bytes merged in pairs to 8 tables of 256 16-bit entries,
 //             8-byte packed codes, 8 queries per block
+//   U4_M32  : 32 tables of 16 bytes merged in pairs to 16, 16-byte packed codes, 8 queries per block
 //
 // LDS layout (64 KB).  Row b (256 bytes) holds, for code-byte value b, 16 slots of 16 bytes.
 // A slot is the entry of one table for all queries of the block (4 floats, or 8 x u16).
@@ -61,11 +62,12 @@ constexpr int RING_PERIOD = 256;  // and, if anything is parked, every this many
 
 // RING: ring entries per wave
 // WIDE16: room for a second set of tables (16-bit entries of 16 queries, 64 KB) beside the scan's own
-template <int RING, bool WIDE16 = false>
+// STAGE: bytes of one query's 8-bit tables
+template <int RING, bool WIDE16 = false, int STAGE = 256>
 struct __align__(16) TunedSmemT {
     uint4 lut[4096];
     uint4 lut16[WIDE16 ? 4096 : 1];   // entry (byte b, table j): two 16-byte halves at (b * 8 + j) * 2
-    uint8_t qstage[WIDE16 ? 16 : 8][256];
+    uint8_t qstage[WIDE16 ? 16 : 8][STAGE];
     // Per wave: lanes that found a candidate park the position of their 16 code bytes here; the
     // positions are turned into list inserts in batches (scan_flush), which recomputes the values.
     uint32_t ring[TUNED_WAVES][RING];
@@ -141,7 +143,10 @@ __device__ __forceinline__ void hist_window_flush(LDS_PTR(SM) sm, int q) {
 
 // KIND_F32P_M8 / _M16: the 8 x 256 and 16 x 256 float scans with pruning by 16-bit lower bounds
 // (see scan_flush_pruned)
-enum { KIND_F32_M8 = 0, KIND_F32_M16 = 1, KIND_U4_M16 = 2, KIND_F32P_M8 = 3, KIND_F32P_M16 = 4, KIND_F32Q_M8 = 5, KIND_U4Q_M16 = 6 };
+enum { KIND_F32_M8 = 0, KIND_F32_M16 = 1, KIND_U4_M16 = 2, KIND_F32P_M8 = 3, KIND_F32P_M16 = 4, KIND_F32Q_M8 = 5, KIND_U4Q_M16 = 6, KIND_U4_M32 = 7 };
+// 32 8-bit entries add up to at most 8160: the last bin of an integer histogram (4095) then holds every sum from there on,
+// and a bound that falls into it is none.
+constexpr int exact_bins(int tables) { return tables == 16 ? HIST_BINS - 1 : HIST_BINS; }   // (tables after merging: 8 or 16)
 constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bound of a float scan of many query groups
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
@@ -284,9 +289,9 @@ __device__ __noinline__ int scan_compact(LDS_PTR(SM) sm, uint64_t *buf, int cnt,
 // is cut to its k smallest keys.
 template <class SM, int KIND, int E>
 __device__ __noinline__ int scan_flush(LDS_PTR(SM) sm, uint64_t *wave_buf, int n) {
-    constexpr bool IS_U4 = KIND == KIND_U4_M16;
+    constexpr bool IS_U4 = KIND == KIND_U4_M16 || KIND == KIND_U4_M32;
     constexpr int QB = IS_U4 ? 8 : 4;
-    constexpr int NT = KIND == KIND_F32_M16 ? 16 : 8;
+    constexpr int NT = KIND == KIND_F32_M16 || KIND == KIND_U4_M32 ? 16 : 8;
     constexpr int CPL = 16 / NT;
     constexpr int CAP = 64 * E;
     static_assert(CAP - 64 * CPL >= 128 && (E <= 8 || CAP - 64 * CPL >= 1024), "a compacted list must leave room for one batch");
@@ -730,7 +735,7 @@ __device__ __noinline__ int scan_flush_u4q(LDS_PTR(SM) sm, uint64_t *wave_buf, i
 // other wave is already doing it, recompute the bound from the histogram.
 constexpr uint32_t REFRESH_MIN_NEW = 16;
 
-template <class SM, bool IS_U4>
+template <class SM, bool IS_U4, int BINS = HIST_BINS>
 __device__ __noinline__ void scan_refresh(LDS_PTR(SM) sm, int q) {
     // the four device words of the query are independent of one another: one round trip
     const unsigned long long gk = __hip_atomic_load(sm->tau_key_global[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -776,7 +781,7 @@ __device__ __noinline__ void scan_refresh(LDS_PTR(SM) sm, int q) {
     }
     if (__builtin_amdgcn_readfirstlane(won) == 0u) return;
     const int bin = hist_threshold(sm->hist[q], sm->topk);
-    if (bin < HIST_BINS) {
+    if (bin < BINS) {
         // every value counted in bins <= bin is at or below this edge
         const uint32_t edge = IS_U4 ? (uint32_t)bin : ref - ((uint32_t)(HIST_BINS - 1 - bin) << HIST_SHIFT);
         if (lane_id() == 0) publish_bound(sm, q, edge);
@@ -912,13 +917,13 @@ enum { TICK_SETUP = 0, TICK_LOOP, TICK_FLUSH, TICK_REFRESH, TICK_EMIT, TICK_OVER
 template <int KIND, int E, int KPAD, int DEPTH>
 __global__ __launch_bounds__(TUNED_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void scan_tuned_kernel(TunedArgs a) {
-    constexpr bool IS_U4 = KIND == KIND_U4_M16 || KIND == KIND_U4Q_M16;   // values are integer sums
+    constexpr bool IS_U4 = KIND == KIND_U4_M16 || KIND == KIND_U4Q_M16 || KIND == KIND_U4_M32;   // values are integer sums
     constexpr bool U4Q = KIND == KIND_U4Q_M16;            // integer sums, scan loop on 8-bit lower bounds, 16 queries
     constexpr bool Q8 = KIND == KIND_F32Q_M8 || U4Q;      // scan loop on 8-bit lower bounds, 16 queries per pass
     constexpr bool PRUNED = KIND == KIND_F32P_M8 || KIND == KIND_F32P_M16 || KIND == KIND_F32Q_M8;   // float values, scan loop on integer lower bounds
     constexpr bool PACKED = IS_U4 || PRUNED;              // scan loop adds packed entries (16-bit: 8 queries, 8-bit: 16)
     constexpr int QB = Q8 ? 16 : PACKED ? 8 : 4;
-    constexpr int NT = KIND == KIND_F32_M16 || KIND == KIND_F32P_M16 ? 16 : 8;   // tables = lookups per code
+    constexpr int NT = KIND == KIND_F32_M16 || KIND == KIND_F32P_M16 || KIND == KIND_U4_M32 ? 16 : 8;   // tables = lookups per code
     constexpr int CB = NT;                                // code bytes (8 or 16)
     constexpr int CPL = 16 / CB;                          // codes per lane per 16-byte load
     constexpr int SUB = 64 * CPL;                         // codes per wave sub-tile (one load per lane)
@@ -928,7 +933,7 @@ void scan_tuned_kernel(TunedArgs a) {
     constexpr int CAP = 64 * E;
     typedef typename std::conditional<IS_U4, U32Val, F32Val>::type V;
     // ring: two tiles fit behind a ring that was not flushed
-    typedef TunedSmemT<RING_FLUSH + 64 * DEPTH, Q8> SM;   // a group of sub-tiles fits behind a ring that was not flushed
+    typedef TunedSmemT<RING_FLUSH + 64 * DEPTH, Q8, KIND == KIND_U4_M32 ? 512 : 256> SM;   // a group of sub-tiles fits behind a ring that was not flushed
     static_assert(TUNED_WAVES != 8 || sizeof(SM) <= 80 * 1024, "two blocks of 8 waves share the 160 KB of a CU");
     __shared__ SM sm;
     LDS_PTR(SM) smp = (LDS_PTR(SM))&sm;
@@ -1001,7 +1006,7 @@ void scan_tuned_kernel(TunedArgs a) {
                 const int gq = group * QB + s;
                 if (gq < a.nq) {
                     qid = gq;
-                    lut = IS_U4 ? (const void *)((const uint8_t *)a.luts + (size_t)gq * 256)
+                    lut = IS_U4 ? (const void *)((const uint8_t *)a.luts + (size_t)gq * (NT * 32))
                                 : (const void *)((const float *)a.luts + (size_t)gq * (NT * 256));
                     if constexpr (PRUNED) { sm.prune_off[s] = a.prune_off[gq]; sm.prune_scale[s] = a.prune_scale[gq]; }
                     if constexpr (Q8 && PRUNED) sm.prune_scale16[s] = a.prune_scale16[gq];
@@ -1163,26 +1168,30 @@ void scan_tuned_kernel(TunedArgs a) {
                 else sm.lut[byte * 16 + j] = pk;
             }
         } else {
-            for (int e = threadIdx.x; e < QB * 256; e += TUNED_THREADS) {
-                const int q = e >> 8;
+            for (int e = threadIdx.x; e < QB * (NT * 32); e += TUNED_THREADS) {
+                const int q = e / (NT * 32);
                 const uint8_t *ql = (const uint8_t *)sm.slot_lut[q];
-                sm.qstage[q][e & 255] = ql ? ql[e & 255] : 0;
+                sm.qstage[q][e % (NT * 32)] = ql ? ql[e % (NT * 32)] : 0;
             }
             __syncthreads();
             // pair-merged tables: T[r][byte] = Q[2r][byte & 15] + Q[2r+1][byte >> 4]
-            for (int e = threadIdx.x; e < 8 * 256; e += TUNED_THREADS) {
-                const int r = e & 7, byte = e >> 3;   // (table fastest: a wave's LDS accesses spread over the bank groups)
+            for (int e = threadIdx.x; e < NT * 256; e += TUNED_THREADS) {
+                const int r = e % NT, byte = e / NT;   // (table fastest: a wave's LDS accesses spread over the bank groups)
                 uint32_t s[8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
                     s[q] = sm.slot_lut[q] ? (uint32_t)sm.qstage[q][(2 * r) * 16 + (byte & 15)] +
                                                 (uint32_t)sm.qstage[q][(2 * r + 1) * 16 + (byte >> 4)]
-                                          : 0x0fffu;   // empty slots never qualify
+                                          : 32767u / NT;   // empty slots never qualify
                 }
                 const uint4 pk = make_uint4(s[0] | (s[1] << 16), s[2] | (s[3] << 16), s[4] | (s[5] << 16),
                                             s[6] | (s[7] << 16));
-                sm.lut[byte * 16 + 2 * r + (byte & 1)] = pk;
-                sm.lut[byte * 16 + 2 * r + 1 - (byte & 1)] = pk;
+                if constexpr (NT == 8) {
+                    sm.lut[byte * 16 + 2 * r + (byte & 1)] = pk;
+                    sm.lut[byte * 16 + 2 * r + 1 - (byte & 1)] = pk;
+                } else {
+                    sm.lut[byte * 16 + r] = pk;
+                }
             }
         }
         __syncthreads();
@@ -1363,7 +1372,7 @@ void scan_tuned_kernel(TunedArgs a) {
             }
             // a wave that keeps finding candidates asks for a new bound without waiting for its turn
             if (refresh_due() || (refresher && pressure >= KPAD / 2)) {
-                scan_refresh<SM, IS_U4>(smp, my_q);
+                scan_refresh<SM, IS_U4, IS_U4 ? exact_bins(NT) : HIST_BINS>(smp, my_q);
                 pressure = 0;
                 PQ_TICK(TICK_REFRESH);
             }
@@ -1508,19 +1517,21 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
 // entries of the block's queries for one code byte (both of its components added) are one 8-byte LDS
 // read, and their sums add up as four 16-bit fields of a 64-bit word.
 constexpr int SEED_QPB = 4;
+template <int NT>   // code bytes = pair-merged tables, 8 or 16
 __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict__ codes, int cnt,
                                                        const uint8_t *__restrict__ qluts, int kq, int nq, unsigned long long *tau_key) {
     static_assert(HIST_BINS == 4096, "sums of 16 bytes index the bins");
+    constexpr uint32_t BINS = (uint32_t)exact_bins(NT);   // cuts from there on are none
     __shared__ __align__(16) uint32_t hist[SEED_QPB][HIST_BINS];
-    __shared__ uint8_t tab[SEED_QPB][256];
-    __shared__ uint2 pair[8][256];
+    __shared__ uint8_t tab[SEED_QPB][NT * 32];
+    __shared__ uint2 pair[NT][256];
     __shared__ uint32_t cut_s[SEED_QPB];
     const int q0 = blockIdx.x * SEED_QPB, tid = threadIdx.x;
     const int myq = tid >> 8, sub = tid & 255;   // 256 threads per query where the queries are handled apart
-    tab[myq][sub] = q0 + myq < nq ? qluts[(size_t)(q0 + myq) * 256 + sub] : (uint8_t)255;
+    for (int i = sub; i < NT * 32; i += 256) tab[myq][i] = q0 + myq < nq ? qluts[(size_t)(q0 + myq) * (NT * 32) + i] : (uint8_t)255;
     for (int i = tid; i < SEED_QPB * HIST_BINS; i += 1024) (&hist[0][0])[i] = 0;
     __syncthreads();
-    for (int e = tid; e < 8 * 256; e += 1024) {
+    for (int e = tid; e < NT * 256; e += 1024) {
         const int r = e >> 8, byte = e & 255;
         uint32_t t[SEED_QPB];
 #pragma unroll
@@ -1537,15 +1548,30 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
         }
         __syncthreads();
     };
-    auto load_code = [&](int i) { return *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8); };
-    auto code_sums = [&](const uint2 c) -> uint64_t {   // four sums of at most 16 * 255 < 4096
+    struct Code { uint32_t w[NT / 4]; };
+    auto load_code = [&](int i) {
+        Code c;
+        if constexpr (NT == 8) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8);
+            c.w[0] = v.x; c.w[1] = v.y;
+        } else {
+            const uint4 v = *reinterpret_cast<const uint4 *>(codes + (size_t)i * 16);
+            c.w[0] = v.x; c.w[1] = v.y; c.w[2] = v.z; c.w[3] = v.w;
+        }
+        return c;
+    };
+    auto code_sums = [&](const Code c) -> uint64_t {   // four sums of at most 2 * NT * 255 < 2^16
         uint64_t acc = 0;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const uint2 v = pair[r][((r < 4 ? c.x : c.y) >> (8 * (r & 3))) & 255u];
+        for (int r = 0; r < NT; ++r) {
+            const uint2 v = pair[r][(c.w[r >> 2] >> (8 * (r & 3))) & 255u];
             acc += ((uint64_t)v.y << 32) | v.x;
         }
         return acc;
+    };
+    auto bin_of = [&](uint64_t acc, int qq) -> uint32_t {   // (the last bin also takes the sums beyond it)
+        const uint32_t sum = (uint32_t)(acc >> (16 * qq)) & 0xffffu;
+        return sum < (uint32_t)HIST_BINS ? sum : (uint32_t)HIST_BINS - 1u;
     };
     // The first 4096 codes are all counted; their kq-th sum bounds that of any superset, so of the other
     // codes only the sums up to it need counting.
@@ -1555,14 +1581,14 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
     auto for_codes = [&](int begin, int end, auto &&f) {
         int i = begin + tid;
         for (; i + 3 * 1024 < end; i += 4 * 1024) {
-            const uint2 c0 = load_code(i), c1 = load_code(i + 1024), c2 = load_code(i + 2048), c3 = load_code(i + 3072);
+            const Code c0 = load_code(i), c1 = load_code(i + 1024), c2 = load_code(i + 2048), c3 = load_code(i + 3072);
             f(i, code_sums(c0)); f(i + 1024, code_sums(c1)); f(i + 2048, code_sums(c2)); f(i + 3072, code_sums(c3));
         }
         for (; i < end; i += 1024) f(i, code_sums(load_code(i)));
     };
     for_codes(0, head, [&](int, uint64_t acc) {
 #pragma unroll
-        for (int qq = 0; qq < SEED_QPB; ++qq) atomicAdd(&hist[qq][(uint32_t)(acc >> (16 * qq)) & 0xffffu], 1u);
+        for (int qq = 0; qq < SEED_QPB; ++qq) atomicAdd(&hist[qq][bin_of(acc, qq)], 1u);
     });
     if (cnt > head) {
         kth_sums();
@@ -1572,13 +1598,13 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
         for_codes(head, cnt, [&](int, uint64_t acc) {
 #pragma unroll
             for (int qq = 0; qq < SEED_QPB; ++qq) {
-                const uint32_t sum = (uint32_t)(acc >> (16 * qq)) & 0xffffu;
-                if (sum <= cut[qq]) atomicAdd(&hist[qq][sum], 1u);
+                const uint32_t bin = bin_of(acc, qq);
+                if (bin <= cut[qq]) atomicAdd(&hist[qq][bin], 1u);
             }
         });
     }
     kth_sums();
-    if (sub == 0 && q0 + myq < nq && cut_s[myq] < 4096u) tau_key[q0 + myq] = ((unsigned long long)cut_s[myq] << 32) | 0xffffffffull;
+    if (sub == 0 && q0 + myq < nq && cut_s[myq] < BINS) tau_key[q0 + myq] = ((unsigned long long)cut_s[myq] << 32) | 0xffffffffull;
     // Integer sums tie: far more than kq codes can share the sum T found above (8-bit tables are coarse where the
     // codes crowd), and a bound on the sum alone lets all of them through.  Rows decide among ties, so the bound is
     // handed on as a whole key as well: with r = kq - count(sum < T), the row at the end of the bucket of 1024 sample
@@ -1593,12 +1619,12 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
     if (sub < 64) {   // the first wave of the query's threads: codes below the cut, codes at the cut
         const uint32_t cut = cut_s[myq];
         uint32_t below = 0;
-        if (cut < 4096u) for (uint32_t b = sub; b < cut; b += 64) below += hist[myq][b];
+        if (cut < BINS) for (uint32_t b = sub; b < cut; b += 64) below += hist[myq][b];
         for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o);
         if (sub == 0) {
             uint32_t r = 0;
             // (worth a pass over the sample only if many codes tie at the cut)
-            if (q0 + myq < nq && cut < 4096u && below < (uint32_t)kq && below + hist[myq][cut] > (uint32_t)kq + 256u &&
+            if (q0 + myq < nq && cut < BINS && below < (uint32_t)kq && below + hist[myq][cut] > (uint32_t)kq + 256u &&
                 (cnt + 1023) / 1024 <= TIE_BUCKETS)
                 r = (uint32_t)kq - below;
             need_s[myq] = r;
@@ -1633,33 +1659,40 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
 // The same over more codes than one block can look at (few query groups, large database):
 // block (s, q) counts the sums of slice s of the first `cnt` codes into the query's bins in device
 // memory, u4_seed_pick_kernel reads the bound off the counts.
+template <int NT>   // code bytes, 8 or 16
 __global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__restrict__ codes, int64_t cnt,
                                                             const uint8_t *__restrict__ qluts, uint32_t *seed_hist) {
     __shared__ uint32_t hist[4096];
-    __shared__ uint8_t tab[256];
+    __shared__ uint8_t tab[NT * 32];
     const int q = blockIdx.y, tid = threadIdx.x;
-    if (tid < 256) tab[tid] = qluts[(size_t)q * 256 + tid];
+    if (tid < NT * 32) tab[tid] = qluts[(size_t)q * (NT * 32) + tid];
     for (int i = tid; i < 4096; i += 1024) hist[i] = 0;
     __syncthreads();
     const int64_t begin = (int64_t)blockIdx.x * (1 << 16);
     const int64_t end = begin + (1 << 16) < cnt ? begin + (1 << 16) : cnt;
     for (int64_t i0 = begin + tid; i0 < end; i0 += 4 * 1024) {
-        uint2 c[4];
+        uint32_t c[4][NT / 4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int64_t i = i0 + u * 1024;
-            c[u] = i < end ? *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8) : make_uint2(0, 0);
+            if constexpr (NT == 8) {
+                const uint2 v = i < end ? *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8) : make_uint2(0, 0);
+                c[u][0] = v.x; c[u][1] = v.y;
+            } else {
+                const uint4 v = i < end ? *reinterpret_cast<const uint4 *>(codes + (size_t)i * 16) : make_uint4(0, 0, 0, 0);
+                c[u][0] = v.x; c[u][1] = v.y; c[u][2] = v.z; c[u][3] = v.w;
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (i0 + u * 1024 >= end) break;
             uint32_t sum = 0;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const uint32_t byte = ((r < 4 ? c[u].x : c[u].y) >> (8 * (r & 3))) & 255u;
+            for (int r = 0; r < NT; ++r) {
+                const uint32_t byte = (c[u][r >> 2] >> (8 * (r & 3))) & 255u;
                 sum += (uint32_t)tab[(2 * r) * 16 + (byte & 15u)] + (uint32_t)tab[(2 * r + 1) * 16 + (byte >> 4)];
             }
-            atomicAdd(&hist[sum], 1u);   // sum <= 16 * 255 < 4096
+            atomicAdd(&hist[sum < 4096u ? sum : 4095u], 1u);   // (16 tables: sum <= 16 * 255 < 4096)
         }
     }
     __syncthreads();
@@ -1667,10 +1700,10 @@ __global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__res
         if (hist[i] != 0u) atomicAdd(&seed_hist[(size_t)q * 4096 + i], hist[i]);
 }
 
-__global__ __launch_bounds__(64) void u4_seed_pick_kernel(const uint32_t *__restrict__ seed_hist, int kq, unsigned long long *tau_key) {
+__global__ __launch_bounds__(64) void u4_seed_pick_kernel(const uint32_t *__restrict__ seed_hist, int kq, int bins, unsigned long long *tau_key) {
     const int q = blockIdx.x;
     const int b = hist_threshold(seed_hist + (size_t)q * 4096, kq);   // one wave; smallest sum with kq counted codes at or below it
-    if (threadIdx.x == 0 && b < HIST_BINS) tau_key[q] = ((unsigned long long)b << 32) | 0xffffffffull;
+    if (threadIdx.x == 0 && b < bins) tau_key[q] = ((unsigned long long)b << 32) | 0xffffffffull;
 }
 
 // Better first bound (every candidate the first bound lets through costs far more than a code the
@@ -2113,6 +2146,7 @@ static int launch_by_kind(pq_ctx *ctx, int kind, bool small, bool stream, const 
 #if !PQ_TUNED_ITEMS_ONLY
         case KIND_F32Q_M8: return launch_kind_sized<KIND_F32Q_M8>(ctx, small, stream, a, nblocks);
         case KIND_U4Q_M16: return launch_kind_sized<KIND_U4Q_M16>(ctx, small, stream, a, nblocks);
+        case KIND_U4_M32: return launch_kind_sized<KIND_U4_M32>(ctx, small, stream, a, nblocks);
 #endif
 #if PQ_TUNED_ITEMS_ONLY
         default: return fail(ctx, PQ_EUNSUPPORTED, "scan_items: kind %d", kind);
@@ -2127,8 +2161,9 @@ static void note_scan(pq_ctx *ctx, int kind, int qb, int passes, const unsigned 
     static const char *const names[] = {"F32_M8 (8x8 float, plain float adds, 4 queries per pass)", "F32_M16 (16x8 float, plain float adds, 4 queries per pass)",
                                         "U4_M16 (16x4 integer, exact 16-bit sums, 8 queries per pass)",
                                         "F32P_M8 (8x8 float on 16-bit lower bounds, 8 queries per pass)", "F32P_M16 (16x8 float on 16-bit lower bounds, 8 queries per pass)",
-                                        "F32Q_M8 (8x8 float on 8-bit lower bounds, 16 queries per pass)", "U4Q_M16 (16x4 integer on 8-bit lower bounds, 16 queries per pass)"};
-    snprintf(ctx->last_scan_name, sizeof(ctx->last_scan_name), "scan_tuned_kernel<%s>, blocks of %d waves", kind >= 0 && kind < 7 ? names[kind] : "?", TUNED_WAVES);
+                                        "F32Q_M8 (8x8 float on 8-bit lower bounds, 16 queries per pass)", "U4Q_M16 (16x4 integer on 8-bit lower bounds, 16 queries per pass)",
+                                        "U4_M32 (32x4 integer, exact 16-bit sums, 8 queries per pass)"};
+    snprintf(ctx->last_scan_name, sizeof(ctx->last_scan_name), "scan_tuned_kernel<%s>, blocks of %d waves", kind >= 0 && kind < 8 ? names[kind] : "?", TUNED_WAVES);
     ctx->last_scan_qpp = qb;
     ctx->last_scan_passes = passes;
     ctx->stat_parked = parked;
@@ -2137,7 +2172,7 @@ static void note_scan(pq_ctx *ctx, int kind, int qb, int passes, const unsigned 
 }
 
 static int qb_of_kind(int kind) {
-    return kind == KIND_F32Q_M8 || kind == KIND_U4Q_M16 ? 16 : (kind == KIND_U4_M16 || kind == KIND_F32P_M8 || kind == KIND_F32P_M16 ? 8 : 4);
+    return kind == KIND_F32Q_M8 || kind == KIND_U4Q_M16 ? 16 : (kind == KIND_U4_M16 || kind == KIND_U4_M32 || kind == KIND_F32P_M8 || kind == KIND_F32P_M16 ? 8 : 4);
 }
 
 // blocks that share a CU: one of 16 waves, two of 8
@@ -2194,7 +2229,7 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
 int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, const void *luts, int nq, int topk,
                       void *out_val, int64_t *out_ids) {
     int rc;
-    const bool is_u4 = kind == KIND_U4_M16;
+    const bool u4_m32 = kind == KIND_U4_M32, is_u4 = kind == KIND_U4_M16 || u4_m32;
     // The 8 x 256 float scan prunes with 16-bit lower bounds when the database is large enough to
     // pay for the preparation (a bound per query from the first PRUNE_INIT codes, then the tables).
     const bool prune = (kind == KIND_F32_M8 || kind == KIND_F32_M16) && n >= PRUNE_MIN_N && opt_int(ctx, PQ_OPT_SCAN_PRUNE, 1) != 0;
@@ -2208,10 +2243,10 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     if (prune) kind = q8 ? KIND_F32Q_M8 : (tables == 16 ? KIND_F32P_M16 : KIND_F32P_M8);
     // the integer scan likewise: with a first bound and enough queries, its loop runs on 8-bit lower bounds of
     // the integer sums, 16 queries per pass
-    const bool u4q = is_u4 && n >= PRUNE_MIN_N && many16;
+    const bool u4q = is_u4 && !u4_m32 && n >= PRUNE_MIN_N && many16;
     if (u4q) kind = KIND_U4Q_M16;
     const int qb = q8 || u4q ? 16 : (is_u4 || prune ? 8 : 4);
-    const int cb = kind == KIND_F32_M16 || kind == KIND_F32P_M16 ? 16 : 8;
+    const int cb = kind == KIND_F32_M16 || kind == KIND_F32P_M16 || u4_m32 ? 16 : 8;
     const int depth = !(q8 || u4q) && (nq + qb - 1) / qb < STREAM_GROUPS ? 8 : 2;
     const int tile = 64 * (16 / cb) * depth;   // codes per wave group (DEPTH sub-tiles)
     const bool small = topk <= 128;
@@ -2360,8 +2395,9 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         if (wide_seed_u4) {
             uint32_t *seed_hist = (uint32_t *)(ws + off_seedhist);
             const dim3 sgrid((unsigned)((seed_codes_f32 + SEED_SLICE - 1) / SEED_SLICE), (unsigned)nq);
-            u4_seed_hist_kernel<<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist);
-            u4_seed_pick_kernel<<<nq, 64, 0, ctx->stream>>>(seed_hist, topk, a.tau_key);
+            if (u4_m32) u4_seed_hist_kernel<16><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist);
+            else u4_seed_hist_kernel<8><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist);
+            u4_seed_pick_kernel<<<nq, 64, 0, ctx->stream>>>(seed_hist, topk, exact_bins(cb), a.tau_key);
         } else {
             // 256 codes per result wanted, between PRUNE_INIT and 262 144 (top-1000: 4.11 -> 3.94 ms per step; twice as many
             // cost the seed kernel more than they save the scan)
@@ -2373,7 +2409,9 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
                 if (seed_codes < by_queries && (int64_t)by_queries <= n / 16) seed_codes = by_queries;
             }
             if ((int64_t)seed_codes > n) seed_codes = (int)n;
-            u4_seed_kernel<<<(nq + SEED_QPB - 1) / SEED_QPB, 1024, 0, ctx->stream>>>(codes, seed_codes, (const uint8_t *)luts, topk, nq, a.tau_key);
+            const unsigned seed_blocks = (unsigned)((nq + SEED_QPB - 1) / SEED_QPB);
+            if (u4_m32) u4_seed_kernel<16><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, (const uint8_t *)luts, topk, nq, a.tau_key);
+            else u4_seed_kernel<8><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, (const uint8_t *)luts, topk, nq, a.tau_key);
         }
         PQ_HIP(ctx, hipGetLastError());
     }

@@ -756,6 +756,36 @@ def test_scan_16_queries_per_pass_first_round_of_short_items(ctx, opts):
         run_int_scan(ctx, codes, orc.CODES_U4_PACKED, quantized_like_tables(r, nq), topk)
 
 
+@pytest.mark.parametrize("n,nq,topk", [(1, 1, 1), (63, 3, 100), (4097, 9, 128), (65_535, 8, 129), (65_537, 11, 1000), (200_003, 260, 100),
+                                      (140_001, 70, 1024), (2_200_001, 2, 1000)])
+def test_scan_u4_32_tables(ctx, n, nq, topk):
+    """32 x 4 codes: tables like quantised distances (small sums), uniform bytes (sums around 4080, where the bins of the
+    bounds end), large entries (all sums beyond the bins), and ties far beyond k."""
+    r = np.random.default_rng(n + nq)
+    packed = r.integers(0, 256, (n, 16), dtype=np.uint8)
+    qluts = np.concatenate([quantized_like_tables(r, nq), quantized_like_tables(r, nq)], axis=1)
+    kinds = [lambda: r.integers(0, 256, (32, 16)), lambda: r.integers(200, 256, (32, 16)), lambda: np.full((32, 16), 255),
+             lambda: r.integers(0, 2, (32, 16))]
+    for q in range(1, nq, 2):
+        qluts[q] = kinds[(q // 2) % len(kinds)]()
+    run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
+
+
+def test_scan_u4_32_tables_copies_and_fixed_scratch(ctx):
+    """A hundred thousand copies of a query's best code (rows decide), and the call that allocates nothing."""
+    r = np.random.default_rng(5)
+    n, nq, topk = 150_003, 20, 100
+    packed = r.integers(0, 256, (n, 16), dtype=np.uint8)
+    qluts = np.concatenate([quantized_like_tables(r, nq), quantized_like_tables(r, nq)], axis=1)
+    best = qluts[0].argmin(axis=1)
+    packed[r.choice(n, 100_000, replace=False)] = (best[0::2] | (best[1::2] << 4)).astype(np.uint8)
+    for k in (topk, 1000):   # (1000: the tuned kernel's lists do not fit the fixed scratch, the general kernel's do)
+        run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, k)
+        s, i = ctx.pq_adc_scan_topk(dev(packed), orc.CODES_U4_PACKED, dev(qluts), k)
+        s2, i2 = ctx.pq_adc_scan_topk(dev(packed), orc.CODES_U4_PACKED, dev(qluts), k, noalloc=True)
+        assert torch.equal(s, s2) and torch.equal(i, i2)
+
+
 # ----------------------------------------------------------------------------- encoded data at full size
 ENC_UNIQUE = 400_000   # vectors encoded by the oracle; the 25 M rows are drawn from them (so every code has ~60 exact copies)
 
