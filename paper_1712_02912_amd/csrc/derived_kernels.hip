@@ -52,6 +52,7 @@ struct DqArgs {
     const uint64_t *cand_off;    // [nq + 1]
     uint32_t *cand_cnt;          // [nq]
     uint64_t *cand;              // keys (integer distance << 32 | row)
+    uint2 *cand_code;            // the codes at those rows (nullptr: not wanted)
 };
 
 struct __align__(16) DqSmem {
@@ -87,6 +88,32 @@ __device__ __forceinline__ int first_bin_reaching(Load load, uint32_t k, uint32_
     if (count_out) *count_out = carry;
     return DQ_BINS;
 }
+
+// Collecting passes: where the keys of a batch go.  Lane q holds the number of the batch's keys of query q of the group
+// (0 for empty slots); one atomic instruction reserves their places for all queries together (one after the other, each
+// with its own round trip to the counter, a batch took longer than the scan that found it: 25 M encoded codes,
+// 1000 queries, 48 M keys: 6.7 -> 3.9 ms).
+struct DqPlaces {
+    uint64_t begin, end;   // the query's list
+    uint32_t slot;         // first place reserved in it
+    __device__ __forceinline__ void list_of(const DqArgs &a, int gq) {
+        begin = gq < a.nq ? a.cand_off[gq] : 0;
+        end = gq < a.nq ? a.cand_off[gq + 1] : 0;
+    }
+    __device__ __forceinline__ void reserve(const DqArgs &a, int gq, uint32_t count) { slot = count != 0u ? atomicAdd(&a.cand_cnt[gq], count) : 0u; }
+    // place `index` of query q's (the list holds exactly the vectors the first pass counted; the comparison only keeps a
+    // disagreement from writing past it)
+    __device__ __forceinline__ void store(const DqArgs &a, int q, bool pass, uint32_t index, uint32_t sum, uint32_t row, uint32_t w0, uint32_t w1) const {
+        const uint64_t first = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(begin >> 32), q) << 32 | __builtin_amdgcn_readlane((uint32_t)begin, q)) +
+                               __builtin_amdgcn_readlane(slot, q);
+        const uint64_t stop = (uint64_t)__builtin_amdgcn_readlane((uint32_t)(end >> 32), q) << 32 | __builtin_amdgcn_readlane((uint32_t)end, q);
+        const uint64_t at = first + index;
+        if (pass && at < stop) {
+            a.cand[at] = ((uint64_t)sum << 32) | row;
+            if (a.cand_code != nullptr) a.cand_code[at] = make_uint2(w0, w1);
+        }
+    }
+};
 
 // MODE 0: counting pass (buckets), MODE 1: collecting pass (ids of the buckets 0..b*)
 template <int MODE>
@@ -228,39 +255,48 @@ __global__ __launch_bounds__(DQ_THREADS) void derived_scan_kernel(DqArgs a) {
         // for every (code, query) that passes the bucket count or the list append.
         auto flush = [&](const int count) {
             reload_tau();
+            DqPlaces places;
+            const int my_q = lane & (DQ_QB - 1), my_gq = group * DQ_QB + my_q;
+            if (MODE == 1) places.list_of(a, my_gq);
             for (int base = 0; base < count; base += 64) {
                 const bool have = base + lane < count;
                 const int pos = have ? (int)sm.ring[wave][base + lane] : ncodes;
+                const uint4 c = load_pair(pos);
                 uint32_t d[2][4];
                 {
                     uint4 v[8];
-                    issue(load_pair(pos), v);
+                    issue(c, v);
                     add_up(v, d);
                 }
+                auto passes = [&](int h, int q, uint32_t &sum) {
+                    sum = (d[h][q >> 1] >> (16 * (q & 1))) & 0xffffu;
+                    return pos + h < ncodes && sum < ((tau[q >> 1] >> (16 * (q & 1))) & 0xffffu);
+                };
+                uint32_t sum;
+                if (MODE == 0) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const bool valid = pos + h < ncodes;
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int q = 0; q < DQ_QB; ++q)
+                            if (passes(h, q, sum)) atomicAdd(&sm.hist[q][sum], 1u);
+                } else {
+                    uint32_t mine = 0;
 #pragma unroll
                     for (int q = 0; q < DQ_QB; ++q) {
-                        const uint32_t sum = (d[h][q >> 1] >> (16 * (q & 1))) & 0xffffu;
-                        const uint32_t thr = (tau[q >> 1] >> (16 * (q & 1))) & 0xffffu;
-                        const bool pass = valid && sum < thr;
-                        if (MODE == 0) {
-                            if (pass) atomicAdd(&sm.hist[q][sum], 1u);
-                        } else {
-                            const uint64_t mask = __ballot(pass);
-                            if (mask != 0ull) {
-                                const int gq = group * DQ_QB + q;
-                                const int first = __builtin_ctzll(mask);
-                                uint32_t slot = 0;
-                                if (lane == first) slot = atomicAdd(&a.cand_cnt[gq], (uint32_t)__popcll(mask));
-                                slot = __shfl(slot, first);
-                                // (the list holds exactly the vectors the first pass counted; the
-                                // comparison only keeps a disagreement from writing past it)
-                                const uint64_t at = a.cand_off[gq] + slot + (uint32_t)mask_prefix(mask);
-                                if (pass && at < a.cand_off[gq + 1]) a.cand[at] = ((uint64_t)sum << 32) | (uint32_t)(cbeg + pos + h);
-                            }
-                        }
+                        const uint32_t keys = (uint32_t)__popcll(__ballot(passes(0, q, sum))) + (uint32_t)__popcll(__ballot(passes(1, q, sum)));
+                        mine = lane == q ? keys : mine;
+                    }
+                    if (__ballot(mine != 0u) == 0ull) continue;
+                    places.reserve(a, my_gq, mine);
+#pragma unroll
+                    for (int q = 0; q < DQ_QB; ++q) {
+                        const bool p0 = passes(0, q, sum);
+                        const uint32_t s0 = sum;
+                        const bool p1 = passes(1, q, sum);
+                        const uint64_t m0 = __ballot(p0), m1 = __ballot(p1);
+                        if ((m0 | m1) == 0ull) continue;
+                        places.store(a, q, p0, (uint32_t)mask_prefix(m0), s0, (uint32_t)(cbeg + pos), c.x, c.y);
+                        places.store(a, q, p1, (uint32_t)(__popcll(m0) + mask_prefix(m1)), sum, (uint32_t)(cbeg + pos + 1), c.z, c.w);
                     }
                 }
             }
@@ -561,6 +597,9 @@ __global__ __launch_bounds__(DQ_THREADS) void derived_scan16_kernel(DqArgs a) {
                 comp_ev[p] = 0x80008000u - (__builtin_amdgcn_readlane(thr_lane, 4 * p) | (__builtin_amdgcn_readlane(thr_lane, 4 * p + 2) << 16));
                 comp_od[p] = 0x80008000u - (__builtin_amdgcn_readlane(thr_lane, 4 * p + 1) | (__builtin_amdgcn_readlane(thr_lane, 4 * p + 3) << 16));
             }
+            DqPlaces places;
+            const int my_q = lane & (DQ16_QB - 1), my_gq = group * DQ16_QB + my_q;
+            if (MODE == 1) places.list_of(a, my_gq);
             for (int base = 0; base < count; base += 64) {
                 const bool have = base + lane < count;
                 const int pos = have ? (int)sm.ring[wave][base + lane] : ncodes;
@@ -608,26 +647,24 @@ __global__ __launch_bounds__(DQ_THREADS) void derived_scan16_kernel(DqArgs a) {
                     }
                 } else {
                     if (__ballot(m != 0u) == 0ull) continue;
+                    uint32_t mine = 0;
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
+                    for (int q = 0; q < DQ16_QB; ++q) {
+                        const uint32_t keys = (uint32_t)__popcll(__ballot((m >> q) & 1u)) + (uint32_t)__popcll(__ballot((m >> (16 + q)) & 1u));
+                        mine = lane == q ? keys : mine;
+                    }
+                    places.reserve(a, my_gq, mine);
 #pragma unroll
-                        for (int q = 0; q < DQ16_QB; ++q) {
-                            const bool pass = ((m >> (h * 16 + q)) & 1u) != 0u;
-                            const uint64_t mask = __ballot(pass);
-                            if (mask != 0ull) {
-                                const uint32_t word = (q & 1) ? od[h][q >> 2] : ev[h][q >> 2];
-                                const uint32_t sum = (q & 2) ? word >> 16 : word & 0xffffu;
-                                const int gq = group * DQ16_QB + q;
-                                const int first = __builtin_ctzll(mask);
-                                uint32_t slot = 0;
-                                if (lane == first) slot = atomicAdd(&a.cand_cnt[gq], (uint32_t)__popcll(mask));
-                                slot = __shfl(slot, first);
-                                // (the list holds exactly the vectors the first pass counted; the
-                                // comparison only keeps a disagreement from writing past it)
-                                const uint64_t at = a.cand_off[gq] + slot + (uint32_t)mask_prefix(mask);
-                                if (pass && at < a.cand_off[gq + 1]) a.cand[at] = ((uint64_t)sum << 32) | (uint32_t)(cbeg + pos + h);
-                            }
-                        }
+                    for (int q = 0; q < DQ16_QB; ++q) {
+                        const bool p0 = ((m >> q) & 1u) != 0u, p1 = ((m >> (16 + q)) & 1u) != 0u;
+                        const uint64_t m0 = __ballot(p0), m1 = __ballot(p1);
+                        if ((m0 | m1) == 0ull) continue;
+                        auto sum_of = [&](int h) {
+                            const uint32_t word = (q & 1) ? od[h][q >> 2] : ev[h][q >> 2];
+                            return (q & 2) ? word >> 16 : word & 0xffffu;
+                        };
+                        places.store(a, q, p0, (uint32_t)mask_prefix(m0), sum_of(0), (uint32_t)(cbeg + pos), c.x, c.y);
+                        places.store(a, q, p1, (uint32_t)(__popcll(m0) + mask_prefix(m1)), sum_of(1), (uint32_t)(cbeg + pos + 1), c.z, c.w);
                     }
                 }
             }
@@ -808,71 +845,183 @@ __global__ __launch_bounds__(256) void derived_qmax_kernel(const uint8_t *codes,
     if (threadIdx.x == 0) qmax[q] = red[0];
 }
 
-// Step 2 for one query per block: precise distance of every candidate from the full codebooks
-// (each of the four terms ||y^j - C^j[c[j]]||^2 summed in double and rounded to float as the table
-// entry of Eq. (tables) would be, the four entries added in double and rounded once, Eq. (adc1)),
-// and the topk smallest (distance, row).  Candidates are taken in tiles; a tile's keys below the
-// current topk-th are sorted in LDS together with the best so far.
-constexpr int RR_THREADS = 1024;
-constexpr int RR_KEEP = 128;            // best keys carried from tile to tile (topk <= 128)
-constexpr int RR_TILE = 2 * RR_THREADS; // candidates per tile
-__global__ __launch_bounds__(RR_THREADS) void derived_rerank_kernel(const uint8_t *codes, const float *codebooks, int k,
-                                                                   int dsub, const float *queries, const uint64_t *cand,
-                                                                   const uint64_t *cand_off, const int64_t *ids, int topk,
-                                                                   float *out_dist, int64_t *out_ids) {
-    __shared__ uint64_t keys[RR_KEEP + RR_TILE + RR_KEEP * 15];   // 4096 keys: a power of two above KEEP + TILE
-    __shared__ float y[4096];
-    __shared__ int nnew;
-    const int q = blockIdx.x, tid = threadIdx.x;
-    const int d = DQ_M * dsub;
-    for (int i = tid; i < d; i += RR_THREADS) y[i] = queries[(size_t)q * d + i];
-    for (int i = tid; i < RR_KEEP; i += RR_THREADS) keys[i] = KEY_EMPTY;
-    if (tid == 0) nnew = 0;
+// Work items of Step 2: a query's candidates in pieces of `piece`.  item_off [nq + 1], item_query [item]; the bounds that
+// the items of a query share are reset.  One block.
+__global__ __launch_bounds__(1024) void derived_items_kernel(const uint32_t *__restrict__ count, int nq, uint32_t piece,
+                                                             uint32_t *__restrict__ item_off, uint32_t *__restrict__ item_query,
+                                                             unsigned long long *__restrict__ tau_key) {
+    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t carry;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) carry = 0;
     __syncthreads();
-    const uint64_t begin = cand_off[q], end = cand_off[q + 1];
-    for (uint64_t base = begin; base < end; base += RR_TILE) {
-        const uint64_t bound = keys[topk - 1];
-        for (int u = 0; u < 2; ++u) {
-            const uint64_t ci = base + (uint64_t)u * RR_THREADS + tid;
-            if (ci >= end) continue;
-            const uint32_t row = (uint32_t)cand[ci];
-            const uint2 c = *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
-            uint32_t idx[4] = {c.x & 0xffffu, c.x >> 16, c.y & 0xffffu, c.y >> 16};
-#pragma unroll
-            for (int j = 0; j < DQ_M; ++j) idx[j] = idx[j] < (uint32_t)k ? idx[j] : (uint32_t)k - 1u;   // indexes are below k by contract
-            double total = 0.0;
-#pragma unroll
-            for (int j = 0; j < DQ_M; ++j) {
-                const float *cent = codebooks + ((size_t)j * k + idx[j]) * dsub;
-                const float *yj = y + j * dsub;
-                double s = 0.0;
-                for (int t = 0; t < dsub; ++t) {
-                    const double diff = (double)yj[t] - (double)cent[t];
-                    s += diff * diff;
-                }
-                total += (double)(float)s;
-            }
-            const uint64_t key = ((uint64_t)f32_to_ord((float)total) << 32) | row;
-            if (key < bound) keys[RR_KEEP + atomicAdd(&nnew, 1)] = key;
+    for (int base = 0; base < nq; base += 1024) {
+        const int q = base + tid;
+        const uint32_t c = q < nq ? (count[q] + piece - 1) / piece : 0;
+        uint32_t incl = c;   // inclusive scan over the wave
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t other = __shfl_up(incl, o);
+            if (lane >= o) incl += other;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        uint32_t before = carry;
+        for (int w = 0; w < wave; ++w) before += wsum[w];
+        if (q < nq) {
+            const uint32_t first = before + incl - c;
+            item_off[q] = first;
+            tau_key[q] = KEY_EMPTY;
+            for (uint32_t i = 0; i < c; ++i) item_query[first + i] = (uint32_t)q;
         }
         __syncthreads();
-        const int total = RR_KEEP + nnew;
-        if (nnew > 0) {
-            int n2 = 256;
-            while (n2 < total) n2 <<= 1;
-            for (int i = total + tid; i < n2; i += RR_THREADS) keys[i] = KEY_EMPTY;
-            block_bitonic_sort(keys, n2);
-        }
-        __syncthreads();
-        if (tid == 0) nnew = 0;
+        if (tid == 1023) carry = before + incl;
         __syncthreads();
     }
-    for (int i = tid; i < topk; i += RR_THREADS) {
-        const uint64_t key = keys[i];
-        const bool have = key != KEY_EMPTY;
-        out_dist[(size_t)q * topk + i] = have ? ord_to_f32((uint32_t)(key >> 32)) : __builtin_inff();
-        const uint32_t row = (uint32_t)key;
-        out_ids[(size_t)q * topk + i] = have ? (ids ? ids[row] : (int64_t)row) : -1;
+    if (tid == 0) item_off[nq] = carry;
+}
+
+// Step 2: precise distance of every candidate from the full codebooks (each of the four terms ||y^j - C^j[c[j]]||^2
+// summed in double and rounded to float as the table entry of Eq. (tables) would be, the four entries added in double
+// and rounded once, Eq. (adc1)).  A block takes a piece of one query's candidates and leaves the topk smallest
+// (distance, row) keys of it for the merge; the topk-th key of a piece is a bound for the other pieces of the query.
+// What bounds it is the traffic of the centroid rows (four per candidate, dsub floats each, from codebooks of
+// 4 k rows that no L2 holds), so a row is read by 8 lanes together, 16 bytes each, two candidates per wave and read,
+// RR_ILP reads on their way.  (A thread per candidate read 4 bytes of 64 different rows per instruction, and one
+// block per query waited for the longest list: 48 M candidates of 1000 queries, the longest 455 000: 11.3 -> 3.2 ms.)
+constexpr int RR_THREADS = 512, RR_WAVES = RR_THREADS / 64;
+constexpr int RR_KEEP = 128;            // best keys carried from tile to tile (topk <= 128)
+constexpr int RR_TILE = 2 * RR_THREADS; // candidates per tile: two batches of 64 per wave
+constexpr int RR_ILP = 4;               // pairs of candidates whose rows are on their way together
+constexpr uint32_t RR_PIECE_MIN = RR_TILE, RR_PIECE_MAX = 16 * RR_TILE;
+
+// v + (v of the lane that the DPP control names)
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// odd rows of 16 lanes of a <-> even rows of b
+__device__ __forceinline__ void swap_rows16(double &a, double &b) {
+    typedef uint32_t pair2 __attribute__((ext_vector_type(2)));
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const pair2 lo = __builtin_bit_cast(pair2, __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false));
+    const pair2 hi = __builtin_bit_cast(pair2, __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false));
+    a = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]);
+    b = __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+// VEC: floats per load (4 where rows start on 16 bytes and hold a multiple of 4 dimensions, else 1)
+template <int VEC>
+__global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uint8_t *codes, const float *codebooks, int k, int dsub, const float *queries,
+                                                                      const uint64_t *cand, const uint2 *cand_code, const uint64_t *cand_off,
+                                                                      const uint32_t *item_off, const uint32_t *item_query, int nq, uint32_t piece,
+                                                                      int topk, unsigned long long *tau_key, uint64_t *partial) {
+    extern __shared__ float4 rr_dyn[];
+    __shared__ uint64_t keys[2048];   // KEEP + TILE, a power of two
+    __shared__ uint2 wcode[RR_WAVES][64];
+    __shared__ float wdist[RR_WAVES][64];
+    __shared__ int nnew;
+    static_assert(RR_KEEP + RR_TILE <= 2048 && RR_ILP % 2 == 0, "layout");
+    float *const y = reinterpret_cast<float *>(rr_dyn);   // [4 * dsub]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int half = lane >> 5, j = (lane >> 3) & 3, l8 = lane & 7;
+    const float *const cb = codebooks + (size_t)j * k * dsub;
+    const uint32_t nitems = item_off[nq];
+    for (uint32_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+        const int q = (int)item_query[item];
+        const uint64_t begin = cand_off[q] + (uint64_t)(item - item_off[q]) * piece;
+        const uint64_t end = begin + piece < cand_off[q + 1] ? begin + piece : cand_off[q + 1];
+        __syncthreads();   // the previous item's keys and query have been read
+        for (int i = tid; i < DQ_M * dsub; i += RR_THREADS) y[i] = queries[(size_t)q * (DQ_M * dsub) + i];
+        for (int i = tid; i < RR_KEEP; i += RR_THREADS) keys[i] = KEY_EMPTY;
+        if (tid == 0) nnew = 0;
+        __syncthreads();
+        const float *const yj = y + j * dsub;
+        for (uint64_t base = begin; base < end; base += RR_TILE) {
+            uint64_t bound = keys[topk - 1];
+            const uint64_t shared = __hip_atomic_load(&tau_key[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            bound = shared < bound ? shared : bound;
+            for (int u = 0; u < 2; ++u) {
+                const uint64_t c0 = base + (uint64_t)(u * RR_THREADS + wave * 64);
+                if (c0 >= end) break;
+                const uint64_t ci = c0 + lane;
+                const bool have = ci < end;
+                const uint32_t row = (uint32_t)cand[have ? ci : c0];
+                wcode[wave][lane] = cand_code != nullptr ? cand_code[have ? ci : c0] : *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
+                asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
+                const uint16_t *const idx16 = reinterpret_cast<const uint16_t *>(wcode[wave]);
+                const int left = end - c0 < 64 ? (int)(end - c0) : 64;
+                for (int s = 0; s < left; s += 2 * RR_ILP) {
+                    // lanes 32 h .. 32 h + 31: candidate s + 2 v + h, row j, dimensions VEC * l8 .. of every 8 * VEC
+                    const float *p[RR_ILP];
+                    double sum[RR_ILP];
+#pragma unroll
+                    for (int v = 0; v < RR_ILP; ++v) {
+                        uint32_t idx = idx16[(s + 2 * v + half) * 4 + j];
+                        idx = idx < (uint32_t)k ? idx : (uint32_t)k - 1u;   // indexes are below k by contract
+                        p[v] = cb + (size_t)idx * dsub;
+                        sum[v] = 0.0;
+                    }
+                    for (int t = VEC * l8; t < dsub; t += 8 * VEC) {
+                        float yv[VEC], cv[RR_ILP][VEC];
+#pragma unroll
+                        for (int v = 0; v < RR_ILP; ++v) {
+                            if (VEC == 4) {
+                                const float4 f = *reinterpret_cast<const float4 *>(p[v] + t);
+                                cv[v][0] = f.x; cv[v][VEC > 1 ? 1 : 0] = f.y; cv[v][VEC > 2 ? 2 : 0] = f.z; cv[v][VEC > 3 ? 3 : 0] = f.w;
+                            } else {
+                                cv[v][0] = p[v][t];
+                            }
+                        }
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) yv[i] = yj[t + i];
+#pragma unroll
+                        for (int v = 0; v < RR_ILP; ++v)
+#pragma unroll
+                            for (int i = 0; i < VEC; ++i) {
+                                const double diff = (double)yv[i] - (double)cv[v][i];
+                                sum[v] += diff * diff;
+                            }
+                    }
+#pragma unroll
+                    for (int v = 0; v < RR_ILP; v += 2) {
+                        double pairsum[2];
+#pragma unroll
+                        for (int w = 0; w < 2; ++w) {
+                            double x = dpp_add<0xB1>(sum[v + w]);   // lane ^ 1 (quad_perm 1,0,3,2)
+                            x = dpp_add<0x4E>(x);                   // lane ^ 2 (quad_perm 2,3,0,1)
+                            x = dpp_add<0x141>(x);                  // the other four of eight (row_half_mirror)
+                            x = (double)(float)x;                   // the table entry
+                            pairsum[w] = dpp_add<0x128>(x);         // tables j and j ^ 1 (row_ror 8)
+                        }
+                        swap_rows16(pairsum[0], pairsum[1]);
+                        const float total = (float)(pairsum[0] + pairsum[1]);   // row of 16 lanes r: candidate s + 2 (v + (r & 1)) + (r >> 1)
+                        if ((lane & 15) == 0) wdist[wave][s + 2 * (v + ((lane >> 4) & 1)) + half] = total;
+                    }
+                }
+                asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
+                const uint64_t key = ((uint64_t)f32_to_ord(wdist[wave][lane]) << 32) | row;
+                if (have && key < bound) keys[RR_KEEP + atomicAdd(&nnew, 1)] = key;
+                asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
+            }
+            __syncthreads();
+            const int added = nnew, total = RR_KEEP + added;
+            if (added > 0) {
+                int n2 = 256;
+                while (n2 < total) n2 <<= 1;
+                for (int i = total + tid; i < n2; i += RR_THREADS) keys[i] = KEY_EMPTY;
+                block_bitonic_sort(keys, n2);
+            }
+            __syncthreads();
+            if (tid == 0) {
+                nnew = 0;
+                if (added > 0 && keys[topk - 1] != KEY_EMPTY) atomicMin(&tau_key[q], (unsigned long long)keys[topk - 1]);
+            }
+            __syncthreads();
+        }
+        for (int i = tid; i < RR_KEEP; i += RR_THREADS) partial[(size_t)item * RR_KEEP + i] = i < topk ? keys[i] : KEY_EMPTY;
     }
 }
 
@@ -983,7 +1132,7 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
         a.work_counter = (uint32_t *)(ws + o_counter);
         a.g_hist = (uint32_t *)(ws + o_hist);
         a.g_bound = (uint32_t *)(ws + o_bound);
-        a.bucket = nullptr; a.cand_off = nullptr; a.cand_cnt = nullptr; a.cand = nullptr;
+        a.bucket = nullptr; a.cand_off = nullptr; a.cand_cnt = nullptr; a.cand = nullptr; a.cand_code = nullptr;
         derived_init_kernel<<<256, 256, 0, s>>>(a.work_counter, a.g_hist, (size_t)nq * DQ_BINS, a.g_bound, nullptr, nq);
         PQ_HIP(ctx, hipGetLastError());
         if (ctx->profiling) {
@@ -1016,17 +1165,30 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     unsigned long long total = 0;
     rc = count_pass(ws, &total);
     if (rc) return rc;
-    // the sizes of the candidate lists decide the rest of the workspace
-    const size_t o_cand = take((size_t)total * 8);
-    if (off > ctx->ws_bytes) {   // a new workspace: the counting pass is made again there (same bits)
-        rc = ws_reserve(ctx, off);
-        if (rc) return rc;
-        ws = (uint8_t *)ctx->ws;
-        unsigned long long again = 0;
-        rc = count_pass(ws, &again);
-        if (rc) return rc;
-        if (again != total) return fail(ctx, PQ_EHIP, "derived_search: the counting pass gave %llu candidates, then %llu", total, again);
+    // The sizes of the candidate lists are known now; they live in the context's other buffer, so that what the counting
+    // pass left in the workspace stays.  Pieces of Step 2: as many as there are blocks four times over.
+    uint64_t per_block = total / (8ull * (unsigned)ctx->num_cu);
+    uint32_t piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_TILE * RR_TILE;
+    if (piece < RR_PIECE_MIN) piece = RR_PIECE_MIN;
+    const size_t max_items = (size_t)(total / piece) + (size_t)nq;
+    const size_t o_partial = 0;
+    const size_t o_items = o_partial + align_up(max_items * RR_KEEP * 8, 256);
+    const size_t o_itemoff = o_items + align_up(max_items * 4, 256);
+    const size_t o_tau = o_itemoff + align_up((size_t)(nq + 1) * 4, 256);
+    const size_t o_cand = o_tau + align_up((size_t)nq * 8, 256);
+    const size_t o_code = o_cand + align_up((size_t)total * 8, 256);
+    // (a copy of the candidates' codes beside the list saves Step 2 a random read of the database per candidate; it is
+    // left out if there is no memory for it)
+    bool with_codes = true;
+    rc = lut_ws_reserve(ctx, o_code + align_up((size_t)total * 8, 256));
+    if (rc == PQ_ENOMEM) {
+        with_codes = false;
+        rc = lut_ws_reserve(ctx, o_code);
     }
+    if (rc) return rc;
+    uint8_t *lists = (uint8_t *)ctx->lut_ws;
+    uint32_t *item_off = (uint32_t *)(lists + o_itemoff), *item_query = (uint32_t *)(lists + o_items);
+    unsigned long long *tau_key = (unsigned long long *)(lists + o_tau);
 
     // Step 1.3, collecting pass
     a.qluts = ws + o_qluts;
@@ -1035,7 +1197,8 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     a.bucket = (const uint32_t *)(ws + o_bucket);
     a.cand_off = (const uint64_t *)(ws + o_candoff);
     a.cand_cnt = (uint32_t *)(ws + o_candcnt);
-    a.cand = (uint64_t *)(ws + o_cand);
+    a.cand = (uint64_t *)(lists + o_cand);
+    a.cand_code = with_codes ? (uint2 *)(lists + o_code) : nullptr;
     derived_init_kernel<<<256, 256, 0, s>>>(a.work_counter, nullptr, 0, nullptr, a.cand_cnt, nq);
     PQ_HIP(ctx, hipGetLastError());
     bind_geometry(a, g_collect);
@@ -1045,9 +1208,17 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
         PQ_HIP(ctx, hipGetLastError());
     }
     // Step 2
-    derived_rerank_kernel<<<nq, RR_THREADS, 0, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_off, nullptr, topk,
-                                                    out_dist, out_ids);
+    derived_items_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), nq, piece, item_off, item_query, tau_key);
     PQ_HIP(ctx, hipGetLastError());
+    const unsigned rr_grid = (unsigned)(max_items < 4 * (size_t)ctx->num_cu ? max_items : 4 * (size_t)ctx->num_cu);
+    const size_t rr_lds = align_up((size_t)d * 4, 16);
+    const bool rr_vec = (dsub & 3) == 0 && ((uintptr_t)codebooks & 15) == 0;
+    auto rerank = rr_vec ? derived_rerank_kernel<4> : derived_rerank_kernel<1>;
+    rerank<<<rr_grid, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, item_off, item_query, nq, piece,
+                                               topk, tau_key, (uint64_t *)(lists + o_partial));
+    PQ_HIP(ctx, hipGetLastError());
+    rc = launch_merge_filtered(ctx, (const uint64_t *)(lists + o_partial), item_off, 0, 1, 1, tau_key, RR_KEEP, nq, topk, nullptr, false, out_dist, out_ids);
+    if (rc) return rc;
     if (bucket_out) PQ_HIP(ctx, hipMemcpyAsync(bucket_out, ws + o_bucket, (size_t)nq * 4, hipMemcpyDeviceToDevice, s));
     if (ncand_out) {
         derived_widen_kernel<<<(nq + 255) / 256, 256, 0, s>>>((const uint32_t *)(ws + o_count), nq, ncand_out);

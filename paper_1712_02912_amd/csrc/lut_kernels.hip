@@ -552,7 +552,7 @@ __global__ __launch_bounds__(256, 2) void build_luts_mfma128_kernel(const Mfma12
 }
 
 // Scratch memory of the 128 x 128 form (operands as doubles and their norms), kept by the context.
-static int lut_ws_reserve(pq_ctx *ctx, size_t bytes) {
+int lut_ws_reserve(pq_ctx *ctx, size_t bytes) {
     if (bytes <= ctx->lut_ws_bytes) return PQ_OK;
     PQ_HIP(ctx, hipStreamSynchronize(ctx->stream));   // kernels already enqueued may still use the old buffer
     if (ctx->lut_ws) {

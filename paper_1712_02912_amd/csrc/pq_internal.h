@@ -49,6 +49,7 @@ int ws_reserve(pq_ctx *ctx, size_t bytes);
 // Make the context's buffer for converted operands (lut_ws) at least `bytes` large; false if that is not possible now
 // (out of memory, or the stream is being captured and the buffer would have to grow), for callers with another way.
 bool lut_ws_try(pq_ctx *ctx, size_t bytes);
+int lut_ws_reserve(pq_ctx *ctx, size_t bytes);   // the same, PQ_OK or an error already recorded
 
 #define PQ_HIP(ctx, call)                                                \
     do {                                                                 \

@@ -195,3 +195,20 @@ def test_derived_search_many_queries_identical_codes_and_worst_case_order(ctx, o
     # the 8-query kernel for the same input (switch)
     opts.set("scan_q8", 0)
     run_case(ctx, cb, cbar, codes, queries, 400, 10)
+
+
+@pytest.mark.parametrize("dsub,nq,n,r2,topk,shift", [(5, 3, 3001, 1024, 7, 0), (32, 2, 40_000, 33_000, 128, 1), (33, 1, 5000, 2049, 1, 0),
+                                                     (36, 17, 2500, 1025, 100, 0), (1, 2, 300, 64, 3, 0)])
+def test_derived_search_rerank_pieces(ctx, dsub, nq, n, r2, topk, shift):
+    """Step 2 at the edges of its pieces (1024 candidates) and rows: dimensions below, at and above the 32 that eight
+    lanes read at once, rows that do not start on 16 bytes, lists of several pieces, a handful of candidates."""
+    cb, cbar, codes, queries = make_problem(dsub * 7 + nq, n, 512, dsub, nq, distinct=200 if nq == 17 else None)
+    if shift:   # codebooks that start on 4 bytes only
+        buf = torch.empty(cb.size + 4, device="cuda")
+        d_cb = buf[shift:shift + cb.size].view(*cb.shape)
+        d_cb.copy_(torch.from_numpy(cb))
+        args = dev(codes.view(np.int16)), dev(cbar), d_cb, dev(queries)
+        plain = ctx.pq_derived_search(args[0], args[1], dev(cb), args[3], r2, topk)
+        moved = ctx.pq_derived_search(*args, r2, topk)
+        assert torch.equal(plain[0], moved[0]) and torch.equal(plain[1], moved[1])
+    run_case(ctx, cb, cbar, codes, queries, r2, topk)
