@@ -120,6 +120,28 @@ __device__ __forceinline__ int wave_append(uint64_t *buf, int cnt, bool pass, ui
     return cnt + __popcll(mask);
 }
 
+// One more in bins[bin] (LDS) for every lane with `in` set.  Values that share their leading bytes count in one bin, and 64
+// atomics to one address are served one after the other: the lanes that share the first lane's bin add together.
+__device__ __forceinline__ void wave_count_bin(uint32_t *bins, bool in, uint32_t bin) {
+    const uint64_t mask = __ballot(in);
+    if (mask == 0ull) return;
+    const int first = __builtin_ctzll(mask);
+    const uint32_t common = __builtin_amdgcn_readlane(bin, first);
+    const uint64_t same = __ballot(in && bin == common);
+    if (lane_id() == first) atomicAdd(&bins[common], (uint32_t)__popcll(same));
+    if (in && bin != common) atomicAdd(&bins[bin], 1u);
+}
+
+// A place from the counter *count (LDS) for every lane with `in` set: one atomic per wave.
+__device__ __forceinline__ int wave_place(int *count, bool in) {
+    const uint64_t mask = __ballot(in);
+    if (mask == 0ull) return 0;
+    const int first = __builtin_ctzll(mask);
+    int at = 0;
+    if (lane_id() == first) at = atomicAdd(count, __popcll(mask));
+    return __builtin_amdgcn_readlane(at, first) + (int)mask_prefix(mask);
+}
+
 // The k-th smallest (k = 1 .. n) of n 32-bit values in LDS, by the whole block (at least 256 threads), by radix
 // selection, most significant byte first: four rounds of a 256-bin count over the values that share the bytes
 // fixed so far.  `bins`: 256 LDS words, `state`: 2 LDS words.  Every thread gets the value; a few barriers in all.
@@ -134,7 +156,7 @@ __device__ inline uint32_t block_kth_smallest_u32(const uint32_t *vals, int n, u
         const uint32_t prefix = state[0], want = state[1];
         for (int i = tid; i < n; i += blockDim.x) {
             const uint32_t v = vals[i];
-            if ((v & fixed) == prefix) atomicAdd(&bins[(v >> shift) & 255u], 1u);
+            wave_count_bin(bins, (v & fixed) == prefix, (v >> shift) & 255u);
         }
         __syncthreads();
         if (tid < 64) {   // one wave: the byte value whose bin holds the `want`-th value
