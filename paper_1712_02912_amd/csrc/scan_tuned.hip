@@ -1659,9 +1659,14 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
 // The same over more codes than one block can look at (few query groups, large database):
 // block (s, q) counts the sums of slice s of the first `cnt` codes into the query's bins in device
 // memory, u4_seed_pick_kernel reads the bound off the counts.
+// The counts of the small sums are also kept slice by slice (slice_hist [query][slice][SLICE_BINS], if there is room for
+// them): codes that tie at the bound's sum far beyond k are told apart by their rows, as in u4_seed_kernel, here by the last
+// row of the slice in which the last tie that is needed falls.  (Sums of 8-bit distance tables that matter are small.  25 M
+// encoded codes, 8 queries, top-1000: call 414 -> 386, 353 -> 312 us on data with many ties.)
+constexpr int SLICE_BINS = 512;
 template <int NT>   // code bytes, 8 or 16
 __global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__restrict__ codes, int64_t cnt,
-                                                            const uint8_t *__restrict__ qluts, uint32_t *seed_hist) {
+                                                            const uint8_t *__restrict__ qluts, uint32_t *seed_hist, uint32_t *slice_hist) {
     __shared__ uint32_t hist[4096];
     __shared__ uint8_t tab[NT * 32];
     const int q = blockIdx.y, tid = threadIdx.x;
@@ -1698,12 +1703,38 @@ __global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__res
     __syncthreads();
     for (int i = tid; i < 4096; i += 1024)
         if (hist[i] != 0u) atomicAdd(&seed_hist[(size_t)q * 4096 + i], hist[i]);
+    if (slice_hist != nullptr && tid < SLICE_BINS) slice_hist[((size_t)q * gridDim.x + blockIdx.x) * SLICE_BINS + tid] = hist[tid];
 }
 
-__global__ __launch_bounds__(64) void u4_seed_pick_kernel(const uint32_t *__restrict__ seed_hist, int kq, int bins, unsigned long long *tau_key) {
-    const int q = blockIdx.x;
-    const int b = hist_threshold(seed_hist + (size_t)q * 4096, kq);   // one wave; smallest sum with kq counted codes at or below it
-    if (threadIdx.x == 0 && b < bins) tau_key[q] = ((unsigned long long)b << 32) | 0xffffffffull;
+__global__ __launch_bounds__(64) void u4_seed_pick_kernel(const uint32_t *__restrict__ seed_hist, int kq, int bins, const uint32_t *__restrict__ slice_hist,
+                                                          int nslices, int64_t cnt, unsigned long long *tau_key) {
+    const int q = blockIdx.x, lane = threadIdx.x;
+    const uint32_t *const hist = seed_hist + (size_t)q * 4096;
+    const int b = hist_threshold(hist, kq);   // one wave; smallest sum with kq counted codes at or below it
+    if (b >= bins) return;
+    uint32_t last_row = 0xffffffffu;
+    if (slice_hist != nullptr && b < SLICE_BINS) {
+        uint32_t below = 0;
+        for (int i = lane; i < b; i += 64) below += hist[i];
+        for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o);
+        const uint32_t need = (uint32_t)kq - below;   // ties wanted, at least one (bin b is the first to reach kq)
+        uint32_t carry = 0;
+        for (int s0 = 0; s0 < nslices; s0 += 64) {
+            uint32_t v = s0 + lane < nslices ? slice_hist[((size_t)q * nslices + s0 + lane) * SLICE_BINS + b] : 0u;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t up = __shfl_up(v, o);
+                if (lane >= o) v += up;
+            }
+            const uint64_t reach = __ballot(carry + v >= need);
+            if (reach != 0ull) {
+                const int64_t end = (int64_t)(s0 + __builtin_ctzll(reach) + 1) * (1 << 16);
+                last_row = (uint32_t)((end < cnt ? end : cnt) - 1);
+                break;
+            }
+            carry += __shfl(v, 63);
+        }
+    }
+    if (lane == 0) tau_key[q] = ((unsigned long long)b << 32) | last_row;
 }
 
 // Better first bound (every candidate the first bound lets through costs far more than a code the
@@ -2247,16 +2278,20 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     if (u4q) kind = KIND_U4Q_M16;
     const int qb = q8 || u4q ? 16 : (is_u4 || prune ? 8 : 4);
     const int cb = kind == KIND_F32_M16 || kind == KIND_F32P_M16 || u4_m32 ? 16 : 8;
-    const int depth = !(q8 || u4q) && (nq + qb - 1) / qb < STREAM_GROUPS ? 8 : 2;
-    const int tile = 64 * (16 / cb) * depth;   // codes per wave group (DEPTH sub-tiles)
     const bool small = topk <= 128;
     const int kpad = small ? 128 : 1024;
     const int cap = 64 * (small ? E_SMALL : E_LARGE);
-    const int ngroups = (nq + qb - 1) / qb;
-    const int64_t block_tile = (int64_t)tile * TUNED_WAVES;
     // persistent blocks: one per CU (64 KB of tables and 16 waves of 128 registers fill a CU)
     int nblocks_max = opt_int(ctx, PQ_OPT_SCAN_BLOCKS, ctx->num_cu);
     if (nblocks_max < 1) nblocks_max = 1;
+    const int ngroups = (nq + qb - 1) / qb;
+    const bool few_groups = !(q8 || u4q) && ngroups < STREAM_GROUPS;   // (the 16-query loops start at 16 groups)
+    // Few query groups stream their codes from memory (eight sub-tiles per group of a wave), unless the database is so
+    // small that a block's share is under four block tiles of that shape: there the finer groups spread it over more
+    // blocks, and it comes from the caches.
+    const bool stream = few_groups && n * ngroups >= (int64_t)nblocks_max * 4 * (8 * 64 * (16 / cb) * TUNED_WAVES);
+    const int tile = 64 * (16 / cb) * (stream ? 8 : 2);   // codes per wave group (DEPTH sub-tiles)
+    const int64_t block_tile = (int64_t)tile * TUNED_WAVES;
 
     // several items per block for balance, chunks of at least 8 block tiles
     // (six for the 16-query loops: 2 .. 4 % faster than four on 25 M codes, more than eight slower again)
@@ -2275,12 +2310,18 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // Up to 8 query groups over a large database (streaming shape): one item per block.  All items are equally long there,
     // so nothing is gained by handing out several, and every item pays its set-up (tables, bounds, first codes) and
     // leaves a result list for the merge (10^8 codes, one query: scan 0.21 -> 0.19 ms, call 0.39 -> 0.34 ms).
-    const int ipb_default = q8 || u4q ? 6 : (ngroups <= 8 && (nq + qb - 1) / qb < STREAM_GROUPS && n >= ((int64_t)1 << 22) ? 1 : 4);
+    const int ipb_default = q8 || u4q ? 6 : (ngroups <= 8 && n >= ((int64_t)1 << 22) ? 1 : 4);
     const int ipb = opt_int(ctx, PQ_OPT_SCAN_ITEMS_PER_BLOCK, ipb_default);
     int64_t nchunks = ipb == 1 ? (nblocks_max >= ngroups ? nblocks_max / ngroups : 1)   // (never more items than blocks)
                                : ((int64_t)ipb * nblocks_max + ngroups - 1) / ngroups;
-    const int64_t max_by_n = (n_main + 8 * block_tile - 1) / (8 * block_tile);
+    // (down to one block tile where chunks of eight would leave blocks without work: 10^5 codes, 16 queries were two
+    // items on the chip and are 50 now: scan 138 -> 29 us)
+    int64_t least_tiles = n_main * ngroups / ((int64_t)nblocks_max * block_tile);
+    least_tiles = least_tiles < 1 ? 1 : (least_tiles > 8 ? 8 : least_tiles);
+    const int64_t max_by_n = (n_main + least_tiles * block_tile - 1) / (least_tiles * block_tile);
     if (nchunks > max_by_n) nchunks = max_by_n;
+    // (a little more than one item per block would be two rounds)
+    if (nchunks * ngroups > nblocks_max && nchunks * ngroups < 2 * (int64_t)nblocks_max && ngroups <= nblocks_max) nchunks = nblocks_max / ngroups;
     const int64_t min_chunks = (n_main + ((int64_t)1 << 30) - 1) >> 30;   // a chunk's rows are counted in 32 bits
     if (nchunks < min_chunks) nchunks = min_chunks;
     if (nchunks < 1) nchunks = 1;
@@ -2305,8 +2346,12 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // Few query groups over a large database: the first bound comes from a larger part of the codes.
     // Measured optimum (10^7 .. 10^9 codes, 1 .. 200 queries): about 64 M code evaluations over all
     // queries of the call, at most a thirty-second of the database per query.
-    const bool few_groups = !(q8 || u4q) && ngroups < STREAM_GROUPS;   // (the 16-query loops start at 16 groups)
+    // Smaller databases: a sixteenth of the codes, at least 16 per result wanted (the sample of a few queries is added up
+    // by a few blocks; 10^5 codes, 16 queries, top-100: 65 536 codes 58 us, 6250 codes 26).
     int64_t seed_codes_f32 = SEED_CODES_STREAM;   // (integer scans use the same count)
+    int seed_codes_few = (int)(n / 16 < SEED_CODES_STREAM ? n / 16 : SEED_CODES_STREAM);
+    if (seed_codes_few < 16 * topk) seed_codes_few = 16 * topk;
+    if (seed_codes_few < PRUNE_INIT) seed_codes_few = PRUNE_INIT;
     if (few_groups) {
         int64_t want = ((int64_t)64 << 20) / (nq > 0 ? nq : 1);
         if (want > n / 32) want = n / 32;
@@ -2322,7 +2367,11 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     const size_t off_pscale16 = off_qtabs16 + (q8 ? (size_t)ngroups * 4096 * sizeof(uint4) : 0);
     const size_t total = prune ? off_pscale16 + (q8 ? align_up((size_t)ntau * 4, 256) : 0)
                                : (wide_seed_u4 ? off_seedhist + (size_t)nq * 4096 * 4 : (seed_plain ? off_poff : off_tau0));
-    rc = ws_reserve(ctx, total);
+    // (counts by slice of the integer scan's wide first bound: left out where the fixed scratch has no room for them)
+    const int seed_slices = (int)((seed_codes_f32 + SEED_SLICE - 1) / SEED_SLICE);
+    const size_t off_slices = align_up(total, 256), slices_bytes = wide_seed_u4 ? (size_t)nq * seed_slices * SLICE_BINS * 4 : 0;
+    const bool with_slices = wide_seed_u4 && !(ctx->ws_fixed && off_slices + slices_bytes > ctx->ws_bytes);
+    rc = ws_reserve(ctx, with_slices ? off_slices + slices_bytes : total);
     if (rc) return rc;
     uint8_t *ws = (uint8_t *)ctx->ws;
 
@@ -2369,7 +2418,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             const int by_queries = (1 << 26) / (nq > 0 ? nq : 1) < (1 << 18) ? (1 << 26) / (nq > 0 ? nq : 1) : (1 << 18);
             if (batch_codes < by_queries && (int64_t)by_queries <= n / 16) batch_codes = by_queries;   // (a small part of the database only)
             if ((int64_t)batch_codes > n) batch_codes = (int)n;
-            const int first_codes = few_groups ? SEED_CODES_STREAM : batch_codes;
+            const int first_codes = few_groups ? seed_codes_few : batch_codes;
             if (tables == 8) f32_seed_refine_kernel<8><<<(nq + SEED_QPB - 1) / SEED_QPB, 1024, 0, ctx->stream>>>(codes, first_codes, (const float *)luts, topk, true, nq, tau0);
             else f32_seed_refine_kernel<16><<<(nq + SEED_QPB - 1) / SEED_QPB, 1024, 0, ctx->stream>>>(codes, first_codes, (const float *)luts, topk, true, nq, tau0);
             PQ_HIP(ctx, hipGetLastError());
@@ -2394,15 +2443,16 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     if (is_u4 && n >= PRUNE_MIN_N) {
         if (wide_seed_u4) {
             uint32_t *seed_hist = (uint32_t *)(ws + off_seedhist);
-            const dim3 sgrid((unsigned)((seed_codes_f32 + SEED_SLICE - 1) / SEED_SLICE), (unsigned)nq);
-            if (u4_m32) u4_seed_hist_kernel<16><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist);
-            else u4_seed_hist_kernel<8><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist);
-            u4_seed_pick_kernel<<<nq, 64, 0, ctx->stream>>>(seed_hist, topk, exact_bins(cb), a.tau_key);
+            uint32_t *slice_hist = with_slices ? (uint32_t *)(ws + off_slices) : nullptr;
+            const dim3 sgrid((unsigned)seed_slices, (unsigned)nq);
+            if (u4_m32) u4_seed_hist_kernel<16><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist, slice_hist);
+            else u4_seed_hist_kernel<8><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist, slice_hist);
+            u4_seed_pick_kernel<<<nq, 64, 0, ctx->stream>>>(seed_hist, topk, exact_bins(cb), slice_hist, seed_slices, seed_codes_f32, a.tau_key);
         } else {
             // 256 codes per result wanted, between PRUNE_INIT and 262 144 (top-1000: 4.11 -> 3.94 ms per step; twice as many
             // cost the seed kernel more than they save the scan)
             int seed_codes = topk * 256 > PRUNE_INIT ? topk * 256 : PRUNE_INIT;
-            if (few_groups) seed_codes = SEED_CODES_STREAM;
+            if (few_groups) seed_codes = seed_codes_few;
             else if (seed_codes > 4 * SEED_CODES_STREAM) seed_codes = 4 * SEED_CODES_STREAM;
             if (!few_groups) {   // (fewer queries: larger sample, as for the float scan)
                 const int by_queries = (1 << 26) / (nq > 0 ? nq : 1) < (1 << 18) ? (1 << 26) / (nq > 0 ? nq : 1) : (1 << 18);
@@ -2420,7 +2470,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         note_scan(ctx, kind, qb, ngroups, a.stats, a.ncand, ntau);
         PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, ctx->stream));
     }
-    rc = launch_by_kind(ctx, kind, small, few_groups, a, nblocks);
+    rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
     if (rc) return rc;
     if (ctx->profiling) {
         PQ_HIP(ctx, hipEventRecord(ctx->ev_end, ctx->stream));

@@ -511,3 +511,24 @@ def test_ivf_quick_full_size_sampled(ctx):
         assert np.isin(owner, gp[q]).all()
     del codes_d
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("nlist,nq,nprobe", [(1, 1, 1), (3, 1, 3), (64, 9, 64), (1000, 1, 65), (4096, 40, 100), (4096, 41, 100), (4097, 2, 7), (8193, 1, 3)])
+def test_ivf_grouping_of_small_calls(ctx, nlist, nq, nprobe):
+    """Calls whose (query, list) pairs one block groups, and their neighbours that take the separate kernels: few and many
+    lists, empty lists, more probes than a wave has lanes; probed lists, distances and ids against the oracle."""
+    r = np.random.default_rng(nlist * 3 + nq)
+    d, m, n, topk = 32, 8, 6000, 30
+    coarse = (r.normal(size=(nlist, d)) * 3).astype(np.float32)
+    sizes = r.multinomial(n, r.dirichlet(np.full(nlist, 0.3)))
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    codes = r.integers(0, 256, (n, m), dtype=np.uint8)
+    cb = (r.normal(size=(m, 256, d // m)) * 2).astype(np.float32)
+    queries = (r.normal(size=(nq, d)) * 3).astype(np.float32)
+    gd, gi, gp = ctx.ivf_adc_search(dev(coarse), dev(offsets), dev(codes), None, dev(cb), binding.CODES_U8, dev(queries), nprobe, topk,
+                                    return_probes=True)
+    gd, gi, gp = host(gd), host(gi), host(gp)
+    od, oi, op = orc.ivf_search(coarse, offsets, codes, None, cb, orc.CODES_U8, queries, nprobe, topk)
+    assert np.array_equal(gp, op)
+    np.testing.assert_allclose(gd, od, rtol=1e-5)
+    assert (gi == oi).mean() > 0.99   # (near ties of random tables)

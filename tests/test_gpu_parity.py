@@ -771,6 +771,24 @@ def test_scan_u4_32_tables(ctx, n, nq, topk):
     run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
 
 
+@pytest.mark.parametrize("m", [16, 32])
+def test_scan_u4_ties_in_the_slices_of_a_wide_first_bound(ctx, m):
+    """Few queries, more than 2^21 codes: the first bound comes from slices of 65 536 codes.  Ties at the k-th sum end in
+    the first slice, in a later one, or only beyond the sample; sums beyond the bins that are kept per slice."""
+    r = np.random.default_rng(m)
+    n = 2_300_011
+    packed = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
+    packed[:70_000] = 0x11            # sum m for query 1, no ties with the zeros
+    packed[70_000:70_500] = 0x00      # in the second slice of the sample
+    packed[n - 3000:] = 0x00          # beyond the sample
+    qluts = r.choice(np.array([0, 1, 40], dtype=np.uint8), size=(4, m, 16), p=[0.4, 0.2, 0.4])
+    qluts[1] = np.arange(16)[None, :]
+    qluts[2] = 60                     # every sum 60 m: a tie of all codes, above the bins of the slices
+    qluts[3] = 7                      # the same below them for 16 tables
+    for topk in (100, 1000):
+        run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
+
+
 def test_scan_u4_32_tables_copies_and_fixed_scratch(ctx):
     """A hundred thousand copies of a query's best code (rows decide), and the call that allocates nothing."""
     r = np.random.default_rng(5)
