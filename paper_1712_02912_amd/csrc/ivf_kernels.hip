@@ -89,6 +89,24 @@ __global__ __launch_bounds__(256) void ivf_select_probes_kernel(const float *__r
         done = s_count >= nprobe && s_count <= SEL_CAP;
         __syncthreads();
     }
+    // Rows of up to SEL_CAP lists: the nprobe-th smallest distance by radix selection in LDS, then the keys up to it (the values
+    // wait behind the places of the keys, which are taken by SEL_CAP / 2 keys at most: more of them, by ties, go the long
+    // way).  (1024 lists, 48 probes: the histogram below, whose bins one thread adds up, 21 us; this 11.)
+    if (!done && nlist <= SEL_CAP && nprobe <= SEL_CAP / 2) {
+        uint32_t *ords = reinterpret_cast<uint32_t *>(cand + SEL_CAP / 2);
+        for (int i = tid; i < nlist; i += 256) ords[i] = f32_to_ord(row[i]);
+        if (tid == 0) s_count = 0;
+        __syncthreads();
+        const uint32_t kth = block_kth_smallest_u32(ords, nlist, (uint32_t)nprobe, part, sel_state);
+        for (int i = tid; i < nlist; i += 256)
+            if (ords[i] <= kth) {
+                const int pos = atomicAdd(&s_count, 1);
+                if (pos < SEL_CAP / 2) cand[pos] = ((uint64_t)ords[i] << 32) | (uint32_t)i;
+            }
+        __syncthreads();
+        done = s_count <= SEL_CAP / 2;
+        __syncthreads();
+    }
     int total = done ? s_count : 0;
     if (!done) {
         for (int i = tid; i < 4096; i += 256) hist[i] = 0;
@@ -225,11 +243,9 @@ __device__ __forceinline__ uint32_t block_scan_round(uint32_t v, uint32_t *wave_
 // (item_off; lists of a larger size class come first) and the number of items.
 // Lists of fewer than short_max codes go to a table of their own (one item per group of short_qs pairs, the whole
 // list, for the kernel of short lists); item_off is then the position in that table and nitems_dev[1] its length.
-__global__ __launch_bounds__(1024) void ivf_plan_kernel(const uint32_t *__restrict__ np,
-                                                        const int64_t *__restrict__ list_offsets, int nlist,
-                                                        uint32_t *pair_off, uint32_t *nc_out, uint32_t *item_off,
-                                                        uint32_t *nitems_dev, uint32_t qb, int64_t short_max, uint32_t short_qs,
-                                                        int64_t uncapped_rows) {
+__device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__restrict__ list_offsets, int nlist,
+                                         uint32_t *pair_off, uint32_t *nc_out, uint32_t *item_off,
+                                         uint32_t *nitems_dev, uint32_t qb, int64_t short_max, uint32_t short_qs, int64_t uncapped_rows) {
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t cls_items[64], cls_base[64], cls_cursor[64];   // 32 size classes of the long lists, 32 of the short ones
     __shared__ uint32_t carry;
@@ -237,17 +253,30 @@ __global__ __launch_bounds__(1024) void ivf_plan_kernel(const uint32_t *__restri
     if (tid < 64) { cls_items[tid] = 0; cls_cursor[tid] = 0; }
     if (tid == 0) carry = 0;
     __syncthreads();
-    for (int l0 = 0; l0 < nlist; l0 += 1024) {
-        const int l = l0 + tid;
-        const uint32_t v = l < nlist ? np[l] : 0u;
-        const uint32_t before = block_scan_round(v, wave_tot, &carry);
-        if (l < nlist) {
-            pair_off[l] = before;
-            const int64_t size = list_offsets[l + 1] - list_offsets[l];
-            const int nc = v > 0 ? ivf_chunks_of(size, uncapped_rows) : 0;
-            nc_out[l] = (uint32_t)nc;
+    // PER consecutive lists per thread and round of the scan (one list each: 65 536 lists are 64 rounds of three barriers and
+    // a round trip to memory, 265 us; 123 now)
+    constexpr int PER = 8;
+    for (int l0 = 0; l0 < nlist; l0 += PER * 1024) {
+        const int l = l0 + PER * tid;
+        uint32_t v[PER], sum = 0;
+        int64_t off[PER + 1];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] = l + i < nlist ? np[l + i] : 0u;
+#pragma unroll
+        for (int i = 0; i <= PER; ++i) off[i] = l + i <= nlist ? list_offsets[l + i] : 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) sum += v[i];
+        uint32_t before = block_scan_round(sum, wave_tot, &carry);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (l + i >= nlist) break;
+            pair_off[l + i] = before;
+            before += v[i];
+            const int64_t size = off[i + 1] - off[i];
+            const int nc = v[i] > 0 ? ivf_chunks_of(size, uncapped_rows) : 0;
+            nc_out[l + i] = (uint32_t)nc;
             const bool is_short = size < short_max;
-            const uint32_t items = is_short ? (nc > 0 ? (v + short_qs - 1) / short_qs : 0u) : ((v + qb - 1) / qb) * (uint32_t)nc;
+            const uint32_t items = is_short ? (nc > 0 ? (v[i] + short_qs - 1) / short_qs : 0u) : ((v[i] + qb - 1) / qb) * (uint32_t)nc;
             if (items > 0) atomicAdd(&cls_items[(is_short ? 32 : 0) + 63 - __builtin_clzll((unsigned long long)size)], items);
         }
     }
@@ -262,8 +291,10 @@ __global__ __launch_bounds__(1024) void ivf_plan_kernel(const uint32_t *__restri
         nitems_dev[1] = run;
     }
     __syncthreads();
+#pragma unroll 4
     for (int l = tid; l < nlist; l += 1024) {
         const uint32_t v = np[l];
+        if (v == 0u) { item_off[l] = 0; continue; }
         const int64_t size = list_offsets[l + 1] - list_offsets[l];
         const bool is_short = size < short_max;
         const uint32_t items = is_short ? (nc_out[l] > 0 ? (v + short_qs - 1) / short_qs : 0u) : ((v + qb - 1) / qb) * nc_out[l];
@@ -275,6 +306,12 @@ __global__ __launch_bounds__(1024) void ivf_plan_kernel(const uint32_t *__restri
         }
     }
 }
+__global__ __launch_bounds__(1024) void ivf_plan_kernel(const uint32_t *__restrict__ np, const int64_t *__restrict__ list_offsets, int nlist,
+                                                        uint32_t *pair_off, uint32_t *nc_out, uint32_t *item_off,
+                                                        uint32_t *nitems_dev, uint32_t qb, int64_t short_max, uint32_t short_qs,
+                                                        int64_t uncapped_rows) {
+    ivf_plan(np, list_offsets, nlist, pair_off, nc_out, item_off, nitems_dev, qb, short_max, short_qs, uncapped_rows);
+}
 
 __global__ void ivf_fill_pairs_kernel(const int32_t *__restrict__ probes, int npairs,
                                       const uint32_t *__restrict__ pair_off, uint32_t *fill, int32_t *pairs_by_list) {
@@ -285,12 +322,9 @@ __global__ void ivf_fill_pairs_kernel(const int32_t *__restrict__ probes, int np
 }
 
 // one thread per list: write the list's items (group-major, chunks of a group consecutive)
-__global__ void ivf_fill_items_kernel(const uint32_t *__restrict__ pair_off, const uint32_t *__restrict__ nc_arr,
-                                      const uint32_t *__restrict__ item_off, const int64_t *__restrict__ list_offsets,
-                                      int nlist, int rows_per_16b, uint32_t qb, IvfItem *items, int64_t short_max,
-                                      const int32_t *__restrict__ pairs_by_list, IvfShortItem *short_items) {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= nlist) return;
+__device__ __forceinline__ void ivf_fill_items(int l, const uint32_t *pair_off, const uint32_t *nc_arr, const uint32_t *item_off,
+                                               const int64_t *__restrict__ list_offsets, int rows_per_16b, uint32_t qb, IvfItem *items,
+                                               int64_t short_max, const int32_t *pairs_by_list, IvfShortItem *short_items) {
     const uint32_t npl = pair_off[l + 1] - pair_off[l];
     const int nc = (int)nc_arr[l];
     if (npl == 0 || nc == 0) return;
@@ -329,22 +363,41 @@ __global__ void ivf_fill_items_kernel(const uint32_t *__restrict__ pair_off, con
     }
 }
 
-// one thread per query: lists (pair, chunk) the query owns, and each pair's first list relative to the query
-__global__ void ivf_pair_lists_kernel(const int32_t *__restrict__ probes, const uint32_t *__restrict__ nc_arr, int nq,
-                                      int nprobe, uint32_t *pair_rel, uint32_t *qlists) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nq) return;
+__global__ void ivf_fill_items_kernel(const uint32_t *__restrict__ pair_off, const uint32_t *__restrict__ nc_arr,
+                                      const uint32_t *__restrict__ item_off, const int64_t *__restrict__ list_offsets,
+                                      int nlist, int rows_per_16b, uint32_t qb, IvfItem *items, int64_t short_max,
+                                      const int32_t *__restrict__ pairs_by_list, IvfShortItem *short_items) {
+    const int l = blockIdx.x * blockDim.x + threadIdx.x;
+    if (l < nlist) ivf_fill_items(l, pair_off, nc_arr, item_off, list_offsets, rows_per_16b, qb, items, short_max, pairs_by_list, short_items);
+}
+
+// one wave per query: lists (pair, chunk) the query owns, and each pair's first list relative to the query
+__device__ __forceinline__ void ivf_pair_lists(int q, const int32_t *__restrict__ probes, const uint32_t *nc_arr, int nprobe, uint32_t *pair_rel,
+                                               uint32_t *qlists) {
+    const int lane = lane_id();
     uint32_t run = 0;
-    for (int r = 0; r < nprobe; ++r) {
-        pair_rel[(size_t)q * nprobe + r] = run;
-        run += nc_arr[probes[(size_t)q * nprobe + r]];
+    for (int r0 = 0; r0 < nprobe; r0 += 64) {
+        const uint32_t v = r0 + lane < nprobe ? nc_arr[probes[(size_t)q * nprobe + r0 + lane]] : 0u;
+        uint32_t incl = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t up = __shfl_up(incl, o);
+            if (lane >= o) incl += up;
+        }
+        if (r0 + lane < nprobe) pair_rel[(size_t)q * nprobe + r0 + lane] = run + incl - v;
+        run += __shfl(incl, 63);
     }
-    qlists[q] = run;
+    if (lane == 0) qlists[q] = run;
+}
+__global__ __launch_bounds__(256) void ivf_pair_lists_kernel(const int32_t *__restrict__ probes, const uint32_t *__restrict__ nc_arr, int nq,
+                                                             int nprobe, uint32_t *pair_rel, uint32_t *qlists) {
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (q < nq) ivf_pair_lists(q, probes, nc_arr, nprobe, pair_rel, qlists);
 }
 
 // single block: exclusive scan of qlists -> qlist_off[nq+1] (1024 values per round: shuffles inside the waves, the
 // 16 wave totals through LDS)
-__global__ __launch_bounds__(1024) void ivf_qlist_scan_kernel(const uint32_t *__restrict__ qlists, int nq, uint32_t *qlist_off) {
+__device__ __forceinline__ void ivf_qlist_scan(const uint32_t *qlists, int nq, uint32_t *qlist_off) {
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t carry;
     const int tid = threadIdx.x;
@@ -357,11 +410,49 @@ __global__ __launch_bounds__(1024) void ivf_qlist_scan_kernel(const uint32_t *__
     }
     if (tid == 0) qlist_off[nq] = carry;
 }
+__global__ __launch_bounds__(1024) void ivf_qlist_scan_kernel(const uint32_t *__restrict__ qlists, int nq, uint32_t *qlist_off) { ivf_qlist_scan(qlists, nq, qlist_off); }
 
 // absolute first result list of every (query, probe) pair: its place within the query's lists plus the query's first list
 __global__ void ivf_pair_abs_kernel(const uint32_t *__restrict__ qlist_off, size_t npairs, int nprobe, uint32_t *pair_out) {
     const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p < npairs) pair_out[p] += qlist_off[p / nprobe];
+}
+
+// The whole grouping of a small call by one block: what the kernels above do, one after the other, with what only they share
+// in LDS.  (Nine launches of a few microseconds each: one query, 48 of 1024 lists, 35 us of them; this 7.)
+constexpr int IVF_GROUP_LISTS = 4096, IVF_GROUP_PAIRS = 4096;   // 64 KB of LDS; pairs that a block of 1024 threads handles in a few rounds
+struct IvfGroupArgs {
+    const int32_t *probes;
+    const int64_t *list_offsets;
+    int nlist, nq, nprobe, rows_per_16b;
+    uint32_t qb;
+    int64_t short_max, uncapped_rows;
+    uint32_t *nc, *nitems_dev, *pair_out, *qlists, *qlist_off;
+    int32_t *pairs_by_list;
+    IvfItem *items;
+    IvfShortItem *short_items;
+};
+__global__ __launch_bounds__(1024) void ivf_group_small_kernel(IvfGroupArgs a) {
+    extern __shared__ uint32_t group_lds[];
+    uint32_t *const np = group_lds, *const fill = np + a.nlist, *const item_off = fill + a.nlist, *const pair_off = item_off + a.nlist;   // (pair_off: one more)
+    const int tid = threadIdx.x, npairs = a.nq * a.nprobe;
+    for (int l = tid; l < 2 * a.nlist; l += 1024) group_lds[l] = 0u;
+    __syncthreads();
+    for (int p = tid; p < npairs; p += 1024) atomicAdd(&np[a.probes[p]], 1u);
+    __syncthreads();
+    ivf_plan(np, a.list_offsets, a.nlist, pair_off, a.nc, item_off, a.nitems_dev, a.qb, a.short_max, (uint32_t)IVF_SHORT_QS, a.uncapped_rows);
+    __syncthreads();
+    for (int p = tid; p < npairs; p += 1024) {
+        const int l = a.probes[p];
+        a.pairs_by_list[pair_off[l] + atomicAdd(&fill[l], 1u)] = p;
+    }
+    for (int q = tid >> 6; q < a.nq; q += 16) ivf_pair_lists(q, a.probes, a.nc, a.nprobe, a.pair_out, a.qlists);
+    __syncthreads();
+    for (int l = tid; l < a.nlist; l += 1024)
+        ivf_fill_items(l, pair_off, a.nc, item_off, a.list_offsets, a.rows_per_16b, a.qb, a.items, a.short_max, a.pairs_by_list, a.short_items);
+    ivf_qlist_scan(a.qlists, a.nq, a.qlist_off);
+    __syncthreads();
+    for (int p = tid; p < npairs; p += 1024) a.pair_out[p] += a.qlist_off[p / a.nprobe];
 }
 
 // First bound per query: float ADC (the tables' entries added in an order that depends on the lane) of up to IVF_SEED_CODES codes taken from the
@@ -377,7 +468,7 @@ template <int M>
 __global__ __launch_bounds__(256) void ivf_seed_kernel(const uint8_t *__restrict__ codes,
                                                        const int64_t *__restrict__ list_offsets,
                                                        const int32_t *__restrict__ probes, const float *__restrict__ luts,
-                                                       int nprobe, int topk, float *tau0) {
+                                                       int nprobe, int topk, int sample, float *tau0) {
     __shared__ __align__(16) float tab[M * 256];
     __shared__ __align__(16) uint32_t hist[HIST_BINS];
     __shared__ uint32_t ref_s;
@@ -439,7 +530,7 @@ __global__ __launch_bounds__(256) void ivf_seed_kernel(const uint8_t *__restrict
         return;
     }
     const uint32_t ref = ref_s;
-    for_codes(IVF_SEED_CODES, [&](uint32_t ord) {
+    for_codes(sample, [&](uint32_t ord) {
         if (ord <= ref) {
             const uint32_t below = (ref - ord) >> HIST_SHIFT;
             atomicAdd(&hist[HIST_BINS - 1 - (below < (uint32_t)HIST_BINS ? below : HIST_BINS - 1)], 1u);
@@ -897,23 +988,39 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
             PQ_HIP(ctx, hipGetLastError());
         }
         // The grouping of the pairs needs the probed lists only: it runs on a stream of the context's own (same priority)
-        // beside the residuals and their tables, and joins the caller's stream before the first bounds.
-        hipStream_t g = ctx->aux_stream;
-        PQ_HIP(ctx, hipEventRecord(ctx->aux_fork, s));
-        PQ_HIP(ctx, hipStreamWaitEvent(g, ctx->aux_fork, 0));
-        ivf_zero_kernel<<<256, 256, 0, g>>>(np, (size_t)nlist);
-        ivf_zero_kernel<<<256, 256, 0, g>>>(fill, (size_t)nlist);
-        ivf_count_pairs_kernel<<<(npairs + 255) / 256, 256, 0, g>>>(probes, npairs, np);
-        ivf_plan_kernel<<<1, 1024, 0, g>>>(np, L->list_offsets, nlist, pair_off, nc, item_off, nitems_dev, item_qb, short_max, (uint32_t)IVF_SHORT_QS,
-                                           quick ? quick_rows : (int64_t)0);
-        ivf_fill_pairs_kernel<<<(npairs + 255) / 256, 256, 0, g>>>(probes, npairs, pair_off, fill, pairs_by_list);
-        ivf_fill_items_kernel<<<(nlist + 255) / 256, 256, 0, g>>>(pair_off, nc, item_off, L->list_offsets, nlist,
-                                                                  rows_per_16b, item_qb, items, short_max, pairs_by_list, short_items);
-        ivf_pair_lists_kernel<<<(nqb + 255) / 256, 256, 0, g>>>(probes, nc, nqb, nprobe, pair_out, qlists);
-        ivf_qlist_scan_kernel<<<1, 1024, 0, g>>>(qlists, nqb, qlist_off);
-        ivf_pair_abs_kernel<<<(unsigned)(((size_t)nqb * nprobe + 255) / 256), 256, 0, g>>>(qlist_off, (size_t)nqb * nprobe, nprobe, pair_out);
+        // beside the residuals and their tables, and joins the caller's stream before the first bounds.  Small calls: one
+        // launch, and with up to 512 pairs (tables of a few microseconds) not worth the events of a second stream.
+        const bool group_small = nlist <= IVF_GROUP_LISTS && npairs <= IVF_GROUP_PAIRS, forked = !(group_small && npairs <= 512);
+        hipStream_t g = forked ? ctx->aux_stream : s;
+        if (forked) {
+            PQ_HIP(ctx, hipEventRecord(ctx->aux_fork, s));
+            PQ_HIP(ctx, hipStreamWaitEvent(g, ctx->aux_fork, 0));
+        }
+        if (group_small) {
+            IvfGroupArgs ga{};
+            ga.probes = probes; ga.list_offsets = L->list_offsets; ga.nlist = nlist; ga.nq = nqb; ga.nprobe = nprobe;
+            ga.rows_per_16b = rows_per_16b; ga.qb = item_qb; ga.short_max = short_max; ga.uncapped_rows = quick ? quick_rows : (int64_t)0;
+            ga.nc = nc; ga.nitems_dev = nitems_dev; ga.pair_out = pair_out; ga.qlists = qlists; ga.qlist_off = qlist_off;
+            ga.pairs_by_list = pairs_by_list; ga.items = items; ga.short_items = short_items;
+            const size_t group_lds_bytes = ((size_t)4 * nlist + 1) * 4;
+            PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(ivf_group_small_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (4 * IVF_GROUP_LISTS + 1) * 4));
+            ivf_group_small_kernel<<<1, 1024, group_lds_bytes, g>>>(ga);
+        } else {
+            // (the two counters of a list lie side by side: one launch clears both)
+            ivf_zero_kernel<<<256, 256, 0, g>>>(np, (size_t)(o_pairoff - o_np) / 4);
+            ivf_count_pairs_kernel<<<(npairs + 255) / 256, 256, 0, g>>>(probes, npairs, np);
+            ivf_plan_kernel<<<1, 1024, 0, g>>>(np, L->list_offsets, nlist, pair_off, nc, item_off, nitems_dev, item_qb, short_max, (uint32_t)IVF_SHORT_QS,
+                                               quick ? quick_rows : (int64_t)0);
+            ivf_fill_pairs_kernel<<<(npairs + 255) / 256, 256, 0, g>>>(probes, npairs, pair_off, fill, pairs_by_list);
+            ivf_fill_items_kernel<<<(nlist + 255) / 256, 256, 0, g>>>(pair_off, nc, item_off, L->list_offsets, nlist,
+                                                                      rows_per_16b, item_qb, items, short_max, pairs_by_list, short_items);
+            ivf_pair_lists_kernel<<<(nqb + 3) / 4, 256, 0, g>>>(probes, nc, nqb, nprobe, pair_out, qlists);
+            ivf_qlist_scan_kernel<<<1, 1024, 0, g>>>(qlists, nqb, qlist_off);
+            ivf_pair_abs_kernel<<<(unsigned)(((size_t)nqb * nprobe + 255) / 256), 256, 0, g>>>(qlist_off, (size_t)nqb * nprobe, nprobe, pair_out);
+        }
         PQ_HIP(ctx, hipGetLastError());
-        PQ_HIP(ctx, hipEventRecord(ctx->aux_join, g));
+        if (forked) PQ_HIP(ctx, hipEventRecord(ctx->aux_join, g));
         // Tables step on the residuals
         {
             const size_t n = (size_t)npairs * d;
@@ -927,7 +1034,7 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
         }
         rc = launch_build_luts(ctx, resid, codebooks, npairs, d, m, k, luts);
         if (rc) return rc;
-        PQ_HIP(ctx, hipStreamWaitEvent(s, ctx->aux_join, 0));   // the work items are laid out
+        if (forked) PQ_HIP(ctx, hipStreamWaitEvent(s, ctx->aux_join, 0));   // the work items are laid out
         if (quick) {
             unsigned long long *tau_q = (unsigned long long *)(ws + o_tauq);
             rc = launch_ivf_quick(ctx, L->codes, L->list_offsets, probes, luts, nqb, nprobe, init, kprime, topk,
@@ -941,8 +1048,16 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
         }
         // Scan step, seeded with a first bound per query
         float *tau0 = (float *)(ws + o_tau0);
-        if (m == 8) ivf_seed_kernel<8><<<nqb, 256, 0, s>>>(L->codes, L->list_offsets, probes, luts, nprobe, topk, tau0);
-        else ivf_seed_kernel<16><<<nqb, 256, 0, s>>>(L->codes, L->list_offsets, probes, luts, nprobe, topk, tau0);
+        // An eighth of the codes that nprobe lists hold on average for a handful of queries (the sample is added up by one
+        // block per query, and the call waits for it), a quarter for more, at least 16 per result wanted.  1 M codes in 1024
+        // lists, 48 probed: one query 16 384 codes 38 us, an eighth 18; 64 queries call 249 us with 16 384 codes, 241 with an
+        // eighth, 223 with a quarter.
+        const int64_t mean_codes = L->ntotal / nlist * nprobe;
+        int sample = (int)(mean_codes / (nqb <= 16 ? 8 : 4) < IVF_SEED_CODES ? mean_codes / (nqb <= 16 ? 8 : 4) : IVF_SEED_CODES);
+        if (sample < 16 * topk) sample = 16 * topk;
+        if (sample < 1024) sample = 1024;
+        if (m == 8) ivf_seed_kernel<8><<<nqb, 256, 0, s>>>(L->codes, L->list_offsets, probes, luts, nprobe, topk, sample, tau0);
+        else ivf_seed_kernel<16><<<nqb, 256, 0, s>>>(L->codes, L->list_offsets, probes, luts, nprobe, topk, sample, tau0);
         PQ_HIP(ctx, hipGetLastError());
         float *pmin = nullptr, *poff = nullptr, *pscale = nullptr;
         if (prune) {
