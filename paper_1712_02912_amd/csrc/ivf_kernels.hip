@@ -284,8 +284,13 @@ __device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__re
     if (tid == 0) {
         pair_off[nlist] = carry;
         uint32_t run = 0;
-        for (int c = 31; c >= 0; --c) { cls_base[c] = run; run += cls_items[c]; }
+        for (int c = 31; c >= 0; --c) {
+            cls_base[c] = run;
+            run += cls_items[c];
+            if (c == IVF_QUICK_LONG_CLASS) nitems_dev[2] = run;   // items of the lists of 2^16 rows and more
+        }
         nitems_dev[0] = run;
+        nitems_dev[4] = nitems_dev[5] = 0u;   // work counters of the Quick ADC scan
         run = 0;
         for (int c = 63; c >= 32; --c) { cls_base[c] = run; run += cls_items[c]; }
         nitems_dev[1] = run;
@@ -885,7 +890,7 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
     const size_t o_pairoff = take((size_t)(nlist + 1) * 4);
     const size_t o_nc = take((size_t)nlist * 4);
     const size_t o_itemoff = take((size_t)nlist * 4);
-    const size_t o_nitems = take(8);   // (long lists' items, short lists' items)
+    const size_t o_nitems = take(32);   // (long lists' items, short lists' items, Quick ADC: items of its long lists, -, two work counters)
     const size_t o_pairs = take(npairs_max * 4);
     const size_t o_items = take(max_items * sizeof(IvfItem));
     const size_t max_short_items = short_max > 0 ? npairs_max / IVF_SHORT_QS + (size_t)nlist + 1 : 0;
@@ -1039,7 +1044,7 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
             unsigned long long *tau_q = (unsigned long long *)(ws + o_tauq);
             rc = launch_ivf_quick(ctx, L->codes, L->list_offsets, probes, luts, nqb, nprobe, init, kprime, topk,
                                   (float *)(ws + o_qmaxp), ws + o_qluts, items, nitems_dev, pairs_by_list, pair_out, nc,
-                                  partial, tau_q, (uint32_t *)(ws + o_qrows), quick_rows);
+                                  partial, tau_q, (uint32_t *)(ws + o_qrows), quick_rows, forked);
             if (rc) return rc;
             rc = launch_merge_filtered(ctx, partial, qlist_off, 0, 0, 1, tau_q, kpad, nqb, topk, L->ids, false,
                                        out_dist + (size_t)q0 * topk, out_ids + (size_t)q0 * topk);

@@ -31,7 +31,7 @@
 namespace pq {
 
 constexpr int QK_QS = 8;          // (query, list) pairs per work item
-constexpr int QK_LONG_MIN = 65536;   // work items of this many rows and more take the blocks of 8 waves
+constexpr int QK_LONG_MIN = 1 << IVF_QUICK_LONG_CLASS;   // lists of this many rows and more take the blocks of 8 waves
 constexpr int QK_BINS = 512;      // sums counted per pass: base .. base + 510, and one bin for everything above
 constexpr int QK_KP = 128;        // kprime at most (the length of a result list)
 constexpr int QK_BATCH = 4;       // codes of a thread on their way at a time
@@ -114,37 +114,54 @@ struct __align__(16) QuickSmem {
     int pair[QK_QS];
     uint32_t out_idx[QK_QS];
     int pending;                                 // pairs whose T is not known yet
+    int item;
+    int single;                                  // the list is this one item: its candidates are final
 };
-// (items of the blocks of 4 waves have fewer than QK_LONG_MIN = 2^16 rows: 16 bits hold a row within the item)
+// (lists of the blocks of 4 waves have fewer than QK_LONG_MIN = 2^16 rows, an item at most one row of alignment more: 16
+// bits hold a row within the item)
 typedef QuickSmem<4, uint16_t> QuickSmemShort;
 typedef QuickSmem<8, uint32_t> QuickSmemLong;
 static_assert(QK_LONG_MIN <= 65536, "rows of short items fit 16 bits");
 static_assert(sizeof(QuickSmemShort) <= 40 * 1024, "four blocks of 4 waves share the 160 KB of a compute unit");
 static_assert(sizeof(QuickSmemLong) <= 80 * 1024, "two blocks of 8 waves per compute unit");
 
-// Blocks of QK_WAVES waves.  LONG: the kernel takes the work items of QK_LONG_MIN rows and more (8 waves, two blocks
-// per compute unit: the longest item of a skewed index is what the call waits for), else the shorter ones (4 waves,
-// four blocks per compute unit).  Items are dealt in a stride of the grid; an item of the other kind is passed over.
+// Blocks of QK_WAVES waves.  LONG: the kernel takes the work items of lists of QK_LONG_MIN rows and more (8 waves, two blocks
+// per compute unit: the longest item of a skewed index is what the call waits for), else the others (4 waves,
+// four blocks per compute unit).  The table of items has those of the long lists first; blocks draw them from a counter.
+// Both kernels are in flight together where the call has a second stream: blocks of the short items move in as
+// those of the long ones leave, instead of waiting for the last long item.
+// A list that is one item (all but the longest) has its candidates reranked here, while its codes are in the caches:
+// the float keys go to the result list directly (the separate rerank fetched 82 M candidates' codes from memory again,
+// one block of 128 threads per pair: 1.86 ms of the billion-code call).
+// 10^9 codes in 65 536 lists, 10 000 queries x 64 probes: both scans and the rerank 14.2 -> 12.6 ms.
 template <int QK_WAVES, bool LONG>
 __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_kernel(const uint8_t *__restrict__ codes,
                                                                        const uint8_t *__restrict__ qluts,
                                                                        const IvfItem *__restrict__ items,
-                                                                       const uint32_t *__restrict__ nitems_dev,
+                                                                       uint32_t *nitems_dev,
                                                                        const int32_t *__restrict__ pairs_by_list,
                                                                        const uint32_t *__restrict__ pair_out, int kprime,
-                                                                       uint64_t *partial, uint32_t *saved_rows, int saved_cap) {
+                                                                       uint64_t *partial, uint32_t *saved_rows, int saved_cap,
+                                                                       const float *__restrict__ luts, const int32_t *__restrict__ probes,
+                                                                       const uint32_t *__restrict__ nc_arr, int nprobe, int topk,
+                                                                       unsigned long long *tau_key) {
     constexpr int QK_THREADS = QK_WAVES * 64;
     extern __shared__ __align__(16) unsigned char quick_smem[];
     typedef typename std::conditional<LONG, uint32_t, uint16_t>::type TieRow;
     QuickSmem<QK_WAVES, TieRow> &sm = *reinterpret_cast<QuickSmem<QK_WAVES, TieRow> *>(quick_smem);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nitems = (int)*nitems_dev;
+    const int first_item = LONG ? 0 : (int)nitems_dev[2], nitems = LONG ? (int)nitems_dev[2] : (int)nitems_dev[0];
+    uint32_t *const work_counter = nitems_dev + (LONG ? 4 : 5);
     // rows of the item that the counting pass found at or below some pair's cap of the moment, per wave in the order
     // the wave met them (ascending): the only rows the collecting pass has to look at again
     uint32_t *my_saved = saved_rows + ((size_t)blockIdx.x * QK_WAVES + wave) * (size_t)saved_cap;
-    for (int item = (int)blockIdx.x; item < nitems; item += (int)gridDim.x) {
+    for (;;) {
+        __syncthreads();   // the item before is done with the shared state
+        if (tid == 0) sm.item = first_item + (int)atomicAdd(work_counter, 1u);
+        __syncthreads();
+        const int item = sm.item;
+        if (item >= nitems) break;
         const IvfItem it = items[item];
-        if (((int)it.ncodes >= QK_LONG_MIN) != LONG) continue;   // (uniform)
         const int skip = (int)(it.skip_slots_chunk & 255u);
         const int nslots = (int)((it.skip_slots_chunk >> 8) & 255u);
         const uint32_t chunk = it.skip_slots_chunk >> 16;
@@ -152,7 +169,7 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
         const int nvalid = ncodes - skip;
         const uint32_t row0 = it.code_begin;
         const uint8_t *base_ptr = codes + (size_t)row0 * 8;
-        __syncthreads();   // the item before is done with the shared state
+        if (tid == 0) sm.single = nc_arr[probes[pairs_by_list[it.pair_pos]]] == 1u ? 1 : 0;   // (an item has at least one pair)
         if (tid < QK_QS) {
             const int pair = tid < nslots ? pairs_by_list[it.pair_pos + tid] : -1;
             sm.pair[tid] = pair;
@@ -410,6 +427,29 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
             }
         }
         __syncthreads();
+        if (sm.single) {
+            // float distances in place of the integer keys; the pairs' float tables take the memory of the bins
+            float *const tabf = reinterpret_cast<float *>(&sm.hist[0][0]);
+            static_assert(sizeof(sm.hist) >= QK_QS * 256 * sizeof(float), "the bins' memory holds the float tables");
+            for (int e = tid; e < nslots * 256; e += QK_THREADS) tabf[e] = luts[(size_t)sm.pair[e >> 8] * 256 + (e & 255)];
+            __syncthreads();
+            for (int e = tid; e < nslots * QK_KP; e += QK_THREADS) {
+                const int s = e / QK_KP, idx = e % QK_KP;
+                const unsigned long long key = sm.sure[s][idx];
+                if (key == KEY_EMPTY) continue;
+                const uint32_t row = (uint32_t)key;
+                const uint2 c = *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
+                sm.sure[s][idx] = ((unsigned long long)f32_to_ord(adc16x4_exact(tabf + s * 256, c)) << 32) | row;
+            }
+            __syncthreads();
+            // a pair's topk-th key bounds its query's result
+            for (int s = wave; s < nslots; s += QK_WAVES) {
+                if (sm.sure[s][topk - 1] == KEY_EMPTY) continue;   // (keys first, empty slots behind)
+                const uint64_t two[2] = {sm.sure[s][lane], sm.sure[s][64 + lane]};
+                const uint64_t kth = wave_select_kth<2>(two, topk);
+                if (lane == 0) atomicMin(&tau_key[sm.pair[s] / nprobe], (unsigned long long)kth);
+            }
+        }
         for (int e = tid; e < nslots * QK_KP; e += QK_THREADS) {
             const int s = e / QK_KP, idx = e % QK_KP;
             partial[(size_t)sm.out_idx[s] * QK_KP + idx] = sm.sure[s][idx];
@@ -418,44 +458,53 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
 }
 
 // ------------------------------------------------------------------------------------------
-// Rerank: one block per (query, list) pair.  The kprime smallest integer keys over the pair's result lists (one list
-// per chunk of the inverted list, any number of them) are its candidates; their float distances replace them in the pair's first list,
-// in ascending order, the other lists are emptied, and the pair's topk-th key (if it has one) bounds the query's result.
-__global__ __launch_bounds__(128) void ivf_quick_rerank_kernel(const uint8_t *__restrict__ codes, const float *__restrict__ luts,
+// Rerank of the pairs whose list is cut into several chunks (the scan has seen to the others).  The kprime smallest integer
+// keys over the pair's result lists (one per chunk, any number of them) are its candidates; their float distances replace
+// them in the pair's first list, the other lists are emptied, and the pair's topk-th key (if it has one) bounds the query's
+// result.  A block looks 256 pairs over for such ones, and takes in seven of a pair's lists at a time (128 threads and one
+// list at a time: 82 sorts one after the other for the longest list of a billion codes, 0.45 ms).
+constexpr int QK_RR_THREADS = 1024, QK_RR_PAIRS = 256, QK_RR_LISTS = QK_RR_THREADS / QK_KP - 1;
+__global__ __launch_bounds__(QK_RR_THREADS) void ivf_quick_rerank_kernel(const uint8_t *__restrict__ codes, const float *__restrict__ luts,
                                                                const int32_t *__restrict__ probes, const uint32_t *__restrict__ nc_arr,
-                                                               const uint32_t *__restrict__ pair_out, int nprobe, int kprime,
+                                                               const uint32_t *__restrict__ pair_out, int npairs, int nprobe, int kprime,
                                                                int topk, uint64_t *partial, unsigned long long *tau_key) {
     __shared__ float tab[256];
-    __shared__ uint64_t keys[2 * QK_KP];
-    const int pair = blockIdx.x, tid = threadIdx.x;
-    const int nc = (int)nc_arr[probes[pair]];
-    uint64_t *lists = partial + (size_t)pair_out[pair] * QK_KP;
-    tab[tid] = luts[(size_t)pair * 256 + tid];
-    tab[tid + 128] = luts[(size_t)pair * 256 + 128 + tid];
-    uint64_t key;
-    if (nc <= 1) {
-        key = nc == 1 ? lists[tid] : KEY_EMPTY;
-    } else {   // a list of several chunks: the smallest keys so far in keys[0 .. 127], the next chunk's list sorted in beside them
-        keys[tid] = lists[tid];
-        for (int c = 1; c < nc; ++c) {
-            keys[QK_KP + tid] = lists[(size_t)c * QK_KP + tid];
-            block_bitonic_sort(keys, 2 * QK_KP);
-        }
-        key = tid < kprime ? keys[tid] : KEY_EMPTY;
-        __syncthreads();
+    __shared__ uint64_t keys[QK_RR_THREADS];
+    __shared__ int todo[QK_RR_PAIRS], ntodo;
+    const int tid = threadIdx.x;
+    if (tid == 0) ntodo = 0;
+    __syncthreads();
+    {
+        const int pair = (int)blockIdx.x * QK_RR_PAIRS + tid;
+        if (tid < QK_RR_PAIRS && pair < npairs && nc_arr[probes[pair]] > 1u) todo[atomicAdd(&ntodo, 1)] = pair;
     }
     __syncthreads();
-    uint64_t fkey = KEY_EMPTY;
-    if (key != KEY_EMPTY) {
-        const uint32_t row = (uint32_t)key;
-        const uint2 c = *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
-        fkey = ((uint64_t)f32_to_ord(adc16x4_exact(tab, c)) << 32) | row;
+    for (int i = 0; i < ntodo; ++i) {
+        const int pair = todo[i], nc = (int)nc_arr[probes[pair]];
+        uint64_t *lists = partial + (size_t)pair_out[pair] * QK_KP;
+        __syncthreads();   // the pair before is done with the tables and keys
+        if (tid < 256) tab[tid] = luts[(size_t)pair * 256 + tid];
+        // the smallest keys so far in keys[0 .. 127], the next chunks' lists sorted in beside them
+        if (tid < QK_KP) keys[tid] = lists[tid];
+        for (int c = 1; c < nc; c += QK_RR_LISTS) {
+            const size_t at = (size_t)c * QK_KP + (size_t)(tid - QK_KP);
+            if (tid >= QK_KP) keys[tid] = at < (size_t)nc * QK_KP ? lists[at] : KEY_EMPTY;
+            block_bitonic_sort(keys, QK_RR_THREADS);
+        }
+        const uint64_t key = tid < kprime ? keys[tid] : KEY_EMPTY;
+        __syncthreads();
+        uint64_t fkey = KEY_EMPTY;
+        if (key != KEY_EMPTY) {
+            const uint32_t row = (uint32_t)key;
+            const uint2 c = *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
+            fkey = ((uint64_t)f32_to_ord(adc16x4_exact(tab, c)) << 32) | row;
+        }
+        if (tid < QK_KP) keys[tid] = fkey;
+        block_bitonic_sort(keys, QK_KP);
+        if (tid < QK_KP) lists[tid] = keys[tid];
+        for (size_t e = QK_KP + tid; e < (size_t)nc * QK_KP; e += QK_RR_THREADS) lists[e] = KEY_EMPTY;
+        if (tid == 0 && keys[topk - 1] != KEY_EMPTY) atomicMin(&tau_key[pair / nprobe], (unsigned long long)keys[topk - 1]);
     }
-    keys[tid] = fkey;
-    block_bitonic_sort(keys, 128);
-    if (nc >= 1) lists[tid] = keys[tid];
-    for (size_t i = 128 + tid; i < (size_t)nc * QK_KP; i += 128) lists[i] = KEY_EMPTY;
-    if (tid == 0 && keys[topk - 1] != KEY_EMPTY) atomicMin(&tau_key[pair / nprobe], (unsigned long long)keys[topk - 1]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -468,9 +517,9 @@ size_t ivf_quick_saved_bytes(const pq_ctx *ctx, int64_t max_item_rows) {
 
 int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offsets, const int32_t *probes,
                      const float *luts, int nq, int nprobe, int init, int kprime, int topk, float *qmax_pair,
-                     uint8_t *qluts, const IvfItem *items, const uint32_t *nitems_dev, const int32_t *pairs_by_list,
+                     uint8_t *qluts, const IvfItem *items, uint32_t *nitems_dev, const int32_t *pairs_by_list,
                      const uint32_t *pair_out, const uint32_t *nc_arr, uint64_t *partial, unsigned long long *tau_key,
-                     uint32_t *saved_rows, int64_t max_item_rows) {
+                     uint32_t *saved_rows, int64_t max_item_rows, bool two_streams) {
     if (kprime < 1 || kprime > QK_KP || topk < 1 || topk > QK_KP || init < 1 || init > QK_INIT_MAX)
         return fail(ctx, PQ_EUNSUPPORTED, "ivf quick adc: kprime and topk must be 1..%d, init 1..%d", QK_KP, QK_INIT_MAX);
     hipStream_t s = ctx->stream;
@@ -496,21 +545,29 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
                                         (int)sizeof(QuickSmemLong)));
         PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(short_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)sizeof(QuickSmemShort)));
-        // the long items first (longest lists come first in the table of items), then the many short ones
+        // the long items first, the many short ones beside them on the context's second stream (calls of few pairs: behind them)
         const int cap_long = ivf_quick_saved_cap(max_item_rows, 8), cap_short = ivf_quick_saved_cap(QK_LONG_MIN, 4);
+        hipStream_t s2 = two_streams ? ctx->aux_stream : s;
+        if (two_streams) PQ_HIP(ctx, hipEventRecord(ctx->aux_fork, s));
         long_kernel<<<ctx->num_cu * 2, 8 * 64, sizeof(QuickSmemLong), s>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
-                                                                       kprime, partial, saved_rows, cap_long);
+                                                                       kprime, partial, saved_rows, cap_long, luts, probes, nc_arr, nprobe, topk, tau_key);
         PQ_HIP(ctx, hipGetLastError());
-        short_kernel<<<ctx->num_cu * 4, 4 * 64, sizeof(QuickSmemShort), s>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
+        if (two_streams) PQ_HIP(ctx, hipStreamWaitEvent(s2, ctx->aux_fork, 0));
+        short_kernel<<<ctx->num_cu * 4, 4 * 64, sizeof(QuickSmemShort), s2>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
                                                                           kprime, partial,
-                                                                          saved_rows + (size_t)ctx->num_cu * 2 * 8 * cap_long, cap_short);
+                                                                          saved_rows + (size_t)ctx->num_cu * 2 * 8 * cap_long, cap_short, luts, probes, nc_arr,
+                                                                          nprobe, topk, tau_key);
         PQ_HIP(ctx, hipGetLastError());
+        if (two_streams) {
+            PQ_HIP(ctx, hipEventRecord(ctx->aux_join, s2));
+            PQ_HIP(ctx, hipStreamWaitEvent(s, ctx->aux_join, 0));
+        }
     }
     if (ctx->profiling) {
         PQ_HIP(ctx, hipEventRecord(ctx->ev_end, s));
         ctx->ev_valid = 1;
     }
-    ivf_quick_rerank_kernel<<<npairs, 128, 0, s>>>(codes, luts, probes, nc_arr, pair_out, nprobe, kprime, topk, partial, tau_key);
+    ivf_quick_rerank_kernel<<<(npairs + QK_RR_PAIRS - 1) / QK_RR_PAIRS, QK_RR_THREADS, 0, s>>>(codes, luts, probes, nc_arr, pair_out, npairs, nprobe, kprime, topk, partial, tau_key);
     PQ_HIP(ctx, hipGetLastError());
     return PQ_OK;
 }

@@ -24,6 +24,7 @@ constexpr uint32_t TAU_REF_UNSET = 0xffffffffu;
 
 // One work item of the IVF search: a chunk of one inverted list for up to QB of the queries
 // that probe the list.
+constexpr int IVF_QUICK_LONG_CLASS = 16;   // Quick ADC: lists of 2^16 rows and more are scanned by the blocks of 8 waves
 struct IvfItem {
     uint32_t code_begin;   // first row of the chunk, rounded down to a 16-byte boundary
     uint32_t ncodes;       // rows from code_begin to the end of the chunk
@@ -37,9 +38,9 @@ struct IvfItem {
 // first result list; tau_key [nq] receives a bound of each query's result for the merge that follows.
 int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offsets, const int32_t *probes,
                      const float *luts, int nq, int nprobe, int init, int kprime, int topk, float *qmax_pair,
-                     uint8_t *qluts, const IvfItem *items, const uint32_t *nitems_dev, const int32_t *pairs_by_list,
+                     uint8_t *qluts, const IvfItem *items, uint32_t *nitems_dev, const int32_t *pairs_by_list,
                      const uint32_t *pair_out, const uint32_t *nc_arr, uint64_t *partial, unsigned long long *tau_key,
-                     uint32_t *saved_rows, int64_t max_item_rows);
+                     uint32_t *saved_rows, int64_t max_item_rows, bool two_streams);
 // bytes of `saved_rows` (rows that the counting pass of a work item hands to its collecting pass, per wave) when no
 // work item has more than max_item_rows rows
 size_t ivf_quick_saved_bytes(const pq_ctx *ctx, int64_t max_item_rows);

@@ -527,8 +527,28 @@ def test_ivf_grouping_of_small_calls(ctx, nlist, nq, nprobe):
     queries = (r.normal(size=(nq, d)) * 3).astype(np.float32)
     gd, gi, gp = ctx.ivf_adc_search(dev(coarse), dev(offsets), dev(codes), None, dev(cb), binding.CODES_U8, dev(queries), nprobe, topk,
                                     return_probes=True)
-    gd, gi, gp = host(gd), host(gi), host(gp)
-    od, oi, op = orc.ivf_search(coarse, offsets, codes, None, cb, orc.CODES_U8, queries, nprobe, topk)
+    gd, gi, gp = gd.cpu().numpy(), gi.cpu().numpy(), gp.cpu().numpy()
+    od, oi = orc.ivf_search(queries, coarse, offsets, codes, None, cb, orc.CODES_U8, nprobe, topk)
+    op, _ = orc.ivf_probe(queries, coarse, nprobe)
     assert np.array_equal(gp, op)
     np.testing.assert_allclose(gd, od, rtol=1e-5)
     assert (gi == oi).mean() > 0.99   # (near ties of random tables)
+
+
+@pytest.mark.parametrize("sizes,kprime,topk", [([65_534, 65_535, 65_536, 65_537, 3], 100, 100), ([70_001, 1, 0, 128, 129, 5000], 128, 10), ([65_535, 40], 10, 20)])
+def test_ivf_quick_lists_around_the_long_ones(ctx, opts, sizes, kprime, topk):
+    """Lists at the size that takes the other kernel, with and without a row of alignment in front, lists that are one item
+    (reranked by the scan) and, cut into chunks, several (reranked behind it): exact against the oracle either way."""
+    r = np.random.default_rng(sum(sizes))
+    nlist, d, n, nq = len(sizes), 32, sum(sizes), 11
+    coarse = (r.normal(size=(nlist, d)) * 3).astype(np.float32)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    packed = r.integers(0, 256, (n, 8), dtype=np.uint8)
+    cb = (r.normal(size=(16, 16, d // 16)) * 2).astype(np.float32)
+    queries = (r.normal(size=(nq, d)) * 3).astype(np.float32)
+    od, oi = orc.ivf_quick_search(queries, coarse, offsets, packed, None, cb, orc.CODES_U4_PACKED, nlist, 500, kprime, topk)
+    for rows in (None, 20_000):
+        if rows:
+            opts.set("ivf_quick_chunk_rows", rows)
+        gd, gi = ctx.ivf_quick_adc_search(dev(coarse), dev(offsets), dev(packed), None, dev(cb), dev(queries), nlist, 500, kprime, topk)[:2]
+        assert np.array_equal(gd.cpu().numpy(), od) and np.array_equal(gi.cpu().numpy(), oi)
