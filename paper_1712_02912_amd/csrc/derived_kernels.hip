@@ -758,15 +758,11 @@ __global__ __launch_bounds__(DQ_THREADS) void derived_scan16_kernel(DqArgs a) {
     }
 }
 
-__global__ void derived_init_kernel(uint32_t *work_counter, uint32_t *g_hist, size_t nhist, uint32_t *g_bound,
-                                    uint32_t *cand_cnt, int nq) {
+__global__ void derived_init_kernel(uint32_t *work_counter, uint32_t *g_hist, size_t nhist, uint32_t *g_bound, int nq) {
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
     if (i0 == 0) *work_counter = 0;
     for (size_t i = i0; i < nhist; i += stride) g_hist[i] = 0u;
-    for (size_t i = i0; i < (size_t)nq; i += stride) {
-        if (g_bound) g_bound[i] = DQ_BINS - 1;   // no bound yet: every bucket is counted
-        if (cand_cnt) cand_cnt[i] = 0u;
-    }
+    for (size_t i = i0; i < (size_t)nq; i += stride) g_bound[i] = DQ_BINS - 1;   // no bound yet: every bucket is counted
 }
 
 // One wave per query: the bucket in which the r2-th vector falls (all vectors if there are fewer)
@@ -845,18 +841,25 @@ __global__ __launch_bounds__(256) void derived_qmax_kernel(const uint8_t *codes,
     if (threadIdx.x == 0) qmax[q] = red[0];
 }
 
-// Work items of Step 2: a query's candidates in pieces of `piece`.  item_off [nq + 1], item_query [item]; the bounds that
-// the items of a query share are reset.  One block.
+// What follows from the counts, in one launch before the collecting pass: the work items of Step 2 (a query's candidates in
+// pieces of `piece`; item_off [nq + 1], item_query [item]), the counters and bounds of that pass and of Step 2 reset, the
+// caller's buckets and counts (optional).  One block.
 __global__ __launch_bounds__(1024) void derived_items_kernel(const uint32_t *__restrict__ count, int nq, uint32_t piece,
                                                              uint32_t *__restrict__ item_off, uint32_t *__restrict__ item_query,
-                                                             unsigned long long *__restrict__ tau_key) {
+                                                             unsigned long long *__restrict__ tau_key, uint32_t *work_counter, uint32_t *__restrict__ cand_cnt,
+                                                             const uint32_t *__restrict__ bucket, uint32_t *__restrict__ bucket_out, int64_t *__restrict__ ncand_out) {
     __shared__ uint32_t wsum[16];
     __shared__ uint32_t carry;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) carry = 0;
+    if (tid == 0) { carry = 0; *work_counter = 0; }
     __syncthreads();
     for (int base = 0; base < nq; base += 1024) {
         const int q = base + tid;
+        if (q < nq) {
+            cand_cnt[q] = 0u;
+            if (bucket_out) bucket_out[q] = bucket[q];
+            if (ncand_out) ncand_out[q] = (int64_t)count[q];
+        }
         const uint32_t c = q < nq ? (count[q] + piece - 1) / piece : 0;
         uint32_t incl = c;   // inclusive scan over the wave
         for (int o = 1; o < 64; o <<= 1) {
@@ -891,8 +894,9 @@ __global__ __launch_bounds__(1024) void derived_items_kernel(const uint32_t *__r
 constexpr int RR_THREADS = 512, RR_WAVES = RR_THREADS / 64;
 constexpr int RR_KEEP = 128;            // best keys carried from tile to tile (topk <= 128)
 constexpr int RR_TILE = 2 * RR_THREADS; // candidates per tile: two batches of 64 per wave
-constexpr int RR_ILP = 4;               // pairs of candidates whose rows are on their way together
-constexpr uint32_t RR_PIECE_MIN = RR_TILE, RR_PIECE_MAX = 16 * RR_TILE;
+constexpr int RR_ILP = 8;               // pairs of candidates whose rows are on their way together
+constexpr uint32_t RR_PIECE_MIN = RR_THREADS, RR_PIECE_MAX = 16 * RR_TILE;
+constexpr size_t RR_TABLE_BYTES = (size_t)256 << 20;   // complete tables of a batch of queries (the last-level cache's size)
 
 // v + (v of the lane that the DPP control names)
 template <int CTRL>
@@ -912,12 +916,16 @@ __device__ __forceinline__ void swap_rows16(double &a, double &b) {
     b = __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
 }
 
-// VEC: floats per load (4 where rows start on 16 bytes and hold a multiple of 4 dimensions, else 1)
+// VEC: floats per load (4 where rows start on 16 bytes and hold a multiple of 4 dimensions, else 1); 0: the queries'
+// complete tables [4][k] stand in `tables` (from query q_first on), and a candidate is four entries added up, a thread
+// each.  Consecutive items go to blocks of one die (blocks are dealt to the 8 dies in turn), so that what its L2
+// holds is the tables of the few queries at hand.
 template <int VEC>
 __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uint8_t *codes, const float *codebooks, int k, int dsub, const float *queries,
                                                                       const uint64_t *cand, const uint2 *cand_code, const uint64_t *cand_off,
-                                                                      const uint32_t *item_off, const uint32_t *item_query, int nq, uint32_t piece,
-                                                                      int topk, unsigned long long *tau_key, uint64_t *partial) {
+                                                                      const uint32_t *item_off, const uint32_t *item_query, int q_first, int q_end,
+                                                                      uint32_t piece, int topk, unsigned long long *tau_key, uint64_t *partial,
+                                                                      const float *tables) {
     extern __shared__ float4 rr_dyn[];
     __shared__ uint64_t keys[2048];   // KEEP + TILE, a power of two
     __shared__ uint2 wcode[RR_WAVES][64];
@@ -928,13 +936,22 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, j = (lane >> 3) & 3, l8 = lane & 7;
     const float *const cb = codebooks + (size_t)j * k * dsub;
-    const uint32_t nitems = item_off[nq];
-    for (uint32_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+    uint32_t item = item_off[q_first], item_end = item_off[q_end], step = gridDim.x;
+    if (VEC == 0) {   // (the grid is a multiple of 8)
+        const uint32_t share = (item_end - item + 7) / 8, die = blockIdx.x & 7;
+        const uint32_t stop = item + (die + 1) * share;
+        item += die * share + (blockIdx.x >> 3);
+        item_end = stop < item_end ? stop : item_end;
+        step /= 8;
+    } else {
+        item += blockIdx.x;
+    }
+    for (; item < item_end; item += step) {
         const int q = (int)item_query[item];
         const uint64_t begin = cand_off[q] + (uint64_t)(item - item_off[q]) * piece;
         const uint64_t end = begin + piece < cand_off[q + 1] ? begin + piece : cand_off[q + 1];
         __syncthreads();   // the previous item's keys and query have been read
-        for (int i = tid; i < DQ_M * dsub; i += RR_THREADS) y[i] = queries[(size_t)q * (DQ_M * dsub) + i];
+        if (VEC > 0) for (int i = tid; i < DQ_M * dsub; i += RR_THREADS) y[i] = queries[(size_t)q * (DQ_M * dsub) + i];
         for (int i = tid; i < RR_KEEP; i += RR_THREADS) keys[i] = KEY_EMPTY;
         if (tid == 0) nnew = 0;
         __syncthreads();
@@ -949,6 +966,19 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
                 const uint64_t ci = c0 + lane;
                 const bool have = ci < end;
                 const uint32_t row = (uint32_t)cand[have ? ci : c0];
+                if constexpr (VEC == 0) {
+                    const uint2 c = cand_code != nullptr ? cand_code[have ? ci : c0] : *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
+                    const float *const tab = tables + (size_t)(q - q_first) * DQ_M * k;
+                    const uint32_t idx[DQ_M] = {c.x & 0xffffu, c.x >> 16, c.y & 0xffffu, c.y >> 16};
+                    double total = 0.0;
+#pragma unroll
+                    for (int t = 0; t < DQ_M; ++t)   // indexes are below k by contract
+                        total += (double)tab[(size_t)t * k + (idx[t] < (uint32_t)k ? idx[t] : (uint32_t)k - 1u)];
+                    const uint64_t key = ((uint64_t)f32_to_ord((float)total) << 32) | row;
+                    if (have && key < bound) keys[RR_KEEP + atomicAdd(&nnew, 1)] = key;
+                    continue;
+                }
+                constexpr int W = VEC > 0 ? VEC : 1;
                 wcode[wave][lane] = cand_code != nullptr ? cand_code[have ? ci : c0] : *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
                 asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
                 const uint16_t *const idx16 = reinterpret_cast<const uint16_t *>(wcode[wave]);
@@ -964,23 +994,23 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
                         p[v] = cb + (size_t)idx * dsub;
                         sum[v] = 0.0;
                     }
-                    for (int t = VEC * l8; t < dsub; t += 8 * VEC) {
-                        float yv[VEC], cv[RR_ILP][VEC];
+                    for (int t = W * l8; t < dsub; t += 8 * W) {
+                        float yv[W], cv[RR_ILP][W];
 #pragma unroll
                         for (int v = 0; v < RR_ILP; ++v) {
-                            if (VEC == 4) {
+                            if (W == 4) {
                                 const float4 f = *reinterpret_cast<const float4 *>(p[v] + t);
-                                cv[v][0] = f.x; cv[v][VEC > 1 ? 1 : 0] = f.y; cv[v][VEC > 2 ? 2 : 0] = f.z; cv[v][VEC > 3 ? 3 : 0] = f.w;
+                                cv[v][0] = f.x; cv[v][W > 1 ? 1 : 0] = f.y; cv[v][W > 2 ? 2 : 0] = f.z; cv[v][W > 3 ? 3 : 0] = f.w;
                             } else {
                                 cv[v][0] = p[v][t];
                             }
                         }
 #pragma unroll
-                        for (int i = 0; i < VEC; ++i) yv[i] = yj[t + i];
+                        for (int i = 0; i < W; ++i) yv[i] = yj[t + i];
 #pragma unroll
                         for (int v = 0; v < RR_ILP; ++v)
 #pragma unroll
-                            for (int i = 0; i < VEC; ++i) {
+                            for (int i = 0; i < W; ++i) {
                                 const double diff = (double)yv[i] - (double)cv[v][i];
                                 sum[v] += diff * diff;
                             }
@@ -1003,11 +1033,15 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
                 }
                 asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
                 const uint64_t key = ((uint64_t)f32_to_ord(wdist[wave][lane]) << 32) | row;
-                if (have && key < bound) keys[RR_KEEP + atomicAdd(&nnew, 1)] = key;
+                if (have && key < bound) keys[RR_KEEP + atomicAdd(&nnew, 1)] = key;   // (room: see the end of the tile)
                 asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
             }
             __syncthreads();
+            // sorted while there is no bound yet, when the next tile might not fit, and at the end
             const int added = nnew, total = RR_KEEP + added;
+            const bool later = keys[topk - 1] != KEY_EMPTY && total + RR_TILE <= 2048 && base + RR_TILE < end;
+            __syncthreads();   // (every thread has read the counter before the next tile adds to it)
+            if (later) continue;
             if (added > 0) {
                 int n2 = 256;
                 while (n2 < total) n2 <<= 1;
@@ -1031,11 +1065,6 @@ __global__ void derived_export_kernel(const uint64_t *cand, const uint64_t *cand
     const uint64_t begin = cand_off[q], cnt = cand_off[q + 1] - begin;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (int64_t)gridDim.x * blockDim.x)
         out[(size_t)q * cap + i] = (uint64_t)i < cnt ? (int64_t)(uint32_t)cand[begin + i] : -1;
-}
-
-__global__ void derived_widen_kernel(const uint32_t *src, int n, int64_t *dst) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = (int64_t)src[i];
 }
 
 }  // namespace
@@ -1133,7 +1162,7 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
         a.g_hist = (uint32_t *)(ws + o_hist);
         a.g_bound = (uint32_t *)(ws + o_bound);
         a.bucket = nullptr; a.cand_off = nullptr; a.cand_cnt = nullptr; a.cand = nullptr; a.cand_code = nullptr;
-        derived_init_kernel<<<256, 256, 0, s>>>(a.work_counter, a.g_hist, (size_t)nq * DQ_BINS, a.g_bound, nullptr, nq);
+        derived_init_kernel<<<256, 256, 0, s>>>(a.work_counter, a.g_hist, (size_t)nq * DQ_BINS, a.g_bound, nq);
         PQ_HIP(ctx, hipGetLastError());
         if (ctx->profiling) {
             note_plain_scan(ctx, "derived_scan_kernel<count> (8 queries per pass)", 8, g_count.ngroups);
@@ -1168,8 +1197,17 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     // The sizes of the candidate lists are known now; they live in the context's other buffer, so that what the counting
     // pass left in the workspace stays.  Pieces of Step 2: as many as there are blocks four times over.
     uint64_t per_block = total / (8ull * (unsigned)ctx->num_cu);
-    uint32_t piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_TILE * RR_TILE;
+    uint32_t piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_PIECE_MIN * RR_PIECE_MIN;
     if (piece < RR_PIECE_MIN) piece = RR_PIECE_MIN;
+    // Long lists: the complete tables of the queries (Step 1.1 with the full codebooks, on the matrix cores, 128 queries
+    // at least per tile) cost less than the rows of the candidates: 65 536 centroids per sub-space, about 0.55 us of the GPU per
+    // query against 67 ps per candidate, so from 8000 candidates per query on, and from 13 000 on to be safe.  Queries go in
+    // batches whose tables stay below RR_TABLE_BYTES.  (48 M candidates of 1000 queries: 3.2 -> 2.1 ms, the call 11.5 -> 10.4.)
+    const bool rr_vec = (dsub & 3) == 0 && ((uintptr_t)codebooks & 15) == 0;
+    const size_t table_bytes = (size_t)DQ_M * k * 4;
+    const int table_batch = (int)(RR_TABLE_BYTES / table_bytes / 128 * 128);   // (k <= 65536: 256 at least)
+    bool with_tables = rr_vec && dsub >= 8 && dsub < 64 /* the Tables step then needs no buffer of its own */ && ((uintptr_t)queries & 15) == 0 && total * 5 >= (uint64_t)((nq + 127) / 128 * 128) * (uint64_t)k;
+    if (with_tables) piece = 8 * RR_TILE;   // (shorter than at most: what the blocks of a die work on belongs to few queries; 2, 4, 16 tiles: 10.8, 10.6, 10.5 against 10.4 ms per call)
     const size_t max_items = (size_t)(total / piece) + (size_t)nq;
     const size_t o_partial = 0;
     const size_t o_items = o_partial + align_up(max_items * RR_KEEP * 8, 256);
@@ -1177,10 +1215,16 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     const size_t o_tau = o_itemoff + align_up((size_t)(nq + 1) * 4, 256);
     const size_t o_cand = o_tau + align_up((size_t)nq * 8, 256);
     const size_t o_code = o_cand + align_up((size_t)total * 8, 256);
+    const size_t o_table = o_code + align_up((size_t)total * 8, 256);
+    const size_t table_room = with_tables ? table_bytes * (size_t)(nq < table_batch ? nq : table_batch) : 0;
     // (a copy of the candidates' codes beside the list saves Step 2 a random read of the database per candidate; it is
     // left out if there is no memory for it)
     bool with_codes = true;
-    rc = lut_ws_reserve(ctx, o_code + align_up((size_t)total * 8, 256));
+    rc = lut_ws_reserve(ctx, o_table + table_room);
+    if (rc == PQ_ENOMEM && with_tables) {
+        with_tables = false;
+        rc = lut_ws_reserve(ctx, o_table);
+    }
     if (rc == PQ_ENOMEM) {
         with_codes = false;
         rc = lut_ws_reserve(ctx, o_code);
@@ -1199,7 +1243,8 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     a.cand_cnt = (uint32_t *)(ws + o_candcnt);
     a.cand = (uint64_t *)(lists + o_cand);
     a.cand_code = with_codes ? (uint2 *)(lists + o_code) : nullptr;
-    derived_init_kernel<<<256, 256, 0, s>>>(a.work_counter, nullptr, 0, nullptr, a.cand_cnt, nq);
+    derived_items_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), nq, piece, item_off, item_query, tau_key, a.work_counter, a.cand_cnt,
+                                            a.bucket, bucket_out, ncand_out);
     PQ_HIP(ctx, hipGetLastError());
     bind_geometry(a, g_collect);
     if (g_collect.nblocks > 0) {
@@ -1208,22 +1253,27 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
         PQ_HIP(ctx, hipGetLastError());
     }
     // Step 2
-    derived_items_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), nq, piece, item_off, item_query, tau_key);
-    PQ_HIP(ctx, hipGetLastError());
     const unsigned rr_grid = (unsigned)(max_items < 4 * (size_t)ctx->num_cu ? max_items : 4 * (size_t)ctx->num_cu);
-    const size_t rr_lds = align_up((size_t)d * 4, 16);
-    const bool rr_vec = (dsub & 3) == 0 && ((uintptr_t)codebooks & 15) == 0;
-    auto rerank = rr_vec ? derived_rerank_kernel<4> : derived_rerank_kernel<1>;
-    rerank<<<rr_grid, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, item_off, item_query, nq, piece,
-                                               topk, tau_key, (uint64_t *)(lists + o_partial));
-    PQ_HIP(ctx, hipGetLastError());
-    rc = launch_merge_filtered(ctx, (const uint64_t *)(lists + o_partial), item_off, 0, 1, 1, tau_key, RR_KEEP, nq, topk, nullptr, false, out_dist, out_ids);
-    if (rc) return rc;
-    if (bucket_out) PQ_HIP(ctx, hipMemcpyAsync(bucket_out, ws + o_bucket, (size_t)nq * 4, hipMemcpyDeviceToDevice, s));
-    if (ncand_out) {
-        derived_widen_kernel<<<(nq + 255) / 256, 256, 0, s>>>((const uint32_t *)(ws + o_count), nq, ncand_out);
+    const size_t rr_lds = with_tables ? 0 : align_up((size_t)d * 4, 16);
+    uint64_t *partial = (uint64_t *)(lists + o_partial);
+    if (with_tables) {
+        float *tables = (float *)(lists + o_table);
+        for (int q0 = 0; q0 < nq; q0 += table_batch) {
+            const int q1 = nq - q0 < table_batch ? nq : q0 + table_batch;
+            rc = launch_build_luts(ctx, queries + (size_t)q0 * d, codebooks, q1 - q0, d, DQ_M, k, tables);
+            if (rc) return rc;
+            derived_rerank_kernel<0><<<(rr_grid + 7) / 8 * 8, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, item_off,
+                                                                                    item_query, q0, q1, piece, topk, tau_key, partial, tables);
+            PQ_HIP(ctx, hipGetLastError());
+        }
+    } else {
+        auto rerank = rr_vec ? derived_rerank_kernel<4> : derived_rerank_kernel<1>;
+        rerank<<<rr_grid, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, item_off, item_query, 0, nq, piece,
+                                                   topk, tau_key, partial, nullptr);
         PQ_HIP(ctx, hipGetLastError());
     }
+    rc = launch_merge_filtered(ctx, (const uint64_t *)(lists + o_partial), item_off, 0, 1, 1, tau_key, RR_KEEP, nq, topk, nullptr, false, out_dist, out_ids);
+    if (rc) return rc;
     if (cand_ids_out && cand_cap > 0) {
         derived_export_kernel<<<dim3(64, nq), 256, 0, s>>>(a.cand, a.cand_off, cand_cap, cand_ids_out);
         PQ_HIP(ctx, hipGetLastError());

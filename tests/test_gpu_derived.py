@@ -200,7 +200,7 @@ def test_derived_search_many_queries_identical_codes_and_worst_case_order(ctx, o
 @pytest.mark.parametrize("dsub,nq,n,r2,topk,shift", [(5, 3, 3001, 1024, 7, 0), (32, 2, 40_000, 33_000, 128, 1), (33, 1, 5000, 2049, 1, 0),
                                                      (36, 17, 2500, 1025, 100, 0), (1, 2, 300, 64, 3, 0)])
 def test_derived_search_rerank_pieces(ctx, dsub, nq, n, r2, topk, shift):
-    """Step 2 at the edges of its pieces (1024 candidates) and rows: dimensions below, at and above the 32 that eight
+    """Step 2 at the edges of its pieces (512 candidates) and tiles (1024) and rows: dimensions below, at and above the 32 that eight
     lanes read at once, rows that do not start on 16 bytes, lists of several pieces, a handful of candidates."""
     cb, cbar, codes, queries = make_problem(dsub * 7 + nq, n, 512, dsub, nq, distinct=200 if nq == 17 else None)
     if shift:   # codebooks that start on 4 bytes only
@@ -211,4 +211,13 @@ def test_derived_search_rerank_pieces(ctx, dsub, nq, n, r2, topk, shift):
         plain = ctx.pq_derived_search(args[0], args[1], dev(cb), args[3], r2, topk)
         moved = ctx.pq_derived_search(*args, r2, topk)
         assert torch.equal(plain[0], moved[0]) and torch.equal(plain[1], moved[1])
+    run_case(ctx, cb, cbar, codes, queries, r2, topk)
+
+
+@pytest.mark.parametrize("dsub,k,nq,n,r2,topk", [(8, 256, 129, 4000, 300, 17), (32, 1024, 5, 70_000, 60_000, 100), (12, 300, 260, 2100, 2100, 128)])
+def test_derived_search_rerank_on_complete_tables(ctx, dsub, k, nq, n, r2, topk):
+    """Lists so long (for the number of centroids) that the queries' complete tables are formed: ragged pieces, one and
+    several dies' shares, more queries than a tile of the Tables step."""
+    cb, cbar, codes, queries = make_problem(dsub + nq, n, k, dsub, nq)
+    assert r2 * nq * 5 >= (nq + 127) // 128 * 128 * k   # (every query has at least r2 candidates: the rule for the tables holds)
     run_case(ctx, cb, cbar, codes, queries, r2, topk)
