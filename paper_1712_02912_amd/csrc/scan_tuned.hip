@@ -151,6 +151,7 @@ constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bou
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
 constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan
+constexpr int64_t U4_SEED_MIN_N = 512;     // the integer scan takes a first bound from here on
 constexpr int PRUNE_INIT = 4096;           // codes looked at for the first bound of every query
 constexpr int PRUNE_MARGIN = 8;      // slack of the integer threshold, in table units
 constexpr float PRUNE_RANGE = 3500.f;  // table units between the sum of the minima and the first bound
@@ -1665,7 +1666,7 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
 // encoded codes, 8 queries, top-1000: call 414 -> 386, 353 -> 312 us on data with many ties.)
 constexpr int SLICE_BINS = 512;
 template <int NT>   // code bytes, 8 or 16
-__global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__restrict__ codes, int64_t cnt,
+__global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__restrict__ codes, int64_t cnt, int slice,
                                                             const uint8_t *__restrict__ qluts, uint32_t *seed_hist, uint32_t *slice_hist) {
     __shared__ uint32_t hist[4096];
     __shared__ uint8_t tab[NT * 32];
@@ -1673,8 +1674,8 @@ __global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__res
     if (tid < NT * 32) tab[tid] = qluts[(size_t)q * (NT * 32) + tid];
     for (int i = tid; i < 4096; i += 1024) hist[i] = 0;
     __syncthreads();
-    const int64_t begin = (int64_t)blockIdx.x * (1 << 16);
-    const int64_t end = begin + (1 << 16) < cnt ? begin + (1 << 16) : cnt;
+    const int64_t begin = (int64_t)blockIdx.x * slice;
+    const int64_t end = begin + slice < cnt ? begin + slice : cnt;
     for (int64_t i0 = begin + tid; i0 < end; i0 += 4 * 1024) {
         uint32_t c[4][NT / 4];
 #pragma unroll
@@ -1707,7 +1708,7 @@ __global__ __launch_bounds__(1024) void u4_seed_hist_kernel(const uint8_t *__res
 }
 
 __global__ __launch_bounds__(64) void u4_seed_pick_kernel(const uint32_t *__restrict__ seed_hist, int kq, int bins, const uint32_t *__restrict__ slice_hist,
-                                                          int nslices, int64_t cnt, unsigned long long *tau_key) {
+                                                          int nslices, int slice, int64_t cnt, unsigned long long *tau_key) {
     const int q = blockIdx.x, lane = threadIdx.x;
     const uint32_t *const hist = seed_hist + (size_t)q * 4096;
     const int b = hist_threshold(hist, kq);   // one wave; smallest sum with kq counted codes at or below it
@@ -1727,7 +1728,7 @@ __global__ __launch_bounds__(64) void u4_seed_pick_kernel(const uint32_t *__rest
             }
             const uint64_t reach = __ballot(carry + v >= need);
             if (reach != 0ull) {
-                const int64_t end = (int64_t)(s0 + __builtin_ctzll(reach) + 1) * (1 << 16);
+                const int64_t end = (int64_t)(s0 + __builtin_ctzll(reach) + 1) * slice;
                 last_row = (uint32_t)((end < cnt ? end : cnt) - 1);
                 break;
             }
@@ -2289,7 +2290,8 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // Few query groups stream their codes from memory (eight sub-tiles per group of a wave), unless the database is so
     // small that a block's share is under four block tiles of that shape: there the finer groups spread it over more
     // blocks, and it comes from the caches.
-    const bool stream = few_groups && n * ngroups >= (int64_t)nblocks_max * 4 * (8 * 64 * (16 / cb) * TUNED_WAVES);
+    const int64_t fine_tile = 2 * 64 * (16 / cb) * TUNED_WAVES;
+    const bool stream = few_groups && (n <= fine_tile || n * ngroups >= (int64_t)nblocks_max * 16 * fine_tile);   // (a single fine tile: nothing to spread)
     const int tile = 64 * (16 / cb) * (stream ? 8 : 2);   // codes per wave group (DEPTH sub-tiles)
     const int64_t block_tile = (int64_t)tile * TUNED_WAVES;
 
@@ -2320,8 +2322,8 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     least_tiles = least_tiles < 1 ? 1 : (least_tiles > 8 ? 8 : least_tiles);
     const int64_t max_by_n = (n_main + least_tiles * block_tile - 1) / (least_tiles * block_tile);
     if (nchunks > max_by_n) nchunks = max_by_n;
-    // (a little more than one item per block would be two rounds)
-    if (nchunks * ngroups > nblocks_max && nchunks * ngroups < 2 * (int64_t)nblocks_max && ngroups <= nblocks_max) nchunks = nblocks_max / ngroups;
+    // (a little more than one item per block would be two rounds: fewer, longer chunks where that is less than the two)
+    if (nchunks * ngroups > nblocks_max && 5 * (nblocks_max / ngroups) > 3 * nchunks) nchunks = nblocks_max / ngroups;
     const int64_t min_chunks = (n_main + ((int64_t)1 << 30) - 1) >> 30;   // a chunk's rows are counted in 32 bits
     if (nchunks < min_chunks) nchunks = min_chunks;
     if (nchunks < 1) nchunks = 1;
@@ -2352,6 +2354,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     int seed_codes_few = (int)(n / 16 < SEED_CODES_STREAM ? n / 16 : SEED_CODES_STREAM);
     if (seed_codes_few < 16 * topk) seed_codes_few = 16 * topk;
     if (seed_codes_few < PRUNE_INIT) seed_codes_few = PRUNE_INIT;
+    if ((int64_t)seed_codes_few > n) seed_codes_few = (int)n;
     if (few_groups) {
         int64_t want = ((int64_t)64 << 20) / (nq > 0 ? nq : 1);
         if (want > n / 32) want = n / 32;
@@ -2359,16 +2362,25 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     }
     const bool wide_ok = opt_int(ctx, PQ_OPT_SCAN_WIDE_SEED, 1) != 0;
     const bool wide_seed = wide_ok && prune && few_groups && tables == 8 && seed_codes_f32 > SEED_SLICE;
-    const bool wide_seed_u4 = wide_ok && is_u4 && few_groups && n >= PRUNE_MIN_N && seed_codes_f32 > SEED_SLICE;
+    // The integer scan of few query groups always takes its first bound from slices, a block for every (slice, query): slices
+    // of 65 536 codes of a large sample, of 8192 codes of the small one (one block per four queries adding up the whole
+    // sample: 1 M codes of 32 indexes, 100 queries 126 us of a call of 480 us; now 365).  Small databases take one as well: without a bound
+    // every code is a candidate at first (10 000 codes of 16 indexes, 29 queries, top-100: two-pass call 282 -> 81 us).
+    const bool seed_u4 = is_u4 && n >= U4_SEED_MIN_N && n >= 2 * (int64_t)topk;
+    bool wide_seed_u4 = wide_ok && seed_u4 && few_groups;
+    const int64_t seed_codes_u4 = seed_codes_f32 > SEED_SLICE ? seed_codes_f32 : seed_codes_few;
+    const int seed_slice_u4 = seed_codes_f32 > SEED_SLICE ? SEED_SLICE : SEED_SLICE / 8;
     const size_t off_seedhist = prune ? off_qtabs + align_up((size_t)ngroups * 256 * tables * sizeof(uint4), 256) : off_tau0;
     // 16 queries per pass: the 16-bit tables of the second test (64 KB per group) and their scales
     const size_t off_seedref = off_seedhist + align_up(wide_seed ? (size_t)nq * HIST_BINS * 4 : 0, 256);   // (wide first bound: reference of the bins per query)
     const size_t off_qtabs16 = off_seedref + align_up(wide_seed ? (size_t)ntau * 4 : 0, 256);
     const size_t off_pscale16 = off_qtabs16 + (q8 ? (size_t)ngroups * 4096 * sizeof(uint4) : 0);
-    const size_t total = prune ? off_pscale16 + (q8 ? align_up((size_t)ntau * 4, 256) : 0)
-                               : (wide_seed_u4 ? off_seedhist + (size_t)nq * 4096 * 4 : (seed_plain ? off_poff : off_tau0));
-    // (counts by slice of the integer scan's wide first bound: left out where the fixed scratch has no room for them)
-    const int seed_slices = (int)((seed_codes_f32 + SEED_SLICE - 1) / SEED_SLICE);
+    const size_t total_plain = prune ? off_pscale16 + (q8 ? align_up((size_t)ntau * 4, 256) : 0) : (seed_plain ? off_poff : off_tau0);
+    // (where the fixed scratch has no room for the bins, the integer scan's first bound comes from one block per four queries;
+    // where it has none for the counts by slice, these are left out)
+    if (wide_seed_u4 && ctx->ws_fixed && off_seedhist + (size_t)nq * 4096 * 4 > ctx->ws_bytes) wide_seed_u4 = false;
+    const size_t total = wide_seed_u4 ? off_seedhist + (size_t)nq * 4096 * 4 : total_plain;
+    const int seed_slices = (int)((seed_codes_u4 + seed_slice_u4 - 1) / seed_slice_u4);
     const size_t off_slices = align_up(total, 256), slices_bytes = wide_seed_u4 ? (size_t)nq * seed_slices * SLICE_BINS * 4 : 0;
     const bool with_slices = wide_seed_u4 && !(ctx->ws_fixed && off_slices + slices_bytes > ctx->ws_bytes);
     rc = ws_reserve(ctx, with_slices ? off_slices + slices_bytes : total);
@@ -2440,14 +2452,14 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
                                                          seed_plain ? 1.f + 4e-6f : 1.f, seed_hist_u4, wide_seed_u4 ? (size_t)nq * 4096 : 0);
         PQ_HIP(ctx, hipGetLastError());
     }
-    if (is_u4 && n >= PRUNE_MIN_N) {
+    if (seed_u4) {
         if (wide_seed_u4) {
             uint32_t *seed_hist = (uint32_t *)(ws + off_seedhist);
             uint32_t *slice_hist = with_slices ? (uint32_t *)(ws + off_slices) : nullptr;
             const dim3 sgrid((unsigned)seed_slices, (unsigned)nq);
-            if (u4_m32) u4_seed_hist_kernel<16><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist, slice_hist);
-            else u4_seed_hist_kernel<8><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, (const uint8_t *)luts, seed_hist, slice_hist);
-            u4_seed_pick_kernel<<<nq, 64, 0, ctx->stream>>>(seed_hist, topk, exact_bins(cb), slice_hist, seed_slices, seed_codes_f32, a.tau_key);
+            if (u4_m32) u4_seed_hist_kernel<16><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_u4, seed_slice_u4, (const uint8_t *)luts, seed_hist, slice_hist);
+            else u4_seed_hist_kernel<8><<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_u4, seed_slice_u4, (const uint8_t *)luts, seed_hist, slice_hist);
+            u4_seed_pick_kernel<<<nq, 64, 0, ctx->stream>>>(seed_hist, topk, exact_bins(cb), slice_hist, seed_slices, seed_slice_u4, seed_codes_u4, a.tau_key);
         } else {
             // 256 codes per result wanted, between PRUNE_INIT and 262 144 (top-1000: 4.11 -> 3.94 ms per step; twice as many
             // cost the seed kernel more than they save the scan)

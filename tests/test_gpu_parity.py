@@ -756,7 +756,7 @@ def test_scan_16_queries_per_pass_first_round_of_short_items(ctx, opts):
         run_int_scan(ctx, codes, orc.CODES_U4_PACKED, quantized_like_tables(r, nq), topk)
 
 
-@pytest.mark.parametrize("n,nq,topk", [(1, 1, 1), (63, 3, 100), (4097, 9, 128), (65_535, 8, 129), (65_537, 11, 1000), (200_003, 260, 100),
+@pytest.mark.parametrize("n,nq,topk", [(1, 1, 1), (63, 3, 100), (1023, 4, 128), (1024, 5, 128), (1023, 300, 600), (3000, 300, 1000), (4097, 9, 128), (65_535, 8, 129), (65_537, 11, 1000), (200_003, 260, 100),
                                       (140_001, 70, 1024), (2_200_001, 2, 1000)])
 def test_scan_u4_32_tables(ctx, n, nq, topk):
     """32 x 4 codes: tables like quantised distances (small sums), uniform bytes (sums around 4080, where the bins of the
@@ -768,6 +768,18 @@ def test_scan_u4_32_tables(ctx, n, nq, topk):
              lambda: r.integers(0, 2, (32, 16))]
     for q in range(1, nq, 2):
         qluts[q] = kinds[(q // 2) % len(kinds)]()
+    run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
+
+
+@pytest.mark.parametrize("n,nq,topk", [(511, 3, 100), (512, 9, 100), (512, 300, 256), (513, 2, 257), (8191, 30, 1000), (8193, 30, 100),
+                                      (20_000, 260, 1000), (4097, 300, 100), (40_000, 7, 1024)])
+def test_scan_u4_first_bound_of_small_databases(ctx, n, nq, topk):
+    """16 x 4 codes from where the integer scan takes a first bound on: one and several slices, few and many queries, k
+    half of the codes and more."""
+    r = np.random.default_rng(n + nq)
+    packed = r.integers(0, 256, (n, 8), dtype=np.uint8)
+    qluts = quantized_like_tables(r, nq)
+    qluts[0] = 255
     run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
 
 
