@@ -2291,7 +2291,9 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // small that a block's share is under four block tiles of that shape: there the finer groups spread it over more
     // blocks, and it comes from the caches.
     const int64_t fine_tile = 2 * 64 * (16 / cb) * TUNED_WAVES;
-    const bool stream = few_groups && (n <= fine_tile || n * ngroups >= (int64_t)nblocks_max * 16 * fine_tile);   // (a single fine tile: nothing to spread)
+    // (Not with the fixed scratch of the call that allocates nothing: more blocks need more of it than it may hold.)
+    const bool spread = !ctx->ws_fixed;
+    const bool stream = few_groups && (!spread || n <= fine_tile || n * ngroups >= (int64_t)nblocks_max * 16 * fine_tile);   // (a single fine tile: nothing to spread)
     const int tile = 64 * (16 / cb) * (stream ? 8 : 2);   // codes per wave group (DEPTH sub-tiles)
     const int64_t block_tile = (int64_t)tile * TUNED_WAVES;
 
@@ -2319,11 +2321,11 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // (down to one block tile where chunks of eight would leave blocks without work: 10^5 codes, 16 queries were two
     // items on the chip and are 50 now: scan 138 -> 29 us)
     int64_t least_tiles = n_main * ngroups / ((int64_t)nblocks_max * block_tile);
-    least_tiles = least_tiles < 1 ? 1 : (least_tiles > 8 ? 8 : least_tiles);
+    least_tiles = least_tiles > 8 || !spread ? 8 : (least_tiles < 1 ? 1 : least_tiles);
     const int64_t max_by_n = (n_main + least_tiles * block_tile - 1) / (least_tiles * block_tile);
     if (nchunks > max_by_n) nchunks = max_by_n;
     // (a little more than one item per block would be two rounds: fewer, longer chunks where that is less than the two)
-    if (nchunks * ngroups > nblocks_max && 5 * (nblocks_max / ngroups) > 3 * nchunks) nchunks = nblocks_max / ngroups;
+    if (spread && nchunks * ngroups > nblocks_max && 5 * (nblocks_max / ngroups) > 3 * nchunks) nchunks = nblocks_max / ngroups;
     const int64_t min_chunks = (n_main + ((int64_t)1 << 30) - 1) >> 30;   // a chunk's rows are counted in 32 bits
     if (nchunks < min_chunks) nchunks = min_chunks;
     if (nchunks < 1) nchunks = 1;

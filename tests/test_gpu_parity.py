@@ -816,6 +816,18 @@ def test_scan_u4_32_tables_copies_and_fixed_scratch(ctx):
         assert torch.equal(s, s2) and torch.equal(i, i2)
 
 
+@pytest.mark.parametrize("fmt,m,k,nq,n", [(orc.CODES_U8, 8, 256, 16, 1_000_003), (orc.CODES_U4_PACKED, 16, 16, 9, 500_001), (orc.CODES_U8, 16, 256, 8, 300_007)])
+def test_scan_long_results_with_fixed_scratch(ctx, fmt, m, k, nq, n):
+    """Long results of a database that plain calls spread over the chip: with the fixed scratch, which has no room for as
+    many blocks' lists, the call is served in fewer."""
+    r = np.random.default_rng(m + nq)
+    codes = dev(r.integers(0, 256, (n, m // 2 if fmt == orc.CODES_U4_PACKED else m), dtype=np.uint8))
+    luts = dev(quantized_like_tables(r, nq) if fmt == orc.CODES_U4_PACKED else (r.random((nq, m, k)) * 50).astype(np.float32))
+    v, i = ctx.pq_adc_scan_topk(codes, fmt, luts, 1000)
+    v2, i2 = ctx.pq_adc_scan_topk(codes, fmt, luts, 1000, noalloc=True)
+    assert torch.equal(i, i2) and torch.equal(v, v2)
+
+
 # ----------------------------------------------------------------------------- encoded data at full size
 ENC_UNIQUE = 400_000   # vectors encoded by the oracle; the 25 M rows are drawn from them (so every code has ~60 exact copies)
 
