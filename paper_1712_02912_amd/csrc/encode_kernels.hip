@@ -89,10 +89,12 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
     if (lane == 0) red[tid >> 6] = amax;
     __syncthreads();
     for (int w = 0; w < 16; ++w) amax = red[w] > amax ? red[w] : amax;
-    // amax in [2^e, 2^(e+1)) becomes [2^10, 2^11); codebooks of extreme magnitude lose bits and settle less
+    // amax in [2^e, 2^(e+1)) becomes [2^10, 2^11), which the error bound relies on.  Where that takes a factor beyond the
+    // powers of two of fp32 (centroids within 2^-116 of their mean), nothing is settled by the ranking.
     int e = amax > 0.f && amax < __builtin_inff() ? ilogbf(amax) : 10;
-    e = 10 - e;
-    e = e > 100 ? 100 : (e < -100 ? -100 : e);
+    e = 10 - e;   // (-117 at least)
+    const bool ranked = amax < __builtin_inff() && e <= 126;
+    e = e > 126 ? 126 : e;
     const float scale = ldexpf(1.f, e);
     for (int c = tid; c < tiles * 16; c += 1024) {
         double norm = 0.0;
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
         EncodeInfo r;
         r.scale = scale;
         r.bound = 1.01f * (p22 + p21 + sqrtf(dims) * p23 + (4.f * dims + 8.f) * p23 + p17);
-        r.cmax2 = amax < __builtin_inff() ? 1.001f * __uint_as_float(cmax_bits) : __builtin_inff();
+        r.cmax2 = ranked ? 1.001f * __uint_as_float(cmax_bits) : __builtin_inff();
         r.pad = 0.f;
         *reinterpret_cast<EncodeInfo *>(offset + nch * 16) = r;
     }

@@ -538,6 +538,28 @@ def test_encode_edges_of_tiles(ctx, ds, m, k, n):
             assert np.array_equal(host(ctx.pq_encode(xd, dev(cb), fmt)), ref), (scale, shift)
 
 
+@pytest.mark.parametrize("ds,m,k", [(8, 4, 256), (16, 2, 40), (5, 4, 16), (33, 2, 256)])
+def test_encode_codebooks_of_extreme_magnitude(ctx, ds, m, k):
+    """Codebooks at both ends of fp32 (subnormal numbers, spreads too small to be scaled into fp16's range, components near
+    the greatest number), some with centroids of widely different size: the nearest centroid is decided in double."""
+    r = np.random.default_rng(ds + k)
+    fmt = orc.CODES_U4_PACKED if k == 16 else orc.CODES_U8
+    n = 3000
+    for scale in (1e-31, 1e-33, 1e-34, 1e-35, 1e-36, 1e-37, 1e-40, 1e-44, 1e30, 1e35, 4e38):
+        for mixed in (False, True):
+            unit = r.random((m, k, ds)) - 0.3
+            if mixed:   # one centroid in four is 2^-90 times as large as the others
+                unit[:, ::4] *= 2.0 ** -90
+            cb = (unit * scale).astype(np.float32)
+            x = ((r.random((n, m, ds)) - 0.3) * scale).astype(np.float32)
+            if mixed:
+                x[::2] *= np.float32(2.0 ** -90)
+            x = x.reshape(n, m * ds)
+            ref = orc.pq_encode(x, cb)
+            got = host(ctx.pq_encode(dev(x), dev(cb), fmt))
+            assert np.array_equal(got, orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref), (scale, mixed)
+
+
 # ----------------------------------------------------------------------------- full size (bench configuration)
 FULL_N, FULL_NQ = 25_000_000, 1000
 SAMPLE_Q = [0, 1, 7, 8, 123, 500, 640, 777, 998, 999]
