@@ -96,6 +96,10 @@ __device__ __forceinline__ int first_bin_reaching(Load load, uint32_t k, uint32_
 struct DqPlaces {
     uint64_t begin, end;   // the query's list
     uint32_t slot;         // first place reserved in it
+    // (readlane returns an int: a low word from 2^31 on must not be sign-extended into the high one)
+    static __device__ __forceinline__ uint64_t of_lane(uint64_t v, int lane) {
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), lane) << 32 | (uint32_t)__builtin_amdgcn_readlane((uint32_t)v, lane);
+    }
     __device__ __forceinline__ void list_of(const DqArgs &a, int gq) {
         begin = gq < a.nq ? a.cand_off[gq] : 0;
         end = gq < a.nq ? a.cand_off[gq + 1] : 0;
@@ -104,9 +108,8 @@ struct DqPlaces {
     // place `index` of query q's (the list holds exactly the vectors the first pass counted; the comparison only keeps a
     // disagreement from writing past it)
     __device__ __forceinline__ void store(const DqArgs &a, int q, bool pass, uint32_t index, uint32_t sum, uint32_t row, uint32_t w0, uint32_t w1) const {
-        const uint64_t first = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(begin >> 32), q) << 32 | __builtin_amdgcn_readlane((uint32_t)begin, q)) +
-                               __builtin_amdgcn_readlane(slot, q);
-        const uint64_t stop = (uint64_t)__builtin_amdgcn_readlane((uint32_t)(end >> 32), q) << 32 | __builtin_amdgcn_readlane((uint32_t)end, q);
+        const uint64_t first = of_lane(begin, q) + (uint32_t)__builtin_amdgcn_readlane(slot, q);
+        const uint64_t stop = of_lane(end, q);
         const uint64_t at = first + index;
         if (pass && at < stop) {
             a.cand[at] = ((uint64_t)sum << 32) | row;

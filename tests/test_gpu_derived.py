@@ -221,3 +221,25 @@ def test_derived_search_rerank_on_complete_tables(ctx, dsub, k, nq, n, r2, topk)
     cb, cbar, codes, queries = make_problem(dsub + nq, n, k, dsub, nq)
     assert r2 * nq * 5 >= (nq + 127) // 128 * 128 * k   # (every query has at least r2 candidates: the rule for the tables holds)
     run_case(ctx, cb, cbar, codes, queries, r2, topk)
+
+
+@pytest.mark.parametrize("n,nq", [(300_000_000, 8), (3_400_000, 640)])
+def test_derived_search_lists_beyond_two_to_the_31(ctx, n, nq):
+    """Equal codes, all of them candidates of every query: more than 2^31 places in the candidate lists (8 and 16 queries per
+    pass over the codes); the first rows are the result, and every list holds every row once."""
+    cb, cbar, codes, queries = make_problem(43, 1, 256, 8, nq)
+    d_codes = torch.empty((n, 4), dtype=torch.int16, device="cuda")
+    d_codes[:] = dev(codes.view(np.int16))[0]
+    big = binding.Context(0)   # (its lists are given back at the end)
+    cap = n if nq == 640 else 0
+    gd, gi, _, ncand, cand = big.pq_derived_search(d_codes, dev(cbar), dev(cb), dev(queries), 1000, 10, cand_cap=cap)
+    torch.cuda.synchronize()
+    big.close()
+    assert n * nq > 2**31 and (ncand == n).all()
+    for q in (0, nq - 1):
+        assert np.array_equal(gi[q].cpu().numpy(), np.arange(10))
+        assert (gd[q] == float(dq.rerank_exact(codes, np.zeros(1, np.int64), cb, queries[q], 1)[0][0])).all()
+        if cap:
+            assert torch.equal(cand[q].sort().values, torch.arange(n, device="cuda"))
+    del d_codes, cand
+    torch.cuda.empty_cache()
