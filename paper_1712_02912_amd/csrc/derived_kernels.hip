@@ -863,7 +863,7 @@ __global__ __launch_bounds__(1024) void derived_items_kernel(const uint32_t *__r
             if (bucket_out) bucket_out[q] = bucket[q];
             if (ncand_out) ncand_out[q] = (int64_t)count[q];
         }
-        const uint32_t c = q < nq ? (count[q] + piece - 1) / piece : 0;
+        const uint32_t c = q < nq ? count[q] / piece + (count[q] % piece != 0u ? 1u : 0u) : 0u;   // (a count may be close to 2^32)
         uint32_t incl = c;   // inclusive scan over the wave
         for (int o = 1; o < 64; o <<= 1) {
             const uint32_t other = __shfl_up(incl, o);

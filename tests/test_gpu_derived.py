@@ -243,3 +243,22 @@ def test_derived_search_lists_beyond_two_to_the_31(ctx, n, nq):
             assert torch.equal(cand[q].sort().values, torch.arange(n, device="cuda"))
     del d_codes, cand
     torch.cuda.empty_cache()
+
+
+def test_derived_search_every_code_of_a_full_bucket(ctx):
+    """Nearly 2^32 equal codes in one bucket: all of them are candidates, the first rows are the result."""
+    n = 2**32 - 100
+    if torch.cuda.mem_get_info()[0] < 150 << 30:
+        pytest.skip("needs 150 GB of device memory")
+    cb, cbar, codes, queries = make_problem(41, 1, 256, 8, 1)
+    d_codes = torch.empty((n, 4), dtype=torch.int16, device="cuda")
+    d_codes[:] = dev(codes.view(np.int16))[0]
+    big = binding.Context(0)   # (its lists are given back at the end)
+    gd, gi, _, ncand, _ = big.pq_derived_search(d_codes, dev(cbar), dev(cb), dev(queries), 1000, 10)
+    torch.cuda.synchronize()
+    big.close()
+    del d_codes
+    torch.cuda.empty_cache()
+    want = dq.rerank_exact(codes, np.zeros(1, np.int64), cb, queries[0], 1)[0][0]
+    assert ncand[0].item() == n
+    assert np.array_equal(gi.cpu().numpy()[0], np.arange(10)) and np.all(gd.cpu().numpy()[0] == want)
