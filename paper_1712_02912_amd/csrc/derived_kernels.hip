@@ -900,6 +900,7 @@ constexpr int RR_TILE = 2 * RR_THREADS; // candidates per tile: two batches of 6
 constexpr int RR_ILP = 8;               // pairs of candidates whose rows are on their way together
 constexpr uint32_t RR_PIECE_MIN = RR_THREADS, RR_PIECE_MAX = 16 * RR_TILE;
 constexpr size_t RR_TABLE_BYTES = (size_t)256 << 20;   // complete tables of a batch of queries (the last-level cache's size)
+constexpr int RR_TABLE_QUERIES = 8192;   // of a batch, and of their sub-vectors as doubles
 
 // v + (v of the lane that the DPP control names)
 template <int CTRL>
@@ -973,10 +974,11 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
                     const uint2 c = cand_code != nullptr ? cand_code[have ? ci : c0] : *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
                     const float *const tab = tables + (size_t)(q - q_first) * DQ_M * k;
                     const uint32_t idx[DQ_M] = {c.x & 0xffffu, c.x >> 16, c.y & 0xffffu, c.y >> 16};
-                    double total = 0.0;
+                    double e[DQ_M];
 #pragma unroll
                     for (int t = 0; t < DQ_M; ++t)   // indexes are below k by contract
-                        total += (double)tab[(size_t)t * k + (idx[t] < (uint32_t)k ? idx[t] : (uint32_t)k - 1u)];
+                        e[t] = (double)tab[(size_t)t * k + (idx[t] < (uint32_t)k ? idx[t] : (uint32_t)k - 1u)];
+                    const double total = (e[0] + e[1]) + (e[2] + e[3]);   // (the order of the other forms)
                     const uint64_t key = ((uint64_t)f32_to_ord((float)total) << 32) | row;
                     if (have && key < bound) keys[RR_KEEP + atomicAdd(&nnew, 1)] = key;
                     continue;
@@ -1015,7 +1017,7 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
 #pragma unroll
                             for (int i = 0; i < W; ++i) {
                                 const double diff = (double)yv[i] - (double)cv[v][i];
-                                sum[v] += diff * diff;
+                                sum[v] = fma(diff, diff, sum[v]);
                             }
                     }
 #pragma unroll
@@ -1060,6 +1062,71 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
         }
         for (int i = tid; i < RR_KEEP; i += RR_THREADS) partial[(size_t)item * RR_KEEP + i] = i < topk ? keys[i] : KEY_EMPTY;
     }
+}
+
+// The queries' sub-vectors as doubles, padded with zeros to DIMS dimensions: [nq][4][DIMS].
+template <int DIMS>
+__global__ __launch_bounds__(256) void derived_widen_kernel(const float *__restrict__ queries, int nq, int dsub, double *__restrict__ wide) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (size_t)nq * DQ_M * DIMS) return;
+    const int t = (int)(i % DIMS);
+    wide[i] = t < dsub ? (double)queries[i / DIMS * dsub + t] : 0.0;   // (a sub-vector follows the other in the query as well)
+}
+
+// Complete tables of a batch of queries for Step 2: entry ||y^j - C^j[i]||^2 from the differences, summed in double and rounded
+// to float, in the very order of derived_rerank_kernel<4> (eight partial sums over dimensions 4 l .. 4 l + 3 of every 32, added
+// pairwise), so that a candidate has the same distance, bit for bit, whichever form measures it.  (The expanded form of the
+// Tables step loses bits where a query nearly hits a centroid, and makes a NaN of an infinite component.)  A thread has one
+// centroid in registers, as doubles, and goes through the queries, whose dimensions are the same for the whole wave and come
+// through scalar loads: two fp64 instructions per dimension, nothing else.  Padding adds zeros and changes no sum.
+// TABLES_MEASURED
+constexpr int DT_QUERIES = 64;   // queries per block: what a centroid row's conversion is spread over
+template <int DIMS>
+__global__ __launch_bounds__(256) void derived_tables_kernel(const double *__restrict__ wide, const float *__restrict__ codebooks, int nq, int k, int dsub,
+                                                             float *__restrict__ tables) {
+    const int i = blockIdx.x * 256 + threadIdx.x, j = blockIdx.y, q0 = blockIdx.z * DT_QUERIES;
+    const float4 *const row = reinterpret_cast<const float4 *>(codebooks + ((size_t)j * k + (i < k ? i : k - 1)) * dsub);
+    double c[DIMS];
+#pragma unroll
+    for (int t = 0; t < DIMS; t += 4) {
+        const bool inside = t < dsub;   // (dsub is a multiple of 4)
+        const float4 f = row[inside ? t / 4 : 0];
+        c[t] = inside ? (double)f.x : 0.0; c[t + 1] = inside ? (double)f.y : 0.0;
+        c[t + 2] = inside ? (double)f.z : 0.0; c[t + 3] = inside ? (double)f.w : 0.0;
+    }
+    const int q1 = q0 + DT_QUERIES < nq ? q0 + DT_QUERIES : nq;
+    for (int q = q0; q < q1; ++q) {
+        const double *const y = wide + ((size_t)q * DQ_M + j) * DIMS;
+        auto part = [&](int l) {
+            double sum = 0.0;
+#pragma unroll
+            for (int t = 4 * l; t < DIMS; t += 32)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double diff = y[t + u] - c[t + u];
+                    sum = fma(diff, diff, sum);
+                }
+            return sum;
+        };
+        auto four = [&](int l) {
+            const double a = part(l) + part(l + 1);
+            return a + (part(l + 2) + part(l + 3));
+        };
+        const double a = four(0);
+        const double entry = a + four(4);
+        if (i < k) tables[((size_t)q * DQ_M + j) * k + i] = (float)entry;
+    }
+}
+
+template <int DIMS>
+static int launch_derived_tables(pq_ctx *ctx, const float *queries, const float *codebooks, int nq, int k, int dsub, double *wide, float *tables) {
+    const size_t values = (size_t)nq * DQ_M * DIMS;
+    derived_widen_kernel<DIMS><<<(unsigned)((values + 255) / 256), 256, 0, ctx->stream>>>(queries, nq, dsub, wide);
+    PQ_HIP(ctx, hipGetLastError());
+    const dim3 grid((k + 255) / 256, DQ_M, (nq + DT_QUERIES - 1) / DT_QUERIES);
+    derived_tables_kernel<DIMS><<<grid, 256, 0, ctx->stream>>>(wide, codebooks, nq, k, dsub, tables);
+    PQ_HIP(ctx, hipGetLastError());
+    return PQ_OK;
 }
 
 // candidate rows of every query as [nq][cap] ids (ascending positions in the list are not sorted), padded with -1
@@ -1202,14 +1269,16 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     uint64_t per_block = total / (8ull * (unsigned)ctx->num_cu);
     uint32_t piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_PIECE_MIN * RR_PIECE_MIN;
     if (piece < RR_PIECE_MIN) piece = RR_PIECE_MIN;
-    // Long lists: the complete tables of the queries (Step 1.1 with the full codebooks, on the matrix cores, 128 queries
-    // at least per tile) cost less than the rows of the candidates: 65 536 centroids per sub-space, about 0.55 us of the GPU per
-    // query against 67 ps per candidate, so from 8000 candidates per query on, and from 13 000 on to be safe.  Queries go in
-    // batches whose tables stay below RR_TABLE_BYTES.  (48 M candidates of 1000 queries: 3.2 -> 2.1 ms, the call 11.5 -> 10.4.)
+    // Long lists: the complete tables of the queries cost less than the rows of the candidates: for 65 536 centroids of 32
+    // dimensions per sub-space 0.78 us of the GPU per query, and 29 ps per candidate for its four entries, against 67 ps for its
+    // four rows: from 20 000 candidates per query on, a third of the centroids.  (48 M candidates of 1000 queries: 3.2 -> 2.2 ms,
+    // the call 11.2 -> 10.1.)  Queries go in batches whose tables stay below RR_TABLE_BYTES.
     const bool rr_vec = (dsub & 3) == 0 && ((uintptr_t)codebooks & 15) == 0;
     const size_t table_bytes = (size_t)DQ_M * k * 4;
-    const int table_batch = (int)(RR_TABLE_BYTES / table_bytes / 128 * 128);   // (k <= 65536: 256 at least)
-    bool with_tables = rr_vec && dsub >= 8 && dsub < 64 /* the Tables step then needs no buffer of its own */ && ((uintptr_t)queries & 15) == 0 && total * 5 >= (uint64_t)((nq + 127) / 128 * 128) * (uint64_t)k;
+    int table_batch = (int)(RR_TABLE_BYTES / table_bytes / 128 * 128);   // (k <= 65536: 256 at least)
+    if (table_batch > RR_TABLE_QUERIES) table_batch = RR_TABLE_QUERIES;
+    const int table_dims = dsub <= 32 ? 32 : 64;   // of a padded sub-vector
+    bool with_tables = rr_vec && dsub >= 8 && dsub < 64 && total * 3 >= (uint64_t)((nq + 127) / 128 * 128) * (uint64_t)k;
     if (with_tables) piece = 8 * RR_TILE;   // (shorter than at most: what the blocks of a die work on belongs to few queries; 2, 4, 16 tiles: 10.8, 10.6, 10.5 against 10.4 ms per call)
     const size_t max_items = (size_t)(total / piece) + (size_t)nq;
     const size_t o_partial = 0;
@@ -1219,11 +1288,13 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     const size_t o_cand = o_tau + align_up((size_t)nq * 8, 256);
     const size_t o_code = o_cand + align_up((size_t)total * 8, 256);
     const size_t o_table = o_code + align_up((size_t)total * 8, 256);
-    const size_t table_room = with_tables ? table_bytes * (size_t)(nq < table_batch ? nq : table_batch) : 0;
+    const size_t batch_queries = (size_t)(nq < table_batch ? nq : table_batch);
+    const size_t o_wide = o_table + align_up(batch_queries * table_bytes, 256);
+    const size_t table_end = o_wide + batch_queries * DQ_M * table_dims * 8;
     // (a copy of the candidates' codes beside the list saves Step 2 a random read of the database per candidate; it is
     // left out if there is no memory for it)
     bool with_codes = true;
-    rc = lut_ws_reserve(ctx, o_table + table_room);
+    rc = lut_ws_reserve(ctx, with_tables ? table_end : o_table);
     if (rc == PQ_ENOMEM && with_tables) {
         with_tables = false;
         rc = lut_ws_reserve(ctx, o_table);
@@ -1261,9 +1332,12 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     uint64_t *partial = (uint64_t *)(lists + o_partial);
     if (with_tables) {
         float *tables = (float *)(lists + o_table);
+        double *wide_queries = (double *)(lists + o_wide);
         for (int q0 = 0; q0 < nq; q0 += table_batch) {
             const int q1 = nq - q0 < table_batch ? nq : q0 + table_batch;
-            rc = launch_build_luts(ctx, queries + (size_t)q0 * d, codebooks, q1 - q0, d, DQ_M, k, tables);
+            const float *batch = queries + (size_t)q0 * d;
+            rc = table_dims == 32 ? launch_derived_tables<32>(ctx, batch, codebooks, q1 - q0, k, dsub, wide_queries, tables)
+                                  : launch_derived_tables<64>(ctx, batch, codebooks, q1 - q0, k, dsub, wide_queries, tables);
             if (rc) return rc;
             derived_rerank_kernel<0><<<(rr_grid + 7) / 8 * 8, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, item_off,
                                                                                     item_query, q0, q1, piece, topk, tau_key, partial, tables);
