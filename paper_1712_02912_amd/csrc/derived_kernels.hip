@@ -1264,8 +1264,8 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     unsigned long long total = 0;
     rc = count_pass(ws, &total);
     if (rc) return rc;
-    // The sizes of the candidate lists are known now; they live in the context's other buffer, so that what the counting
-    // pass left in the workspace stays.  Pieces of Step 2: as many as there are blocks four times over.
+    // The sizes of the candidate lists are known now; they live in a buffer of their own, so that what the counting pass left
+    // in the workspace stays.  Pieces of Step 2: as many as there are blocks four times over.
     uint64_t per_block = total / (8ull * (unsigned)ctx->num_cu);
     uint32_t piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_PIECE_MIN * RR_PIECE_MIN;
     if (piece < RR_PIECE_MIN) piece = RR_PIECE_MIN;
@@ -1294,17 +1294,18 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     // (a copy of the candidates' codes beside the list saves Step 2 a random read of the database per candidate; it is
     // left out if there is no memory for it)
     bool with_codes = true;
-    rc = lut_ws_reserve(ctx, with_tables ? table_end : o_table);
+    auto reserve_lists = [&](size_t bytes) { return buf_reserve(ctx, &ctx->derived_lists, bytes, "the candidate lists"); };
+    rc = reserve_lists(with_tables ? table_end : o_table);
     if (rc == PQ_ENOMEM && with_tables) {
         with_tables = false;
-        rc = lut_ws_reserve(ctx, o_table);
+        rc = reserve_lists(o_table);
     }
     if (rc == PQ_ENOMEM) {
         with_codes = false;
-        rc = lut_ws_reserve(ctx, o_code);
+        rc = reserve_lists(o_code);
     }
     if (rc) return rc;
-    uint8_t *lists = (uint8_t *)ctx->lut_ws;
+    uint8_t *lists = (uint8_t *)ctx->derived_lists.p;
     uint32_t *item_off = (uint32_t *)(lists + o_itemoff), *item_query = (uint32_t *)(lists + o_items);
     unsigned long long *tau_key = (unsigned long long *)(lists + o_tau);
 

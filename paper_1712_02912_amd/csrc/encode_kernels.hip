@@ -537,15 +537,22 @@ int launch_encode(pq_ctx *ctx, const float *vectors, const float *codebooks, int
     const int ds = d / m, packed = cf == PQ_CODES_U4_PACKED ? 1 : 0;
     const int64_t nblocks = (n + ER - 1) / ER;
     if (nblocks > 0x7fffffff) return fail(ctx, PQ_EUNSUPPORTED, "encode: more than 2^37 vectors");
-    // the centroids as matrix operands need scratch memory; a call that cannot have it (none free, or the buffer would
-    // have to grow while the stream is being captured) takes the form that needs none
+    // The centroids as matrix operands need scratch memory.  A call that cannot have it takes the form that needs none, and so
+    // does every call on a stream that is being captured: its graph holds no memory of the context, which a later call may
+    // give back, and can be replayed for as long as the caller's own buffers live.
     const int chunks = (ds + 15) / 16, nch = chunks <= 2 ? chunks : 4, tiles = (k + 15) / 16;
     const size_t image_bytes = (size_t)encode_image_len(tiles, nch) * sizeof(uint4);
-    if (ds <= ENC_MAX_DS && lut_ws_try(ctx, (size_t)m * image_bytes)) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
+    if (ds <= ENC_MAX_DS && capture == hipStreamCaptureStatusNone &&
+        buf_reserve(ctx, &ctx->encode_images, (size_t)m * image_bytes, "the centroid images of the encoder") == PQ_OK) {
         EncodeArgs A{};
         A.x = vectors; A.codebooks = codebooks; A.codes = codes; A.n = n; A.d = d; A.ds = ds; A.m = m; A.k = k; A.packed = packed;
         A.code_bytes = packed ? m / 2 : m; A.tiles = tiles;
-        A.images = (const uint4 *)ctx->lut_ws;
+        A.images = (const uint4 *)ctx->encode_images.p;
         A.words = (A.code_bytes & 3) == 0 && ((uintptr_t)codes & 3) == 0;
         const uintptr_t bases = (uintptr_t)vectors | (uintptr_t)codebooks;
         const int vec = (ds & 3) == 0 && (bases & 15) == 0 ? 4 : ((ds & 1) == 0 && (bases & 7) == 0 ? 2 : 1);
@@ -562,7 +569,7 @@ int launch_encode(pq_ctx *ctx, const float *vectors, const float *codebooks, int
         parts = parts < 1 ? 1 : (parts > units ? units : parts);
         A.bytes_per_y = (units + parts - 1) / parts * unit;
         parts = (A.code_bytes + A.bytes_per_y - 1) / A.bytes_per_y;
-        encode_prep_kernel<<<m, 1024, 0, ctx->stream>>>(codebooks, k, ds, nch, tiles, (uint4 *)ctx->lut_ws);
+        encode_prep_kernel<<<m, 1024, 0, ctx->stream>>>(codebooks, k, ds, nch, tiles, (uint4 *)ctx->encode_images.p);
         PQ_HIP(ctx, hipGetLastError());
         const dim3 grid((unsigned)bx, (unsigned)parts);
         const size_t lds = image_bytes * (resident ? m : 1);

@@ -552,7 +552,7 @@ __global__ __launch_bounds__(256, 2) void build_luts_mfma128_kernel(const Mfma12
 }
 
 // Scratch memory of the 128 x 128 form (operands as doubles and their norms), kept by the context.
-int lut_ws_reserve(pq_ctx *ctx, size_t bytes) {
+static int lut_ws_reserve(pq_ctx *ctx, size_t bytes) {
     if (bytes <= ctx->lut_ws_bytes) return PQ_OK;
     PQ_HIP(ctx, hipStreamSynchronize(ctx->stream));   // kernels already enqueued may still use the old buffer
     if (ctx->lut_ws) {
@@ -570,16 +570,6 @@ int lut_ws_reserve(pq_ctx *ctx, size_t bytes) {
     ctx->lut_ws = p;
     ctx->lut_ws_bytes = want;
     return PQ_OK;
-}
-
-bool lut_ws_try(pq_ctx *ctx, size_t bytes) {
-    if (bytes <= ctx->lut_ws_bytes) return true;
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return status == hipStreamCaptureStatusNone && lut_ws_reserve(ctx, bytes) == PQ_OK;
 }
 
 // Launch of the 128 x 128 form: two blocks per compute unit (a multiple of 8 blocks, one share per die).

@@ -1,5 +1,6 @@
 // C-ABI entry points of libpqadc: argument validation, context and workspace handling.
 // The kernels and their launchers live in the other translation units.
+#include <initializer_list>
 #include <stdarg.h>
 #include <stdlib.h>
 #include <string.h>
@@ -44,6 +45,29 @@ int ws_reserve(pq_ctx *ctx, size_t bytes) {
     ctx->ws = p;
     ctx->ws_bytes = want;
     return PQ_OK;
+}
+
+int buf_reserve(pq_ctx *ctx, pq_buf *buf, size_t bytes, const char *what) {
+    if (bytes <= buf->bytes) return PQ_OK;
+    PQ_HIP(ctx, hipStreamSynchronize(ctx->stream));   // kernels already enqueued may still use the old buffer
+    if (buf->p) {
+        PQ_HIP(ctx, hipFree(buf->p));
+        buf->p = nullptr;
+        buf->bytes = 0;
+    }
+    hipError_t e = hipSuccess;
+    for (const size_t spare : {bytes / 4, (size_t)0}) {   // with room to grow, or what is needed
+        const size_t want = align_up(bytes + spare, (size_t)1 << 20);
+        void *p = nullptr;
+        e = hipMalloc(&p, want);
+        if (e == hipSuccess) {
+            buf->p = p;
+            buf->bytes = want;
+            return PQ_OK;
+        }
+        (void)hipGetLastError();
+    }
+    return fail(ctx, PQ_ENOMEM, "allocation of %zu bytes for %s failed: %s", bytes, what, hipGetErrorString(e));
 }
 
 static bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
@@ -152,6 +176,8 @@ int pq_destroy(pq_ctx *ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->lut_ws) (void)hipFree(ctx->lut_ws);
+    if (ctx->encode_images.p) (void)hipFree(ctx->encode_images.p);
+    if (ctx->derived_lists.p) (void)hipFree(ctx->derived_lists.p);
     if (ctx->host_pin) (void)hipHostFree(ctx->host_pin);
     if (ctx->aux_stream) {
         (void)hipStreamSynchronize(ctx->aux_stream);

@@ -14,6 +14,12 @@ enum pq_option_id {
 };
 constexpr int PQ_OPT_UNSET = -2147483647 - 1;
 
+// A device buffer that its context keeps and grows on demand.
+struct pq_buf {
+    void *p;
+    size_t bytes;
+};
+
 struct pq_ctx {
     int device;
     hipStream_t stream;
@@ -22,6 +28,9 @@ struct pq_ctx {
     int ws_fixed;      // ws must not grow: a request beyond ws_bytes is an error
     void *lut_ws;      // Tables step of many tiles: operands as doubles and their norms, grown on demand
     size_t lut_ws_bytes;
+    // (buffers of their own: a captured Tables step holds the address of lut_ws, which these calls must not move)
+    pq_buf encode_images;   // pq_encode: the centroids as matrix operands
+    pq_buf derived_lists;   // pq_derived_search: candidate lists, result lists, tables of Step 2
     void *host_pin;    // 256 bytes of pinned host memory for the few words a call reads back
     hipStream_t aux_stream;          // ivf_adc_search: work that does not depend on the tables runs beside them
     hipEvent_t aux_fork, aux_join;
@@ -46,10 +55,8 @@ int fail(pq_ctx *ctx, int code, const char *fmt, ...);
 int hip_fail(pq_ctx *ctx, hipError_t e, const char *what);
 // Make the workspace at least `bytes` large; returns PQ_OK or an error already recorded.
 int ws_reserve(pq_ctx *ctx, size_t bytes);
-// Make the context's buffer for converted operands (lut_ws) at least `bytes` large; false if that is not possible now
-// (out of memory, or the stream is being captured and the buffer would have to grow), for callers with another way.
-bool lut_ws_try(pq_ctx *ctx, size_t bytes);
-int lut_ws_reserve(pq_ctx *ctx, size_t bytes);   // the same, PQ_OK or an error already recorded
+// The same for a buffer of the context that has one use (`what`, for the message).
+int buf_reserve(pq_ctx *ctx, pq_buf *buf, size_t bytes, const char *what);
 
 #define PQ_HIP(ctx, call)                                                \
     do {                                                                 \

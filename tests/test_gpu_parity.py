@@ -560,6 +560,39 @@ def test_encode_codebooks_of_extreme_magnitude(ctx, ds, m, k):
             assert np.array_equal(got, orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref), (scale, mixed)
 
 
+@pytest.mark.parametrize("m,k,warm", [(8, 256, True), (8, 256, False), (16, 16, True)])
+def test_encode_in_a_captured_graph(m, k, warm):
+    """A graph with pq_encode is replayed on new vectors while later calls on the context, eager ones with larger codebooks
+    among them, make its buffers grow: every replay gives the codes of its vectors."""
+    r = np.random.default_rng(m)
+    stream = torch.cuda.Stream()
+    g_ctx = binding.Context(0, stream)
+    fmt = orc.CODES_U4_PACKED if k == 16 else orc.CODES_U8
+    n, ds = 5000, 16
+    cb = r.normal(size=(m, k, ds)).astype(np.float32)
+    with torch.cuda.stream(stream):
+        x, d_cb = torch.empty((n, m * ds), device="cuda"), dev(cb)
+        if warm:
+            g_ctx.pq_encode(x.zero_(), d_cb, fmt)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            codes = g_ctx.pq_encode(x, d_cb, fmt)
+        for i in range(4):
+            host_x = r.normal(size=(n, m * ds)).astype(np.float32)
+            x.copy_(torch.from_numpy(host_x))
+            graph.replay()
+            # eager work between the replays: the encoder's own buffer and that of the Tables step grow
+            big_m = 16 << i
+            big_x, big_cb = torch.randn((300, big_m * 64), device="cuda"), torch.randn((big_m, 256, 64), device="cuda")
+            g_ctx.pq_encode(big_x, big_cb)
+            g_ctx.pq_build_luts(torch.randn((1024 << i, 128), device="cuda"), torch.randn((2, 1024 << i, 64), device="cuda"))
+            torch.empty(1 << 24, dtype=torch.uint8, device="cuda").fill_(255)
+            ref = orc.pq_encode(host_x, cb)
+            assert np.array_equal(host(codes), orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref), i
+    g_ctx.close()
+
+
 # ----------------------------------------------------------------------------- full size (bench configuration)
 FULL_N, FULL_NQ = 25_000_000, 1000
 SAMPLE_Q = [0, 1, 7, 8, 123, 500, 640, 777, 998, 999]
