@@ -552,3 +552,27 @@ def test_ivf_quick_lists_around_the_long_ones(ctx, opts, sizes, kprime, topk):
             opts.set("ivf_quick_chunk_rows", rows)
         gd, gi = ctx.ivf_quick_adc_search(dev(coarse), dev(offsets), dev(packed), None, dev(cb), dev(queries), nlist, 500, kprime, topk)[:2]
         assert np.array_equal(gd.cpu().numpy(), od) and np.array_equal(gi.cpu().numpy(), oi)
+
+
+@pytest.mark.parametrize("nq,topk", [(1, 128), (520, 128), (513, 100)])
+def test_ivf_quick_result_lists_from_the_farthest_to_the_nearest(ctx, nq, topk):
+    """1024 result lists of 128 keys of which each holds nearer codes than those before it, and one far code that keeps the
+    bound of the result loose: nearly all 131 072 keys lie within the bound, and those met first are the greatest."""
+    nlist, size = 1024, 128
+    base = np.zeros((16, 16, 1), np.float32)
+    base[0, :, 0], base[1, :, 0], base[2, :, 0] = np.arange(16), np.arange(16) * 17, np.arange(16) * 291
+    base[15, 1, 0] = 1e5
+    digits = np.stack(np.meshgrid(np.arange(16), np.arange(16), np.arange(16), indexing="ij"), -1).reshape(-1, 3)
+    dist = sum(base[j, digits[:, j], 0].astype(np.float64) ** 2 for j in range(3))
+    order = np.argsort(dist, kind="stable")
+    order = order[np.concatenate([[True], np.diff(dist[order]) > 0])][:nlist][::-1]   # distances all different, descending
+    idx = np.zeros((nlist, size, 16), np.uint8)
+    idx[:, :, :3] = digits[order][:, None, :]
+    idx[:, 5, 15] = 1   # the far code of every list
+    packed = orc.pack_u4(idx.reshape(-1, 16))
+    coarse = np.zeros((nlist, 16), np.float32)   # lists equally far: probed in their order
+    offsets = np.arange(nlist + 1, dtype=np.int64) * size
+    query = np.zeros((1, 16), np.float32)
+    od, oi = orc.ivf_quick_search(query, coarse, offsets, packed, None, base, orc.CODES_U4_PACKED, nlist, 200, 128, topk)
+    gd, gi = ctx.ivf_quick_adc_search(dev(coarse), dev(offsets), dev(packed), None, dev(base), dev(np.repeat(query, nq, 0)), nlist, 200, 128, topk)[:2]
+    assert np.array_equal(gd.cpu().numpy(), np.repeat(od, nq, 0)) and np.array_equal(gi.cpu().numpy(), np.repeat(oi, nq, 0))
