@@ -89,6 +89,11 @@ const char *pq_version(void);
  *                             ranked by matrix-core distances, the nearest measured exactly; same lists)
  *   ivf_coarse_f16 (1)        0: the ranking pass over all lists on the fp32 matrix cores (default: on the fp16 ones,
  *                             every operand as the sum of two halves: the accuracy of fp32, a third of the time)
+ *   encode_split16 (1)        0: pq_encode measures every centroid in double (default: centroids of up to 64 dimensions per
+ *                             sub-space ranked on the fp16 matrix cores first; same codes)
+ *   derived_tables (unset)    1 / 0: Step 2 of pq_derived_search on complete tables of the queries / on the centroids' rows
+ *                             (unset: by the lengths of the candidate lists; same results)
+ *   derived_code_copy (1)     0: Step 2 reads the candidates' codes from the database, not from copies beside the lists
  *   ivf_quick_chunk_rows (1048576)  ivf_quick_adc_search: rows per work item at most (1024 ... 2^20); a list longer than
  *                             this is scanned in chunks, and a query's result lists (one per chunk of each of its
  *                             lists, at most nprobe + ntotal / this value) are part of the workspace */

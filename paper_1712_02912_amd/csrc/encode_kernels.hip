@@ -547,7 +547,7 @@ int launch_encode(pq_ctx *ctx, const float *vectors, const float *codebooks, int
         (void)hipGetLastError();
         capture = hipStreamCaptureStatusActive;
     }
-    if (ds <= ENC_MAX_DS && capture == hipStreamCaptureStatusNone &&
+    if (ds <= ENC_MAX_DS && capture == hipStreamCaptureStatusNone && opt_int(ctx, PQ_OPT_ENCODE_SPLIT16, 1) != 0 &&
         buf_reserve(ctx, &ctx->encode_images, (size_t)m * image_bytes, "the centroid images of the encoder") == PQ_OK) {
         EncodeArgs A{};
         A.x = vectors; A.codebooks = codebooks; A.codes = codes; A.n = n; A.d = d; A.ds = ds; A.m = m; A.k = k; A.packed = packed;

@@ -260,6 +260,22 @@ def test_derived_search_rerank_infinite_components(ctx):
     assert torch.isinf(gd[:, 60:]).any() and not torch.isnan(gd).any()
 
 
+@pytest.mark.parametrize("dsub,nq,n,r2", [(8, 3, 3000, 1024), (32, 9, 20_000, 5000), (36, 650, 4000, 900), (7, 650, 2500, 300), (60, 2, 5000, 5000)])
+def test_derived_search_forms_of_step_2(ctx, opts, dsub, nq, n, r2):
+    """Complete tables or centroid rows, codes copied beside the lists or read from the database (what calls short of memory
+    take): the same distances and rows bit for bit, and those of the oracle."""
+    cb, cbar, codes, queries = make_problem(dsub + nq, n, 512, dsub, nq)
+    first = None
+    for tables, copies in ((0, 1), (1, 1), (1, 0), (0, 0)):
+        opts.set("derived_tables", tables)
+        opts.set("derived_code_copy", copies)
+        if first is None or not copies:
+            run_case(ctx, cb, cbar, codes, queries, r2, 20)
+        got = ctx.pq_derived_search(dev(codes.view(np.int16)), dev(cbar), dev(cb), dev(queries), r2, 20)[:2]
+        first = first or got
+        assert torch.equal(got[0], first[0]) and torch.equal(got[1], first[1]), (tables, copies)
+
+
 @pytest.mark.parametrize("n,nq", [(300_000_000, 8), (3_400_000, 640)])
 def test_derived_search_lists_beyond_two_to_the_31(ctx, n, nq):
     """Equal codes, all of them candidates of every query: more than 2^31 places in the candidate lists (8 and 16 queries per

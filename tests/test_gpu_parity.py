@@ -560,6 +560,26 @@ def test_encode_codebooks_of_extreme_magnitude(ctx, ds, m, k):
             assert np.array_equal(got, orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref), (scale, mixed)
 
 
+@pytest.mark.parametrize("ds,m,k,n", [(1, 8, 256, 65), (7, 4, 255, 511), (8, 16, 16, 513), (16, 8, 256, 3001), (17, 3, 33, 130),
+                                      (30, 32, 16, 301), (60, 2, 16, 200), (64, 2, 17, 129)])
+def test_encode_without_scratch(ctx, opts, ds, m, k, n):
+    """The form that captured calls and calls without memory take, and the one by ranking: the same codes, packed ones too."""
+    r = np.random.default_rng(ds + m)
+    fmt = orc.CODES_U4_PACKED if k == 16 else orc.CODES_U8
+    cb = r.normal(size=(m, k, ds)).astype(np.float32)
+    cb[:, k // 2] = cb[:, 1]   # ties
+    x = r.normal(size=(n, m, ds)).astype(np.float32)
+    x[n // 3] = cb[:, k - 1]
+    x[n // 2] = cb[:, 1]
+    x[n // 4] *= np.float32(1e5)
+    x = x.reshape(n, m * ds)
+    ref = orc.pq_encode(x, cb)
+    ref = orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref
+    for split in (1, 0):
+        opts.set("encode_split16", split)
+        assert np.array_equal(host(ctx.pq_encode(dev(x), dev(cb), fmt)), ref), split
+
+
 @pytest.mark.parametrize("m,k,warm", [(8, 256, True), (8, 256, False), (16, 16, True)])
 def test_encode_in_a_captured_graph(m, k, warm):
     """A graph with pq_encode is replayed on new vectors while later calls on the context, eager ones with larger codebooks
