@@ -531,8 +531,8 @@ def test_ivf_grouping_of_small_calls(ctx, nlist, nq, nprobe):
     od, oi = orc.ivf_search(queries, coarse, offsets, codes, None, cb, orc.CODES_U8, nprobe, topk)
     op, _ = orc.ivf_probe(queries, coarse, nprobe)
     assert np.array_equal(gp, op)
-    np.testing.assert_allclose(gd, od, rtol=1e-5)
-    assert (gi == oi).mean() > 0.99   # (near ties of random tables)
+    for q in range(nq):
+        check_float_topk_ranked(gd[q], gi[q], od[q], oi[q])
 
 
 @pytest.mark.parametrize("sizes,kprime,topk", [([65_534, 65_535, 65_536, 65_537, 3], 100, 100), ([70_001, 1, 0, 128, 129, 5000], 128, 10), ([65_535, 40], 10, 20)])
