@@ -1859,61 +1859,16 @@ __global__ __launch_bounds__(1024) void f32_seed_refine_kernel(const uint8_t *__
     }
 }
 
-// The same refinement over more codes than one block can look at (flat scans of few
-// query groups over large databases, where every candidate the first bound lets through costs more
-// than a code it dismisses): block (s, q) counts the distances of slice s at or below the query's
-// bound in the bins of the scan's histogram and adds its counts to the query's bins in device memory;
-// f32_seed_pick_kernel then lowers the bound to the smallest bin edge with at least k distances.
-constexpr int SEED_SLICE = 1 << 16;
-__global__ __launch_bounds__(1024) void f32_seed_hist_kernel(const uint8_t *__restrict__ codes, int64_t cnt,
-                                                             const float *__restrict__ luts, const float *__restrict__ tau0,
-                                                             uint32_t *seed_hist) {
-    __shared__ float tab[8 * 256];
-    __shared__ uint32_t hist[HIST_BINS];
-    const int q = blockIdx.y, tid = threadIdx.x;
-    for (int i = tid; i < 2048; i += 1024) tab[i] = luts[(size_t)q * 2048 + i];
-    for (int i = tid; i < HIST_BINS; i += 1024) hist[i] = 0;
-    __syncthreads();
-    const uint32_t ref = f32_to_ord(tau0[q]);
-    const int64_t begin = (int64_t)blockIdx.x * SEED_SLICE;
-    const int64_t end = begin + SEED_SLICE < cnt ? begin + SEED_SLICE : cnt;
-    for (int64_t i0 = begin + tid; i0 < end; i0 += 4 * 1024) {
-        uint2 c[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t i = i0 + u * 1024;
-            c[u] = i < end ? *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8) : make_uint2(0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (i0 + u * 1024 >= end) break;
-            float d = tab[c[u].x & 255u];
-            d += tab[256 + ((c[u].x >> 8) & 255u)];
-            d += tab[512 + ((c[u].x >> 16) & 255u)];
-            d += tab[768 + (c[u].x >> 24)];
-            d += tab[1024 + (c[u].y & 255u)];
-            d += tab[1280 + ((c[u].y >> 8) & 255u)];
-            d += tab[1536 + ((c[u].y >> 16) & 255u)];
-            d += tab[1792 + (c[u].y >> 24)];
-            const uint32_t ord = f32_to_ord(d);
-            if (ord <= ref) {
-                const uint32_t below = (ref - ord) >> HIST_SHIFT;
-                atomicAdd(&hist[HIST_BINS - 1 - (below < HIST_BINS ? below : HIST_BINS - 1)], 1u);
-            }
-        }
-    }
-    __syncthreads();
-    for (int i = tid; i < HIST_BINS; i += 1024)
-        if (hist[i] != 0u) atomicAdd(&seed_hist[(size_t)q * HIST_BINS + i], hist[i]);
-}
-
-// The same sample without a pass before it: the bins hang below ref0 = the sum of the tables' greatest entries (no
+// The same refinement over more codes than one block can look at (flat scans of few query groups over large databases, where
+// every candidate the first bound lets through costs more than a code it dismisses), without a pass before it: block
+// (s, q) counts the distances of slice s in bins that hang below ref0 = the sum of the tables' greatest entries (no
 // distance exceeds it; 4096 bins of 0.2 % reach down to 1/4000 of it), which every block works out for itself from
-// the tables it stages anyway.  A block counts its first 4096 codes in full; the k-th smallest of those bounds the
-// k-th smallest of the whole sample, so of its other codes only the ones at or below that bin edge are counted.
+// the tables it stages anyway, and adds its counts to the query's bins in device memory.  A block counts its first 4096 codes
+// in full; the k-th smallest of those bounds the k-th smallest of the whole sample, so of its other codes only the ones at or
+// below that bin edge are counted.
 // Blocks of `slice` codes (many short blocks when few queries share the launch: the pass is a chain of load latencies,
 // not bandwidth).
-constexpr int SEED2_SLICE = 1 << 14;
+constexpr int SEED_SLICE = 1 << 16, SEED2_SLICE = 1 << 14;
 __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__restrict__ codes, int64_t cnt, int slice,
                                                               const float *__restrict__ luts, int k, uint32_t *seed_hist,
                                                               float *seed_ref) {
@@ -1979,19 +1934,6 @@ __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__r
     __syncthreads();
     for (int i = tid; i < HIST_BINS; i += 1024)
         if (hist[i] != 0u) atomicAdd(&seed_hist[(size_t)q * HIST_BINS + i], hist[i]);
-}
-
-__global__ __launch_bounds__(64) void f32_seed_pick_kernel(const uint32_t *__restrict__ seed_hist, int k, float *tau0) {
-    const int q = blockIdx.x;
-    const int b = hist_threshold(seed_hist + (size_t)q * HIST_BINS, k);   // one wave
-    if (threadIdx.x == 0 && b < HIST_BINS) {
-        const uint32_t ref = f32_to_ord(tau0[q]);
-        tau0[q] = ord_to_f32(ref - ((uint32_t)(HIST_BINS - 1 - b) << HIST_SHIFT));
-    }
-}
-
-__global__ void zero_u32_kernel(uint32_t *p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
 // 16-bit tables of the pruned float scan.  Blocks (group, y) of 256 threads: every block of a group works out the
