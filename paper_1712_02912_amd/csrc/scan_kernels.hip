@@ -488,9 +488,10 @@ int launch_scan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const void
         return w16::launch_scan_tuned(ctx, 2, codes, n, luts, nq, topk, out_val, out_ids);
     // 32 tables: scan of 1 M codes, 100 queries, top-1000 10.5 -> 0.24 ms, two-pass call 10.8 -> 0.38.  Under 1024 codes and
     // with short results the general kernel's single launch is the shorter way (300 codes, 29 queries, call 60 us against 79;
-    // 2500 codes 100 against 78).  With the fixed scratch of the call that allocates nothing, requests that do not fit there go
+    // 2500 codes 100 against 78), and so it is where every code is in the result (600 codes, 29 queries, top-1000: 34 us against
+    // 97; top-500 208 against 103).  With the fixed scratch of the call that allocates nothing, requests that do not fit there go
     // on to the general kernel, which may need less.
-    if (!general && cf == PQ_CODES_U4_PACKED && lf == PQ_LUT_U8 && k == 16 && m == 32 && (n >= 1024 || topk > 128)) {
+    if (!general && cf == PQ_CODES_U4_PACKED && lf == PQ_LUT_U8 && k == 16 && m == 32 && (n >= 1024 || (topk > 128 && n > topk))) {
         const int rc = w16::launch_scan_tuned(ctx, 7, codes, n, luts, nq, topk, out_val, out_ids);
         if (!(rc == PQ_ENOMEM && ctx->ws_fixed)) return rc;
     }
