@@ -2238,7 +2238,19 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     const int64_t fine_tile = 2 * 64 * (16 / cb) * TUNED_WAVES;
     // (Not with the fixed scratch of the call that allocates nothing: more blocks need more of it than it may hold.)
     const bool spread = !ctx->ws_fixed;
-    const bool stream = few_groups && (!spread || n <= fine_tile || n * ngroups >= (int64_t)nblocks_max * 16 * fine_tile);   // (a single fine tile: nothing to spread)
+    const bool large = n * ngroups >= (int64_t)nblocks_max * 16 * fine_tile;
+    // Long result lists of three queries and more in up to four groups cost more per item than its share of the codes (their
+    // keys, the block's way to a good bound, a list of up to 1024 keys per query for the merge): from half a million codes on, two
+    // million with three or four groups, they are served in large tiles by half of the blocks (a quarter for one group and the longest results: not the few queries
+    // and the 32 tables whose scan is fast), until there are more code bytes than half of the blocks fetch in time (128 MB; 256 MB with
+    // 16 float tables, whose scan is slower; 25 M 8 x 8 codes, 6 queries 254 us against 211 on all blocks).  Top-1000, large tiles on half or a
+    // quarter of the blocks against fine tiles on all, and what chunks of 131 072 codes had been: 8 x 8 codes, 2.5 M, 8 queries
+    // 172 us, 233, 192; 29 queries 231, 296, 220; 10 M, 8 queries 191, 270, 192; top-129, 10 M, 8 queries 128, 176, 136; 16 x 4
+    // codes, 2.5 M, 29 queries 213, 301, 209.  (1080 calls of 0.2 to 16 M codes and 1 to 200 queries; more groups, and one or two
+    // queries, are better off on all blocks.)
+    const bool long_lists = spread && !small && few_groups && nq > 2 && ngroups <= 4 && n >= (int64_t)1 << (ngroups <= 2 ? 19 : 21) &&
+                            n * cb < (int64_t)1 << (cb == 16 && !is_u4 ? 28 : 27);
+    const bool stream = few_groups && (!spread || n <= fine_tile || large || long_lists);   // (a single fine tile: nothing to spread)
     const int tile = 64 * (16 / cb) * (stream ? 8 : 2);   // codes per wave group (DEPTH sub-tiles)
     const int64_t block_tile = (int64_t)tile * TUNED_WAVES;
 
@@ -2269,6 +2281,10 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     least_tiles = least_tiles > 8 || !spread ? 8 : (least_tiles < 1 ? 1 : least_tiles);
     const int64_t max_by_n = (n_main + least_tiles * block_tile - 1) / (least_tiles * block_tile);
     if (nchunks > max_by_n) nchunks = max_by_n;
+    if (long_lists && (ngroups <= 2 || !large)) {
+        const int64_t most = nblocks_max / (ngroups == 1 && topk > 512 && !u4_m32 && (nq > 4 || cb == 16) ? 4 : 2) / ngroups;
+        if (nchunks > most) nchunks = most > 1 ? most : 1;
+    }
     // (a little more than one item per block would be two rounds: fewer, longer chunks where that is less than the two)
     if (spread && nchunks * ngroups > nblocks_max && 5 * (nblocks_max / ngroups) > 3 * nchunks) nchunks = nblocks_max / ngroups;
     const int64_t min_chunks = (n_main + ((int64_t)1 << 30) - 1) >> 30;   // a chunk's rows are counted in 32 bits

@@ -903,6 +903,24 @@ def test_scan_long_results_with_fixed_scratch(ctx, fmt, m, k, nq, n):
     assert torch.equal(i, i2) and torch.equal(v, v2)
 
 
+@pytest.mark.parametrize("fmt,m,k,nq,n,topk", [(orc.CODES_U8, 8, 256, 3, 524_289, 129), (orc.CODES_U8, 8, 256, 8, 600_001, 1000), (orc.CODES_U4_PACKED, 16, 16, 9, 700_003, 513),
+                                               (orc.CODES_U4_PACKED, 32, 16, 6, 540_003, 1024), (orc.CODES_U8, 16, 256, 29, 2_100_001, 300)])
+def test_scan_long_results_on_part_of_the_blocks(ctx, opts, fmt, m, k, nq, n, topk):
+    """Long results of a few groups of queries, served in large tiles by half or a quarter of the blocks: the same lists
+    whatever the number of blocks, integer sums against the oracle."""
+    r = np.random.default_rng(n + nq)
+    codes = r.integers(0, 256, (n, m // 2 if fmt == orc.CODES_U4_PACKED else m), dtype=np.uint8)
+    if fmt == orc.CODES_U4_PACKED:
+        luts = np.concatenate([quantized_like_tables(r, nq)] * (m // 16), axis=1)
+        run_int_scan(ctx, codes, fmt, luts, topk)
+    else:
+        luts = (r.random((nq, m, k)) * 50).astype(np.float32)
+    v, i = ctx.pq_adc_scan_topk(dev(codes), fmt, dev(luts), topk)
+    opts.set("scan_blocks", 37)
+    v2, i2 = ctx.pq_adc_scan_topk(dev(codes), fmt, dev(luts), topk)
+    assert torch.equal(i, i2) and torch.equal(v, v2)
+
+
 # ----------------------------------------------------------------------------- encoded data at full size
 ENC_UNIQUE = 400_000   # vectors encoded by the oracle; the 25 M rows are drawn from them (so every code has ~60 exact copies)
 
