@@ -29,6 +29,7 @@
 // units (about 0.2 % of the value), 4096 bins reaching down to 1/256 of the reference, smaller
 // values lumped in the first bin; candidates seen before the reference exists are not counted.
 #include <stddef.h>
+#include <math.h>
 #include <type_traits>
 
 #include "pq_internal.h"
@@ -2312,9 +2313,15 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // Measured optimum (10^7 .. 10^9 codes, 1 .. 200 queries): about 64 M code evaluations over all
     // queries of the call, at most a thirty-second of the database per query.
     // Smaller databases: a sixteenth of the codes, at least 16 per result wanted (the sample of a few queries is added up
-    // by a few blocks; 10^5 codes, 16 queries, top-100: 65 536 codes 58 us, 6250 codes 26).
+    // by a few blocks; 10^5 codes, 16 queries, top-100: 65 536 codes 58 us, 6250 codes 26), and more the more candidates the bound
+    // lets through, nq topk n / sample of them: their sum with the sample's cost is least near 0.6 sqrt(nq topk n) (16 tables,
+    // 70 000 codes, 240 queries, top-100: a sixteenth 215 us, a quarter 122, all 152; 8 tables, 150 000 codes, 16 queries,
+    // top-1000 148, 132, 143; top-1 62, 74, 86).
     int64_t seed_codes_f32 = SEED_CODES_STREAM;   // (integer scans use the same count)
-    int seed_codes_few = (int)(n / 16 < SEED_CODES_STREAM ? n / 16 : SEED_CODES_STREAM);
+    const double seed_balance = 0.625 * sqrt((double)nq * (double)topk * (double)n);
+    int64_t seed_few = n / 16 > (int64_t)seed_balance ? n / 16 : (int64_t)seed_balance;
+    if (seed_few > SEED_CODES_STREAM) seed_few = SEED_CODES_STREAM;
+    int seed_codes_few = (int)seed_few;
     if (seed_codes_few < 16 * topk) seed_codes_few = 16 * topk;
     if (seed_codes_few < PRUNE_INIT) seed_codes_few = PRUNE_INIT;
     if ((int64_t)seed_codes_few > n) seed_codes_few = (int)n;
