@@ -428,6 +428,7 @@ __global__ void ivf_pair_abs_kernel(const uint32_t *__restrict__ qlist_off, size
 // The whole grouping of a small call by one block: what the kernels above do, one after the other, with what only they share
 // in LDS.  (Nine launches of a few microseconds each: one query, 48 of 1024 lists, 35 us of them; this 7.)
 constexpr int IVF_GROUP_LISTS = 4096, IVF_GROUP_PAIRS = 4096;   // 64 KB of LDS; pairs that a block of 1024 threads handles in a few rounds
+constexpr int IVF_GROUP_QUERIES = 512;   // (a wave per query, one after the other: 1500 queries, one list each, call 249 us against 215)
 struct IvfGroupArgs {
     const int32_t *probes;
     const int64_t *list_offsets;
@@ -997,7 +998,7 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
         // The grouping of the pairs needs the probed lists only: it runs on a stream of the context's own (same priority)
         // beside the residuals and their tables, and joins the caller's stream before the first bounds.  Small calls: one
         // launch, and with up to 512 pairs (tables of a few microseconds) not worth the events of a second stream.
-        const bool group_small = nlist <= IVF_GROUP_LISTS && npairs <= IVF_GROUP_PAIRS, forked = !(group_small && npairs <= 512);
+        const bool group_small = nlist <= IVF_GROUP_LISTS && npairs <= IVF_GROUP_PAIRS && nqb <= IVF_GROUP_QUERIES, forked = !(group_small && npairs <= 512);
         hipStream_t g = forked ? ctx->aux_stream : s;
         if (forked) {
             PQ_HIP(ctx, hipEventRecord(ctx->aux_fork, s));
