@@ -1045,9 +1045,11 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
         if (forked) PQ_HIP(ctx, hipStreamWaitEvent(s, ctx->aux_join, 0));   // the work items are laid out
         if (quick) {
             unsigned long long *tau_q = (unsigned long long *)(ws + o_tauq);
+            // (two streams: both scans in flight together, 4096 lists, 8 M codes, 300 queries x 4 lists 0.77 of the time; without
+            // long lists 1.05 of it, and of calls of few pairs on many lists 1.08)
             rc = launch_ivf_quick(ctx, L->codes, L->list_offsets, probes, luts, nqb, nprobe, init, kprime, topk,
                                   (float *)(ws + o_qmaxp), ws + o_qluts, items, nitems_dev, pairs_by_list, pair_out, nc,
-                                  partial, tau_q, (uint32_t *)(ws + o_qrows), quick_rows, forked);
+                                  partial, tau_q, (uint32_t *)(ws + o_qrows), quick_rows, (size_t)nqb * lists_per_query, forked && (nlist <= IVF_GROUP_LISTS || npairs >= IVF_GROUP_PAIRS));
             if (rc) return rc;
             rc = launch_merge_filtered(ctx, partial, qlist_off, 0, 0, 1, tau_q, kpad, nqb, topk, L->ids, false,
                                        out_dist + (size_t)q0 * topk, out_ids + (size_t)q0 * topk);

@@ -519,7 +519,7 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
                      const float *luts, int nq, int nprobe, int init, int kprime, int topk, float *qmax_pair,
                      uint8_t *qluts, const IvfItem *items, uint32_t *nitems_dev, const int32_t *pairs_by_list,
                      const uint32_t *pair_out, const uint32_t *nc_arr, uint64_t *partial, unsigned long long *tau_key,
-                     uint32_t *saved_rows, int64_t max_item_rows, bool two_streams) {
+                     uint32_t *saved_rows, int64_t max_item_rows, size_t most_items, bool two_streams) {
     if (kprime < 1 || kprime > QK_KP || topk < 1 || topk > QK_KP || init < 1 || init > QK_INIT_MAX)
         return fail(ctx, PQ_EUNSUPPORTED, "ivf quick adc: kprime and topk must be 1..%d, init 1..%d", QK_KP, QK_INIT_MAX);
     hipStream_t s = ctx->stream;
@@ -549,11 +549,13 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
         const int cap_long = ivf_quick_saved_cap(max_item_rows, 8), cap_short = ivf_quick_saved_cap(QK_LONG_MIN, 4);
         hipStream_t s2 = two_streams ? ctx->aux_stream : s;
         if (two_streams) PQ_HIP(ctx, hipEventRecord(ctx->aux_fork, s));
-        long_kernel<<<ctx->num_cu * 2, 8 * 64, sizeof(QuickSmemLong), s>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
+        // (no more blocks than there can be items: each draws from the counter, one after the other)
+        auto blocks = [&](int full) { return (unsigned)(most_items < (size_t)full ? most_items : (size_t)full); };
+        long_kernel<<<blocks(ctx->num_cu * 2), 8 * 64, sizeof(QuickSmemLong), s>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
                                                                        kprime, partial, saved_rows, cap_long, luts, probes, nc_arr, nprobe, topk, tau_key);
         PQ_HIP(ctx, hipGetLastError());
         if (two_streams) PQ_HIP(ctx, hipStreamWaitEvent(s2, ctx->aux_fork, 0));
-        short_kernel<<<ctx->num_cu * 4, 4 * 64, sizeof(QuickSmemShort), s2>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
+        short_kernel<<<blocks(ctx->num_cu * 4), 4 * 64, sizeof(QuickSmemShort), s2>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
                                                                           kprime, partial,
                                                                           saved_rows + (size_t)ctx->num_cu * 2 * 8 * cap_long, cap_short, luts, probes, nc_arr,
                                                                           nprobe, topk, tau_key);
