@@ -1269,18 +1269,18 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     uint64_t per_block = total / (8ull * (unsigned)ctx->num_cu);
     uint32_t piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_PIECE_MIN * RR_PIECE_MIN;
     if (piece < RR_PIECE_MIN) piece = RR_PIECE_MIN;
-    // Long lists: the complete tables of the queries cost less than the rows of the candidates: for 65 536 centroids of 32
-    // dimensions per sub-space 0.78 us of the GPU per query, and 29 ps per candidate for its four entries, against 67 ps for its
-    // four rows: from 20 000 candidates per query on, a third of the centroids.  (25 M codes, 1000 queries with 41 000 candidates
-    // each on average: call 9.33 -> 8.83 ms, with 52 000: 10.98 -> 10.42.  Fewer than 128 queries count as 128, which is on the
-    // safe side: 10 queries with 66 000 each are served in 0.67 ms on rows and would be in 0.57 on tables.)  Queries go in
-    // batches whose tables stay below RR_TABLE_BYTES.
+    // Long lists: the complete tables of the queries cost less than the rows of the candidates.  65 536 centroids of 32 dimensions
+    // per sub-space: 0.78 us of the GPU per query and 29 ps per candidate for its four entries, against 50 to 67 ps for its four
+    // rows: from half as many candidates as centroids on.  (25 M codes, 1000 queries with 41 000 candidates each on average:
+    // call 9.33 -> 8.83 ms, with 52 000: 10.98 -> 10.42; 100 000 codes, 100 queries, 32 768 each 508 -> 468 us, 16 384 each
+    // 345 against 395.)  Rows below 24 dimensions cost less and the tables the same: from as many candidates as centroids on.
+    // Fewer than 128 queries count as 128.  Queries go in batches whose tables stay below RR_TABLE_BYTES.
     const bool rr_vec = (dsub & 3) == 0 && ((uintptr_t)codebooks & 15) == 0;
     const size_t table_bytes = (size_t)DQ_M * k * 4;
     int table_batch = (int)(RR_TABLE_BYTES / table_bytes / 128 * 128);   // (k <= 65536: 256 at least)
     if (table_batch > RR_TABLE_QUERIES) table_batch = RR_TABLE_QUERIES;
     const int table_dims = dsub <= 32 ? 32 : 64;   // of a padded sub-vector
-    bool with_tables = total * 3 >= (uint64_t)((nq + 127) / 128 * 128) * (uint64_t)k;
+    bool with_tables = total * (dsub < 24 ? 1 : 2) >= (uint64_t)((nq + 127) / 128 * 128) * (uint64_t)k;
     with_tables = rr_vec && dsub >= 8 && dsub < 64 && opt_int(ctx, PQ_OPT_DERIVED_TABLES, with_tables ? 1 : 0) != 0;
     if (with_tables) piece = 8 * RR_TILE;   // (shorter than at most: what the blocks of a die work on belongs to few queries; 2, 4, 16 tiles: 10.8, 10.6, 10.5 against 10.4 ms per call)
     const size_t max_items = (size_t)(total / piece) + (size_t)nq;

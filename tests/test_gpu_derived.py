@@ -215,11 +215,11 @@ def test_derived_search_rerank_pieces(ctx, dsub, nq, n, r2, topk, shift):
 
 
 @pytest.mark.parametrize("dsub,k,nq,n,r2,topk", [(8, 256, 129, 4000, 300, 17), (32, 1024, 5, 70_000, 60_000, 100), (12, 300, 260, 2100, 2100, 128)])
-def test_derived_search_rerank_on_complete_tables(ctx, dsub, k, nq, n, r2, topk):
-    """Lists so long (for the number of centroids) that the queries' complete tables are formed: ragged pieces, one and
+def test_derived_search_rerank_on_complete_tables(ctx, opts, dsub, k, nq, n, r2, topk):
+    """The queries' complete tables, as for lists that are long for the number of centroids: ragged pieces, one and
     several dies' shares, more queries than a tile of the Tables step."""
     cb, cbar, codes, queries = make_problem(dsub + nq, n, k, dsub, nq)
-    assert r2 * nq * 3 >= (nq + 127) // 128 * 128 * k   # (every query has at least r2 candidates: the rule for the tables holds)
+    opts.set("derived_tables", 1)
     run_case(ctx, cb, cbar, codes, queries, r2, topk)
 
 
@@ -236,26 +236,30 @@ def exact_case(ctx, cb, cbar, codes, queries, topk):
 
 @pytest.mark.parametrize("dsub", [8, 32, 60])
 @pytest.mark.parametrize("nq", [1, 40, 129])
-def test_derived_search_rerank_near_hits(ctx, nq, dsub):
+def test_derived_search_rerank_near_hits(ctx, opts, nq, dsub):
     """Queries that nearly hit a vector (5e-5 of its length away): the terms are sums of squared differences in double, where
     norms and products of that size would have lost the distance.  The same bits for a query alone and among others."""
     cb, cbar, codes, _ = make_problem(nq + dsub, 3000, 1024, dsub, 1)
     near = cb[np.arange(4)[None, :], codes[:nq].astype(np.int64)].reshape(nq, 4 * dsub)
     queries = (near * np.float32(1 + 5e-5)).astype(np.float32)
+    opts.set("derived_tables", 1)
     gd, gi = exact_case(ctx, cb, cbar, codes, queries, 20)
+    opts.set("derived_tables", 0)
     assert np.array_equal(gi[:, 0].cpu().numpy(), np.arange(nq))
     for q in (0, nq - 1):
         d1, i1 = exact_case(ctx, cb, cbar, codes, queries[q:q + 1], 20)
         assert torch.equal(d1[0], gd[q]) and torch.equal(i1[0], gi[q])
 
 
-def test_derived_search_rerank_infinite_components(ctx):
+@pytest.mark.parametrize("tables", [0, 1])
+def test_derived_search_rerank_infinite_components(ctx, opts, tables):
     """Centroids with infinite components: their codes are infinitely far and stand behind the finite ones, by row."""
     cb, cbar, codes, queries = make_problem(31, 120, 256, 32, 130)
     cb[1, 7, 3] = np.inf
     cb[2, 9, 31] = -np.inf
     codes[::3, 1] = 7
     codes[1::7, 2] = 9
+    opts.set("derived_tables", tables)
     gd, _ = exact_case(ctx, cb, cbar, codes, queries, 128)
     assert torch.isinf(gd[:, 60:]).any() and not torch.isnan(gd).any()
 
