@@ -49,7 +49,7 @@ typedef float enc_float4 __attribute__((ext_vector_type(4)));
 constexpr int ENC_MAX_DS = 64;      // 4 chunks of 16 dimensions: 64 KB of LDS for the centroids, 128 registers for the vectors
 constexpr int ENC_VECS = 64;        // vectors per wave (4 tiles of 16): one LDS read of centroids feeds 8 matrix instructions
 constexpr size_t ENC_RESIDENT_BYTES = 156 * 1024;   // of 160 KB of LDS
-constexpr float ENC_NO_CENTROID = -1e38f;   // start value of rows past the last centroid
+constexpr float ENC_NO_CENTROID = -1e38f;   // start value of rows past the last centroid and of copies of an earlier one
 
 struct EncodeInfo { float scale, bound, cmax2, pad; };   // per sub-space: S_j; error bound; ||c||_max^2 in scaled units (inf: nothing is settled)
 
@@ -60,7 +60,8 @@ __host__ __device__ constexpr int encode_image_len(int tiles, int nch) { return 
 __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restrict__ codebooks, int k, int ds, int nch, int tiles,
                                                            uint4 *__restrict__ images) {
     __shared__ float red[16], mean[ENC_MAX_DS];
-    __shared__ unsigned int cmax_bits;
+    __shared__ unsigned int cmax_bits, row_hash[256];
+    __shared__ bool copy_of_earlier[256];
     const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const float *cb = codebooks + (size_t)j * k * ds;
     uint4 *const image = images + (size_t)j * encode_image_len(tiles, nch);
@@ -96,17 +97,44 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
     const bool ranked = amax < __builtin_inff() && e <= 126;
     e = e > 126 ? 126 : e;
     const float scale = ldexpf(1.f, e);
-    for (int c = tid; c < tiles * 16; c += 1024) {
+    for (int c = tid; c < tiles * 16; c += 1024) {   // (one round: 256 at most)
         double norm = 0.0;
+        unsigned int hash = 2166136261u;
         if (c < k)
             for (int t = 0; t < ds; ++t) {
-                const double v = (double)((cb[(size_t)c * ds + t] - mean[t]) * scale);
+                const float x = cb[(size_t)c * ds + t];
+                const double v = (double)((x - mean[t]) * scale);
                 norm += v * v;
+                hash = (hash ^ __float_as_uint(x)) * 16777619u;
             }
+        row_hash[c] = hash;
+        copy_of_earlier[c] = false;
         start[c] = c < k ? (float)(-0.5 * norm) : ENC_NO_CENTROID;
         if (c < k) {
             const float nf = (float)norm;
             atomicMax(&cmax_bits, __float_as_uint(nf == nf ? nf : __builtin_inff()));   // (non-negative floats order like their bits)
+        }
+    }
+    __syncthreads();
+    // Equal centroids (a sub-space that is constant in the data has nothing else) tie for every vector they are nearest to, and the
+    // ranking would leave them all open.  The smallest index wins a tie, so the copies take no part, like rows past the last one.
+    // (400 000 vectors, 8 x 256: all centroids equal 9.1 -> 0.20 ms, every one there twice 0.55 -> 0.21; looking for them 2 us.)
+    {
+        const int c = tid & 255, quarter = tid >> 8;   // four threads per centroid
+        int equal = -1;   // (an earlier row of the same hash)
+        if (c < k) {
+            const unsigned int hash = row_hash[c];
+#pragma unroll 8
+            for (int e = quarter; e < c; e += 4) equal = row_hash[e] == hash ? e : equal;
+        }
+        if (equal >= 0) {
+            bool same = true;
+#pragma unroll 4
+            for (int t = 0; t < ds; ++t) same = same && __float_as_uint(cb[(size_t)equal * ds + t]) == __float_as_uint(cb[(size_t)c * ds + t]);
+            if (same) {
+                copy_of_earlier[c] = true;
+                start[c] = ENC_NO_CENTROID;
+            }
         }
     }
     if (tid < nch * 16) offset[tid] = mean[tid] * scale;
@@ -128,7 +156,7 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int t = ch * 16 + 8 * (g & 1) + q;
-            const float v = c < k && t < ds ? (cb[(size_t)c * ds + t] - mean[t]) * scale : 0.f;
+            const float v = c < k && t < ds && !copy_of_earlier[c] ? (cb[(size_t)c * ds + t] - mean[t]) * scale : 0.f;
             const _Float16 hi = (_Float16)v;
             h[q] = g >> 1 ? (_Float16)(v - (float)hi) : hi;
         }

@@ -580,6 +580,24 @@ def test_encode_without_scratch(ctx, opts, ds, m, k, n):
         assert np.array_equal(host(ctx.pq_encode(dev(x), dev(cb), fmt)), ref), split
 
 
+@pytest.mark.parametrize("ds,m,k,n", [(16, 4, 256, 2000), (7, 4, 16, 500), (1, 8, 256, 300), (40, 2, 100, 700)])
+@pytest.mark.parametrize("distinct", [1, 2, 37])
+def test_encode_equal_centroids(ctx, ds, m, k, n, distinct):
+    """Codebooks with copies of centroids, one with an infinite component among them: the first copy is the code."""
+    r = np.random.default_rng(ds + distinct)
+    fmt = orc.CODES_U4_PACKED if k == 16 else orc.CODES_U8
+    pool = r.normal(size=(m, distinct, ds)).astype(np.float32)
+    if distinct == 37:
+        pool[1, 5, ds - 1] = np.inf
+    cb = pool[:, r.integers(0, distinct, k)]
+    x = r.normal(size=(n, m, ds)).astype(np.float32)
+    x[::3] = cb[:, r.integers(0, k)]
+    x = x.reshape(n, m * ds)
+    with np.errstate(invalid="ignore"):
+        ref = orc.pq_encode(x, cb)
+    assert np.array_equal(host(ctx.pq_encode(dev(x), dev(cb), fmt)), orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref)
+
+
 @pytest.mark.parametrize("m,k,warm", [(8, 256, True), (8, 256, False), (16, 16, True)])
 def test_encode_in_a_captured_graph(m, k, warm):
     """A graph with pq_encode is replayed on new vectors while later calls on the context, eager ones with larger codebooks
