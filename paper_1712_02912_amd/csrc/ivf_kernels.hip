@@ -1060,14 +1060,14 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
         float *tau0 = (float *)(ws + o_tau0);
         // The sample of a query is added up by one block, and the candidates that its bound lets through, topk codes / sample of
         // them, are sorted out by the `workers` blocks that scan for one query at a time: their sum is least near a multiple of
-        // sqrt(topk codes / workers), 16 with 8 tables (16-bit lower bounds: a loose bound costs exact distances as well), 6
+        // sqrt(topk codes / workers), 20 with 8 tables (16-bit lower bounds: a loose bound costs exact distances as well), 6
         // with 16.  Lists differ in length and the long ones decide, hence eight lists more than are probed.  At least 16 per result
         // wanted and 1024.  8 M codes in 4096 lists, 8 tables, one list probed, top-128: 16 queries 221 us with 2048 codes, 116
         // with 8192; 1500 queries 750 and 407 with 16 384; 1 M codes in 1024 lists, 48 probed, one query, top-100: this kernel 38 us
-        // with 16 384 codes, 18 with 5900.
+        // with 16 384 codes, 18 with 5900; encoded data, 16 queries, 152 us with 5000, 140 with 7000.
         const double codes_probed = (double)L->ntotal / nlist * (nprobe + 8);
         const double workers = nqb >= 1024 ? 1.0 : (1024.0 / nqb < nprobe ? 1024.0 / nqb : (double)nprobe);
-        const double balance = (m == 8 ? 16.0 : 6.0) * sqrt((double)topk * codes_probed / workers);
+        const double balance = (m == 8 ? 20.0 : 6.0) * sqrt((double)topk * codes_probed / workers);
         int sample = balance < (double)IVF_SEED_CODES ? (int)balance : IVF_SEED_CODES;
         if (sample < 16 * topk) sample = 16 * topk;
         if (sample < 1024) sample = 1024;
