@@ -13,9 +13,13 @@
  *     no pointer past the call.  Arrays are dense, row-major, in the shapes given.
  *   - Work is enqueued on the HIP stream the context was created with and is
  *     asynchronous: results are valid after that stream is synchronised.
- *   - The context owns a device workspace that grows on demand (hipMalloc inside the
- *     call when a larger one is needed, otherwise no allocation).  One context must
- *     not be used from two host threads at once.
+ *   - The context owns device memory that grows on demand (hipMalloc inside the call when
+ *     more is needed, otherwise no allocation) and is given back by pq_destroy: a workspace
+ *     that all calls share, and buffers for the converted operands of large Tables and Index
+ *     steps, the centroid images of pq_encode and the candidate lists of pq_derived_search.
+ *     A HIP graph that captured a call holds the addresses it used; they stay valid until a
+ *     call that needs more.  pq_encode under capture uses none of this memory.  One context
+ *     must not be used from two host threads at once.
  *   - Return value: PQ_OK (0) or a negative pq_status.  Arguments are validated before
  *     anything is enqueued (a PQ_EINVAL / PQ_ESHAPE / PQ_EUNSUPPORTED leaves the outputs
  *     untouched); a PQ_EHIP or PQ_ENOMEM, and the PQ_ESHAPE of pq_derived_search for a
@@ -119,7 +123,10 @@ int pq_rotate(pq_ctx *ctx, const float *vectors, const float *rot, int64_t n, in
 /* Encoder of the product quantizer (Section 2.3.1, "Vector Encoding"): sub-vector j of every
  * vector is replaced by the index of the closest centroid of codebook j,
  *   code_j(x) = argmin_i || x^j - C^j[i] ||^2, ties to the smallest i,
- * decided on distances computed in double precision.
+ * decided on distances computed in double precision.  Centroids of up to 64 dimensions are ranked on the fp16 matrix
+ * cores first (operands as two halves, from scratch memory of at most 67 KB per sub-space); where the ranking's error bound
+ * leaves the nearest one open, the definition decides.  Longer ones, calls that cannot have the scratch memory and calls
+ * on a stream that is being captured measure every centroid: the same codes.
  *   vectors [n][d] f32, codebooks [m][k][d/m] f32  ->  codes [n][code_bytes] u8
  * (PQ_CODES_U8: m bytes, k <= 256; PQ_CODES_U4_PACKED: m/2 bytes, k <= 16, m even).
  * Requires d % m == 0. */
@@ -150,8 +157,8 @@ int pq_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf
  *   out_val [nq][topk] f32 (float tables) or u32 (u8 tables, plain integer sums, no
  *   saturation); out_ids [nq][topk] i64.
  * Covered: (U8 codes, F32 tables, k = 256, m = 8 or 16), (U4 codes, U8 tables, k = 16,
- * m = 16), and any (U8 | U4 codes, F32 | U8 tables) with m*k <= 8192 through a slower
- * general kernel.  1 <= topk <= 1024, 0 <= n < 2^32; `codes` 16-byte aligned.
+ * m = 16; m = 32 from 1024 codes on, or from topk + 1 for topk above 128), and any (U8 | U4
+ * codes, F32 | U8 tables) with m*k <= 8192 through a slower general kernel.  1 <= topk <= 1024, 0 <= n < 2^32; `codes` 16-byte aligned.
  * Float sums add the m entries in fp32, in table order or in a rotation of it (the result
  * differs from the exact sum by at most (m-1) * 2^-24 relative either way).  For k = 256,
  * m = 8 or 16 and n >= 65536 the kernel first dismisses codes by integer lower bounds of their
@@ -159,9 +166,11 @@ int pq_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf
  * for the codes they cannot rule out) and forms float sums only for the rest; the result is
  * that of the plain definition.  The bounds are 16-bit sums for 8 queries per pass over the
  * codes, or, for m = 8 and 249 queries and more, 8-bit sums for 16 queries per pass.
- * Integer sums are exact; with 249 queries and more and n >= 65536 the integer scan also
- * runs on 8-bit lower bounds of its sums (16 queries per pass) and adds up the exact sums
- * only for the codes that pass.
+ * Integer sums are exact; with 249 queries and more and n >= 65536 the integer scan of 16
+ * tables also runs on 8-bit lower bounds of its sums (16 queries per pass) and adds up the
+ * exact sums only for the codes that pass.  Every scan of these shapes starts from a first
+ * bound of the result, found on a sample of the codes (float scans from 4096 codes on, integer
+ * scans from 512 and twice topk).
  * (Switches: pq_set_option.) */
 int pq_adc_scan_topk(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf, const void *luts,
                      pq_lut_fmt lf, int nq, int m, int k, int topk, void *out_val, int64_t *out_ids);
@@ -177,7 +186,8 @@ int pq_adc_scan_topk(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt c
  * Limit: the scratch the scan needs must fit.  That holds for the tuned shapes with topk <= 128 and
  * fewer than 249 queries, whatever n is (about 120 MiB on 256 compute units), and for calls of the
  * general kernel with few (chunk, query) blocks; a request that does not fit returns PQ_ENOMEM with a
- * message naming both sizes, and nothing has been enqueued.
+ * message naming both sizes, and nothing has been enqueued.  32 x 4 codes whose lists do not fit go to the
+ * general kernel before that.
  * Every call on a GPU shares that GPU's array (whatever the context or stream): calls that overlap
  * in time on one GPU race.  The array keeps the last call's contents; everything that must start
  * from a known value (work counter, bounds, histograms, candidate counters) is cleared by the call's
@@ -207,9 +217,10 @@ int pq_rerank_f32(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf, 
  *   Step 2    the buckets are taken in increasing order until r2 vectors are in; the bucket
  *             of the r2-th vector is finished, so the candidates of a query are all codes up
  *             to that bucket b* (all codes if n < r2).  Their precise distances
- *             sum_j || y^j - C^j[c[j]] ||^2 come from the full codebooks (each term summed in
- *             double and rounded to f32 like a table entry, the four terms added in double,
- *             rounded once); the topk smallest (distance, row) are returned, padded with
+ *             sum_j || y^j - C^j[c[j]] ||^2 come from the full codebooks (each term a sum of
+ *             squared differences in double, rounded to f32 like a table entry, the four terms
+ *             added in double, rounded once; the same bits whether the terms are formed candidate
+ *             by candidate or, for long lists, in complete tables of the queries); the topk smallest (distance, row) are returned, padded with
  *             (+inf, -1).
  *   codes [n][4] u16 (device, 16-byte aligned; index c[j] < k), derived_codebooks [4][256][d/4],
  *   codebooks [4][k][d/4], queries [nq][d]  ->  out_dist [nq][topk] f32, out_ids [nq][topk] i64.
@@ -218,7 +229,8 @@ int pq_rerank_f32(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf, 
  * with -1 (PQ_ESHAPE if a query has more than cand_cap candidates).
  * The capped-buckets lists of the thesis are replaced by two passes over the codes (bucket
  * counts, then the ids of the buckets 0..b*); between them the call waits for the stream and
- * reads the nq list sizes back to size its workspace.  With 640 queries and more the second pass
+ * reads the lists' total size back to size their memory: 16 bytes per candidate (8, if there is
+ * no more), 1 KB per 512 candidates or more, and for long lists up to 256 MB of tables.  With 640 queries and more the second pass
  * takes 16 queries per pass over the codes (lower bounds of the integer sums in the loop, exact
  * sums for the codes that pass; option scan_q8 = 0: 8 queries per pass as for fewer queries).
  * Covered: m = 4, d % 4 == 0, d <= 4096, 256 <= k <= 65536, 1 <= topk <= 128, r2 >= 1,

@@ -531,7 +531,7 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
     if (ctx->profiling) {
         PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, s));
         snprintf(ctx->last_scan_name, sizeof(ctx->last_scan_name),
-                 "ivf_quick_scan_kernel (16x4 codes, 8-bit tables of 8 (query, list) pairs per work item; blocks of 8 waves for items of %d rows and more, of 4 waves for the others)", QK_LONG_MIN);
+                 "ivf_quick_scan_kernel (16x4 codes, 8-bit tables of 8 (query, list) pairs per work item; blocks of 8 waves for lists of %d rows and more, of 4 waves for the others)", QK_LONG_MIN);
         ctx->last_scan_qpp = QK_QS;
         ctx->last_scan_passes = 2;
         ctx->stat_parked = nullptr;

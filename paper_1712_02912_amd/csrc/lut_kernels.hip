@@ -565,7 +565,7 @@ static int lut_ws_reserve(pq_ctx *ctx, size_t bytes) {
     const hipError_t e = hipMalloc(&p, want);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        return fail(ctx, PQ_ENOMEM, "allocation of %zu bytes for the operands of the Tables step failed: %s", want, hipGetErrorString(e));
+        return fail(ctx, PQ_ENOMEM, "allocation of %zu bytes for the converted operands of a Tables or Index step failed: %s", want, hipGetErrorString(e));
     }
     ctx->lut_ws = p;
     ctx->lut_ws_bytes = want;

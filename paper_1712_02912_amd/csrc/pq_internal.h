@@ -27,7 +27,7 @@ struct pq_ctx {
     void *ws;          // device workspace, grown on demand (or the fixed scratch of the call that allocates nothing)
     size_t ws_bytes;
     int ws_fixed;      // ws must not grow: a request beyond ws_bytes is an error
-    void *lut_ws;      // Tables step of many tiles: operands as doubles and their norms, grown on demand
+    void *lut_ws;      // converted operands of Tables steps of many tiles (as doubles) and of the Index step (as halves), grown on demand
     size_t lut_ws_bytes;
     // (buffers of their own: a captured Tables step holds the address of lut_ws, which these calls must not move)
     pq_buf encode_images;   // pq_encode: the centroids as matrix operands
