@@ -2,7 +2,7 @@
 
 A step is one pass of the whole path over one batch of synthetic input, inputs resident in HBM:
   headline (BASELINE config 1): tables for 1000 queries + float ADC scan of 25 M 8-byte codes + top-100.
-Beside it, each as an object of the same JSON line:
+Beside it:
   config1_encoded      the same step on codes encoded from mixture vectors (pq_encode on the GPU);
   pq16x4 / pq16x4_encoded   config 2: tables, qmax pre-scan, 8-bit tables, integer scan top-1000, fp32 rerank top-100;
   streaming_pq8x8 / streaming_pq16x4   few queries over 25 M / 10^8 / 10^9 codes: every byte from HBM once per pass;
@@ -10,7 +10,7 @@ Beside it, each as an object of the same JSON line:
   ivf_config4          config 4: 10^9 codes in 65 536 Zipf-sized lists, 10 000 queries, nprobe 64;
   ivf_quick_adc_config4  the same index searched with Quick ADC (16 x 4 codes, 8-bit tables, integer scan, float rerank);
   cpu_baseline         the oracle's scan on the host cores (a bounded sample of config 1).
-Prints ONE JSON line.
+Prints ONE JSON line: the headline, and of each of these its time, value and agreement with the oracle (--detail FILE: the full records).
 """
 import argparse
 import json
@@ -110,6 +110,7 @@ def main():
     ap.add_argument("--streaming-n", type=int, nargs="+", default=[25_000_000, 100_000_000, 1_000_000_000])
     ap.add_argument("--streaming-queries", type=int, nargs="+", default=None,
                     help="numbers of queries of the streaming cases (default: 1 8 64 256 for 8x8, 1 8 for 16x4)")
+    ap.add_argument("--detail", default=None, metavar="FILE", help="write every leg's full record there (the printed line is a summary)")
     ap.add_argument("--calibration-copy-mib", type=int, default=0,
                     help="also run one plain copy kernel of this many MiB (counter calibration under rocprofv3)")
     args = ap.parse_args()
@@ -459,7 +460,37 @@ def main():
             result["ivf_config4"]["cpu_baseline"] = cpu_baseline_ivf(ivf, min(args.ivf_cpu_queries, 10000), args.topk)
         if ivf_quick is not None:
             result["ivf_quick_adc_config4"]["cpu_baseline"] = cpu_baseline_ivf_quick(ivf_quick, min(args.ivf_cpu_queries // 2, 10000), args.topk)
-    print(json.dumps(result))
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(result, f, indent=1)
+    print(json.dumps(summary(result)))
+
+
+def rounded(v):
+    return float("%.5g" % v) if isinstance(v, float) else v
+
+
+def summary(result):
+    """The line that is printed: the headline with its roofline and oracle timing, and per further leg its time, its value and whether
+    the oracle agreed (two kilobytes; --detail writes everything)."""
+    line = {k: rounded(v) for k, v in result.items() if not isinstance(v, dict)}
+    line["config"] = result["config"]
+    line["roofline"] = {k: rounded(result["roofline"][k]) for k in ("bound", "achieved", "peak", "unit", "frac", "traffic", "kernel_ms")}
+    line["roofline"]["lds_frac"] = rounded(result["roofline"]["lds"]["frac"])
+    if "cpu_baseline" in result:
+        line["cpu_baseline"] = {k: rounded(result["cpu_baseline"][k]) for k in ("value", "unit", "cores", "kind", "gpu_matches_oracle_on_sample")}
+    legs = {}
+    for name, leg in result.items():
+        if not isinstance(leg, dict) or name in ("config", "roofline", "pruning", "cpu_baseline"):
+            continue
+        if "cases" in leg:
+            legs[name] = ["%d codes x %d: %.4g ms" % (c["codes"], c["queries"], c["call_ms"]) for c in leg["cases"]]
+            continue
+        legs[name] = {short: rounded(leg[k]) for k, short in (("ms_per_step", "ms"), ("ms_per_call", "ms"), ("value", "value")) if k in leg}
+        if "cpu_baseline" in leg:
+            legs[name]["oracle"] = leg["cpu_baseline"]["gpu_matches_oracle_on_sample"]
+    line["legs"] = legs
+    return line
 
 
 def ids_agree(gpu_ids, orc_ids):
