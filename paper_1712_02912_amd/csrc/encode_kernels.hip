@@ -34,8 +34,8 @@ namespace pq {
 // centroids within twice the bound of the largest value are measured as the definition has it, in double; which these
 // are is known if no lane has two of them, else the ranking of the 16 vectors concerned is repeated.
 //
-// Bound by the vector instructions: 2.25 per (vector, centroid) pair of a lane, the matrix cores busy in parallel for about
-// the same time; splitting the vectors and, with 16 centroids, waiting for their rows.  Measured, against the fp64 form
+// Bound by issue: vector instructions (2.25 per (vector, centroid) pair of a lane) hold the SIMDs for 59 % of the cycles, matrix
+// instructions, which do not overlap with them, for 26 %; with 16 centroids 59 % and 4 %, the rest waits for rows.  Measured, against the fp64 form
 // below (which reads each centroid tile once per 64 vectors and is bound by fp64 conversions, LDS and the fp64 matrix rate):
 //   4 M vectors, d = 128, 8 x 256    17.0 -> 1.7 ms (0.09 ms of it measuring what the ranking leaves open)
 //   4 M vectors, d = 128, 16 x 16     7.5 -> 1.3 ms
