@@ -214,10 +214,10 @@ def test_derived_search_rerank_pieces(ctx, dsub, nq, n, r2, topk, shift):
     run_case(ctx, cb, cbar, codes, queries, r2, topk)
 
 
-@pytest.mark.parametrize("dsub,k,nq,n,r2,topk", [(8, 256, 129, 4000, 300, 17), (32, 1024, 5, 70_000, 60_000, 100), (12, 300, 260, 2100, 2100, 128)])
+@pytest.mark.parametrize("dsub,k,nq,n,r2,topk", [(8, 256, 129, 4000, 300, 17), (32, 1024, 5, 70_000, 60_000, 100), (12, 300, 260, 2100, 2100, 128), (8, 65536, 300, 1500, 400, 20)])
 def test_derived_search_rerank_on_complete_tables(ctx, opts, dsub, k, nq, n, r2, topk):
     """The queries' complete tables, as for lists that are long for the number of centroids: ragged pieces, one and
-    several dies' shares, more queries than a tile of the Tables step."""
+    several dies' shares, more queries than a block takes and, with 65 536 centroids, than one batch of tables."""
     cb, cbar, codes, queries = make_problem(dsub + nq, n, k, dsub, nq)
     opts.set("derived_tables", 1)
     run_case(ctx, cb, cbar, codes, queries, r2, topk)
