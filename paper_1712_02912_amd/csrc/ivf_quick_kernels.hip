@@ -35,6 +35,7 @@ constexpr int QK_LONG_MIN = 1 << IVF_QUICK_LONG_CLASS;   // lists of this many r
 constexpr int QK_BINS = 512;      // sums counted per pass: base .. base + 510, and one bin for everything above
 constexpr int QK_KP = 128;        // kprime at most (the length of a result list)
 constexpr int QK_BATCH = 4;       // codes of a thread on their way at a time
+constexpr int QK_DBINS = IVF_QUICK_DBINS;   // bins of a query's float distances, over 0 .. qmax
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(256) void ivf_quick_qmax_kernel(const uint8_t *__re
                                                              const int64_t *__restrict__ list_offsets,
                                                              const int32_t *__restrict__ probes, const float *__restrict__ luts,
                                                              int nprobe, int init, int topk, float *qmax_pair,
-                                                             unsigned long long *tau_key) {
+                                                             unsigned long long *tau_key, uint32_t *dist_bins, float *dist_inv) {
     __shared__ float tab[256];
     __shared__ uint32_t vals[QK_INIT_MAX];
     __shared__ uint32_t bins[256], state[2];
@@ -92,7 +93,27 @@ __global__ __launch_bounds__(256) void ivf_quick_qmax_kernel(const uint8_t *__re
     float qmax = __builtin_inff();
     if (count > 0) qmax = ord_to_f32(block_kth_smallest_u32(vals, count, (uint32_t)(topk < count ? topk : count), bins, state));
     for (int r = tid; r < nprobe; r += 256) qmax_pair[(size_t)q * nprobe + r] = qmax;
+    static_assert(QK_DBINS == 256, "a thread per bin");
+    if (dist_bins) dist_bins[(size_t)q * QK_DBINS + tid] = 0u;
     if (tid == 0) tau_key[q] = KEY_EMPTY;
+    if (tid == 0 && dist_bins) {
+        const float inv = (float)QK_DBINS / qmax;
+        dist_inv[q] = qmax > 0.f && inv < __builtin_inff() ? inv : 0.f;   // (0, NaN, infinity or subnormal qmax: no bins)
+    }
+}
+
+// What a query's bound says about the integer sums of one of its pairs.  A code of float distance D = sum of its entries t_j has
+// 8-bit entries of at most (t_j - qmin) * scale each (rounded down, or 255 where that is more), so D <= tau implies
+// sum <= (tau - 16 qmin) * scale: codes of greater sums are in no result, whether or not they are among the kprime smallest of
+// their pair.  The factors 1 + 1e-6 and the unit on top cover the roundings of D, t_j - qmin and the product (2^-22 together).
+// Returns the greatest sum that can matter, -1 if none can, QK_NO_CAP without a bound (no tau yet, or NaN anywhere).
+constexpr int QK_NO_CAP = 0xfffe;
+__device__ __forceinline__ int quick_sum_cap(unsigned long long tau_key, float qmin, float scale) {
+    if (tau_key == KEY_EMPTY) return QK_NO_CAP;
+    const double tau = (double)ord_to_f32((uint32_t)(tau_key >> 32));
+    const double c = (tau + fabs(tau) * 1e-6 - 16.0 * (double)qmin) * (double)scale * (1.0 + 1e-6);
+    if (!(c < (double)(QK_NO_CAP - 1))) return QK_NO_CAP;
+    return c < 0.0 ? -1 : (int)c + 1;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -111,6 +132,11 @@ struct __align__(16) QuickSmem {
     uint32_t cap[QK_QS];                         // sums above it are not counted (the kprime-th smallest sum so far)
     uint32_t cum_t[QK_QS];                       // sums from `base` on below the cap (all counted sums while none is reached)
     int reached[QK_QS];
+    int tcap[QK_QS];                             // the greatest sum that the query's bound leaves a chance (quick_sum_cap)
+    float qmin[QK_QS], scale[QK_QS], dinv[QK_QS];
+    unsigned long long tau[QK_QS];               // the query's bound when the item began
+    int counted[QK_QS];                          // candidates put into the query's bins
+    int alive[QK_QS];                            // some code of the pair can be in the result
     int pair[QK_QS];
     uint32_t out_idx[QK_QS];
     int pending;                                 // pairs whose T is not known yet
@@ -125,6 +151,14 @@ static_assert(QK_LONG_MIN <= 65536, "rows of short items fit 16 bits");
 static_assert(sizeof(QuickSmemShort) <= 40 * 1024, "four blocks of 4 waves share the 160 KB of a compute unit");
 static_assert(sizeof(QuickSmemLong) <= 80 * 1024, "two blocks of 8 waves per compute unit");
 
+// per pair: smallest entry (NaN: the tables hold one) and scale of the 8-bit tables; per query: bins of the candidates' float
+// distances and their factor
+struct QuickBound {
+    const float *qmin, *scale;
+    uint32_t *dist_bins;
+    const float *dist_inv;
+};
+
 // Blocks of QK_WAVES waves.  LONG: the kernel takes the work items of lists of QK_LONG_MIN rows and more (8 waves, two blocks
 // per compute unit: the longest item of a skewed index is what the call waits for), else the others (4 waves,
 // four blocks per compute unit).  The table of items has those of the long lists first; blocks draw them from a counter.
@@ -134,7 +168,12 @@ static_assert(sizeof(QuickSmemLong) <= 80 * 1024, "two blocks of 8 waves per com
 // the float keys go to the result list directly (the separate rerank fetched 82 M candidates' codes from memory again,
 // one block of 128 threads per pair: 1.86 ms of the billion-code call).
 // 10^9 codes in 65 536 lists, 10 000 queries x 64 probes: both scans and the rerank 14.2 -> 12.6 ms.
-template <int QK_WAVES, bool LONG>
+// BOUNDS: sums of different pairs have no common scale, but a query's bound on the float distance is a bound on each pair's
+// sums (quick_sum_cap), so the lists scanned first cut down what the later ones count, save, collect and rerank: most lists
+// then hold fewer than kprime codes that matter, and the whole prefix of sums up to the bound is kept, which is what makes
+// the candidates of a pair those of the definition as far as the result can see them.  Both scans 12.4 -> 9.9 ms (with the
+// final bounds known from the start they would take 8 ms: the rest is the loop's LDS reads and additions).
+template <int QK_WAVES, bool LONG, bool BOUNDS>
 __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_kernel(const uint8_t *__restrict__ codes,
                                                                        const uint8_t *__restrict__ qluts,
                                                                        const IvfItem *__restrict__ items,
@@ -144,13 +183,14 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
                                                                        uint64_t *partial, uint32_t *saved_rows, int saved_cap,
                                                                        const float *__restrict__ luts, const int32_t *__restrict__ probes,
                                                                        const uint32_t *__restrict__ nc_arr, int nprobe, int topk,
-                                                                       unsigned long long *tau_key) {
+                                                                       unsigned long long *tau_key, QuickBound qb) {
     constexpr int QK_THREADS = QK_WAVES * 64;
     extern __shared__ __align__(16) unsigned char quick_smem[];
     typedef typename std::conditional<LONG, uint32_t, uint16_t>::type TieRow;
     QuickSmem<QK_WAVES, TieRow> &sm = *reinterpret_cast<QuickSmem<QK_WAVES, TieRow> *>(quick_smem);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int first_item = LONG ? 0 : (int)nitems_dev[2], nitems = LONG ? (int)nitems_dev[2] : (int)nitems_dev[0];
+    const bool share = BOUNDS && nitems - first_item > (int)gridDim.x;   // (items of one round all begin without bounds)
     uint32_t *const work_counter = nitems_dev + (LONG ? 4 : 5);
     // rows of the item that the counting pass found at or below some pair's cap of the moment, per wave in the order
     // the wave met them (ascending): the only rows the collecting pass has to look at again
@@ -177,10 +217,24 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
             sm.sure_cnt[tid] = 0;
             sm.below[tid] = 0u;
             sm.base[tid] = 0u;
-            sm.tstar[tid] = 0xffffu;
-            sm.found[tid] = (tid >= nslots || nvalid <= kprime) ? 1 : 0;
+            sm.counted[tid] = 0;
+            if constexpr (!BOUNDS) {
+                sm.alive[tid] = tid < nslots;
+                sm.tcap[tid] = QK_NO_CAP;
+                sm.tstar[tid] = 0xffffu;
+                sm.found[tid] = (tid >= nslots || nvalid <= kprime) ? 1 : 0;
+            }
         }
         __syncthreads();
+        // (what the query's bound says of the pair: requested by the last wave, beside the tables)
+        float cap_min = 0.f, cap_scale = 0.f, cap_inv = 0.f;
+        unsigned long long cap_tau = 0ull;
+        const int cap_slot = tid - (QK_THREADS - 64);
+        const int cap_pair = cap_slot >= 0 && cap_slot < nslots ? sm.pair[cap_slot] : -1;
+        if (BOUNDS && cap_pair >= 0) {
+            cap_tau = __hip_atomic_load(tau_key + cap_pair / nprobe, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            cap_min = qb.qmin[cap_pair]; cap_scale = qb.scale[cap_pair]; cap_inv = qb.dist_inv[cap_pair / nprobe];
+        }
         // ---- the 8-bit tables of the item's pairs, widened to 16 bits, pair s in half s of the slot
         if (tid < 256) {
             uint32_t w[4] = {0u, 0u, 0u, 0u};
@@ -192,7 +246,20 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
             }
             sm.tab[tid] = make_uint4(w[0], w[1], w[2], w[3]);
         }
-        __syncthreads();
+        if (BOUNDS && cap_slot >= 0 && cap_slot < QK_QS) {
+            const int tcap = cap_pair >= 0 ? quick_sum_cap(cap_tau, cap_min, cap_scale) : -1;
+            sm.tau[cap_slot] = cap_tau; sm.qmin[cap_slot] = cap_min; sm.scale[cap_slot] = cap_scale; sm.dinv[cap_slot] = cap_inv;
+            sm.tcap[cap_slot] = tcap;
+            sm.alive[cap_slot] = tcap >= 0;
+            sm.tstar[cap_slot] = tcap == QK_NO_CAP ? 0xffffu : tcap < 0 ? 0u : (uint32_t)tcap;
+            sm.found[cap_slot] = (tcap < 0 || nvalid <= kprime) ? 1 : 0;
+        }
+        if constexpr (!BOUNDS) {
+            __syncthreads();
+        } else if (__syncthreads_or(cap_slot >= 0 && cap_slot < QK_QS && sm.tcap[cap_slot] >= 0) == 0) {   // no code of the list can be in a result
+            for (int e = tid; e < nslots * QK_KP; e += QK_THREADS) partial[(size_t)sm.out_idx[e / QK_KP] * QK_KP + e % QK_KP] = KEY_EMPTY;
+            continue;
+        }
 
         // sums of one code for the eight pairs: four registers of two 16-bit sums
         uint32_t tab_lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)sm.tab;   // LDS address of the tables
@@ -252,7 +319,8 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
                 if (attempt > 0) use_saved = false;   // (rows of a second counting pass would be saved twice: all rows are looked at again)
                 for (int i = tid; i < QK_QS * QK_BINS; i += QK_THREADS) (&sm.hist[0][0])[i] = 0u;
                 if (tid < QK_QS) {
-                    sm.cap[tid] = sm.base[tid] + (uint32_t)(QK_BINS - 2);
+                    const uint32_t last = sm.base[tid] + (uint32_t)(QK_BINS - 2);
+                    sm.cap[tid] = BOUNDS && sm.tcap[tid] < (int)last ? (uint32_t)sm.tcap[tid] : last;   // (a pair without a chance is not counted)
                     sm.reached[tid] = 0;
                     sm.cum_t[tid] = 0u;
                 }
@@ -288,9 +356,13 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
                         }
                     });
                     __syncthreads();
+                    const bool refresh = share && seg_len >= 8 * QK_BATCH * QK_THREADS;
                     // a wave reads the bins of a pair: lane l owns bins 8 l .. 8 l + 7 (the last bin stays empty)
                     for (int s = wave; s < QK_QS; s += QK_WAVES) {
                         if (sm.found[s]) continue;   // (uniform)
+                        // (the bound falls while other lists of the query are scanned)
+                        unsigned long long tau_now = KEY_EMPTY;
+                        if (refresh) tau_now = __hip_atomic_load(tau_key + sm.pair[s] / nprobe, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         uint32_t b8[8], tot = 0u;
 #pragma unroll
                         for (int t = 0; t < 8; ++t) { b8[t] = sm.hist[s][lane * 8 + t]; tot += b8[t]; }
@@ -314,16 +386,25 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
                         } else if (lane == 63) {
                             sm.cum_t[s] = incl;   // all sums counted so far
                         }
+                        if (refresh && lane == 0) sm.tcap[s] = quick_sum_cap(tau_now, sm.qmin[s], sm.scale[s]);
                     }
                     __syncthreads();
+                    if constexpr (BOUNDS) {
+                        if (tid < QK_QS && sm.found[tid] == 0 && sm.tcap[tid] < (int)sm.cap[tid]) sm.cap[tid] = sm.tcap[tid] < 0 ? 0u : (uint32_t)sm.tcap[tid];
+                        __syncthreads();
+                    }
                     seg_begin = seg_end;
                 }
                 if (tid < QK_QS && sm.found[tid] == 0) {
-                    sm.below[tid] += sm.cum_t[tid];
-                    if (sm.reached[tid]) {
+                    if (BOUNDS && (sm.tcap[tid] < 0 || (uint32_t)sm.tcap[tid] <= sm.cap[tid])) {   // every sum the bound leaves is counted: fewer than kprime, or as many with ties
                         sm.tstar[tid] = sm.cap[tid];
                         sm.found[tid] = 1;
-                    } else {   // fewer than kprime sums up to base + 510: count the next 511 values
+                    } else if (sm.reached[tid]) {
+                        sm.below[tid] += sm.cum_t[tid];
+                        sm.tstar[tid] = sm.cap[tid];
+                        sm.found[tid] = 1;
+                    } else {
+                        sm.below[tid] += sm.cum_t[tid];   // fewer than kprime sums up to base + 510: count the next 511 values
                         sm.base[tid] += (uint32_t)(QK_BINS - 1);
                         atomicAdd(&sm.pending, 1);
                     }
@@ -339,13 +420,15 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
             uint32_t tplus[4] = {0u, 0u, 0u, 0u};   // T + 1 per pair (0 for empty slots: nothing passes)
             uint32_t tval[QK_QS];
             int need[QK_QS], tcnt[QK_QS];
+            bool alive[QK_QS];
 #pragma unroll
             for (int s = 0; s < QK_QS; ++s) {
                 tval[s] = sm.tstar[s];
-                const uint32_t tp = s < nslots ? (tval[s] < 0xffffu ? tval[s] + 1u : 0xffffu) : 0u;
+                alive[s] = BOUNDS ? sm.alive[s] != 0 : s < nslots;
+                const uint32_t tp = alive[s] ? (tval[s] < 0xffffu ? tval[s] + 1u : 0xffffu) : 0u;
                 tplus[s >> 1] |= tp << (16 * (s & 1));
                 // rows at T that can still be candidates: kprime less the sums below T (none when every code is taken)
-                need[s] = (s < nslots && tval[s] < 0xffffu) ? kprime - (int)sm.below[s] : 0;
+                need[s] = (alive[s] && tval[s] < 0xffffu) ? kprime - (int)sm.below[s] : 0;
                 tcnt[s] = 0;
             }
             scnt = __builtin_amdgcn_readfirstlane(scnt);
@@ -373,7 +456,7 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
 #pragma unroll
                 for (int s = 0; s < QK_QS; ++s) {
                     const uint32_t sum = (acc[s >> 1] >> (16 * (s & 1))) & 0xffffu;
-                    const bool in = valid && s < nslots;
+                    const bool in = valid && alive[s];
                     if (in && sum < tval[s]) {
                         const int at = atomicAdd(&sm.sure_cnt[s], 1);   // (fewer than kprime such codes exist)
                         sm.sure[s][at] = ((unsigned long long)sum << 32) | (row0 + (uint32_t)i);
@@ -439,15 +522,58 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
                 if (key == KEY_EMPTY) continue;
                 const uint32_t row = (uint32_t)key;
                 const uint2 c = *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
-                sm.sure[s][idx] = ((unsigned long long)f32_to_ord(adc16x4_exact(tabf + s * 256, c)) << 32) | row;
+                const float dist = adc16x4_exact(tabf + s * 256, c);
+                const unsigned long long fkey = ((unsigned long long)f32_to_ord(dist) << 32) | row;
+                sm.sure[s][idx] = fkey;
+                if (share && fkey <= sm.tau[s] && sm.dinv[s] > 0.f) {   // (a key above the bound says nothing new)
+                    const float at = dist * sm.dinv[s];
+                    if (at >= 0.f && at < (float)QK_DBINS) {
+                        atomicAdd(&qb.dist_bins[(size_t)(sm.pair[s] / nprobe) * QK_DBINS + (int)at], 1u);
+                        sm.counted[s] = 1;
+                    }
+                }
             }
             __syncthreads();
-            // a pair's topk-th key bounds its query's result
+            // two bounds of the query's result: the pair's topk-th key, and the bin edge at or below which topk candidates of all
+            // the query's lists so far lie
             for (int s = wave; s < nslots; s += QK_WAVES) {
-                if (sm.sure[s][topk - 1] == KEY_EMPTY) continue;   // (keys first, empty slots behind)
-                const uint64_t two[2] = {sm.sure[s][lane], sm.sure[s][64 + lane]};
-                const uint64_t kth = wave_select_kth<2>(two, topk);
-                if (lane == 0) atomicMin(&tau_key[sm.pair[s] / nprobe], (unsigned long long)kth);
+                if (sm.sure[s][BOUNDS ? 0 : topk - 1] == KEY_EMPTY) continue;   // (keys first, empty slots behind)
+                const int q = sm.pair[s] / nprobe;
+                const unsigned long long before = BOUNDS ? sm.tau[s] : KEY_EMPTY;
+                unsigned long long bound = before;
+                if (sm.sure[s][topk - 1] != KEY_EMPTY) {
+                    const uint64_t two[2] = {sm.sure[s][lane], sm.sure[s][64 + lane]};
+                    const uint64_t kth = wave_select_kth<2>(two, topk);
+                    if (kth < bound) bound = kth;
+                }
+                if (BOUNDS && sm.counted[s]) {
+                    uint32_t b4[4], tot = 0u;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        b4[t] = __hip_atomic_load(qb.dist_bins + (size_t)q * QK_DBINS + lane * 4 + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        tot += b4[t];
+                    }
+                    uint32_t incl = tot;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const uint32_t up = __shfl_up(incl, o);
+                        if (lane >= o) incl += up;
+                    }
+                    const uint64_t reach = __ballot(incl >= (uint32_t)topk);
+                    if (reach != 0ull) {
+                        const int first = __builtin_ctzll(reach);
+                        int bin = lane * 4;
+                        uint32_t cum = incl - tot;
+#pragma unroll
+                        for (int t = 0; t < 3; ++t) if (cum + b4[t] < (uint32_t)topk) { cum += b4[t]; ++bin; } else break;
+                        bin = __builtin_amdgcn_readlane(bin, first);
+                        // (dist * dinv < bin + 1 in fp32, so dist is below this edge)
+                        const float edge = (float)(bin + 1) / sm.dinv[s] * (1.f + 1e-6f);
+                        const unsigned long long key = ((unsigned long long)f32_to_ord(edge) << 32) | 0xffffffffull;
+                        if (key < bound) bound = key;
+                    }
+                }
+                if (lane == 0 && bound < before) atomicMin(&tau_key[q], bound);
             }
         }
         for (int e = tid; e < nslots * QK_KP; e += QK_THREADS) {
@@ -467,7 +593,7 @@ constexpr int QK_RR_THREADS = 1024, QK_RR_PAIRS = 256, QK_RR_LISTS = QK_RR_THREA
 __global__ __launch_bounds__(QK_RR_THREADS) void ivf_quick_rerank_kernel(const uint8_t *__restrict__ codes, const float *__restrict__ luts,
                                                                const int32_t *__restrict__ probes, const uint32_t *__restrict__ nc_arr,
                                                                const uint32_t *__restrict__ pair_out, int npairs, int nprobe, int kprime,
-                                                               int topk, uint64_t *partial, unsigned long long *tau_key) {
+                                                               int topk, uint64_t *partial, unsigned long long *tau_key, QuickBound qb) {
     __shared__ float tab[256];
     __shared__ uint64_t keys[QK_RR_THREADS];
     __shared__ int todo[QK_RR_PAIRS], ntodo;
@@ -491,7 +617,12 @@ __global__ __launch_bounds__(QK_RR_THREADS) void ivf_quick_rerank_kernel(const u
             if (tid >= QK_KP) keys[tid] = at < (size_t)nc * QK_KP ? lists[at] : KEY_EMPTY;
             block_bitonic_sort(keys, QK_RR_THREADS);
         }
-        const uint64_t key = tid < kprime ? keys[tid] : KEY_EMPTY;
+        // Chunks scanned under different bounds left out different sums; below the bound of now none did, and there the smallest
+        // keys are those of the whole list.
+        const int tcap = qb.qmin ? quick_sum_cap(__hip_atomic_load(tau_key + pair / nprobe, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), qb.qmin[pair], qb.scale[pair])
+                                 : QK_NO_CAP;
+        uint64_t key = tid < kprime ? keys[tid] : KEY_EMPTY;
+        if (tcap != QK_NO_CAP && (int64_t)(key >> 32) > (int64_t)tcap) key = KEY_EMPTY;
         __syncthreads();
         uint64_t fkey = KEY_EMPTY;
         if (key != KEY_EMPTY) {
@@ -519,14 +650,15 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
                      const float *luts, int nq, int nprobe, int init, int kprime, int topk, float *qmax_pair,
                      uint8_t *qluts, const IvfItem *items, uint32_t *nitems_dev, const int32_t *pairs_by_list,
                      const uint32_t *pair_out, const uint32_t *nc_arr, uint64_t *partial, unsigned long long *tau_key,
-                     uint32_t *saved_rows, int64_t max_item_rows, size_t most_items, bool two_streams) {
+                     uint32_t *dist_bins, float *dist_inv, float *qmin, float *scale, uint32_t *saved_rows, int64_t max_item_rows, size_t most_items, bool two_streams, bool bounds) {
     if (kprime < 1 || kprime > QK_KP || topk < 1 || topk > QK_KP || init < 1 || init > QK_INIT_MAX)
         return fail(ctx, PQ_EUNSUPPORTED, "ivf quick adc: kprime and topk must be 1..%d, init 1..%d", QK_KP, QK_INIT_MAX);
     hipStream_t s = ctx->stream;
     const int npairs = nq * nprobe;
-    ivf_quick_qmax_kernel<<<nq, 256, 0, s>>>(codes, list_offsets, probes, luts, nprobe, init, topk, qmax_pair, tau_key);
+    ivf_quick_qmax_kernel<<<nq, 256, 0, s>>>(codes, list_offsets, probes, luts, nprobe, init, topk, qmax_pair, tau_key, bounds ? dist_bins : nullptr, dist_inv);
     PQ_HIP(ctx, hipGetLastError());
-    int rc = launch_quantize_luts(ctx, luts, npairs, 16, 16, qmax_pair, qluts, nullptr, nullptr);
+    const QuickBound qb = {bounds ? qmin : nullptr, bounds ? scale : nullptr, dist_bins, dist_inv};
+    int rc = launch_quantize_luts(ctx, luts, npairs, 16, 16, qmax_pair, qluts, bounds ? qmin : nullptr, bounds ? scale : nullptr, bounds);
     if (rc) return rc;
     if (ctx->profiling) {
         PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, s));
@@ -539,8 +671,8 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
         ctx->stat_ncand_len = 0;
     }
     {
-        auto long_kernel = ivf_quick_scan_kernel<8, true>;
-        auto short_kernel = ivf_quick_scan_kernel<4, false>;
+        auto long_kernel = bounds ? ivf_quick_scan_kernel<8, true, true> : ivf_quick_scan_kernel<8, true, false>;
+        auto short_kernel = bounds ? ivf_quick_scan_kernel<4, false, true> : ivf_quick_scan_kernel<4, false, false>;
         PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(long_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)sizeof(QuickSmemLong)));
         PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(short_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -552,13 +684,13 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
         // (no more blocks than there can be items: each draws from the counter, one after the other)
         auto blocks = [&](int full) { return (unsigned)(most_items < (size_t)full ? most_items : (size_t)full); };
         long_kernel<<<blocks(ctx->num_cu * 2), 8 * 64, sizeof(QuickSmemLong), s>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
-                                                                       kprime, partial, saved_rows, cap_long, luts, probes, nc_arr, nprobe, topk, tau_key);
+                                                                       kprime, partial, saved_rows, cap_long, luts, probes, nc_arr, nprobe, topk, tau_key, qb);
         PQ_HIP(ctx, hipGetLastError());
         if (two_streams) PQ_HIP(ctx, hipStreamWaitEvent(s2, ctx->aux_fork, 0));
         short_kernel<<<blocks(ctx->num_cu * 4), 4 * 64, sizeof(QuickSmemShort), s2>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
                                                                           kprime, partial,
                                                                           saved_rows + (size_t)ctx->num_cu * 2 * 8 * cap_long, cap_short, luts, probes, nc_arr,
-                                                                          nprobe, topk, tau_key);
+                                                                          nprobe, topk, tau_key, qb);
         PQ_HIP(ctx, hipGetLastError());
         if (two_streams) {
             PQ_HIP(ctx, hipEventRecord(ctx->aux_join, s2));
@@ -569,7 +701,7 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
         PQ_HIP(ctx, hipEventRecord(ctx->ev_end, s));
         ctx->ev_valid = 1;
     }
-    ivf_quick_rerank_kernel<<<(npairs + QK_RR_PAIRS - 1) / QK_RR_PAIRS, QK_RR_THREADS, 0, s>>>(codes, luts, probes, nc_arr, pair_out, npairs, nprobe, kprime, topk, partial, tau_key);
+    ivf_quick_rerank_kernel<<<(npairs + QK_RR_PAIRS - 1) / QK_RR_PAIRS, QK_RR_THREADS, 0, s>>>(codes, luts, probes, nc_arr, pair_out, npairs, nprobe, kprime, topk, partial, tau_key, qb);
     PQ_HIP(ctx, hipGetLastError());
     return PQ_OK;
 }

@@ -1315,7 +1315,7 @@ __global__ __launch_bounds__(256) void quantize_luts_kernel(const float *__restr
 // Queries of 256 entries (16 x 16 tables): one wave per query, four entries per lane, the same operations (one block per
 // query was bound by its launches: 640 000 (query, list) pairs 0.55 -> 0.14 ms).
 __global__ __launch_bounds__(256) void quantize_luts256_kernel(const float4 *__restrict__ luts, int nq, const float *__restrict__ qmax,
-                                                               uint32_t *__restrict__ qluts, float *qmin_out, float *scale_out) {
+                                                               uint32_t *__restrict__ qluts, float *qmin_out, float *scale_out, bool mark_nan) {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (q >= nq) return;
     const float4 v = luts[(size_t)q * 64 + lane];
@@ -1337,17 +1337,18 @@ __global__ __launch_bounds__(256) void quantize_luts256_kernel(const float4 *__r
         w |= (uint32_t)(t >= 255.0f ? (uint8_t)255 : (uint8_t)floorf(t)) << (8 * i);
     }
     qluts[(size_t)q * 64 + lane] = w;
+    const bool has_nan = mark_nan && __ballot(__builtin_isnan(v.x) || __builtin_isnan(v.y) || __builtin_isnan(v.z) || __builtin_isnan(v.w)) != 0ull;
     if (lane == 0) {
-        if (qmin_out) qmin_out[q] = qmin;
+        if (qmin_out) qmin_out[q] = has_nan ? __builtin_nanf("") : qmin;
         if (scale_out) scale_out[q] = scale;
     }
 }
 
 int launch_quantize_luts(pq_ctx *ctx, const float *luts, int nq, int m, int k, const float *qmax, uint8_t *qluts,
-                         float *qmin_out, float *scale_out) {
+                         float *qmin_out, float *scale_out, bool mark_nan) {
     if (nq == 0) return PQ_OK;
     if (m * k == 256 && ((uintptr_t)luts & 15) == 0 && ((uintptr_t)qluts & 3) == 0)
-        quantize_luts256_kernel<<<(nq + 3) / 4, 256, 0, ctx->stream>>>((const float4 *)luts, nq, qmax, (uint32_t *)qluts, qmin_out, scale_out);
+        quantize_luts256_kernel<<<(nq + 3) / 4, 256, 0, ctx->stream>>>((const float4 *)luts, nq, qmax, (uint32_t *)qluts, qmin_out, scale_out, mark_nan);
     else
         quantize_luts_kernel<<<nq, 256, 0, ctx->stream>>>(luts, m * k, qmax, qluts, qmin_out, scale_out);
     PQ_HIP(ctx, hipGetLastError());

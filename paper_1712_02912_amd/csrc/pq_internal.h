@@ -84,7 +84,7 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 int launch_build_luts(pq_ctx *ctx, const float *queries, const float *codebooks, int nq, int d, int m, int k,
                       float *luts);
 int launch_quantize_luts(pq_ctx *ctx, const float *luts, int nq, int m, int k, const float *qmax,
-                         uint8_t *qluts, float *qmin_out, float *scale_out);
+                         uint8_t *qluts, float *qmin_out, float *scale_out, bool mark_nan = false);   // (16 x 16 tables: qmin_out NaN where an entry is)
 int launch_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const float *luts, int nq, int m,
                         int k, int init, int kq, float *qmax_out);
 int launch_rerank(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const float *luts, int nq, int m, int k,

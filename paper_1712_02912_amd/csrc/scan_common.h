@@ -35,12 +35,15 @@ struct IvfItem {
 
 // IVF search with Quick ADC (ivf_quick_kernels.hip): the query-wide qmax, the 8-bit tables of every pair, the integer
 // scan of the work items to the kprime candidates of every (pair, chunk) and their float rerank into the pair's
-// first result list; tau_key [nq] receives a bound of each query's result for the merge that follows.
+// first result list; tau_key [nq] receives a bound of each query's result for the merge that follows.  With `bounds`, what is
+// found in one list of a query rules out codes of its other lists; scratch for it: dist_bins [nq][IVF_QUICK_DBINS] and
+// dist_inv [nq], qmin and scale [nq * nprobe].
+constexpr int IVF_QUICK_DBINS = 256;   // bins of a query's float distances
 int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offsets, const int32_t *probes,
                      const float *luts, int nq, int nprobe, int init, int kprime, int topk, float *qmax_pair,
                      uint8_t *qluts, const IvfItem *items, uint32_t *nitems_dev, const int32_t *pairs_by_list,
                      const uint32_t *pair_out, const uint32_t *nc_arr, uint64_t *partial, unsigned long long *tau_key,
-                     uint32_t *saved_rows, int64_t max_item_rows, size_t most_items, bool two_streams);
+                     uint32_t *dist_bins, float *dist_inv, float *qmin, float *scale, uint32_t *saved_rows, int64_t max_item_rows, size_t most_items, bool two_streams, bool bounds);
 // bytes of `saved_rows` (rows that the counting pass of a work item hands to its collecting pass, per wave) when no
 // work item has more than max_item_rows rows
 size_t ivf_quick_saved_bytes(const pq_ctx *ctx, int64_t max_item_rows);

@@ -576,3 +576,31 @@ def test_ivf_quick_result_lists_from_the_farthest_to_the_nearest(ctx, nq, topk):
     od, oi = orc.ivf_quick_search(query, coarse, offsets, packed, None, base, orc.CODES_U4_PACKED, nlist, 200, 128, topk)
     gd, gi = ctx.ivf_quick_adc_search(dev(coarse), dev(offsets), dev(packed), None, dev(base), dev(np.repeat(query, nq, 0)), nlist, 200, 128, topk)[:2]
     assert np.array_equal(gd.cpu().numpy(), np.repeat(od, nq, 0)) and np.array_equal(gi.cpu().numpy(), np.repeat(oi, nq, 0))
+
+
+@pytest.mark.parametrize("kprime,topk,chunk_rows,special", [(128, 100, None, None), (100, 1, None, None), (20, 128, 1024, None), (128, 128, 1024, "ties"),
+                                                            (64, 10, None, "huge"), (128, 50, None, "equal")])
+def test_ivf_quick_bounds_across_lists(ctx, opts, kprime, topk, chunk_rows, special):
+    """Calls whose lists rule out codes of one another (512 rows a list and more, thousands of pairs, more items than blocks):
+    exact against the oracle, with lists in chunks, sums that tie, infinite distances, and a query on top of its codes."""
+    r = np.random.default_rng(kprime + topk)
+    sizes = [600] * 20 + [2500, 3000, 70, 0, 128, 129, 1500, 700, 1023, 1024, 1025, 40]
+    nlist, d, n, nq, nprobe = len(sizes), 32, sum(sizes), 1100, 16
+    coarse = (r.normal(size=(nlist, d)) * 3).astype(np.float32)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    packed = r.integers(0, 256, (n, 8), dtype=np.uint8)
+    cb = (r.normal(size=(16, 16, d // 16)) * 2).astype(np.float32)
+    queries = (r.normal(size=(nq, d)) * 3).astype(np.float32)
+    if special == "ties":
+        packed = packed[r.integers(0, 5, n)]
+    if special == "huge":
+        cb[3, 5] = 1e30
+    if special == "equal":   # all codes the same, of distance zero from the queries that are a list's centroid plus their vector
+        packed[:] = packed[0]
+        idx = np.stack([packed[0] & 15, packed[0] >> 4], 1).reshape(-1)
+        queries[:nlist] = coarse + np.concatenate([cb[j, idx[j]] for j in range(16)])
+    if chunk_rows:
+        opts.set("ivf_quick_chunk_rows", chunk_rows)
+    od, oi = orc.ivf_quick_search(queries, coarse, offsets, packed, None, cb, orc.CODES_U4_PACKED, nprobe, 500, kprime, topk)
+    gd, gi = ctx.ivf_quick_adc_search(dev(coarse), dev(offsets), dev(packed), None, dev(cb), dev(queries), nprobe, 500, kprime, topk)[:2]
+    assert np.array_equal(gd.cpu().numpy(), od) and np.array_equal(gi.cpu().numpy(), oi)
