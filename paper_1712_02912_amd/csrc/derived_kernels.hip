@@ -16,7 +16,9 @@
 // bounds the bucket of the r2-th from above, so every vector at or below the final bucket is
 // always counted); the bucket b* of the r2-th vector and the exact number of vectors in the
 // buckets 0..b* follow from the counts.  A second pass over the codes, with b* fixed, writes the
-// ids of exactly those vectors into a list whose size is known beforehand.  Both passes run the
+// ids of exactly those vectors into a list whose size is known beforehand.  Where the database is large, the first pass looks
+// at a sample only (see launch_derived_search), the second lists what its bounds let through, and the counts are taken from
+// the lists.  Both passes run the
 // same loop: 8 queries per pass over a chunk of codes, tables in LDS as 16-bit entries (8 queries
 // per 16-byte slot, the four tables stored four times in the rotated slot order of lds_walk.h,
 // so every read is conflict-free), four lookups and three packed adds per code, one packed
@@ -38,6 +40,7 @@ constexpr int DQ_BINS = 1024;       // buckets: integer distances are at most 4 
 constexpr int DQ_SUB = 128;         // codes per wave sub-tile (16 bytes = two codes per lane)
 constexpr uint32_t DQ_THR_MAX = 0x7fffu;   // "every sum passes" (sums stay below 1024)
 constexpr int DQ_DEPTH = 4;         // sub-tiles per group of a wave
+constexpr int64_t DQ_SAMPLE_PAIRS = (int64_t)5 << 24;   // (code, query) pairs from which on a sample may replace the counting pass
 constexpr int DQ_RING = 64 * (DQ_DEPTH + 1);   // parked rows per wave: a group's worth behind an unflushed rest
 
 struct DqArgs {
@@ -784,6 +787,90 @@ __global__ __launch_bounds__(64) void derived_bucket_kernel(const uint32_t *g_hi
     }
 }
 
+// A sample of the codes: one of every `step`, at a place in its step that its number's hash picks (the database may be periodic),
+// so that a run of similar codes, as in a database ordered by cluster, is represented to within a code or two.
+__global__ __launch_bounds__(256) void derived_sample_kernel(const uint2 *__restrict__ codes, int64_t nsample, uint32_t step, uint2 *__restrict__ sample) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < nsample) sample[i] = codes[i * step + (((uint32_t)i * 2654435761u) >> 16) % step];
+}
+
+// As derived_bucket_kernel from the counts of a sample (a share 1 / ratio of the codes): the bucket in which the sample's want-th vector falls, and
+// room for the vectors up to it: six standard deviations of the sample's count more than it says.
+__global__ __launch_bounds__(64) void derived_sample_bucket_kernel(const uint32_t *g_hist, int64_t n, uint32_t want, double ratio, uint32_t *bucket,
+                                                                   uint32_t *room) {
+    const int q = blockIdx.x;
+    const uint32_t *gh = g_hist + (size_t)q * DQ_BINS;
+    uint32_t cnt = 0;
+    const int b = first_bin_reaching([&](int i) { return gh[i]; }, want, &cnt);
+    if (threadIdx.x == 0) {
+        bucket[q] = (uint32_t)(b < DQ_BINS ? b : DQ_BINS - 1);
+        const double most = ((double)cnt + 6.0 * sqrt((double)cnt) + 16.0) * ratio;
+        room[q] = most < (double)n ? (uint32_t)most : (uint32_t)n;
+    }
+}
+
+// After a collecting pass on the bounds of a sample: per query the bucket of its r2-th vector and the number of vectors up to it, from the
+// keys of its list (all vectors up to the sample's bucket, in no order); count 2^32 - 1 where the list did not fit or holds
+// fewer than r2 vectors.  One block per query.
+__global__ __launch_bounds__(1024) void derived_settle_kernel(const uint64_t *__restrict__ cand, const uint64_t *__restrict__ cand_off,
+                                                              uint32_t *cand_cnt, int r2, uint32_t *bucket, uint32_t *count) {
+    __shared__ uint32_t hist[DQ_BINS];
+    const int q = blockIdx.x, tid = threadIdx.x;
+    for (int i = tid; i < DQ_BINS; i += 1024) hist[i] = 0u;
+    const uint64_t begin = cand_off[q], room = cand_off[q + 1] - begin;
+    const uint32_t len = cand_cnt[q];
+    __syncthreads();
+    if (len <= room)
+        for (uint32_t i0 = 0; i0 < len; i0 += 4096u) {   // (four keys of a thread on their way)
+            uint32_t sum[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t i = i0 + (uint32_t)(u * 1024 + tid);
+                sum[u] = i < len && i >= i0 ? (uint32_t)(cand[begin + i] >> 32) : (uint32_t)DQ_BINS;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) wave_count_bin(hist, sum[u] < (uint32_t)DQ_BINS, sum[u]);
+            if (i0 + 4096u < i0) break;   // (a list may end near 2^32)
+        }
+    __syncthreads();
+    if (tid >= 64) return;
+    uint32_t cnt = 0;
+    const int b = first_bin_reaching([&](int i) { return hist[i]; }, (uint32_t)r2, &cnt);
+    if (tid == 0) {
+        const bool open = b >= DQ_BINS;   // fewer than r2 vectors, or a list that did not fit
+        bucket[q] = open ? 0u : (uint32_t)b;
+        count[q] = open ? 0xffffffffu : cnt;
+    }
+}
+
+// What the host needs of the settled lists: summary[0] = keys in all lists, summary[1] = the first query whose count exceeds `cap`
+// (nq if none; cap < 0: no limit), summary[2] = that query's count, summary[3] = queries left open.  One block.
+__global__ __launch_bounds__(1024) void derived_summary_kernel(const uint32_t *__restrict__ count, const uint32_t *__restrict__ cand_cnt, int nq, long long cap,
+                                                               unsigned long long *__restrict__ summary) {
+    __shared__ unsigned long long total;
+    __shared__ int bad, open;
+    if (threadIdx.x == 0) { total = 0; bad = nq; open = 0; }
+    __syncthreads();
+    for (int q = threadIdx.x; q < nq; q += 1024) {
+        if (count[q] == 0xffffffffu) atomicAdd(&open, 1);
+        else if (cap >= 0 && (long long)count[q] > cap) atomicMin(&bad, q);
+        atomicAdd(&total, (unsigned long long)cand_cnt[q]);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        summary[0] = total;
+        summary[1] = (unsigned long long)bad;
+        summary[2] = bad < nq ? count[bad] : 0;
+        summary[3] = (unsigned long long)open;
+    }
+}
+
+__global__ void derived_reset_kernel(uint32_t *work_counter, uint32_t *cand_cnt, int nq) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *work_counter = 0;
+    if (i < nq) cand_cnt[i] = 0u;
+}
+
 // Offsets of the candidate lists (exclusive prefix sum of the nq counts, one block) and what the host
 // needs of them: summary[0] = total, summary[1] = the first query whose count exceeds `cap` (nq if
 // none), summary[2] = that query's count.
@@ -845,25 +932,29 @@ __global__ __launch_bounds__(256) void derived_qmax_kernel(const uint8_t *codes,
 }
 
 // What follows from the counts, in one launch before the collecting pass: the work items of Step 2 (a query's candidates in
-// pieces of `piece`; item_off [nq + 1], item_query [item]), the counters and bounds of that pass and of Step 2 reset, the
-// caller's buckets and counts (optional).  One block.
-__global__ __launch_bounds__(1024) void derived_items_kernel(const uint32_t *__restrict__ count, int nq, uint32_t piece,
+// pieces of `piece`; item_off [nq + 1], item_query [item]; list_len: entries of the lists, more than the counts where they hold
+// vectors of later buckets too), the counters of that pass (if given) and the bounds of Step 2 reset, the caller's buckets and
+// counts (optional).  One block.
+__global__ __launch_bounds__(1024) void derived_items_kernel(const uint32_t *__restrict__ count, const uint32_t *list_len, int nq, uint32_t piece,
                                                              uint32_t *__restrict__ item_off, uint32_t *__restrict__ item_query,
                                                              unsigned long long *__restrict__ tau_key, uint32_t *work_counter, uint32_t *__restrict__ cand_cnt,
                                                              const uint32_t *__restrict__ bucket, uint32_t *__restrict__ bucket_out, int64_t *__restrict__ ncand_out) {
     __shared__ uint32_t wsum[16];
     __shared__ uint32_t carry;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) { carry = 0; *work_counter = 0; }
+    if (tid == 0) {
+        carry = 0;
+        if (work_counter) *work_counter = 0;
+    }
     __syncthreads();
     for (int base = 0; base < nq; base += 1024) {
         const int q = base + tid;
         if (q < nq) {
-            cand_cnt[q] = 0u;
+            if (cand_cnt) cand_cnt[q] = 0u;
             if (bucket_out) bucket_out[q] = bucket[q];
             if (ncand_out) ncand_out[q] = (int64_t)count[q];
         }
-        const uint32_t c = q < nq ? count[q] / piece + (count[q] % piece != 0u ? 1u : 0u) : 0u;   // (a count may be close to 2^32)
+        const uint32_t c = q < nq ? list_len[q] / piece + (list_len[q] % piece != 0u ? 1u : 0u) : 0u;   // (a length may be close to 2^32)
         uint32_t incl = c;   // inclusive scan over the wave
         for (int o = 1; o < 64; o <<= 1) {
             const uint32_t other = __shfl_up(incl, o);
@@ -927,7 +1018,7 @@ __device__ __forceinline__ void swap_rows16(double &a, double &b) {
 template <int VEC>
 __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uint8_t *codes, const float *codebooks, int k, int dsub, const float *queries,
                                                                       const uint64_t *cand, const uint2 *cand_code, const uint64_t *cand_off,
-                                                                      const uint32_t *item_off, const uint32_t *item_query, int q_first, int q_end,
+                                                                      const uint32_t *cand_len, const uint32_t *bucket, const uint32_t *item_off, const uint32_t *item_query, int q_first, int q_end,
                                                                       uint32_t piece, int topk, unsigned long long *tau_key, uint64_t *partial,
                                                                       const float *tables) {
     extern __shared__ float4 rr_dyn[];
@@ -953,7 +1044,8 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
     for (; item < item_end; item += step) {
         const int q = (int)item_query[item];
         const uint64_t begin = cand_off[q] + (uint64_t)(item - item_off[q]) * piece;
-        const uint64_t end = begin + piece < cand_off[q + 1] ? begin + piece : cand_off[q + 1];
+        const uint64_t list_end = cand_off[q] + cand_len[q], end = begin + piece < list_end ? begin + piece : list_end;
+        const uint32_t last_sum = bucket[q];   // (entries of later buckets are no candidates)
         __syncthreads();   // the previous item's keys and query have been read
         if (VEC > 0) for (int i = tid; i < DQ_M * dsub; i += RR_THREADS) y[i] = queries[(size_t)q * (DQ_M * dsub) + i];
         for (int i = tid; i < RR_KEEP; i += RR_THREADS) keys[i] = KEY_EMPTY;
@@ -968,10 +1060,12 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
                 const uint64_t c0 = base + (uint64_t)(u * RR_THREADS + wave * 64);
                 if (c0 >= end) break;
                 const uint64_t ci = c0 + lane;
-                const bool have = ci < end;
-                const uint32_t row = (uint32_t)cand[have ? ci : c0];
+                bool have = ci < end;
+                const uint64_t entry = cand[have ? ci : c0];
+                const uint32_t row = (uint32_t)entry;
                 if constexpr (VEC == 0) {
                     const uint2 c = cand_code != nullptr ? cand_code[have ? ci : c0] : *reinterpret_cast<const uint2 *>(codes + (size_t)row * 8);
+                    have = have && (uint32_t)(entry >> 32) <= last_sum;
                     const float *const tab = tables + (size_t)(q - q_first) * DQ_M * k;
                     const uint32_t idx[DQ_M] = {c.x & 0xffffu, c.x >> 16, c.y & 0xffffu, c.y >> 16};
                     double e[DQ_M];
@@ -1038,6 +1132,7 @@ __global__ __launch_bounds__(RR_THREADS, 4) void derived_rerank_kernel(const uin
                 }
                 asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
                 const uint64_t key = ((uint64_t)f32_to_ord(wdist[wave][lane]) << 32) | row;
+                have = have && (uint32_t)(entry >> 32) <= last_sum;
                 if (have && key < bound) keys[RR_KEEP + atomicAdd(&nnew, 1)] = key;   // (room: see the end of the tile)
                 asm volatile("" : : : "memory");   // (the wave's LDS accesses stay in order)
             }
@@ -1079,7 +1174,6 @@ __global__ __launch_bounds__(256) void derived_widen_kernel(const float *__restr
 // Tables step loses bits where a query nearly hits a centroid, and makes a NaN of an infinite component.)  A thread has one
 // centroid in registers, as doubles, and goes through the queries, whose dimensions are the same for the whole wave and come
 // through scalar loads: two fp64 instructions per dimension, nothing else.  Padding adds zeros and changes no sum.
-// TABLES_MEASURED
 constexpr int DT_QUERIES = 64;   // queries per block: what a centroid row's conversion is spread over
 template <int DIMS>
 __global__ __launch_bounds__(256) void derived_tables_kernel(const double *__restrict__ wide, const float *__restrict__ codebooks, int nq, int k, int dsub,
@@ -1129,12 +1223,25 @@ static int launch_derived_tables(pq_ctx *ctx, const float *queries, const float 
     return PQ_OK;
 }
 
-// candidate rows of every query as [nq][cap] ids (ascending positions in the list are not sorted), padded with -1
-__global__ void derived_export_kernel(const uint64_t *cand, const uint64_t *cand_off, int64_t cap, int64_t *out) {
+// candidate rows of every query as [nq][cap] ids (ascending positions in the list are not sorted), padded with -1.  Lists that hold
+// nothing else (place == nullptr), or, from place[q] on (0 at the start), the entries of the buckets up to bucket[q].
+__global__ void derived_export_kernel(const uint64_t *cand, const uint64_t *cand_off, const uint32_t *cand_len, const uint32_t *bucket,
+                                      const uint32_t *count, uint32_t *place, int64_t cap, int64_t *out) {
     const int q = blockIdx.y;
-    const uint64_t begin = cand_off[q], cnt = cand_off[q + 1] - begin;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (int64_t)gridDim.x * blockDim.x)
-        out[(size_t)q * cap + i] = (uint64_t)i < cnt ? (int64_t)(uint32_t)cand[begin + i] : -1;
+    const uint64_t begin = cand_off[q], cnt = count[q];
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = first; i < cap; i += stride) {
+        if ((uint64_t)i >= cnt) out[(size_t)q * cap + i] = -1;
+        else if (place == nullptr) out[(size_t)q * cap + i] = (int64_t)(uint32_t)cand[begin + i];
+    }
+    if (place == nullptr) return;
+    const int64_t len = cand_len[q];
+    for (int64_t i = first; i < len; i += stride) {
+        const uint64_t entry = cand[begin + i];
+        if ((uint32_t)(entry >> 32) > bucket[q]) continue;
+        const uint32_t at = atomicAdd(&place[q], 1u);
+        if ((int64_t)at < cap) out[(size_t)q * cap + at] = (int64_t)(uint32_t)entry;
+    }
 }
 
 }  // namespace
@@ -1155,14 +1262,14 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
 
     // work items: chunk of codes x group of 8 or 16 queries, chunk-major (blocks running together share chunks)
     struct Geometry { int ngroups, nblocks; int64_t nchunks, chunk_codes, nitems; };
-    auto geometry = [&](int qb) {
+    auto geometry = [&](int qb, int64_t n, int min_tiles) {
         Geometry g;
         g.ngroups = (nq + qb - 1) / qb;
         const int64_t block_tile = (int64_t)DQ_SUB * DQ_WAVES;
         int nblocks_max = opt_int(ctx, PQ_OPT_SCAN_BLOCKS, ctx->num_cu);
         if (nblocks_max < 1) nblocks_max = 1;
         int64_t nchunks = ((int64_t)opt_int(ctx, PQ_OPT_SCAN_ITEMS_PER_BLOCK, 4) * nblocks_max + g.ngroups - 1) / g.ngroups;
-        const int64_t max_by_n = (n + 8 * block_tile - 1) / (8 * block_tile);
+        const int64_t max_by_n = (n + min_tiles * block_tile - 1) / (min_tiles * block_tile);
         if (nchunks > max_by_n) nchunks = max_by_n;
         const int64_t min_chunks = (n + ((int64_t)1 << 30) - 1) >> 30;   // a chunk's rows are counted in 32 bits
         if (nchunks < min_chunks) nchunks = min_chunks;
@@ -1176,11 +1283,24 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
         g.nblocks = (int)(g.nitems < nblocks_max ? g.nitems : nblocks_max);
         return g;
     };
-    const Geometry g_count = geometry(DQ_QB), g_collect = geometry(wide ? DQ16_QB : DQ_QB);
+    const Geometry g_count = geometry(DQ_QB, n, 8), g_collect = geometry(wide ? DQ16_QB : DQ_QB, n, 8);
     if (g_count.nitems > 0x3fffffff) return fail(ctx, PQ_EUNSUPPORTED, "derived_search: too many work items (%lld)", (long long)g_count.nitems);
     auto bind_geometry = [&](DqArgs &a, const Geometry &g) {
         a.chunk_codes = g.chunk_codes; a.nchunks = (int)g.nchunks; a.ngroups = g.ngroups; a.nitems = (int)g.nitems;
     };
+
+    // One pass over the codes instead of two where the counting pass is long and a share of the codes says where the r2-th vector
+    // falls: a sample, one code of every sample_step, gives each query a bucket that holds the r2-th vector with 4.5 standard
+    // deviations of the sample's count to spare and the room for its list, the collecting pass lists everything up to it, and
+    // the buckets and counts are taken from the lists (derived_settle_kernel).  Entries of later buckets stay in the lists and are
+    // passed over by Step 2.  A query whose list turns out too short or does not fit sends the call to the two passes.
+    // The sample holds 150 of the r2 vectors at least; below 84 M pairs the additional launches and the second wait cost what the
+    // shorter count saves.  Call: 25 M codes, 1000 queries, r2 = 10 000 9.95 -> 6.75 ms, r2 = 1000 8.30 -> 5.88; 8 M, 100,
+    // 10 000 0.73 -> 0.59; 25 M, 8, 10 000 0.556 -> 0.527; 1 M, 100, 1000 0.233 -> 0.218; but 2 M, 30, 10 000 0.272 -> 0.307
+    // and 8 M, 8, 10 000 0.307 -> 0.318.
+    int sample_step = r2 / 150 < 16 ? r2 / 150 : 16;
+    if (sample_step < 3 || n < (int64_t)r2 * 32 || n * nq < DQ_SAMPLE_PAIRS || opt_int(ctx, PQ_OPT_DERIVED_SAMPLE, 1) == 0) sample_step = 0;
+    const int64_t nsample = sample_step > 0 ? n / sample_step : 0;
 
     // workspace, first part: tables and counts
     size_t off = 0;
@@ -1210,6 +1330,9 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     };
 
     const size_t o_summary = take(256);
+    const size_t o_sbucket = take((size_t)nq * 4);
+    const size_t o_room = take((size_t)nq * 4);
+    const size_t o_sample = take((size_t)nsample * 8);
     const size_t first_part_all = off;
     int rc = ws_reserve(ctx, first_part_all);
     if (rc) return rc;
@@ -1219,116 +1342,197 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
         ctx->host_pin = p;
     }
     DqArgs a;
-    a.codes = codes; a.n = n; a.nq = nq; a.r2 = r2;
-    // Steps 1.1 to 1.3 (counting pass) in the workspace `ws`; leaves the buckets, the counts and the
-    // offsets of the candidate lists there and brings their total (and the first list beyond
-    // cand_cap, if any) to the host: three words through pinned memory.
-    auto count_pass = [&](uint8_t *ws, unsigned long long *total) -> int {
-        int rc = prepare(ws);
-        if (rc) return rc;
-        bind_geometry(a, g_count);
+    a.nq = nq;
+    auto summary_to_host = [&](uint8_t *ws) -> int {   // (a handful of words through pinned memory)
+        PQ_HIP(ctx, hipMemcpyAsync(ctx->host_pin, ws + o_summary, 32, hipMemcpyDeviceToHost, s));
+        PQ_HIP(ctx, hipStreamSynchronize(s));
+        return PQ_OK;
+    };
+    auto cap_error = [&]() {
+        const unsigned long long *pin = (const unsigned long long *)ctx->host_pin;
+        return fail(ctx, PQ_ESHAPE, "derived_search: query %d has %u candidates, cand_cap is %lld", (int)pin[1], (unsigned)pin[2], (long long)cand_cap);
+    };
+    const long long cap_arg = cand_ids_out ? (long long)cand_cap : -1;
+    // The counts of `len` codes up to the bucket of a query's `want`-th vector among them, in the workspace.
+    auto count_codes = [&](uint8_t *ws, const Geometry &g, const uint8_t *some, int64_t len, int want) -> int {
+        bind_geometry(a, g);
+        a.codes = some; a.n = len;
         a.qluts = ws + o_qluts;
         a.work_counter = (uint32_t *)(ws + o_counter);
         a.g_hist = (uint32_t *)(ws + o_hist);
         a.g_bound = (uint32_t *)(ws + o_bound);
         a.bucket = nullptr; a.cand_off = nullptr; a.cand_cnt = nullptr; a.cand = nullptr; a.cand_code = nullptr;
+        a.r2 = want;
         derived_init_kernel<<<256, 256, 0, s>>>(a.work_counter, a.g_hist, (size_t)nq * DQ_BINS, a.g_bound, nq);
         PQ_HIP(ctx, hipGetLastError());
+        if (g.nblocks > 0) {
+            derived_scan_kernel<0><<<g.nblocks, DQ_THREADS, 0, s>>>(a);
+            PQ_HIP(ctx, hipGetLastError());
+        }
+        return PQ_OK;
+    };
+    // Steps 1.1 to 1.3 (counting pass) in the workspace `ws`; leaves the buckets, the counts and the
+    // offsets of the candidate lists there and brings their total (and the first list beyond
+    // cand_cap, if any) to the host: three words through pinned memory.
+    auto count_pass = [&](uint8_t *ws, unsigned long long *total) -> int {
         if (ctx->profiling) {
             note_plain_scan(ctx, "derived_scan_kernel<count> (8 queries per pass)", 8, g_count.ngroups);
             PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, s));
         }
-        if (g_count.nblocks > 0) {
-            derived_scan_kernel<0><<<g_count.nblocks, DQ_THREADS, 0, s>>>(a);
-            PQ_HIP(ctx, hipGetLastError());
-        }
+        int rc = count_codes(ws, g_count, codes, n, r2);
+        if (rc) return rc;
         if (ctx->profiling) {
             PQ_HIP(ctx, hipEventRecord(ctx->ev_end, s));
             ctx->ev_valid = 1;
         }
         derived_bucket_kernel<<<nq, 64, 0, s>>>(a.g_hist, n, r2, (uint32_t *)(ws + o_bucket), (uint32_t *)(ws + o_count));
         PQ_HIP(ctx, hipGetLastError());
-        derived_offsets_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), nq, cand_ids_out ? (long long)cand_cap : -1,
-                                                  (unsigned long long *)(ws + o_candoff), (unsigned long long *)(ws + o_summary));
+        derived_offsets_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), nq, cap_arg, (unsigned long long *)(ws + o_candoff),
+                                                  (unsigned long long *)(ws + o_summary));
         PQ_HIP(ctx, hipGetLastError());
-        unsigned long long *pin = (unsigned long long *)ctx->host_pin;
-        PQ_HIP(ctx, hipMemcpyAsync(pin, ws + o_summary, 24, hipMemcpyDeviceToHost, s));
-        PQ_HIP(ctx, hipStreamSynchronize(s));
-        if (pin[1] < (unsigned long long)nq)
-            return fail(ctx, PQ_ESHAPE, "derived_search: query %d has %u candidates, cand_cap is %lld", (int)pin[1], (unsigned)pin[2],
-                        (long long)cand_cap);
+        rc = summary_to_host(ws);
+        if (rc) return rc;
+        const unsigned long long *pin = (const unsigned long long *)ctx->host_pin;
+        if (pin[1] < (unsigned long long)nq) return cap_error();
         *total = pin[0];
         return PQ_OK;
     };
     uint8_t *ws = (uint8_t *)ctx->ws;
-    unsigned long long total = 0;
-    rc = count_pass(ws, &total);
+    rc = prepare(ws);
     if (rc) return rc;
-    // The sizes of the candidate lists are known now; they live in a buffer of their own, so that what the counting pass left
-    // in the workspace stays.  Pieces of Step 2: as many as there are blocks four times over.
-    uint64_t per_block = total / (8ull * (unsigned)ctx->num_cu);
-    uint32_t piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_PIECE_MIN * RR_PIECE_MIN;
-    if (piece < RR_PIECE_MIN) piece = RR_PIECE_MIN;
-    // Long lists: the complete tables of the queries cost less than the rows of the candidates.  65 536 centroids of 32 dimensions
-    // per sub-space: 0.78 us of the GPU per query and 29 ps per candidate for its four entries, against 50 to 67 ps for its four
-    // rows: from half as many candidates as centroids on.  (25 M codes, 1000 queries with 41 000 candidates each on average:
-    // call 9.33 -> 8.83 ms, with 52 000: 10.98 -> 10.42; 100 000 codes, 100 queries, 32 768 each 508 -> 468 us, 16 384 each
-    // 345 against 395.)  Rows below 24 dimensions cost less and the tables the same: from as many candidates as centroids on.
-    // Fewer than 128 queries count as 128.  Queries go in batches whose tables stay below RR_TABLE_BYTES.
     const bool rr_vec = (dsub & 3) == 0 && ((uintptr_t)codebooks & 15) == 0;
     const size_t table_bytes = (size_t)DQ_M * k * 4;
     int table_batch = (int)(RR_TABLE_BYTES / table_bytes / 128 * 128);   // (k <= 65536: 256 at least)
     if (table_batch > RR_TABLE_QUERIES) table_batch = RR_TABLE_QUERIES;
     const int table_dims = dsub <= 32 ? 32 : 64;   // of a padded sub-vector
-    bool with_tables = total * (dsub < 24 ? 1 : 2) >= (uint64_t)((nq + 127) / 128 * 128) * (uint64_t)k;
-    with_tables = rr_vec && dsub >= 8 && dsub < 64 && opt_int(ctx, PQ_OPT_DERIVED_TABLES, with_tables ? 1 : 0) != 0;
-    if (with_tables) piece = 8 * RR_TILE;   // (shorter than at most: what the blocks of a die work on belongs to few queries; 2, 4, 16 tiles: 10.8, 10.6, 10.5 against 10.4 ms per call)
-    const size_t max_items = (size_t)(total / piece) + (size_t)nq;
-    const size_t o_partial = 0;
-    const size_t o_items = o_partial + align_up(max_items * RR_KEEP * 8, 256);
-    const size_t o_itemoff = o_items + align_up(max_items * 4, 256);
-    const size_t o_tau = o_itemoff + align_up((size_t)(nq + 1) * 4, 256);
-    const size_t o_cand = o_tau + align_up((size_t)nq * 8, 256);
-    const size_t o_code = o_cand + align_up((size_t)total * 8, 256);
-    const size_t o_table = o_code + align_up((size_t)total * 8, 256);
-    const size_t batch_queries = (size_t)(nq < table_batch ? nq : table_batch);
-    const size_t o_wide = o_table + align_up(batch_queries * table_bytes, 256);
-    const size_t table_end = o_wide + batch_queries * DQ_M * table_dims * 8;
-    // (a copy of the candidates' codes beside the list saves Step 2 a random read of the database per candidate; it is
-    // left out if there is no memory for it)
-    bool with_codes = opt_int(ctx, PQ_OPT_DERIVED_CODE_COPY, 1) != 0;
-    auto reserve_lists = [&](size_t bytes) { return buf_reserve(ctx, &ctx->derived_lists, bytes, "the candidate lists"); };
-    rc = reserve_lists(with_tables ? table_end : o_table);
-    if (rc == PQ_ENOMEM && with_tables) {
-        with_tables = false;
-        rc = reserve_lists(o_table);
-    }
-    if (rc == PQ_ENOMEM) {
-        with_codes = false;
-        rc = reserve_lists(o_code);
-    }
-    if (rc) return rc;
-    uint8_t *lists = (uint8_t *)ctx->derived_lists.p;
-    uint32_t *item_off = (uint32_t *)(lists + o_itemoff), *item_query = (uint32_t *)(lists + o_items);
-    unsigned long long *tau_key = (unsigned long long *)(lists + o_tau);
+    unsigned long long total = 0;
+    uint32_t piece = RR_PIECE_MIN;
+    bool with_tables = false;
+    size_t max_items = 0, o_partial = 0, o_cand = 0, o_code = 0, o_table = 0, o_wide = 0;
+    uint8_t *lists = nullptr;
+    uint32_t *item_off = nullptr, *item_query = nullptr;
+    unsigned long long *tau_key = nullptr;
+    for (;; sample_step = 0) {   // (once more, with the two passes, if the lists of a sample's bounds do not do)
+        const bool sampled = sample_step > 0;
+        if (sampled) {
+            derived_sample_kernel<<<(unsigned)((nsample + 255) / 256), 256, 0, s>>>((const uint2 *)codes, nsample, (uint32_t)sample_step, (uint2 *)(ws + o_sample));
+            PQ_HIP(ctx, hipGetLastError());
+            const double ratio = (double)n / (double)nsample, w = (double)r2 / ratio;
+            const uint32_t want = (uint32_t)ceil(w + 4.5 * sqrt(w) + 4.0);
+            rc = count_codes(ws, geometry(DQ_QB, nsample, 32), ws + o_sample, nsample, (int)want);
+            if (rc) return rc;
+            derived_sample_bucket_kernel<<<nq, 64, 0, s>>>(a.g_hist, n, want, ratio, (uint32_t *)(ws + o_sbucket), (uint32_t *)(ws + o_room));
+            PQ_HIP(ctx, hipGetLastError());
+            derived_offsets_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_room), nq, -1, (unsigned long long *)(ws + o_candoff),
+                                                      (unsigned long long *)(ws + o_summary));
+            PQ_HIP(ctx, hipGetLastError());
+            rc = summary_to_host(ws);
+            if (rc) return rc;
+            total = *(const unsigned long long *)ctx->host_pin;   // (room for that many)
+        } else {
+            rc = count_pass(ws, &total);
+            if (rc) return rc;
+        }
+        // The sizes of the candidate lists are known now; they live in a buffer of their own, so that what the counting pass left
+        // in the workspace stays.  Pieces of Step 2: as many as there are blocks four times over.
+        const uint64_t per_block = total / (8ull * (unsigned)ctx->num_cu);
+        piece = per_block > RR_PIECE_MAX ? RR_PIECE_MAX : (uint32_t)per_block / RR_PIECE_MIN * RR_PIECE_MIN;
+        if (piece < RR_PIECE_MIN) piece = RR_PIECE_MIN;
+        // Long lists: the complete tables of the queries cost less than the rows of the candidates.  65 536 centroids of 32 dimensions
+        // per sub-space: 0.78 us of the GPU per query and 29 ps per candidate for its four entries, against 50 to 67 ps for its four
+        // rows: from half as many candidates as centroids on.  (25 M codes, 1000 queries with 41 000 candidates each on average:
+        // call 9.33 -> 8.83 ms, with 52 000: 10.98 -> 10.42; 100 000 codes, 100 queries, 32 768 each 508 -> 468 us, 16 384 each
+        // 345 against 395.)  Rows below 24 dimensions cost less and the tables the same: from as many candidates as centroids on.
+        // Fewer than 128 queries count as 128.  Queries go in batches whose tables stay below RR_TABLE_BYTES.
+        // (the room of a sample's lists is about a fifth more than their entries)
+        const uint64_t entries = sampled ? total / 6 * 5 : total;
+        with_tables = entries * (dsub < 24 ? 1 : 2) >= (uint64_t)((nq + 127) / 128 * 128) * (uint64_t)k;
+        with_tables = rr_vec && dsub >= 8 && dsub < 64 && opt_int(ctx, PQ_OPT_DERIVED_TABLES, with_tables ? 1 : 0) != 0;
+        if (with_tables) piece = 8 * RR_TILE;   // (shorter than at most: what the blocks of a die work on belongs to few queries; 2, 4, 16 tiles: 10.8, 10.6, 10.5 against 10.4 ms per call)
+        max_items = (size_t)(total / piece) + (size_t)nq;
+        o_partial = 0;
+        const size_t o_items = o_partial + align_up(max_items * RR_KEEP * 8, 256);
+        const size_t o_itemoff = o_items + align_up(max_items * 4, 256);
+        const size_t o_tau = o_itemoff + align_up((size_t)(nq + 1) * 4, 256);
+        o_cand = o_tau + align_up((size_t)nq * 8, 256);
+        o_code = o_cand + align_up((size_t)total * 8, 256);
+        o_table = o_code + align_up((size_t)total * 8, 256);
+        const size_t batch_queries = (size_t)(nq < table_batch ? nq : table_batch);
+        o_wide = o_table + align_up(batch_queries * table_bytes, 256);
+        const size_t table_end = o_wide + batch_queries * DQ_M * table_dims * 8;
+        // (a copy of the candidates' codes beside the list saves Step 2 a random read of the database per candidate; it is
+        // left out if there is no memory for it)
+        bool with_codes = opt_int(ctx, PQ_OPT_DERIVED_CODE_COPY, 1) != 0;
+        auto reserve_lists = [&](size_t bytes) { return buf_reserve(ctx, &ctx->derived_lists, bytes, "the candidate lists"); };
+        rc = reserve_lists(with_tables ? table_end : o_table);
+        if (rc == PQ_ENOMEM && sampled) continue;   // (lists of the exact sizes are shorter)
+        if (rc == PQ_ENOMEM && with_tables) {
+            with_tables = false;
+            rc = reserve_lists(o_table);
+        }
+        if (rc == PQ_ENOMEM) {
+            with_codes = false;
+            rc = reserve_lists(o_code);
+        }
+        if (rc) return rc;
+        lists = (uint8_t *)ctx->derived_lists.p;
+        item_off = (uint32_t *)(lists + o_itemoff);
+        item_query = (uint32_t *)(lists + o_items);
+        tau_key = (unsigned long long *)(lists + o_tau);
 
-    // Step 1.3, collecting pass
-    a.qluts = ws + o_qluts;
-    a.work_counter = (uint32_t *)(ws + o_counter);
-    a.g_hist = nullptr; a.g_bound = nullptr;
-    a.bucket = (const uint32_t *)(ws + o_bucket);
-    a.cand_off = (const uint64_t *)(ws + o_candoff);
-    a.cand_cnt = (uint32_t *)(ws + o_candcnt);
-    a.cand = (uint64_t *)(lists + o_cand);
-    a.cand_code = with_codes ? (uint2 *)(lists + o_code) : nullptr;
-    derived_items_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), nq, piece, item_off, item_query, tau_key, a.work_counter, a.cand_cnt,
-                                            a.bucket, bucket_out, ncand_out);
-    PQ_HIP(ctx, hipGetLastError());
-    bind_geometry(a, g_collect);
-    if (g_collect.nblocks > 0) {
-        if (wide) derived_scan16_kernel<1><<<g_collect.nblocks, DQ_THREADS, 0, s>>>(a);
-        else derived_scan_kernel<1><<<g_collect.nblocks, DQ_THREADS, 0, s>>>(a);
+        // Step 1.3, collecting pass
+        a.qluts = ws + o_qluts;
+        a.work_counter = (uint32_t *)(ws + o_counter);
+        a.g_hist = nullptr; a.g_bound = nullptr;
+        a.codes = codes; a.n = n;
+        a.bucket = (const uint32_t *)(ws + (sampled ? o_sbucket : o_bucket));
+        a.cand_off = (const uint64_t *)(ws + o_candoff);
+        a.cand_cnt = (uint32_t *)(ws + o_candcnt);
+        a.cand = (uint64_t *)(lists + o_cand);
+        a.cand_code = with_codes ? (uint2 *)(lists + o_code) : nullptr;
+        auto make_items = [&](const uint32_t *list_len, uint32_t *reset_counter, uint32_t *reset_cnt) -> int {
+            derived_items_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), list_len, nq, piece, item_off, item_query, tau_key, reset_counter, reset_cnt,
+                                                    (const uint32_t *)(ws + o_bucket), bucket_out, ncand_out);
+            PQ_HIP(ctx, hipGetLastError());
+            return PQ_OK;
+        };
+        if (sampled) {
+            derived_reset_kernel<<<(nq + 255) / 256, 256, 0, s>>>(a.work_counter, a.cand_cnt, nq);
+            PQ_HIP(ctx, hipGetLastError());
+        } else {
+            rc = make_items((const uint32_t *)(ws + o_count), a.work_counter, a.cand_cnt);
+            if (rc) return rc;
+        }
+        bind_geometry(a, g_collect);
+        if (sampled && ctx->profiling) {
+            note_plain_scan(ctx, wide ? "derived_scan16_kernel<collect> (16 queries per pass, up to the buckets of a sample)"
+                                      : "derived_scan_kernel<collect> (8 queries per pass, up to the buckets of a sample)", wide ? DQ16_QB : DQ_QB, g_collect.ngroups);
+            PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, s));
+        }
+        if (g_collect.nblocks > 0) {
+            if (wide) derived_scan16_kernel<1><<<g_collect.nblocks, DQ_THREADS, 0, s>>>(a);
+            else derived_scan_kernel<1><<<g_collect.nblocks, DQ_THREADS, 0, s>>>(a);
+            PQ_HIP(ctx, hipGetLastError());
+        }
+        if (!sampled) break;
+        if (ctx->profiling) {
+            PQ_HIP(ctx, hipEventRecord(ctx->ev_end, s));
+            ctx->ev_valid = 1;
+        }
+        derived_settle_kernel<<<nq, 1024, 0, s>>>(a.cand, a.cand_off, a.cand_cnt, r2, (uint32_t *)(ws + o_bucket), (uint32_t *)(ws + o_count));
         PQ_HIP(ctx, hipGetLastError());
+        derived_summary_kernel<<<1, 1024, 0, s>>>((const uint32_t *)(ws + o_count), a.cand_cnt, nq, cap_arg, (unsigned long long *)(ws + o_summary));
+        PQ_HIP(ctx, hipGetLastError());
+        rc = summary_to_host(ws);
+        if (rc) return rc;
+        const unsigned long long *pin = (const unsigned long long *)ctx->host_pin;
+        if (pin[3] != 0) continue;
+        if (pin[1] < (unsigned long long)nq) return cap_error();
+        total = pin[0];
+        max_items = (size_t)(total / piece) + (size_t)nq;   // (no more than there is room for)
+        rc = make_items(a.cand_cnt, nullptr, nullptr);
+        if (rc) return rc;
+        break;
     }
     // Step 2
     const unsigned rr_grid = (unsigned)(max_items < 4 * (size_t)ctx->num_cu ? max_items : 4 * (size_t)ctx->num_cu);
@@ -1343,20 +1547,26 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
             rc = table_dims == 32 ? launch_derived_tables<32>(ctx, batch, codebooks, q1 - q0, k, dsub, wide_queries, tables)
                                   : launch_derived_tables<64>(ctx, batch, codebooks, q1 - q0, k, dsub, wide_queries, tables);
             if (rc) return rc;
-            derived_rerank_kernel<0><<<(rr_grid + 7) / 8 * 8, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, item_off,
-                                                                                    item_query, q0, q1, piece, topk, tau_key, partial, tables);
+            derived_rerank_kernel<0><<<(rr_grid + 7) / 8 * 8, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, a.cand_cnt,
+                                                                                    (const uint32_t *)(ws + o_bucket), item_off, item_query, q0, q1, piece, topk, tau_key, partial, tables);
             PQ_HIP(ctx, hipGetLastError());
         }
     } else {
         auto rerank = rr_vec ? derived_rerank_kernel<4> : derived_rerank_kernel<1>;
-        rerank<<<rr_grid, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, item_off, item_query, 0, nq, piece,
+        rerank<<<rr_grid, RR_THREADS, rr_lds, s>>>(codes, codebooks, k, dsub, queries, a.cand, a.cand_code, a.cand_off, a.cand_cnt, (const uint32_t *)(ws + o_bucket), item_off, item_query, 0, nq, piece,
                                                    topk, tau_key, partial, nullptr);
         PQ_HIP(ctx, hipGetLastError());
     }
     rc = launch_merge_filtered(ctx, (const uint64_t *)(lists + o_partial), item_off, 0, 1, 1, tau_key, RR_KEEP, nq, topk, nullptr, false, out_dist, out_ids);
     if (rc) return rc;
     if (cand_ids_out && cand_cap > 0) {
-        derived_export_kernel<<<dim3(64, nq), 256, 0, s>>>(a.cand, a.cand_off, cand_cap, cand_ids_out);
+        const bool mixed = sample_step > 0;   // (lists with entries of later buckets)
+        if (mixed) {
+            derived_reset_kernel<<<(nq + 255) / 256, 256, 0, s>>>(a.work_counter, (uint32_t *)(ws + o_room), nq);
+            PQ_HIP(ctx, hipGetLastError());
+        }
+        derived_export_kernel<<<dim3(64, nq), 256, 0, s>>>(a.cand, a.cand_off, a.cand_cnt, (const uint32_t *)(ws + o_bucket), (const uint32_t *)(ws + o_count),
+                                                           mixed ? (uint32_t *)(ws + o_room) : nullptr, cand_cap, cand_ids_out);
         PQ_HIP(ctx, hipGetLastError());
     }
     return PQ_OK;

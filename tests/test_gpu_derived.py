@@ -319,3 +319,59 @@ def test_derived_search_every_code_of_a_full_bucket(ctx):
     want = dq.rerank_exact(codes, np.zeros(1, np.int64), cb, queries[0], 1)[0][0]
     assert ncand[0].item() == n
     assert np.array_equal(gi.cpu().numpy()[0], np.arange(10)) and np.all(gd.cpu().numpy()[0] == want)
+
+
+def sample_rows(n, r2):
+    """Rows that the sample of pq_derived_search looks at (one of every `step`, picked by a hash of its number)."""
+    step = min(r2 // 150, 16)
+    i = np.arange(n // step, dtype=np.uint64)
+    return (i * step + ((i * 2654435761) % 2 ** 32 >> 16) % step).astype(np.int64), step
+
+
+@pytest.mark.parametrize("nq", [260, 645])
+@pytest.mark.parametrize("order", ["random", "sorted", "equal", "sample_nearer", "sample_farther", "few_near"])
+def test_derived_search_on_the_bounds_of_a_sample(ctx, opts, order, nq):
+    """One collecting pass on the bounds of a sample against the two passes: the same distances, rows, buckets and candidate sets, also
+    where the sample misleads (too few vectors up to its bucket, lists that do not fit) and the call falls back."""
+    n, r2, topk = 330_007, 10_000, 20
+    cb, cbar, codes, queries = make_problem(71, n, 512, 4, nq)
+    rows, step = sample_rows(n, r2)
+    if order == "sorted":
+        codes = codes[np.lexsort(codes.T & 255)]
+    if order == "equal":
+        codes[:] = codes[17]
+    if order != "random" and order != "sorted" and order != "equal":
+        # `near`: codes of centroids close to all queries, whose scatter is small here
+        queries = (queries * 1e-2).astype(np.float32)
+        centre = queries.mean(0).reshape(4, 4)
+        best = np.stack([((cbar[j] - centre[j]) ** 2).sum(1).argsort()[:4] for j in range(4)])
+        r = np.random.default_rng(5)
+        near = lambda count: np.stack([best[j][r.integers(0, 4, count)] for j in range(4)], 1).astype(np.uint16)
+        if order == "sample_nearer":      # 900 near vectors, all of them in the sample, which takes them for 14 400
+            codes[rows[:900]] = near(900)
+        if order == "sample_farther":     # the vectors between the sample's near ones and the rest are near too: 16 times its estimate and more
+            codes[:] = near(n)
+            far = np.setdiff1d(rows, rows[::23])
+            codes[far] = np.stack([((cbar[j] - centre[j]) ** 2).sum(1).argsort()[-4:][r.integers(0, 4, len(far))] for j in range(4)], 1)
+        if order == "few_near":           # r2 - 1 near vectors, anywhere
+            codes[r.permutation(n)[:r2 - 1]] = near(r2 - 1)
+    args = (dev(codes.view(np.int16)), dev(cbar), dev(cb), dev(queries), r2, topk)
+    opts.set("derived_sample", 0)
+    two = [t.cpu().numpy() for t in ctx.pq_derived_search(*args)[:4]]
+    cap = int(two[3].max())
+    assert (two[3] >= r2).all()
+    # the candidate sets, as sums over the rows of a hash each (all rows: up to 660 MB a call)
+    def sets():
+        out = ctx.pq_derived_search(*args, cand_cap=cap)
+        ids = out[4]
+        h = (ids + 1) * 2654435761 % 4294967291 * (ids >= 0)
+        return [t.cpu().numpy() for t in out[:4]] + [h.sum(1).cpu().numpy(), (ids >= 0).sum(1).cpu().numpy()]
+    ref = sets()
+    opts.set("derived_sample", 1)
+    for got, want in zip(ctx.pq_derived_search(*args)[:4], two):
+        assert np.array_equal(got.cpu().numpy(), want)
+    for got, want in zip(sets(), ref):
+        assert np.array_equal(got, want)
+    if cap > 0:
+        with pytest.raises(RuntimeError, match="cand_cap"):
+            ctx.pq_derived_search(*args, cand_cap=cap - 1)
