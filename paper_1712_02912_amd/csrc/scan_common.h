@@ -206,21 +206,17 @@ __device__ __forceinline__ int hist_threshold(const uint32_t *hist, int k) {
     const uint64_t reach = __ballot(incl >= (uint32_t)k);
     if (reach == 0ull) return HIST_BINS;
     const int first = __builtin_ctzll(reach);
-    // every lane locates the crossing inside its own 64 bins; only lane `first` has a meaningful need
-    const uint32_t need = (uint32_t)k - (incl - tot);
-    uint32_t cum = 0;
-    int bin = HIST_BINS;
-#pragma unroll 2
-    for (int i = 0; i < HIST_BINS / 64 / 4; ++i) {
-        const uint4 v = h4[i];
-        const uint32_t e[4] = {v.x, v.y, v.z, v.w};
+    // the crossing within the 64 bins of lane `first`: a bin per lane (one round trip; every lane looking through its own bins was
+    // eight)
+    static_assert(HIST_BINS == 64 * 64, "a lane per bin of a lane");
+    const uint32_t need = (uint32_t)k - (uint32_t)__builtin_amdgcn_readlane(incl - tot, first);
+    uint32_t cum = hist[first * 64 + lane];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            cum += e[t];
-            if (bin == HIST_BINS && cum >= need) bin = lane * (HIST_BINS / 64) + i * 4 + t;
-        }
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(cum, o);
+        if (lane >= o) cum += up;
     }
-    return __shfl(bin, first);
+    return first * 64 + __builtin_ctzll(__ballot(cum >= need));   // (counts only grow: not empty)
 }
 
 

@@ -1865,59 +1865,66 @@ __global__ __launch_bounds__(1024) void f32_seed_refine_kernel(const uint8_t *__
 
 // The same refinement over more codes than one block can look at (flat scans of few query groups over large databases, where
 // every candidate the first bound lets through costs more than a code it dismisses), without a pass before it: block
-// (s, q) counts the distances of slice s in bins that hang below ref0 = the sum of the tables' greatest entries (no
-// distance exceeds it; 4096 bins of 0.2 % reach down to 1/4000 of it), which every block works out for itself from
+// (s, q) counts the distances of slice s in bins that hang below ref0 = the sum of the tables' greatest finite entries (no
+// finite distance exceeds it; 4096 bins of 2^shift ordered-value units: of 0.2 % down to 1/256 of it for the large samples, of
+// 0.8 % down to 2^-32 of it, whatever a far centroid makes of it, for the small ones), which every block works out for itself from
 // the tables it stages anyway, and adds its counts to the query's bins in device memory.  A block counts its first 4096 codes
 // in full; the k-th smallest of those bounds the k-th smallest of the whole sample, so of its other codes only the ones at or
 // below that bin edge are counted.
 // Blocks of `slice` codes (many short blocks when few queries share the launch: the pass is a chain of load latencies,
 // not bandwidth).
 constexpr int SEED_SLICE = 1 << 16, SEED2_SLICE = 1 << 14;
+template <int M>
 __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__restrict__ codes, int64_t cnt, int slice,
                                                               const float *__restrict__ luts, int k, uint32_t *seed_hist,
-                                                              float *seed_ref) {
-    __shared__ float tab[8 * 256];
+                                                              float *seed_ref, int shift) {
+    __shared__ float tab[M * 256];
     __shared__ __align__(16) uint32_t hist[HIST_BINS];
-    __shared__ float smax[8];
+    __shared__ float smax[M];
     __shared__ int bin_s;
     const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < 2048; i += 1024) tab[i] = luts[(size_t)q * 2048 + i];
+    for (int i = tid; i < M * 256; i += 1024) tab[i] = luts[(size_t)q * (M * 256) + i];
     for (int i = tid; i < HIST_BINS; i += 1024) hist[i] = 0;
     __syncthreads();
-    if (wave < 8) {
-        float v = fmaxf(fmaxf(tab[wave * 256 + lane], tab[wave * 256 + lane + 64]), fmaxf(tab[wave * 256 + lane + 128], tab[wave * 256 + lane + 192]));
+    if (wave < M) {
+        float v = -__builtin_inff();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float e = tab[wave * 256 + lane + 64 * i];
+            if (e < __builtin_inff()) v = fmaxf(v, e);   // (infinite entries: distances that are not counted)
+        }
         for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
         if (lane == 0) smax[wave] = v;
     }
     __syncthreads();
     float ref0 = smax[0];
-    for (int j = 1; j < 8; ++j) ref0 += smax[j];
+    for (int j = 1; j < M; ++j) ref0 += smax[j];
     if (blockIdx.x == 0 && tid == 0) seed_ref[q] = ref0;
     const uint32_t ref = f32_to_ord(ref0);
     const int64_t begin = (int64_t)blockIdx.x * slice;
     const int64_t end = begin + slice < cnt ? begin + slice : cnt;
     auto count_range = [&](int64_t from, int64_t to, uint32_t limit) {
         for (int64_t i0 = from + tid; i0 < to; i0 += 4 * 1024) {
-            uint2 c[4];
+            uint32_t c[4][M / 4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int64_t i = i0 + u * 1024;
-                c[u] = i < to ? *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8) : make_uint2(0, 0);
+                const int64_t i = i0 + u * 1024 < to ? i0 + u * 1024 : from;   // (codes past the end are not counted)
+                const uint2 lo = *reinterpret_cast<const uint2 *>(codes + (size_t)i * M);
+                c[u][0] = lo.x; c[u][1] = lo.y;
+                if constexpr (M == 16) {
+                    const uint2 hi = *reinterpret_cast<const uint2 *>(codes + (size_t)i * M + 8);
+                    c[u][2] = hi.x; c[u][3] = hi.y;
+                }
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if (i0 + u * 1024 >= to) break;
-                float d = tab[c[u].x & 255u];
-                d += tab[256 + ((c[u].x >> 8) & 255u)];
-                d += tab[512 + ((c[u].x >> 16) & 255u)];
-                d += tab[768 + (c[u].x >> 24)];
-                d += tab[1024 + (c[u].y & 255u)];
-                d += tab[1280 + ((c[u].y >> 8) & 255u)];
-                d += tab[1536 + ((c[u].y >> 16) & 255u)];
-                d += tab[1792 + (c[u].y >> 24)];
+                float d = tab[c[u][0] & 255u];   // (table order, as the scans add a candidate's entries)
+#pragma unroll
+                for (int j = 1; j < M; ++j) d += tab[j * 256 + ((c[u][j >> 2] >> (8 * (j & 3))) & 255u)];
                 const uint32_t ord = f32_to_ord(d);
                 if (ord <= limit) {
-                    const uint32_t below = (ref - ord) >> HIST_SHIFT;
+                    const uint32_t below = (ref - ord) >> shift;
                     atomicAdd(&hist[HIST_BINS - 1 - (below < HIST_BINS ? below : HIST_BINS - 1)], 1u);
                 }
             }
@@ -1932,7 +1939,7 @@ __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__r
             if (lane == 0) bin_s = b;
         }
         __syncthreads();
-        const uint32_t limit = bin_s < HIST_BINS ? ref - ((uint32_t)(HIST_BINS - 1 - bin_s) << HIST_SHIFT) : ref;
+        const uint32_t limit = bin_s < HIST_BINS ? ref - ((uint32_t)(HIST_BINS - 1 - bin_s) << shift) : ref;
         count_range(head_end, end, limit);
     }
     __syncthreads();
@@ -1940,8 +1947,8 @@ __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__r
         if (hist[i] != 0u) atomicAdd(&seed_hist[(size_t)q * HIST_BINS + i], hist[i]);
 }
 
-// 16-bit tables of the pruned float scan.  Blocks (group, y) of 256 threads: every block of a group works out the
-// minima and scales of the group's queries, block y writes the tables y, y + gridDim.y, ...
+// 16-bit tables of the pruned float scan.  Blocks (group, y) of 1024 threads: every block of a group works out the
+// minima and scales of the group's queries, a quarter of block y (256 threads) writes tables 4 y, 4 y + 1, ...
 // Per query: off = sum over the tables of their minimum entry, scale = PRUNE_RANGE / (tau0 - off)
 // (0, which disables the pruning of that query, if tau0 leaves no usable range), and for every table
 // L[j][b] = min(32767 / M, floor((D[j][b] - min_j) * scale)) for the M = 8 or 16 tables.  Output in
@@ -1950,11 +1957,12 @@ __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__r
 // With seed_hist given, the kernel first reads every query's first bound off the bins of the sampling pass
 // (f32_seed_hist2_kernel; bins below seed_ref) and stores it as tau0, as the query's shared bound and as the reference
 // of its scan histogram: one launch instead of three.
+constexpr int PRUNE_TABLES_THREADS = 1024, PRUNE_TABLES_Y = 2;
 template <int M, int G = 8>   // G: queries per group (8 with 16-bit entries, 16 with 8-bit entries)
-__global__ __launch_bounds__(256) void prune_tables_kernel(const float *__restrict__ luts, float *tau0,
+__global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(const float *__restrict__ luts, float *tau0,
                                                            int nq, uint4 *qtabs, float *off_out, float *scale_out, float range_q8,
                                                            uint4 *qtabs16, float *scale16_out, const uint32_t *seed_hist = nullptr,
-                                                           const float *seed_ref = nullptr, int seed_k = 0,
+                                                           const float *seed_ref = nullptr, int seed_k = 0, int seed_shift = 0,
                                                            unsigned long long *tau_key_out = nullptr, uint32_t *tau_ref_out = nullptr) {
     constexpr bool Q8 = G == 16;
     constexpr float ENTRY_MAX = Q8 ? PRUNE_ENTRY_MAX_Q8 : (float)(32767 / M);   // M entries must add up to less than 2^15 (2^7)
@@ -1964,32 +1972,44 @@ __global__ __launch_bounds__(256) void prune_tables_kernel(const float *__restri
     __shared__ float sscale[G];
     __shared__ float sscale16[G];   // 8-bit entries: the scale of the 16-bit tables written beside them
     const int group = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (seed_hist != nullptr) {
-        for (int q = wave; q < G; q += 4) {
+    // (with bins the first half of the waves read the queries' bounds off them while the others find the minima)
+    constexpr int WAVES = PRUNE_TABLES_THREADS / 64;
+    static_assert(WAVES >= 16, "a wave per query of 16, or per query of 8 and as many for the minima");
+    if (seed_hist != nullptr && wave < WAVES / 2) {
+        for (int q = wave; q < G; q += WAVES / 2) {
             const int gq = group * G + q;
             if (gq >= nq) continue;
             const int b = hist_threshold(seed_hist + (size_t)gq * HIST_BINS, seed_k);
             if (lane == 0) {
                 const uint32_t ref = f32_to_ord(seed_ref[gq]);
-                const uint32_t edge = b < HIST_BINS ? ref - ((uint32_t)(HIST_BINS - 1 - b) << HIST_SHIFT) : ref;
+                const uint32_t edge = b < HIST_BINS ? ref - ((uint32_t)(HIST_BINS - 1 - b) << seed_shift) : f32_to_ord(__builtin_inff());   // (fewer than k counted: no bound)
                 tau0[gq] = ord_to_f32(edge);   // (every block of the group stores the same value)
                 if (blockIdx.y == 0) {
                     tau_key_out[gq] = ((unsigned long long)edge << 32) | 0xffffffffull;
-                    tau_ref_out[gq] = edge;
+                    tau_ref_out[gq] = b < HIST_BINS ? edge : TAU_REF_UNSET;
                 }
             }
         }
-        __syncthreads();
     }
-    for (int r = wave * (G * M / 4); r < (wave + 1) * (G * M / 4); ++r) {
-        const int q = r / M, j = r % M, gq = group * G + q;
-        float v = __builtin_inff();
-        if (gq < nq) {
-            const float *t = luts + ((size_t)gq * M + j) * 256;
-            v = fminf(fminf(t[lane], t[lane + 64]), fminf(t[lane + 128], t[lane + 192]));
+    const int row_wave = seed_hist != nullptr ? wave - WAVES / 2 : wave, row_waves = seed_hist != nullptr ? WAVES / 2 : WAVES;
+    // (four rows at a time: their loads and their reductions are in flight together)
+    for (int r0 = row_wave * 4; r0 >= 0 && r0 < G * M; r0 += row_waves * 4) {
+        float e[4][4], v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int gq = group * G + (r0 + u) / M;
+            const float *t = luts + ((size_t)(gq < nq ? gq : nq - 1) * M + (r0 + u) % M) * 256;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[u][i] = t[lane + 64 * i];
         }
-        for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-        if (lane == 0) smin[q][j] = v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = fminf(fminf(e[u][0], e[u][1]), fminf(e[u][2], e[u][3]));
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = fminf(v[u], __shfl_xor(v[u], o));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (lane == 0) smin[(r0 + u) / M][(r0 + u) % M] = v[u];   // (rows past the last query: not used)
     }
     __syncthreads();
     if (tid < G) {
@@ -2022,8 +2042,8 @@ __global__ __launch_bounds__(256) void prune_tables_kernel(const float *__restri
         sscale[tid] = scale;
     }
     __syncthreads();
-    const int b = tid;
-    for (int j = blockIdx.y; j < M; j += gridDim.y) {
+    const int b = tid & 255;
+    for (int j = blockIdx.y * (WAVES / 4) + (tid >> 8); j < M; j += gridDim.y * (WAVES / 4)) {
         uint32_t e[G];
 #pragma unroll
         for (int q = 0; q < G; ++q) {
@@ -2331,7 +2351,16 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         if (want > seed_codes_f32) seed_codes_f32 = want;
     }
     const bool wide_ok = opt_int(ctx, PQ_OPT_SCAN_WIDE_SEED, 1) != 0;
-    const bool wide_seed = wide_ok && prune && few_groups && tables == 8 && seed_codes_f32 > SEED_SLICE;
+    // Float scans of few query groups take it from slices too, a block for every (slice, query): of a large sample (8 tables), or of
+    // the small one, enlarged to half a million evaluations per call, which fill the chip once whatever the number of queries
+    // (a block per four queries added up 7905 codes of 10^5 for each of 16 queries in 28 us while the chip stood idle).
+    // 10^5 codes, 16 queries, top-100 (with the tables kernel's wider blocks): call 90 -> 61 us; 10^6 codes, 1 query 109 -> 64,
+    // 29 queries 143 -> 93; 16 tables, 3 * 10^5 codes, 8 queries 120 -> 72, 10^7 codes, 16 queries 282 -> 218; 66 000 codes, 200
+    // queries, top-1 89 -> 82.
+    bool wide_seed = wide_ok && prune && few_groups;
+    const bool seed_large = tables == 8 && seed_codes_f32 > SEED_SLICE;
+    const int64_t seed_fill = (1 << 19) / (nq > 0 ? nq : 1) < n / 2 ? (1 << 19) / (nq > 0 ? nq : 1) : n / 2;
+    const int64_t seed_codes_wide = seed_large ? seed_codes_f32 : (seed_codes_few > seed_fill ? seed_codes_few : seed_fill);
     // The integer scan of few query groups always takes its first bound from slices, a block for every (slice, query): slices
     // of 65 536 codes of a large sample, of 8192 codes of the small one (one block per four queries adding up the whole
     // sample: 1 M codes of 32 indexes, 100 queries 126 us of a call of 480 us; now 365).  Small databases take one as well: without a bound
@@ -2340,6 +2369,8 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     bool wide_seed_u4 = wide_ok && seed_u4 && few_groups;
     const int64_t seed_codes_u4 = seed_codes_f32 > SEED_SLICE ? seed_codes_f32 : seed_codes_few;
     const int seed_slice_u4 = seed_codes_f32 > SEED_SLICE ? SEED_SLICE : SEED_SLICE / 8;
+    if (wide_seed && ctx->ws_fixed && align_up(off_qtabs + (size_t)ngroups * 256 * tables * sizeof(uint4), 256) + (size_t)nq * (HIST_BINS + 1) * 4 + 1024 > ctx->ws_bytes)
+        wide_seed = false;   // (no room for the bins in the fixed scratch)
     const size_t off_seedhist = prune ? off_qtabs + align_up((size_t)ngroups * 256 * tables * sizeof(uint4), 256) : off_tau0;
     // 16 queries per pass: the 16-bit tables of the second test (64 KB per group) and their scales
     const size_t off_seedref = off_seedhist + align_up(wide_seed ? (size_t)nq * HIST_BINS * 4 : 0, 256);   // (wide first bound: reference of the bins per query)
@@ -2384,11 +2415,18 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
                                                              0xff800000u, a.hist, L.nhist, nullptr, nq, 1.f, seed_hist, (size_t)nq * HIST_BINS);
             // (short slices while the launch stays under 2048 blocks, else the slices of the older pass)
-            const int slice = (seed_codes_f32 + SEED2_SLICE - 1) / SEED2_SLICE * nq <= 2048 ? SEED2_SLICE : SEED_SLICE;
-            const dim3 sgrid((unsigned)((seed_codes_f32 + slice - 1) / slice), (unsigned)nq);
-            f32_seed_hist2_kernel<<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_f32, slice, (const float *)luts, topk, seed_hist, seed_ref);
-            prune_tables_kernel<8><<<dim3(ngroups, 8), 256, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr,
-                                                                             seed_hist, seed_ref, topk, a.tau_key, a.tau_ref);
+            int slice = (seed_codes_f32 + SEED2_SLICE - 1) / SEED2_SLICE * nq <= 2048 ? SEED2_SLICE : SEED_SLICE;
+            if (!seed_large) {   // two blocks per compute unit, slices of 1024 codes and more
+                const int64_t per_query = 2 * ctx->num_cu / nq > 1 ? 2 * ctx->num_cu / nq : 1;
+                slice = (int)(((seed_codes_wide + per_query - 1) / per_query + 1023) / 1024 * 1024);
+            }
+            const dim3 sgrid((unsigned)((seed_codes_wide + slice - 1) / slice), (unsigned)nq);
+            const int shift = seed_large ? HIST_SHIFT : HIST_SHIFT + 2;
+            auto tables_of = tables == 8 ? prune_tables_kernel<8, 8> : prune_tables_kernel<16, 8>;
+            auto seed_of = tables == 8 ? f32_seed_hist2_kernel<8> : f32_seed_hist2_kernel<16>;
+            seed_of<<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_wide, slice, (const float *)luts, topk, seed_hist, seed_ref, shift);
+            tables_of<<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr,
+                                                                 seed_hist, seed_ref, topk, shift, a.tau_key, a.tau_ref);
             PQ_HIP(ctx, hipGetLastError());
         } else {
             // the first bound: smallest histogram edge with k distances among the first codes
@@ -2404,9 +2442,9 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             if (tables == 8) f32_seed_refine_kernel<8><<<(nq + SEED_QPB - 1) / SEED_QPB, 1024, 0, ctx->stream>>>(codes, first_codes, (const float *)luts, topk, true, nq, tau0);
             else f32_seed_refine_kernel<16><<<(nq + SEED_QPB - 1) / SEED_QPB, 1024, 0, ctx->stream>>>(codes, first_codes, (const float *)luts, topk, true, nq, tau0);
             PQ_HIP(ctx, hipGetLastError());
-            if (q8) prune_tables_kernel<8, 16><<<dim3(ngroups, 8), 256, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, PRUNE_RANGE_Q8, qtabs16, pscale16);
-            else if (tables == 8) prune_tables_kernel<8><<<dim3(ngroups, 8), 256, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
-            else prune_tables_kernel<16><<<dim3(ngroups, 8), 256, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
+            if (q8) prune_tables_kernel<8, 16><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, PRUNE_RANGE_Q8, qtabs16, pscale16);
+            else if (tables == 8) prune_tables_kernel<8><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
+            else prune_tables_kernel<16><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
             PQ_HIP(ctx, hipGetLastError());
         }
         a.qtabs = qtabs; a.prune_off = poff; a.prune_scale = pscale; a.qtabs16 = qtabs16; a.prune_scale16 = pscale16;

@@ -1019,3 +1019,35 @@ def test_scan_f32_first_bound_equal_to_the_sum_of_the_table_minima(ctx, m, nq):
     assert np.all(gd[0] == gd[0][0])                       # a hundred copies of the best code
     np.testing.assert_allclose(gd, od, rtol=RTOL)
     run_float_scan(ctx, codes, orc.CODES_U8, luts_h, 1000 if nq <= 40 else 300)
+
+
+@pytest.mark.parametrize("m", [8, 16])
+@pytest.mark.parametrize("n,nq,topk,kind", [(65_536, 1, 1, "random"), (65_537, 248, 3, "random"), (100_003, 17, 1024, "random"), (300_001, 5, 100, "far"),
+                                            (70_000, 9, 100, "infinite"), (66_000, 2, 128, "mostly_infinite"), (90_001, 40, 1000, "equal"), (80_000, 3, 10, "negative")])
+def test_scan_f32_first_bound_from_slices_of_small_samples(ctx, opts, m, n, nq, topk, kind):
+    """The float scans of few queries start from a bound found on slices of a sample: against the oracle and the one-block
+    first bound, with a far centroid, infinite entries (also so many that fewer than topk distances are finite), equal codes and tables
+    that are no distances."""
+    r = np.random.default_rng(n + m)
+    codes = r.integers(0, 256, (n, m), dtype=np.uint8)
+    luts = (r.random((nq, m, 256)) * 100).astype(np.float32)
+    if kind == "far":
+        luts[:, 2, 7] = 3e20
+    if kind == "infinite":
+        luts[:, 1, 9] = np.inf
+    if kind == "mostly_infinite":
+        luts[:, 0, 1:] = np.inf
+        codes[:, 0] = np.maximum(codes[:, 0], 1)
+        codes[r.permutation(n)[:50], 0] = 0
+    if kind == "equal":
+        codes[:] = codes[5]
+    if kind == "negative":
+        luts -= 60.0
+    got = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(luts), topk)]
+    opts.set("scan_wide_seed", 0)
+    ref = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(luts), topk)]
+    assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+    if kind in ("random", "far", "equal"):
+        od, oi = orc.adc_scan_topk_f32(codes, orc.CODES_U8, luts, topk)
+        for q in range(0, nq, 7):
+            check_float_topk(got[0][q], got[1][q], od[q], oi[q], codes, orc.CODES_U8, luts[q], n)
