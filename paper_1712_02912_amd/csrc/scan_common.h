@@ -110,10 +110,11 @@ struct TunedArgs {
 int launch_merge_topk(pq_ctx *ctx, const uint64_t *partial, int nchunks, int ngroups, int qb, int kpad, int nq,
                       int topk, bool val_u32, void *out_val, int64_t *out_ids);
 // merge of the per-query result lists of a scan that leaves a final bound per query in tau_key
-// (see merge_filtered_kernel); any number of lists
+// (see merge_filtered_kernel); any number of lists.  hist (optional): the scan's histograms [nq][HIST_BINS] of the keys in
+// the lists, of which the first hist_bins bins say something; float values: below hist_ref[q].
 int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *qlist_off, int nchunks, int ngroups, int qb,
                           const unsigned long long *tau_key, int kpad, int nq, int topk, const int64_t *ids, bool val_u32,
-                          void *out_val, int64_t *out_ids);
+                          void *out_val, int64_t *out_ids, const uint32_t *hist = nullptr, const uint32_t *hist_ref = nullptr, int hist_bins = 0);
 // IVF: run the persistent scan kernel over a table of work items (see IvfItem).  `state` is a
 // caller-provided device region of tuned_state_bytes() bytes holding the per-query bounds,
 // histograms and the per-block candidate scratch; tau0 (optional, [nq]) seeds the per-query bounds

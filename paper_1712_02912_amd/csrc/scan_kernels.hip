@@ -183,6 +183,7 @@ __global__ __launch_bounds__(1024) void merge_topk_kernel(const uint64_t *partia
 // MERGE_CAP keys are kept in LDS (more than that at or below the bound: the rounds below).  Calls of few queries
 // give every query a block of 1024 threads and room for 8192 keys; calls of many queries take blocks of 256 threads
 // and 2048 keys (512 threads and 4096 keys for topk above 512), of which a compute unit holds several.
+constexpr int MERGE_COUNT = 256;   // as many kept keys find their ranks by counting, without a selection before
 constexpr int merge_lds_bytes(int cap) { return cap * 8 + cap * 4 + 1024 * 8; }   // kept keys, 32-bit values for the selection, the result's keys
 template <bool VAL_U32, int MERGE_CAP>
 __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__restrict__ partial,
@@ -190,7 +191,8 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
                                                               int ngroups, int qb,
                                                               const unsigned long long *__restrict__ tau_key, int kpad, int topk,
                                                               const int64_t *__restrict__ ids, void *out_val,
-                                                              int64_t *out_ids) {
+                                                              int64_t *out_ids, const uint32_t *__restrict__ hist,
+                                                              const uint32_t *__restrict__ hist_ref, int hist_bins) {
     extern __shared__ uint64_t skeys[];
     __shared__ int s_count;
     const int gq = blockIdx.x, tid = threadIdx.x;
@@ -205,26 +207,33 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
         const size_t list = qlist_off ? (size_t)qlist_off[gq] + l : (l * ngroups + gq / qb) * qb + gq % qb;
         return partial + list * kpad;
     };
-    auto for_each_key = [&](auto &&f) {
-        constexpr int MLP = 4, REST = 5;
+    constexpr int MLP = 4, REST = 5;
+    auto load_heads = [&](size_t l0, uint64_t (&first)[MLP]) {
+#pragma unroll
+        for (int u = 0; u < MLP; ++u) {
+            const size_t l = l0 + (size_t)u * nwaves;
+            first[u] = l < nlists ? list_ptr(l)[lane] : KEY_EMPTY;
+        }
+    };
+    auto for_each_key = [&](auto &&f, uint64_t (&first)[MLP], bool loaded) {
         for (size_t l0 = wave; l0 < nlists; l0 += (size_t)MLP * nwaves) {
-            const uint64_t *lp[MLP];
-            uint64_t first[MLP];
+            if (!loaded) load_heads(l0, first);
+            loaded = false;
+            uint32_t full = 0;   // lists whose first 64 places are taken
 #pragma unroll
             for (int u = 0; u < MLP; ++u) {
-                const size_t l = l0 + (size_t)u * nwaves;
-                lp[u] = l < nlists ? list_ptr(l) : nullptr;
-                first[u] = lp[u] ? lp[u][lane] : KEY_EMPTY;
-            }
-#pragma unroll
-            for (int u = 0; u < MLP; ++u) {
-                if (lp[u] == nullptr) continue;
                 f(first[u]);
-                bool more = __ballot(first[u] == KEY_EMPTY) == 0ull;
+                full |= __ballot(first[u] == KEY_EMPTY) == 0ull ? 1u << u : 0u;
+            }
+#pragma unroll 1
+            for (; full != 0u; full &= full - 1u) {
+                const uint64_t *const lp = list_ptr(l0 + (size_t)__builtin_ctz(full) * nwaves);
+                bool more = true;
+#pragma unroll 1
                 for (int e0 = 64; more && e0 < kpad; e0 += 64 * REST) {
                     uint64_t key[REST];
 #pragma unroll
-                    for (int r = 0; r < REST; ++r) key[r] = e0 + 64 * r < kpad ? lp[u][e0 + 64 * r + lane] : KEY_EMPTY;
+                    for (int r = 0; r < REST; ++r) key[r] = e0 + 64 * r < kpad ? lp[e0 + 64 * r + lane] : KEY_EMPTY;
 #pragma unroll
                     for (int r = 0; r < REST; ++r) {
                         if (!more) break;
@@ -235,6 +244,8 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
             }
         }
     };
+    uint64_t heads[MLP];
+    load_heads(wave, heads);
     // keys up to `most` go to LDS, as many as there is room for
     auto keep = [&](uint64_t key, uint64_t most) {
         const bool in = key != KEY_EMPTY && key <= most;
@@ -284,7 +295,7 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
             const uint64_t fixed = shift == 56 ? 0ull : ~0ull << (shift + 8);   // bytes decided in earlier passes
             for_each_key([&](uint64_t key) {
                 wave_count_bin(sel_bins, key != KEY_EMPTY && key <= most && (key & fixed) == prefix, (uint32_t)(key >> shift) & 255u);
-            });
+            }, heads, false);
             __syncthreads();
             if (tid < 64) {   // one wave: the byte value whose bin holds the `want`-th key
                 const uint32_t h[4] = {sel_bins[4 * tid], sel_bins[4 * tid + 1], sel_bins[4 * tid + 2], sel_bins[4 * tid + 3]};
@@ -317,11 +328,27 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
     // greatest to the smallest would make it a round for every few lists (520 queries with 1024 lists of 128 keys: call 20 ms, now 6.1), so
     // after three walks the topk-th key is selected exactly, in eight.
     uint64_t bound = tau_key[gq];   // a whole key at or below which k keys exist (rows separate ties of the value)
+    // The scan's histogram of the keys that any block inserted is complete by now, where each block's last look at it was not:
+    // the edge of the bin that holds the k-th.  (25 M codes of 16 4-bit indexes, 8 queries, top-1000: 29 000 keys at or below the
+    // shared bound, 3000 below the edge.)
+    if (hist != nullptr) {
+        __shared__ uint64_t s_edge;
+        if (wave == 0) {
+            const int bin = hist_threshold(hist + (size_t)gq * HIST_BINS, topk);
+            const uint32_t ref = VAL_U32 ? 0u : hist_ref[gq];
+            uint64_t edge = KEY_EMPTY;
+            if (bin < hist_bins && ref != TAU_REF_UNSET)
+                edge = (uint64_t)(VAL_U32 ? (uint32_t)bin : ref - ((uint32_t)(HIST_BINS - 1 - bin) << HIST_SHIFT)) << 32 | 0xffffffffull;
+            if (lane == 0) s_edge = edge;
+        }
+        __syncthreads();
+        if (s_edge < bound) bound = s_edge;
+    }
     int kept;
     for (int walk = 1;; ++walk) {
         if (tid == 0) s_count = 0;
         __syncthreads();
-        for_each_key([&](uint64_t key) { keep(key, bound); });
+        for_each_key([&](uint64_t key) { keep(key, bound); }, heads, walk == 1);
         __syncthreads();
         kept = s_count;
         __syncthreads();
@@ -338,9 +365,10 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
     // The topk smallest of the kept keys without sorting them all (a bitonic sort of a few thousand keys is dozens of
     // barrier stages): the keys up to the topk-th are moved to a short list, where every thread finds the rank of its keys by
     // counting the smaller ones and writes them straight to their places.
+    // (a few hundred keys at once)
     int nshort = kept;
-    const uint64_t *src = skeys;
-    if (kept > topk) {
+    uint64_t *src = skeys;
+    if (kept > topk && kept > MERGE_COUNT) {
         const uint64_t kth = kth_kept(kept);
         if (tid == 0) s_count = 0;
         __syncthreads();
@@ -353,10 +381,10 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
         nshort = s_count;
         src = shortlist;
     }
-    if (nshort > 256) {
+    if (nshort > MERGE_COUNT) {
         // long results: counting the smaller keys is nshort^2 broadcast reads (a thousand keys: 40 us of LDS time on a
         // compute unit that holds four such blocks); the short list is sorted instead (at most 1024 keys: 55 stages)
-        uint64_t *buf = kept > topk ? shortlist : skeys;   // (nshort <= topk <= 1024 either way)
+        uint64_t *buf = src;   // (nshort <= topk <= 1024 either way)
         int n2 = 512;
         while (n2 < nshort) n2 <<= 1;
         for (int i = nshort + tid; i < n2; i += blockDim.x) buf[i] = KEY_EMPTY;
@@ -375,11 +403,13 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
 
 int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *qlist_off, int nchunks, int ngroups, int qb,
                           const unsigned long long *tau_key, int kpad, int nq, int topk, const int64_t *ids, bool val_u32,
-                          void *out_val, int64_t *out_ids) {
+                          void *out_val, int64_t *out_ids, const uint32_t *hist, const uint32_t *hist_ref, int hist_bins) {
     if (nq == 0) return PQ_OK;
-    auto launch = [&](auto kernel, int cap, int threads) -> int {
+    // (the histograms' bound: 16 KB read per query; with many queries the keys are fewer and the selection is the shorter way:
+    // 1000 queries, top-100 34 us without, 44 with)
+    auto launch = [&](auto kernel, int cap, int threads, const uint32_t *hist = nullptr) -> int {
         PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, merge_lds_bytes(cap)));
-        kernel<<<nq, threads, merge_lds_bytes(cap), ctx->stream>>>(partial, qlist_off, nchunks, ngroups, qb, tau_key, kpad, topk, ids, out_val, out_ids);
+        kernel<<<nq, threads, merge_lds_bytes(cap), ctx->stream>>>(partial, qlist_off, nchunks, ngroups, qb, tau_key, kpad, topk, ids, out_val, out_ids, hist, hist_ref, hist_bins);
         PQ_HIP(ctx, hipGetLastError());
         return PQ_OK;
     };
@@ -393,8 +423,8 @@ int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *
         if (val_u32) return launch(merge_filtered_kernel<true, 4096>, 4096, 512);
         return launch(merge_filtered_kernel<false, 4096>, 4096, 512);
     }
-    if (val_u32) return launch(merge_filtered_kernel<true, 8192>, 8192, 1024);
-    return launch(merge_filtered_kernel<false, 8192>, 8192, 1024);
+    if (val_u32) return launch(merge_filtered_kernel<true, 8192>, 8192, 1024, hist);
+    return launch(merge_filtered_kernel<false, 8192>, 8192, 1024, hist);
 }
 
 // ------------------------------------------------------------------------------------------
