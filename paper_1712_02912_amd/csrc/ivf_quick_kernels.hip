@@ -35,10 +35,12 @@ constexpr int QK_LONG_MIN = 1 << IVF_QUICK_LONG_CLASS;   // lists of this many r
 constexpr int QK_BINS = 512;      // sums counted per pass: base .. base + 510, and one bin for everything above
 constexpr int QK_KP = 128;        // kprime at most (the length of a result list)
 constexpr int QK_BATCH = 4;       // codes of a thread on their way at a time
+constexpr float QK_LB_RANGE = 104.f;   // units of the lower bounds between the sum of the minima and the cap (at most 118)
 constexpr int QK_DBINS = IVF_QUICK_DBINS;   // bins of a query's float distances, over 0 .. qmax
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t pk_add_u16(uint32_t a, uint32_t b) {
     const u16x2 r = __builtin_bit_cast(u16x2, a) + __builtin_bit_cast(u16x2, b);
@@ -119,6 +121,7 @@ __device__ __forceinline__ int quick_sum_cap(unsigned long long tau_key, float q
 // ------------------------------------------------------------------------------------------
 template <int QK_WAVES, typename TieRow>
 struct __align__(16) QuickSmem {
+    uint2 lbtab[256];                            // slot j * 16 + i: 4-bit lower bounds of the entries (j, i) of the 8 pairs as bytes
     uint4 tab[256];                              // slot j * 16 + i: the 8-bit entries (j, i) of the 8 pairs as 16-bit values
     uint32_t hist[QK_QS][QK_BINS];
     unsigned long long sure[QK_QS][QK_KP];       // keys below the pair's T (fewer than kprime)
@@ -139,6 +142,9 @@ struct __align__(16) QuickSmem {
     int alive[QK_QS];                            // some code of the pair can be in the result
     int pair[QK_QS];
     uint32_t out_idx[QK_QS];
+    uint4 minw[16];                              // smallest entry of sub-quantizer j of the 8 pairs as 16-bit values
+    uint2 lbbias;                                // per pair 0x80 minus its T in units of the bounds, as bytes
+    uint32_t seg_saved[2];                       // rows saved in the last segment and in this one
     int pending;                                 // pairs whose T is not known yet
     int item;
     int single;                                  // the list is this one item: its candidates are final
@@ -171,10 +177,13 @@ struct QuickBound {
 // BOUNDS: sums of different pairs have no common scale, but a query's bound on the float distance is a bound on each pair's
 // sums (quick_sum_cap), so the lists scanned first cut down what the later ones count, save, collect and rerank: most lists
 // then hold fewer than kprime codes that matter, and the whole prefix of sums up to the bound is kept, which is what makes
-// the candidates of a pair those of the definition as far as the result can see them.  Both scans 12.4 -> 9.9 ms (with the
-// final bounds known from the start they would take 8 ms: the rest is the loop's LDS reads and additions).
+// the candidates of a pair those of the definition as far as the result can see them.  Both scans 12.4 -> 9.9 ms.
+// Once a segment of an item saves less than a quarter of its rows, the next ones run on byte-wide lower bounds of the sums
+// (build_lb), 16 8-byte LDS reads and 16 three-operand additions per code and eight pairs instead of twice that, and only rows that pass get their
+// sums; with the next codes requested ahead and four waves per SIMD (128 registers, the cold parts spill) the long items take 5.1 -> 3.4 ms, call 13.5 ->
+// 12.4.  What is left of the short items (5.5 ms, 107 000 of them) is to two thirds set-up, histograms, result lists and rerank.
 template <int QK_WAVES, bool LONG, bool BOUNDS>
-__global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_kernel(const uint8_t *__restrict__ codes,
+__global__ __launch_bounds__(QK_WAVES * 64, LONG && !BOUNDS ? 2 : 4) void ivf_quick_scan_kernel(const uint8_t *__restrict__ codes,
                                                                        const uint8_t *__restrict__ qluts,
                                                                        const IvfItem *__restrict__ items,
                                                                        uint32_t *nitems_dev,
@@ -291,21 +300,106 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
             return valid && any != 0u;
         };
         // f(row index within the item, code) for every code of the item; a thread meets its rows in ascending order,
-        // and so does a wave (lane by lane within a step, step by step)
-        auto for_codes = [&](int begin, int end, auto &&f) {
-            for (int i0 = begin + tid; i0 < end; i0 += QK_BATCH * QK_THREADS) {
-                uint2 c[QK_BATCH];
+        // and so does a wave (lane by lane within a step, step by step).  Long items with bounds request the next batch before the
+        // current one is looked at; the short ones have no registers to spare for it (billion codes, call 12.5 ms; with it 13.0).
+        constexpr bool AHEAD = LONG && BOUNDS;
+        auto for_batches = [&](int begin, int end, auto &&f) {   // f(row of the first code, codes)
+            uint2 c[QK_BATCH], next[QK_BATCH];
+            auto load = [&](int i0, uint2 (&to)[QK_BATCH]) {
 #pragma unroll
                 for (int u = 0; u < QK_BATCH; ++u) {
                     const int i = i0 + u * QK_THREADS;
-                    c[u] = i < end ? *reinterpret_cast<const uint2 *>(base_ptr + (size_t)i * 8) : make_uint2(0u, 0u);
+                    to[u] = i < end ? *reinterpret_cast<const uint2 *>(base_ptr + (size_t)i * 8) : make_uint2(0u, 0u);
                 }
+            };
+            if constexpr (AHEAD) load(begin + tid, c);
+            for (int i0 = begin + tid; i0 < end; i0 += QK_BATCH * QK_THREADS) {
+                if constexpr (!AHEAD) load(i0, c);
+                else load(i0 + QK_BATCH * QK_THREADS, next);
+                f(i0, c);
+                if constexpr (AHEAD) {
 #pragma unroll
-                for (int u = 0; u < QK_BATCH; ++u) {
-                    const int i = i0 + u * QK_THREADS;
-                    f(i, c[u], i < end);
+                    for (int u = 0; u < QK_BATCH; ++u) c[u] = next[u];
                 }
             }
+        };
+        auto for_codes = [&](int begin, int end, auto &&f) {
+            for_batches(begin, end, [&](int i0, const uint2 (&c)[QK_BATCH]) {
+#pragma unroll
+                for (int u = 0; u < QK_BATCH; ++u) f(i0 + u * QK_THREADS, c[u], i0 + u * QK_THREADS < end);
+            });
+        };
+
+        // Lower bounds of the sums in bytes: entry (j, i) of a pair becomes min(15, floor((entry - min_j) * f)) with f = QK_LB_RANGE /
+        // (cap - sum of the minima + 1), at most 1, so that a sum at or below the cap has a bound below T = floor((cap - sum of the
+        // minima) * f) + 1 <= QK_LB_RANGE + 1.  Eight pairs fill an 8-byte slot: half the LDS traffic and half the additions of the
+        // exact sums.  The first eight entries (at most 120) start from 0x80 - T, so bit 7 of a byte says that they reach T alone;
+        // without it the other eight are added to its low seven bits and bit 7 says that all of them do.  No byte ever carries.
+        // (all threads; after a barrier that follows the last change of the caps, ends with one)
+        auto build_lb = [&](const bool first_time) {
+            if (tid < 256) {
+                const uint4 e = sm.tab[tid];
+                const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
+                uint32_t mw[4];
+                if (first_time) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) mw[p] = ew[p];
+#pragma unroll
+                    for (int o = 1; o < 16; o <<= 1)   // (the 16 lanes of a sub-quantizer)
+#pragma unroll
+                        for (int p = 0; p < 4; ++p)
+                            mw[p] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, mw[p]), __builtin_bit_cast(u16x2, (uint32_t)__shfl_xor(mw[p], o))));
+                    if ((tid & 15) == 0) sm.minw[tid >> 4] = make_uint4(mw[0], mw[1], mw[2], mw[3]);
+                }
+            }
+            if (first_time) __syncthreads();
+            if (tid < 256) {
+                uint32_t off[4] = {0u, 0u, 0u, 0u};   // sums of the minima
+#pragma unroll 4
+                for (int j = 0; j < 16; ++j) {
+                    const uint4 m = sm.minw[j];
+                    off[0] += m.x; off[1] += m.y; off[2] += m.z; off[3] += m.w;
+                }
+                const uint4 e = sm.tab[tid], mine = sm.minw[tid >> 4];
+                const uint32_t ew[4] = {e.x, e.y, e.z, e.w}, mw[4] = {mine.x, mine.y, mine.z, mine.w};
+                uint32_t l[2] = {0u, 0u}, bias[2] = {0u, 0u};
+#pragma unroll
+                for (int s = 0; s < QK_QS; ++s) {
+                    const int sh = 16 * (s & 1);
+                    const int room = (int)sm.cap[s] - (int)((off[s >> 1] >> sh) & 0xffffu);
+                    float f = QK_LB_RANGE / (float)(room + 1);
+                    f = room >= 0 && f < 1.f ? f : 1.f;
+                    const float x = (float)(((ew[s >> 1] >> sh) & 0xffffu) - ((mw[s >> 1] >> sh) & 0xffffu)) * f;
+                    l[s >> 2] |= (uint32_t)fminf(x, 15.f) << (8 * (s & 3));
+                    const uint32_t t = sm.found[s] == 0 && room >= 0 ? (uint32_t)((float)room * f * (1.f + 1e-5f)) + 1u : 0u;   // (0: nothing passes)
+                    bias[s >> 2] |= (0x80u - t) << (8 * (s & 3));
+                }
+                sm.lbtab[tid] = make_uint2(l[0], l[1]);
+                if (tid == 0) sm.lbbias = make_uint2(bias[0], bias[1]);
+            }
+            __syncthreads();
+        };
+        uint32_t lb_lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)sm.lbtab;
+        asm volatile("" : "+v"(lb_lds));
+        // whether some pair's bound is below its T
+        auto bound_passes = [&](const uint2 c, const uint2 bias) {
+            uint32_t lo8[2] = {(c.x << 3) & 0x78787878u, (c.y << 3) & 0x78787878u};
+            uint32_t hi8[2] = {(c.x >> 1) & 0x78787878u, (c.y >> 1) & 0x78787878u};
+            asm volatile("" : "+v"(lo8[0]), "+v"(lo8[1]), "+v"(hi8[0]), "+v"(hi8[1]));
+            auto entry = [&](int j) {
+                const uint32_t word = (j & 1) ? hi8[j >> 3] : lo8[j >> 3];
+                const uint32_t addr = lb_lds | ((word >> (8 * ((j >> 1) & 3))) & 0xffu);   // (the tables start on a 256-byte boundary)
+                return *(const __attribute__((address_space(3))) u32x2 *)(uintptr_t)(addr + (uint32_t)j * 128u);
+            };
+            uint32_t a0 = bias.x, a1 = bias.y, b0 = 0u, b1 = 0u;
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) {
+                const u32x2 e0 = entry(j), e1 = entry(j + 1), f0 = entry(j + 8), f1 = entry(j + 9);
+                a0 = a0 + e0.x + e1.x; a1 = a1 + e0.y + e1.y;
+                b0 = b0 + f0.x + f1.x; b1 = b1 + f0.y + f1.y;
+            }
+            const uint32_t t0 = ((a0 & 0x7f7f7f7fu) + b0) | a0, t1 = ((a1 & 0x7f7f7f7fu) + b1) | a1;
+            return (t0 & t1 & 0x80808080u) != 0x80808080u;
         };
 
         // ---- counting passes: T of every pair.  Sums of base .. base + 510 are counted (one pass unless fewer than
@@ -324,8 +418,11 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
                     sm.reached[tid] = 0;
                     sm.cum_t[tid] = 0u;
                 }
-                if (tid == 0) sm.pending = 0;
+                if (tid == 0) { sm.pending = 0; sm.seg_saved[0] = sm.seg_saved[1] = 0u; }
                 __syncthreads();
+                uint32_t seg_rows = 0u;   // rows of the segment before
+                int seg_nr = 0;
+                bool lb_ready = false;
                 uint32_t lo[QK_QS];
                 bool open[QK_QS];
 #pragma unroll
@@ -338,24 +435,72 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG ? 2 : 4) void ivf_quick_scan_ke
                         capv[s] = sm.cap[s];
                         if (open[s]) capplus[s >> 1] |= (capv[s] + 1u) << (16 * (s & 1));
                     }
-                    for_codes(seg_begin, seg_end, [&](int i, const uint2 c, bool valid) {
-                        uint32_t acc[4];
-                        const bool pass = sums_below(c, valid, capplus, acc);
+                    if constexpr (BOUNDS) scnt = __builtin_amdgcn_readfirstlane(scnt);
+                    const int scnt0 = scnt;
+                    auto save = [&](int i, bool pass) {
                         const uint64_t mask = __ballot(pass);
                         if (mask == 0ull) return;
-                        {
-                            const int pos = scnt + mask_prefix(mask);
-                            if (pass && pos < saved_cap) my_saved[pos] = (uint32_t)i;
-                            scnt += __popcll(mask);
-                        }
-                        if (!pass) return;
+                        const int pos = scnt + mask_prefix(mask);
+                        if (pass && pos < saved_cap) my_saved[pos] = (uint32_t)i;
+                        scnt += __popcll(mask);
+                    };
+                    auto count = [&](const uint32_t (&acc)[4]) {
 #pragma unroll
                         for (int s = 0; s < QK_QS; ++s) {
                             const uint32_t sum = (acc[s >> 1] >> (16 * (s & 1))) & 0xffffu;
                             if (open[s] && sum >= lo[s] && sum <= capv[s]) atomicAdd(&sm.hist[s][sum - lo[s]], 1u);
                         }
-                    });
+                    };
+                    // Where the segment before saved few of its rows, this one is scanned by the lower bounds, and only the rows they
+                    // let through get their sums, 64 at a time.
+                    const bool by_bounds = BOUNDS && attempt == 0 && seg_nr > 0 && seg_end - seg_begin >= QK_THREADS * 2 &&
+                                           sm.seg_saved[(seg_nr - 1) & 1] * 4u < seg_rows;   // (uniform: read behind the barriers of the segment before)
+                    if (BOUNDS && by_bounds) {
+                        build_lb(!lb_ready);
+                        lb_ready = true;
+                        const uint2 bias = sm.lbbias;
+                        // (the bounds of a batch before any of them is looked at: their LDS reads overlap)
+                        for_batches(seg_begin, seg_end, [&](int i0, const uint2 (&c)[QK_BATCH]) {
+                            bool pass[QK_BATCH], some = false;
+#pragma unroll
+                            for (int u = 0; u < QK_BATCH; ++u) {
+                                pass[u] = bound_passes(c[u], bias) & (i0 + u * QK_THREADS < seg_end);
+                                some |= pass[u];
+                            }
+                            if (__ballot(some) == 0ull) return;
+#pragma unroll
+                            for (int u = 0; u < QK_BATCH; ++u) save(i0 + u * QK_THREADS, pass[u]);
+                        });
+                        scnt = __builtin_amdgcn_readfirstlane(scnt);
+                        list_fence();   // (the rows were stored by other lanes)
+                        const int have = scnt < saved_cap ? scnt : saved_cap;
+                        for (int e0 = scnt0 + lane; e0 < have; e0 += QK_BATCH * 64) {
+                            uint32_t r[QK_BATCH];
+                            uint2 c[QK_BATCH];
+#pragma unroll
+                            for (int u = 0; u < QK_BATCH; ++u) r[u] = e0 + u * 64 < have ? my_saved[e0 + u * 64] : (uint32_t)skip;
+#pragma unroll
+                            for (int u = 0; u < QK_BATCH; ++u) c[u] = *reinterpret_cast<const uint2 *>(base_ptr + (size_t)r[u] * 8);
+#pragma unroll
+                            for (int u = 0; u < QK_BATCH; ++u) {
+                                uint32_t acc[4];
+                                if (sums_below(c[u], e0 + u * 64 < have, capplus, acc)) count(acc);
+                            }
+                        }
+                    } else {
+                        for_codes(seg_begin, seg_end, [&](int i, const uint2 c, bool valid) {
+                            uint32_t acc[4];
+                            const bool pass = sums_below(c, valid, capplus, acc);
+                            if (__ballot(pass) == 0ull) return;
+                            save(i, pass);
+                            if (pass) count(acc);
+                        });
+                    }
+                    if (BOUNDS && lane == 0) atomicAdd(&sm.seg_saved[seg_nr & 1], (uint32_t)(scnt - scnt0));
+                    seg_rows = (uint32_t)(seg_end - seg_begin);
                     __syncthreads();
+                    if (BOUNDS && tid == 0) sm.seg_saved[(seg_nr + 1) & 1] = 0u;   // (read above, and next added to behind the barriers below)
+                    ++seg_nr;
                     const bool refresh = share && seg_len >= 8 * QK_BATCH * QK_THREADS;
                     // a wave reads the bins of a pair: lane l owns bins 8 l .. 8 l + 7 (the last bin stays empty)
                     for (int s = wave; s < QK_QS; s += QK_WAVES) {

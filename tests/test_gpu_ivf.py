@@ -579,13 +579,16 @@ def test_ivf_quick_result_lists_from_the_farthest_to_the_nearest(ctx, nq, topk):
 
 
 @pytest.mark.parametrize("kprime,topk,chunk_rows,special", [(128, 100, None, None), (100, 1, None, None), (20, 128, 1024, None), (128, 128, 1024, "ties"),
-                                                            (64, 10, None, "huge"), (128, 50, None, "equal")])
+                                                            (64, 10, None, "huge"), (128, 50, None, "equal"), (128, 100, None, "long"), (100, 7, 50_000, "long")])
 def test_ivf_quick_bounds_across_lists(ctx, opts, kprime, topk, chunk_rows, special):
     """Calls whose lists rule out codes of one another (512 rows a list and more, thousands of pairs, more items than blocks):
     exact against the oracle, with lists in chunks, sums that tie, infinite distances, and a query on top of its codes."""
     r = np.random.default_rng(kprime + topk)
     sizes = [600] * 20 + [2500, 3000, 70, 0, 128, 129, 1500, 700, 1023, 1024, 1025, 40]
-    nlist, d, n, nq, nprobe = len(sizes), 32, sum(sizes), 1100, 16
+    nq = 1100
+    if special == "long":   # lists of the large blocks beside short ones
+        sizes, nq = [70_001, 66_003, 131_072] + [900] * 13 + [9000, 20_001], 300
+    nlist, d, n, nprobe = len(sizes), 32, sum(sizes), 16
     coarse = (r.normal(size=(nlist, d)) * 3).astype(np.float32)
     offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     packed = r.integers(0, 256, (n, 8), dtype=np.uint8)
