@@ -331,7 +331,7 @@ __global__ void ivf_fill_pairs_kernel(const int32_t *__restrict__ probes, int np
 // one thread per list: write the list's items (group-major, chunks of a group consecutive)
 __device__ __forceinline__ void ivf_fill_items(int l, const uint32_t *pair_off, const uint32_t *nc_arr, const uint32_t *item_off,
                                                const int64_t *__restrict__ list_offsets, int rows_per_16b, uint32_t qb, IvfItem *items,
-                                               int64_t short_max, const int32_t *pairs_by_list, IvfShortItem *short_items) {
+                                               int64_t short_max, const int32_t *pairs_by_list, IvfShortItem *short_items, bool mark_chunked) {
     const uint32_t npl = pair_off[l + 1] - pair_off[l];
     const int nc = (int)nc_arr[l];
     if (npl == 0 || nc == 0) return;
@@ -364,7 +364,7 @@ __device__ __forceinline__ void ivf_fill_items(int l, const uint32_t *pair_off, 
             it.code_begin = (uint32_t)aligned;
             it.ncodes = (uint32_t)(ce - aligned);
             it.pair_pos = pair_off[l] + (uint32_t)g * qb;
-            it.skip_slots_chunk = (uint32_t)(cb - aligned) | ((uint32_t)nslots << 8) | ((uint32_t)c << 16);
+            it.skip_slots_chunk = (uint32_t)(cb - aligned) | (mark_chunked && nc > 1 ? 128u : 0u) | ((uint32_t)nslots << 8) | ((uint32_t)c << 16);
             items[item_off[l] + (uint32_t)g * nc + c] = it;
         }
     }
@@ -373,9 +373,9 @@ __device__ __forceinline__ void ivf_fill_items(int l, const uint32_t *pair_off, 
 __global__ void ivf_fill_items_kernel(const uint32_t *__restrict__ pair_off, const uint32_t *__restrict__ nc_arr,
                                       const uint32_t *__restrict__ item_off, const int64_t *__restrict__ list_offsets,
                                       int nlist, int rows_per_16b, uint32_t qb, IvfItem *items, int64_t short_max,
-                                      const int32_t *__restrict__ pairs_by_list, IvfShortItem *short_items) {
+                                      const int32_t *__restrict__ pairs_by_list, IvfShortItem *short_items, bool mark_chunked) {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l < nlist) ivf_fill_items(l, pair_off, nc_arr, item_off, list_offsets, rows_per_16b, qb, items, short_max, pairs_by_list, short_items);
+    if (l < nlist) ivf_fill_items(l, pair_off, nc_arr, item_off, list_offsets, rows_per_16b, qb, items, short_max, pairs_by_list, short_items, mark_chunked);
 }
 
 // one wave per query: lists (pair, chunk) the query owns, and each pair's first list relative to the query
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(1024) void ivf_group_small_kernel(IvfGroupArgs a) {
     for (int q = tid >> 6; q < a.nq; q += 16) ivf_pair_lists(q, a.probes, a.nc, a.nprobe, a.pair_out, a.qlists);
     __syncthreads();
     for (int l = tid; l < a.nlist; l += 1024)
-        ivf_fill_items(l, pair_off, a.nc, item_off, a.list_offsets, a.rows_per_16b, a.qb, a.items, a.short_max, a.pairs_by_list, a.short_items);
+        ivf_fill_items(l, pair_off, a.nc, item_off, a.list_offsets, a.rows_per_16b, a.qb, a.items, a.short_max, a.pairs_by_list, a.short_items, a.uncapped_rows > 0);
     ivf_qlist_scan(a.qlists, a.nq, a.qlist_off);
     __syncthreads();
     for (int p = tid; p < npairs; p += 1024) a.pair_out[p] += a.qlist_off[p / a.nprobe];
@@ -1026,7 +1026,7 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
                                                quick ? quick_rows : (int64_t)0);
             ivf_fill_pairs_kernel<<<(npairs + 255) / 256, 256, 0, g>>>(probes, npairs, pair_off, fill, pairs_by_list);
             ivf_fill_items_kernel<<<(nlist + 255) / 256, 256, 0, g>>>(pair_off, nc, item_off, L->list_offsets, nlist,
-                                                                      rows_per_16b, item_qb, items, short_max, pairs_by_list, short_items);
+                                                                      rows_per_16b, item_qb, items, short_max, pairs_by_list, short_items, quick);
             ivf_pair_lists_kernel<<<(nqb + 3) / 4, 256, 0, g>>>(probes, nc, nqb, nprobe, pair_out, qlists);
             ivf_qlist_scan_kernel<<<1, 1024, 0, g>>>(qlists, nqb, qlist_off);
             ivf_pair_abs_kernel<<<(unsigned)(((size_t)nqb * nprobe + 255) / 256), 256, 0, g>>>(qlist_off, (size_t)nqb * nprobe, nprobe, pair_out);

@@ -190,8 +190,7 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG && !BOUNDS ? 2 : 4) void ivf_qu
                                                                        const int32_t *__restrict__ pairs_by_list,
                                                                        const uint32_t *__restrict__ pair_out, int kprime,
                                                                        uint64_t *partial, uint32_t *saved_rows, int saved_cap,
-                                                                       const float *__restrict__ luts, const int32_t *__restrict__ probes,
-                                                                       const uint32_t *__restrict__ nc_arr, int nprobe, int topk,
+                                                                       const float *__restrict__ luts, int nprobe, int topk,
                                                                        unsigned long long *tau_key, QuickBound qb) {
     constexpr int QK_THREADS = QK_WAVES * 64;
     extern __shared__ __align__(16) unsigned char quick_smem[];
@@ -211,14 +210,14 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG && !BOUNDS ? 2 : 4) void ivf_qu
         const int item = sm.item;
         if (item >= nitems) break;
         const IvfItem it = items[item];
-        const int skip = (int)(it.skip_slots_chunk & 255u);
+        const int skip = (int)(it.skip_slots_chunk & 127u);
         const int nslots = (int)((it.skip_slots_chunk >> 8) & 255u);
         const uint32_t chunk = it.skip_slots_chunk >> 16;
         const int ncodes = (int)it.ncodes;            // rows from code_begin; the first `skip` belong to the list before
         const int nvalid = ncodes - skip;
         const uint32_t row0 = it.code_begin;
         const uint8_t *base_ptr = codes + (size_t)row0 * 8;
-        if (tid == 0) sm.single = nc_arr[probes[pairs_by_list[it.pair_pos]]] == 1u ? 1 : 0;   // (an item has at least one pair)
+        if (tid == 0) sm.single = (it.skip_slots_chunk & 128u) != 0u ? 0 : 1;
         if (tid < QK_QS) {
             const int pair = tid < nslots ? pairs_by_list[it.pair_pos + tid] : -1;
             sm.pair[tid] = pair;
@@ -659,7 +658,9 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG && !BOUNDS ? 2 : 4) void ivf_qu
             // float distances in place of the integer keys; the pairs' float tables take the memory of the bins
             float *const tabf = reinterpret_cast<float *>(&sm.hist[0][0]);
             static_assert(sizeof(sm.hist) >= QK_QS * 256 * sizeof(float), "the bins' memory holds the float tables");
-            for (int e = tid; e < nslots * 256; e += QK_THREADS) tabf[e] = luts[(size_t)sm.pair[e >> 8] * 256 + (e & 255)];
+            for (int e = tid; e < nslots * 256; e += QK_THREADS) {
+                if (!BOUNDS || sm.sure[e >> 8][0] != KEY_EMPTY) tabf[e] = luts[(size_t)sm.pair[e >> 8] * 256 + (e & 255)];   // (no candidates: no tables)
+            }
             __syncthreads();
             for (int e = tid; e < nslots * QK_KP; e += QK_THREADS) {
                 const int s = e / QK_KP, idx = e % QK_KP;
@@ -829,13 +830,12 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
         // (no more blocks than there can be items: each draws from the counter, one after the other)
         auto blocks = [&](int full) { return (unsigned)(most_items < (size_t)full ? most_items : (size_t)full); };
         long_kernel<<<blocks(ctx->num_cu * 2), 8 * 64, sizeof(QuickSmemLong), s>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
-                                                                       kprime, partial, saved_rows, cap_long, luts, probes, nc_arr, nprobe, topk, tau_key, qb);
+                                                                       kprime, partial, saved_rows, cap_long, luts, nprobe, topk, tau_key, qb);
         PQ_HIP(ctx, hipGetLastError());
         if (two_streams) PQ_HIP(ctx, hipStreamWaitEvent(s2, ctx->aux_fork, 0));
         short_kernel<<<blocks(ctx->num_cu * 4), 4 * 64, sizeof(QuickSmemShort), s2>>>(codes, qluts, items, nitems_dev, pairs_by_list, pair_out,
                                                                           kprime, partial,
-                                                                          saved_rows + (size_t)ctx->num_cu * 2 * 8 * cap_long, cap_short, luts, probes, nc_arr,
-                                                                          nprobe, topk, tau_key, qb);
+                                                                          saved_rows + (size_t)ctx->num_cu * 2 * 8 * cap_long, cap_short, luts, nprobe, topk, tau_key, qb);
         PQ_HIP(ctx, hipGetLastError());
         if (two_streams) {
             PQ_HIP(ctx, hipEventRecord(ctx->aux_join, s2));

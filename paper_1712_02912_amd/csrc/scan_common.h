@@ -29,7 +29,7 @@ struct IvfItem {
     uint32_t code_begin;   // first row of the chunk, rounded down to a 16-byte boundary
     uint32_t ncodes;       // rows from code_begin to the end of the chunk
     uint32_t pair_pos;     // position in pairs_by_list of the item's first (query, list) pair
-    uint32_t skip_slots_chunk;   // bits 0-7: rows at the front that belong to the previous list,
+    uint32_t skip_slots_chunk;   // bits 0-6: rows at the front that belong to the previous list, bit 7 (Quick ADC): the list has several chunks,
                                  // bits 8-15: number of pairs (slots), bits 16-31: chunk index in the list
 };
 
