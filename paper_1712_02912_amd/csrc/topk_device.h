@@ -182,11 +182,37 @@ __device__ inline uint32_t block_kth_smallest_u32(const uint32_t *vals, int n, u
     return state[0];
 }
 
-// One step of a bitonic network within the wave: the key of lane ^ stride, the smaller one kept by the lower lane where `up`.
-__device__ __forceinline__ uint64_t wave_bitonic_step(uint64_t key, int lane, int stride, bool up) {
-    const uint64_t other = __shfl_xor((unsigned long long)key, stride);
-    const bool keep_small = ((lane & stride) == 0) == up;
+// The 32 bits that lane ^ STRIDE holds, by lane moves of the vector unit: a shuffle takes each half of a key through LDS instead.
+template <int STRIDE>
+__device__ __forceinline__ uint32_t wave_xor_u32(uint32_t v) {
+    static_assert(STRIDE == 1 || STRIDE == 2 || STRIDE == 4 || STRIDE == 8 || STRIDE == 16 || STRIDE == 32, "a power of two within the wave");
+    if constexpr (STRIDE == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true);         // quad_perm [1,0,3,2]
+    else if constexpr (STRIDE == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, true);    // quad_perm [2,3,0,1]
+    else if constexpr (STRIDE == 4)                                                                             // half row mirrored (^ 7), quads mirrored (^ 3)
+        return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true), 0x1b, 0xf, 0xf, true);
+    else if constexpr (STRIDE == 8) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);   // row of 16 rotated by 8
+    else if constexpr (STRIDE == 16) {   // odd rows of the first with even rows of the second: the pair's lower row twice, its upper row twice
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (lane_id() & 16) ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return (lane_id() & 32) ? r[0] : r[1];
+    }
+}
+
+// One step of a bitonic network within the wave: the key of lane ^ STRIDE, the smaller one kept by the lower lane where `up`.
+template <int STRIDE>
+__device__ __forceinline__ uint64_t wave_bitonic_step(uint64_t key, int lane, bool up) {
+    const uint64_t other = (uint64_t)wave_xor_u32<STRIDE>((uint32_t)(key >> 32)) << 32 | wave_xor_u32<STRIDE>((uint32_t)key);
+    const bool keep_small = ((lane & STRIDE) == 0) == up;
     return (other < key) == keep_small ? other : key;
+}
+// The steps of strides STRIDE, STRIDE / 2 .. 1.
+template <int STRIDE>
+__device__ __forceinline__ uint64_t wave_bitonic_merge(uint64_t key, int lane, bool up) {
+    key = wave_bitonic_step<STRIDE>(key, lane, up);
+    if constexpr (STRIDE > 1) key = wave_bitonic_merge<STRIDE / 2>(key, lane, up);
+    return key;
 }
 
 // In-LDS bitonic sort (ascending) of n2 keys, n2 a power of two, by the whole block: few registers and little code, a barrier
@@ -231,13 +257,13 @@ __device__ inline void block_bitonic_sort(uint64_t *s, int n2) {
             const bool asc = ((t * 64) & size) == 0;
             uint64_t key = s[t * 64 + lane];
             if (size == 64) {   // (sorted from scratch: ascending and descending runs in turn)
-#pragma unroll
-                for (int sub = 2; sub < 64; sub <<= 1)
-#pragma unroll
-                    for (int stride = sub >> 1; stride > 0; stride >>= 1) key = wave_bitonic_step(key, lane, stride, (lane & sub) == 0);
+                key = wave_bitonic_merge<1>(key, lane, (lane & 2) == 0);
+                key = wave_bitonic_merge<2>(key, lane, (lane & 4) == 0);
+                key = wave_bitonic_merge<4>(key, lane, (lane & 8) == 0);
+                key = wave_bitonic_merge<8>(key, lane, (lane & 16) == 0);
+                key = wave_bitonic_merge<16>(key, lane, (lane & 32) == 0);
             }
-#pragma unroll
-            for (int stride = 32; stride > 0; stride >>= 1) key = wave_bitonic_step(key, lane, stride, asc);
+            key = wave_bitonic_merge<32>(key, lane, asc);
             s[t * 64 + lane] = key;
         }
     }
