@@ -11,11 +11,13 @@
 // (the wave meets ids in increasing order, so a later code equal to its own k-th key can never
 // replace it).  At the end of the block the 8 wave lists are merged to one list of k keys; the
 // merge kernel sorts the lists of all chunks of a query and writes the result.
+#include <math.h>
 #include <type_traits>
 
 #include "pq_internal.h"
 #include "scan_common.h"
 #include "topk_device.h"
+#include "lds_walk.h"
 
 namespace pq {
 
@@ -42,10 +44,10 @@ struct ScanArgs {
 // and writes KPAD keys (padded with KEY_EMPTY) to `out`.
 template <int QB, int E, int KPAD>
 __device__ __forceinline__ void block_merge_lists(uint64_t *block_scratch, int (*wave_cnt)[QB], int k,
-                                                   uint64_t *out_item) {
+                                                   uint64_t *out_item, uint32_t queries = ~0u) {
     constexpr int CAP = 64 * E;
     const int wave = threadIdx.x >> 6, lane = lane_id();
-    if (wave < QB) {
+    if (wave < QB && ((queries >> wave) & 1u) != 0u) {
         const int q = wave;
         uint64_t *acc = block_scratch + (size_t)(0 * QB + q) * CAP;
         int cnt = wave_cnt[0][q];
@@ -140,6 +142,342 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_generic_kernel(ScanArgs a, 
     list_fence();
     __syncthreads();
     block_merge_lists<QB, E, KPAD>(block_scratch, wave_cnt, a.topk, a.partial + (size_t)blockIdx.x * QB * KPAD);
+}
+
+// ------------------------------------------------------------------------------------------
+// 32-bit codes: 4 float tables of 256 entries, 4 queries per block, two blocks of 8 waves per CU.
+//
+// Row b of the tables in LDS (256 bytes) holds the entries of code byte b for the four queries as 16-byte slots, every table
+// in four copies; a lane reads slot (lane + 4 s) & 15 at step s, so the 16 lanes that the LDS serves together always read 16
+// different bank groups and a code costs four reads without conflicts for four queries.  What bounds the loop is these
+// reads: 32 cycles per 64 codes and four queries (4 M codes, 100 queries: 81 us for the chip, the kernel 204; set-up and end of
+// its 2000 items and the exact tests of tied codes take the rest).  The rotated order of the
+// additions makes the sum a filter only, with a margin of its rounding; codes at or below the bound are added up again in table
+// order, so values and ids are those of the general kernel.
+// Bounds: a sample of the codes is counted first in the bins of a histogram per query (codes4_sample_kernel), the scan adds
+// the candidates beyond the sample's rows, and waves that find many read the bin of the k-th from it; keys cut from a wave's
+// or a block's lists bound the rows of tied codes as well.
+// Call, general kernel -> this one: 10^6 codes, 6 queries, top-100 337 -> 67 us; 4 M codes, top-100, 25 queries 1060 -> 147,
+// 100 queries 1830 -> 260, top-1024 7380 -> 381; 30 000 codes, 3 queries 64 -> 38; 4096 codes, one query 59 -> 37, 16 queries,
+// top-1024 471 -> 114.  An atomic for each of the
+// equal values counted made the 25 queries' call 441 us, folding the longer lists instead of sorting them the 100 queries' 596.
+constexpr int C4_QB = 4, C4_TAB = 4 * 256;
+constexpr int64_t C4_MIN_N = 4096;     // smaller databases: the general kernel (its merge sorts few lists there, and there is little to sample)
+
+struct Codes4Args {
+    const uint32_t *codes;
+    int64_t n, chunk_codes, nsample;   // the first nsample rows are counted by the sampling pass
+    int nitems, ngroups, nq, topk;     // item = chunk * ngroups + group
+    const float *luts;
+    unsigned long long *tau_key;       // [nq] at least topk keys are at or below it
+    uint32_t *hist;                    // [nq][HIST_BINS], bins of 2^HIST_SHIFT ordered-value units that end at ref
+    uint32_t *ref;                     // [nq]
+    float *margin;                     // [nq] between a sum in rotated order and the value (NaN: sums may overflow, no filter)
+    uint64_t *scratch;                 // [nblocks][SCAN_WAVES][C4_QB][64 * E]
+    uint64_t *partial;                 // [nitems][C4_QB][KPAD]
+};
+
+// One wave: the sum of a query's greatest finite entries per table (the reference of its histogram: whatever lies above it is
+// not counted) and of their greatest magnitudes.
+__device__ __forceinline__ void codes4_table_sums(const float *__restrict__ lut, float &top, float &mag) {
+    const int lane = lane_id();
+    top = mag = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float t = -__builtin_inff(), a = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float e = lut[j * 256 + i * 64 + lane];
+            if (e < __builtin_inff()) t = fmaxf(t, e);
+            if (fabsf(e) < __builtin_inff()) a = fmaxf(a, fabsf(e));
+        }
+        for (int o = 32; o > 0; o >>= 1) { t = fmaxf(t, __shfl_xor(t, o)); a = fmaxf(a, __shfl_xor(a, o)); }
+        top += t;
+        mag += a;
+    }
+}
+
+__global__ void codes4_clear_kernel(uint4 *hist, size_t n4) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = i0; i < n4; i += stride) hist[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Block (q, s) counts the values of slice s of the sample.  Of its bins only those up to its own k-th can hold the sample's
+// k-th: they go to the query's bins in device memory.
+__global__ __launch_bounds__(SCAN_THREADS) void codes4_sample_kernel(Codes4Args a, int slice, int nslices) {
+    __shared__ float tab[C4_TAB];
+    __shared__ __align__(16) uint32_t hist[HIST_BINS];
+    __shared__ uint32_t ref_s;
+    __shared__ int bin_s;
+    const int q = blockIdx.x / nslices, tid = threadIdx.x;
+    const float *lut = a.luts + (size_t)q * C4_TAB;
+    for (int i = tid; i < C4_TAB; i += SCAN_THREADS) tab[i] = lut[i];
+    for (int i = tid; i < HIST_BINS; i += SCAN_THREADS) hist[i] = 0;
+    if (tid < 64) {
+        float top, mag;
+        codes4_table_sums(lut, top, mag);
+        if (tid == 0) ref_s = f32_to_ord(top);
+    }
+    __syncthreads();
+    const uint32_t ref = ref_s;
+    const int64_t begin = (int64_t)(blockIdx.x % nslices) * slice, end = begin + slice < a.nsample ? begin + slice : a.nsample;
+    for (int64_t i0 = begin + tid; i0 < end; i0 += 4 * SCAN_THREADS) {
+        uint32_t c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = i0 + u * SCAN_THREADS < end ? a.codes[i0 + u * SCAN_THREADS] : 0u;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float d = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d += tab[j * 256 + ((c[u] >> (8 * j)) & 255u)];
+            const uint32_t ord = f32_to_ord(d);
+            if (i0 + u * SCAN_THREADS < end && d < __builtin_inff() && ord <= ref) {
+                const uint32_t below = (ref - ord) >> HIST_SHIFT;
+                atomicAdd(&hist[HIST_BINS - 1 - (below < HIST_BINS ? below : HIST_BINS - 1)], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    if (tid < 64) {
+        const int b = hist_threshold(hist, a.topk);
+        if (tid == 0) bin_s = b;
+    }
+    __syncthreads();
+    for (int i = tid; i < HIST_BINS && i <= bin_s; i += SCAN_THREADS)
+        if (hist[i] != 0u) atomicAdd(&a.hist[(size_t)q * HIST_BINS + i], hist[i]);
+}
+
+// What the items of a query start from, one wave per query.  (Read off the histogram by every item instead, which has to
+// drop its L2's copies for that: 10^6 codes, 6 queries, scan 64 us.)
+__global__ __launch_bounds__(64) void codes4_pick_kernel(Codes4Args a) {
+    const int q = blockIdx.x;
+    float top, mag;
+    codes4_table_sums(a.luts + (size_t)q * C4_TAB, top, mag);
+    const uint32_t ref = f32_to_ord(top);
+    const int b = hist_threshold(a.hist + (size_t)q * HIST_BINS, a.topk);
+    if (threadIdx.x == 0) {
+        a.ref[q] = ref;
+        // two orders of four additions differ by at most six roundings of the magnitudes' sum (3.6e-7 of it)
+        a.margin[q] = mag < 1e38f ? mag * 1e-6f : __builtin_nanf("");
+        a.tau_key[q] = (unsigned long long)(b < HIST_BINS ? ref - ((uint32_t)(HIST_BINS - 1 - b) << HIST_SHIFT) : 0xff800000u) << 32 | 0xffffffffull;
+    }
+}
+
+template <int E, int KPAD>
+__global__ __launch_bounds__(SCAN_THREADS, 4) void scan_codes4_kernel(Codes4Args a) {
+    constexpr int QB = C4_QB, CAP = 64 * E, UNROLL = 4, STEP = 64 * UNROLL;
+    __shared__ uint4 lut[4096];
+    __shared__ unsigned long long key_blk[QB];   // at least topk keys of the query are at or below it
+    __shared__ float margin[QB];
+    __shared__ int found;
+    __shared__ uint32_t ref_s[QB];
+    __shared__ int wave_cnt[SCAN_WAVES][QB];
+    __shared__ uint32_t ring[SCAN_WAVES][STEP + 64];   // rows of the item whose sums passed, waiting for the exact test
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
+    const char *const lut_bytes = (const char *)lut;
+    uint64_t *const block_scratch = a.scratch + (size_t)blockIdx.x * SCAN_WAVES * QB * CAP;
+    uint64_t *const wave_buf = block_scratch + (size_t)wave * QB * CAP;
+    uint32_t bases = 0;   // slot offsets of the four steps
+#pragma unroll
+    for (int s = 0; s < 4; ++s) bases |= ((((uint32_t)lane + 4u * s) & 15u) << 4) << (8 * s);
+    const uint32_t rot = ((uint32_t)lane >> 2) & 3u;   // the table of step 0
+    // keys of a wave's list at which it is cut to the k smallest: there must be room for 64 more, and short results find their
+    // k-th key, which rules out ties, long before that
+    const int list_most = 2 * a.topk + 32 < CAP - 64 ? 2 * a.topk + 32 : CAP - 64;
+
+    for (int item = blockIdx.x; item < a.nitems; item += gridDim.x) {
+        const int q0 = item % a.ngroups * QB;
+        const int64_t begin = (int64_t)(item / a.ngroups) * a.chunk_codes;
+        const int64_t end = begin + a.chunk_codes < a.n ? begin + a.chunk_codes : a.n;
+        auto publish = [&](int q, unsigned long long key) {   // (one lane)
+            __hip_atomic_fetch_min(&key_blk[q], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            atomicMin(&a.tau_key[q0 + q], key);
+        };
+        auto bound_of = [&](int q) { return __hip_atomic_load(&key_blk[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+        auto edge_key = [&](int q) -> unsigned long long {   // (one wave) the edge of the bin that holds the k-th counted value
+            const int b = hist_threshold(a.hist + (size_t)(q0 + q) * HIST_BINS, a.topk);
+            return b < HIST_BINS ? (unsigned long long)(ref_s[q] - ((uint32_t)(HIST_BINS - 1 - b) << HIST_SHIFT)) << 32 | 0xffffffffull : KEY_EMPTY;
+        };
+        __syncthreads();   // the last item is done with the tables and the counts
+        for (int e = tid; e < C4_TAB; e += SCAN_THREADS) {
+            uint32_t v[QB];
+#pragma unroll
+            for (int q = 0; q < QB; ++q) v[q] = q0 + q < a.nq ? __float_as_uint(a.luts[(size_t)(q0 + q) * C4_TAB + e]) : 0u;
+            const int j = e >> 8, b = e & 255;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) lut[b * 16 + 4 * j + ((c + b) & 3)] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+        if (lane < QB) wave_cnt[wave][lane] = 0;
+        if (tid < QB) {
+            const bool used = q0 + tid < a.nq;   // (a slot without a query: no code passes, see reload)
+            key_blk[tid] = used ? __hip_atomic_load(&a.tau_key[q0 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+            margin[tid] = used ? a.margin[q0 + tid] : 0.f;
+            ref_s[tid] = used ? a.ref[q0 + tid] : 0u;
+        }
+        __syncthreads();
+
+        float thr[QB];   // a rotated sum above it is no candidate
+        auto reload = [&]() {
+#pragma unroll
+            for (int q = 0; q < QB; ++q) {
+                const float t = q0 + q < a.nq ? ord_to_f32((uint32_t)(bound_of(q) >> 32)) + margin[q] : -__builtin_inff();
+                thr[q] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(t)));
+            }
+        };
+        reload();
+        int added = 0;   // keys this wave has added since it last looked at a histogram
+        // Parked rows, 64 at a time: the values in table order, and the lists.
+        auto flush = [&](int count) {
+#pragma unroll 1
+            for (int base = 0; base < count; base += 64) {
+                const bool have = base + lane < count;
+                const int64_t row = begin + (have ? ring[wave][base + lane] : 0u);
+                const uint32_t code = a.codes[row];
+                float val[QB] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint4 e = lut[((code >> (8 * j)) & 255u) * 16 + 4 * j + (lane & 3)];
+                    val[0] += __uint_as_float(e.x); val[1] += __uint_as_float(e.y);
+                    val[2] += __uint_as_float(e.z); val[3] += __uint_as_float(e.w);
+                }
+#pragma unroll 1
+                for (int q = 0; q < QB && q0 + q < a.nq; ++q) {
+                    const float v = q == 0 ? val[0] : q == 1 ? val[1] : q == 2 ? val[2] : val[3];
+                    const uint32_t ord = f32_to_ord(v);
+                    const uint64_t key = (uint64_t)ord << 32 | (uint32_t)row;
+                    const bool pass = have && v < __builtin_inff() && key <= bound_of(q);
+                    const uint64_t mask = __ballot(pass);
+                    if (mask == 0ull) continue;
+                    uint64_t *const buf = wave_buf + (size_t)q * CAP;
+                    int cnt = wave_append(buf, wave_cnt[wave][q], pass, key);
+                    const uint32_t below = (ref_s[q] - ord) >> HIST_SHIFT;   // (equal values add together: one atomic for them)
+                    wave_count_bin(a.hist + (size_t)(q0 + q) * HIST_BINS, pass && row >= a.nsample && ord <= ref_s[q],
+                                   HIST_BINS - 1 - (below < HIST_BINS ? below : HIST_BINS - 1));
+                    added += __popcll(mask);
+                    if (cnt > list_most) {
+                        const uint64_t kth = wave_compact<E>(buf, cnt, a.topk);
+                        if (kth != KEY_EMPTY && lane == 0) publish(q, kth);
+                    }
+                    wave_cnt[wave][q] = cnt;   // (the same from every lane)
+                }
+            }
+        };
+        // steps of 256 codes, the next step's codes on their way while one is scanned
+        const int ncodes = (int)(end - begin), nsteps = (ncodes + STEP - 1) / STEP;
+        const uint32_t *const codes = a.codes + begin;
+        auto load_step = [&](int s, uint32_t (&c)[UNROLL]) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const int i = s * STEP + u * 64 + lane;
+                c[u] = codes[i < ncodes ? i : ncodes - 1];
+            }
+        };
+        uint32_t next[UNROLL];
+        load_step(wave, next);
+        int iter = 0, parked = 0;
+        for (int s = wave; s < nsteps; s += SCAN_WAVES, ++iter) {
+            uint32_t cur[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) cur[u] = next[u];
+            load_step(s + SCAN_WAVES, next);
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const uint32_t w = __builtin_amdgcn_alignbyte(cur[u], cur[u], rot);
+                float d[QB];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const uint32_t off = t == 0 ? lut_offset<0>(w, bases) : t == 1 ? lut_offset<1>(w, bases) : t == 2 ? lut_offset<2>(w, bases) : lut_offset<3>(w, bases);
+                    const float4 e = *reinterpret_cast<const float4 *>(lut_bytes + off);
+                    if (t == 0) { d[0] = e.x; d[1] = e.y; d[2] = e.z; d[3] = e.w; }
+                    else { d[0] += e.x; d[1] += e.y; d[2] += e.z; d[3] += e.w; }
+                }
+                // (written as "not above": NaN sums and thresholds pass to the exact test)
+                const int i = s * STEP + u * 64 + lane;
+                const uint64_t hit = __ballot(i < ncodes && (!(d[0] > thr[0]) || !(d[1] > thr[1]) || !(d[2] > thr[2]) || !(d[3] > thr[3])));
+                if (__builtin_expect(hit != 0ull, 0)) {
+                    if ((hit >> lane) & 1ull) ring[wave][parked + mask_prefix(hit)] = (uint32_t)i;
+                    parked += __popcll(hit);
+                }
+            }
+            const bool last = s + SCAN_WAVES >= nsteps;
+            if (parked >= 64 || (last && parked > 0)) {   // whole batches; what is left moves to the front
+                const int take = last ? parked : parked & ~63;
+                flush(take);
+                parked -= take;
+                if (lane < parked) ring[wave][lane] = ring[wave][take + lane];
+                if (added >= KPAD / 2) {
+                    added = 0;
+                    const int q = wave & (QB - 1);
+                    if (q0 + q < a.nq) {
+                        const unsigned long long key = edge_key(q);
+                        if (lane == 0) publish(q, key);
+                    }
+                }
+                reload();
+            }
+            if ((iter & 3) == 3) reload();
+        }
+        list_fence();
+        __syncthreads();
+        // End of item.  Lists that fit side by side are copied; longer ones (encoded data ties: 4 M codes hold thousands of
+        // copies of a near code) are sorted in the memory of the tables, and their k-th key bounds the items that follow; the
+        // longest are folded one into the other.
+        int total[QB];
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+            total[q] = 0;
+            for (int w = 0; w < SCAN_WAVES; ++w) total[q] += wave_cnt[w][q];
+        }
+        uint64_t *const out = a.partial + (size_t)item * QB * KPAD;
+        uint64_t *const keys = (uint64_t *)lut;
+        constexpr int SORT_KEYS = sizeof(lut) / 8;
+        uint32_t fold = 0;
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+            const uint64_t *const src = wave_buf + (size_t)q * CAP;
+            uint64_t *const to = out + (size_t)q * KPAD;
+            if (total[q] <= KPAD) {
+                int at = 0;
+                for (int w = 0; w < wave; ++w) at += wave_cnt[w][q];
+                for (int i = lane; i < wave_cnt[wave][q]; i += 64) to[at + i] = key_load(src + i);
+                for (int i = total[q] + tid; i < KPAD; i += SCAN_THREADS) to[i] = KEY_EMPTY;
+            } else if (total[q] <= SORT_KEYS) {
+                __syncthreads();   // (the last query's keys have been read)
+                if (tid == 0) found = 0;
+                __syncthreads();
+                const uint64_t bound = bound_of(q);
+                const int cnt = wave_cnt[wave][q];
+                for (int i0 = 0; i0 < cnt; i0 += 64) {
+                    const uint64_t key = i0 + lane < cnt ? key_load(src + i0 + lane) : KEY_EMPTY;
+                    const bool in = key <= bound;
+                    const int at = wave_place(&found, in);
+                    if (in) keys[at] = key;
+                }
+                __syncthreads();
+                const int nkeys = found;
+                int n2 = 64;
+                while (n2 < nkeys) n2 <<= 1;
+                for (int i = nkeys + tid; i < n2; i += SCAN_THREADS) keys[i] = KEY_EMPTY;
+                block_bitonic_sort(keys, n2);
+                for (int i = tid; i < KPAD; i += SCAN_THREADS) to[i] = i < n2 ? keys[i] : KEY_EMPTY;
+                if (tid == 0 && nkeys >= a.topk) atomicMin(&a.tau_key[q0 + q], (unsigned long long)keys[a.topk - 1]);
+            } else {
+                fold |= 1u << q;
+            }
+        }
+        if (fold != 0u) {
+            __syncthreads();   // every wave has read the counts before any of them changes
+            for (int q = 0; q < QB; ++q) {   // (the fold makes room list by list: at most k keys in each)
+                if (((fold >> q) & 1u) == 0u) continue;
+                int cnt = wave_cnt[wave][q];
+                if (cnt > a.topk) wave_compact<E>(wave_buf + (size_t)q * CAP, cnt, a.topk);
+                wave_cnt[wave][q] = cnt;
+            }
+            list_fence();
+            __syncthreads();
+            block_merge_lists<QB, E, KPAD>(block_scratch, wave_cnt, a.topk, out, fold);
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -509,6 +847,66 @@ static int run_generic(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, con
     return launch_merge_topk(ctx, a.partial, (int)nchunks, ngroups, qb, kpad, nq, topk, lut_u8, out_val, out_ids);
 }
 
+// 32-bit codes (see scan_codes4_kernel).  The sample: its counting costs about as much as the candidates its bound lets
+// through, topk n / sample per query, near 4 sqrt(topk n) codes.
+static int run_codes4(pq_ctx *ctx, const uint8_t *codes, int64_t n, const float *luts, int nq, int topk, void *out_val, int64_t *out_ids) {
+    const bool small = topk <= 128;
+    const int kpad = small ? 128 : 1024, cap = small ? 256 : 2048;
+    Codes4Args a;
+    a.codes = (const uint32_t *)codes; a.n = n; a.nq = nq; a.topk = topk; a.luts = luts;
+    a.ngroups = (nq + C4_QB - 1) / C4_QB;
+    // chunks for one round of two blocks per CU, of at least 4096 codes; large ones in four rounds, of which the later find
+    // the bounds of the earlier
+    int64_t nchunks = 2 * ctx->num_cu / a.ngroups;
+    if (nchunks > n / 4096) nchunks = n / 4096;
+    if (nchunks >= 1 && n / nchunks >= (1 << 17)) nchunks = 8 * ctx->num_cu / a.ngroups;
+    if (nchunks < (n >> 28) + 1) nchunks = (n >> 28) + 1;   // (rows of an item are counted in 32 bits)
+    a.chunk_codes = ((n + nchunks - 1) / nchunks + 255) / 256 * 256;
+    nchunks = (n + a.chunk_codes - 1) / a.chunk_codes;
+    a.nitems = (int)(nchunks * a.ngroups);
+    const int nblocks = a.nitems < 2 * ctx->num_cu ? a.nitems : 2 * ctx->num_cu;
+    int64_t sample = (int64_t)(4.0 * sqrt((double)topk * (double)n));
+    if (sample < 16 * (int64_t)topk) sample = 16 * (int64_t)topk;
+    a.nsample = sample < n ? sample : n;
+
+    const size_t tau_bytes = align_up((size_t)nq * 8, 256), ref_bytes = align_up((size_t)nq * 4, 256), hist_bytes = (size_t)nq * HIST_BINS * 4;
+    const size_t scratch_bytes = (size_t)nblocks * SCAN_WAVES * C4_QB * cap * 8;
+    int rc = ws_reserve(ctx, tau_bytes + 2 * ref_bytes + hist_bytes + scratch_bytes + (size_t)a.nitems * C4_QB * kpad * 8);
+    if (rc) return rc;
+    uint8_t *ws = (uint8_t *)ctx->ws;
+    a.tau_key = (unsigned long long *)ws; ws += tau_bytes;
+    a.ref = (uint32_t *)ws; ws += ref_bytes;
+    a.margin = (float *)ws; ws += ref_bytes;
+    a.hist = (uint32_t *)ws; ws += hist_bytes;
+    a.scratch = (uint64_t *)ws; ws += scratch_bytes;
+    a.partial = (uint64_t *)ws;
+
+    hipStream_t s = ctx->stream;
+    codes4_clear_kernel<<<nq < 1024 ? nq : 1024, 256, 0, s>>>((uint4 *)a.hist, hist_bytes / 16);
+    PQ_HIP(ctx, hipGetLastError());
+    // slices for four blocks per CU, of at least 2048 codes
+    const int64_t per_query = 4 * ctx->num_cu / nq > 1 ? 4 * ctx->num_cu / nq : 1;
+    int64_t slice = ((a.nsample + per_query - 1) / per_query + 2047) / 2048 * 2048;
+    const int nslices = (int)((a.nsample + slice - 1) / slice);
+    codes4_sample_kernel<<<(unsigned)nslices * (unsigned)nq, SCAN_THREADS, 0, s>>>(a, (int)slice, nslices);
+    PQ_HIP(ctx, hipGetLastError());
+    codes4_pick_kernel<<<nq, 64, 0, s>>>(a);
+    PQ_HIP(ctx, hipGetLastError());
+    if (ctx->profiling) {
+        note_plain_scan(ctx, "scan_codes4_kernel (4 queries per block)", C4_QB, a.ngroups);
+        PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, s));
+    }
+    if (small) scan_codes4_kernel<4, 128><<<nblocks, SCAN_THREADS, 0, s>>>(a);
+    else scan_codes4_kernel<32, 1024><<<nblocks, SCAN_THREADS, 0, s>>>(a);
+    PQ_HIP(ctx, hipGetLastError());
+    if (ctx->profiling) {
+        PQ_HIP(ctx, hipEventRecord(ctx->ev_end, s));
+        ctx->ev_valid = 1;
+    }
+    return launch_merge_filtered(ctx, a.partial, nullptr, (int)nchunks, a.ngroups, C4_QB, a.tau_key, kpad, nq, topk, nullptr, false,
+                                 out_val, out_ids, a.hist, a.ref, HIST_BINS);
+}
+
 int launch_scan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const void *luts, int lf, int nq, int m, int k,
                 int topk, void *out_val, int64_t *out_ids) {
     const bool general = opt_int(ctx, PQ_OPT_SCAN_FORCE_GENERAL, 0) != 0;
@@ -523,6 +921,10 @@ int launch_scan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const void
     // on to the general kernel, which may need less.
     if (!general && cf == PQ_CODES_U4_PACKED && lf == PQ_LUT_U8 && k == 16 && m == 32 && (n >= 1024 || (topk > 128 && n > topk))) {
         const int rc = w16::launch_scan_tuned(ctx, 7, codes, n, luts, nq, topk, out_val, out_ids);
+        if (!(rc == PQ_ENOMEM && ctx->ws_fixed)) return rc;
+    }
+    if (!general && cf == PQ_CODES_U8 && lf == PQ_LUT_F32 && k == 256 && m == 4 && n >= C4_MIN_N) {
+        const int rc = run_codes4(ctx, codes, n, (const float *)luts, nq, topk, out_val, out_ids);
         if (!(rc == PQ_ENOMEM && ctx->ws_fixed)) return rc;
     }
     if ((int64_t)m * k <= 8192)

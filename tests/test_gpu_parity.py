@@ -1051,3 +1051,45 @@ def test_scan_f32_first_bound_from_slices_of_small_samples(ctx, opts, m, n, nq, 
         od, oi = orc.adc_scan_topk_f32(codes, orc.CODES_U8, luts, topk)
         for q in range(0, nq, 7):
             check_float_topk(got[0][q], got[1][q], od[q], oi[q], codes, orc.CODES_U8, luts[q], n)
+
+
+@pytest.mark.parametrize("n,nq,topk,kind", [(4096, 1, 1, "random"), (4097, 4, 100, "random"), (4351, 5, 1024, "random"), (8192, 3, 128, "equal"),
+                                            (70_001, 9, 129, "few_values"), (100_003, 7, 100, "far"), (50_000, 2, 100, "infinite"),
+                                            (60_000, 6, 128, "mostly_infinite"), (300_001, 17, 100, "negative"), (40_000, 4, 1000, "overflow"),
+                                            (500_003, 33, 1024, "random"), (20_000, 1100, 10, "random")])
+def test_scan_f32_four_byte_codes(ctx, opts, n, nq, topk, kind):
+    """32-bit codes: values and ids are those of the general kernel, whatever order the filter adds in: with ties, a far centroid,
+    infinite entries (also so many that fewer than topk distances are finite), tables that are no distances and sums that
+    overflow in one order of the additions but not in another."""
+    r = np.random.default_rng(n)
+    codes = r.integers(0, 256, (n, 4), dtype=np.uint8)
+    luts = (r.random((nq, 4, 256)) * 100).astype(np.float32)
+    if kind == "equal":
+        codes[:] = codes[5]
+    if kind == "few_values":
+        luts = np.round(luts / 20)
+    if kind == "far":
+        luts[:, 2, 7] = 3e20
+    if kind == "infinite":
+        luts[:, 1, 9] = np.inf
+        luts[:, 3, 2] = -np.inf
+        luts[:, 0, 5] = np.nan
+    if kind == "mostly_infinite":
+        luts[:, 0, 1:] = np.inf
+        codes[:, 0] = np.maximum(codes[:, 0], 1)
+        codes[r.permutation(n)[:50], 0] = 0
+    if kind == "negative":
+        luts -= 60.0
+    if kind == "overflow":
+        luts[:, 0, :128] = 3e38
+        luts[:, 1, :128] = -3e38
+        luts[:, 2, :64] = 3e38
+        luts[:, 3, :64] = -3e38
+    got = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(luts), topk)]
+    opts.set("scan_force_general", 1)
+    ref = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(luts), topk)]
+    assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+    if kind == "random":
+        od, oi = orc.adc_scan_topk_f32(codes, orc.CODES_U8, luts, topk)
+        for q in range(0, nq, 7):
+            check_float_topk(got[0][q], got[1][q], od[q], oi[q], codes, orc.CODES_U8, luts[q], n)
