@@ -40,7 +40,7 @@ namespace pq {
 //   4 M vectors, d = 128, 8 x 256    17.0 -> 1.7 ms (0.09 ms of it measuring what the ranking leaves open)
 //   4 M vectors, d = 128, 16 x 16     7.5 -> 1.3 ms
 //   500 k, d = 960, 16 x 256         10.9 -> 1.8 ms (0.36 ms)      500 k, d = 960, 32 x 16   3.3 -> 0.97 ms
-//   1000 vectors, d = 128, 8 x 256    159 -> 51 us
+//   1000 vectors, d = 128, 8 x 256    159 -> 28 us
 // Tried: images of one sub-space at a time in LDS for all sizes (2.0 against 1.7 ms: barriers, and no wave can fetch
 // ahead of the others); a whole wave measuring all 256 centroids of an open vector (3.9 ms in all: strided reads).
 typedef _Float16 enc_half8 __attribute__((ext_vector_type(8)));
@@ -55,21 +55,34 @@ struct EncodeInfo { float scale, bound, cmax2, pad; };   // per sub-space: S_j; 
 
 // One block per sub-space.  Image of a sub-space: the centroids as matrix operands [tile of 16][chunk][lane][8 halves],
 // then the start values -||c||^2 / 2 [tiles * 16], the mean centroid times S_j [chunks * 16] and an EncodeInfo.
+// A chain of passes over one codebook on one compute unit, bound by their latency: the codebook is read once into LDS (rows of
+// an odd length: no bank is met twice by lanes of neighbouring rows).  8 x 256 of 16 dimensions 15 -> 11.5 us, 16 x 256 of 60 25 -> 18.
+constexpr int enc_prep_row(int ds) { return ds | 1; }
 __host__ __device__ constexpr int encode_image_len(int tiles, int nch) { return tiles * nch * 64 + tiles * 4 + nch * 4 + 1; }   // in uint4
 
 __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restrict__ codebooks, int k, int ds, int nch, int tiles,
                                                            uint4 *__restrict__ images) {
     __shared__ float red[16], mean[ENC_MAX_DS];
-    __shared__ unsigned int cmax_bits, row_hash[256];
+    __shared__ unsigned int cmax_bits, row_hash[256], part_hash[4][256];
+    __shared__ double part_norm[4][256];
     __shared__ bool copy_of_earlier[256];
     const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const float *cb = codebooks + (size_t)j * k * ds;
+    extern __shared__ float cb[];   // component t of centroid c at c * row + t
+    const int row = enc_prep_row(ds);
+    // 16, 32 or 64 lanes per centroid, so that no index is divided
+    const int seg_bits = ds <= 16 ? 4 : ds <= 32 ? 5 : 6, my_t = tid & ((1 << seg_bits) - 1), my_c = tid >> seg_bits, c_step = 1024 >> seg_bits;
+    if (my_t < ds) {
+        const float *const src = codebooks + (size_t)j * k * ds;
+#pragma unroll 4
+        for (int c = my_c; c < k; c += c_step) cb[c * row + my_t] = src[(size_t)c * ds + my_t];
+    }
+    __syncthreads();
     uint4 *const image = images + (size_t)j * encode_image_len(tiles, nch);
     float *const start = reinterpret_cast<float *>(image + tiles * nch * 64), *const offset = start + tiles * 16;
     for (int t = tid >> 6; t < ENC_MAX_DS; t += 16) {   // (any value near the centroids does)
         float sum = 0.f;
         if (t < ds)
-            for (int c = lane; c < k; c += 64) sum += cb[(size_t)c * ds + t] / (float)k;
+            for (int c = lane; c < k; c += 64) sum += cb[c * row + t] / (float)k;
         for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
         if (lane == 0) mean[t] = sum;
     }
@@ -77,11 +90,12 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
     __syncthreads();
     float amax = 0.f;
     bool finite = true;
-    for (int i = tid; i < k * ds; i += 1024) {
-        const float v = fabsf(cb[i] - mean[i % ds]);
-        finite = finite && v < __builtin_inff();
-        amax = v > amax ? v : amax;
-    }
+    if (my_t < ds)
+        for (int c = my_c; c < k; c += c_step) {
+            const float v = fabsf(cb[c * row + my_t] - mean[my_t]);
+            finite = finite && v < __builtin_inff();
+            amax = v > amax ? v : amax;
+        }
     if (!finite) amax = __builtin_inff();
     for (int o = 32; o > 0; o >>= 1) {
         const float other = __shfl_xor(amax, o);
@@ -97,17 +111,25 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
     const bool ranked = amax < __builtin_inff() && e <= 126;
     e = e > 126 ? 126 : e;
     const float scale = ldexpf(1.f, e);
-    for (int c = tid; c < tiles * 16; c += 1024) {   // (one round: 256 at most)
+    {   // norms and hashes, a quarter of the dimensions per thread (256 centroids at most)
+        const int c = tid & 255, quarter = tid >> 8, len = (ds + 3) / 4;
         double norm = 0.0;
         unsigned int hash = 2166136261u;
         if (c < k)
-            for (int t = 0; t < ds; ++t) {
-                const float x = cb[(size_t)c * ds + t];
+            for (int t = quarter * len; t < (quarter + 1) * len && t < ds; ++t) {
+                const float x = cb[c * row + t];
                 const double v = (double)((x - mean[t]) * scale);
                 norm += v * v;
                 hash = (hash ^ __float_as_uint(x)) * 16777619u;
             }
-        row_hash[c] = hash;
+        part_norm[quarter][c] = norm;
+        part_hash[quarter][c] = hash;
+    }
+    __syncthreads();
+    if (tid < tiles * 16) {
+        const int c = tid;
+        const double norm = (part_norm[0][c] + part_norm[1][c]) + (part_norm[2][c] + part_norm[3][c]);
+        row_hash[c] = ((part_hash[0][c] * 16777619u ^ part_hash[1][c]) * 16777619u ^ part_hash[2][c]) * 16777619u ^ part_hash[3][c];
         copy_of_earlier[c] = false;
         start[c] = c < k ? (float)(-0.5 * norm) : ENC_NO_CENTROID;
         if (c < k) {
@@ -130,7 +152,7 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
         if (equal >= 0) {
             bool same = true;
 #pragma unroll 4
-            for (int t = 0; t < ds; ++t) same = same && __float_as_uint(cb[(size_t)equal * ds + t]) == __float_as_uint(cb[(size_t)c * ds + t]);
+            for (int t = 0; t < ds; ++t) same = same && __float_as_uint(cb[equal * row + t]) == __float_as_uint(cb[c * row + t]);
             if (same) {
                 copy_of_earlier[c] = true;
                 start[c] = ENC_NO_CENTROID;
@@ -156,7 +178,7 @@ __global__ __launch_bounds__(1024) void encode_prep_kernel(const float *__restri
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int t = ch * 16 + 8 * (g & 1) + q;
-            const float v = c < k && t < ds && !copy_of_earlier[c] ? (cb[(size_t)c * ds + t] - mean[t]) * scale : 0.f;
+            const float v = c < k && t < ds && !copy_of_earlier[c] ? (cb[c * row + t] - mean[t]) * scale : 0.f;
             const _Float16 hi = (_Float16)v;
             h[q] = g >> 1 ? (_Float16)(v - (float)hi) : hi;
         }
@@ -585,19 +607,25 @@ int launch_encode(pq_ctx *ctx, const float *vectors, const float *codebooks, int
         const uintptr_t bases = (uintptr_t)vectors | (uintptr_t)codebooks;
         const int vec = (ds & 3) == 0 && (bases & 15) == 0 ? 4 : ((ds & 1) == 0 && (bases & 7) == 0 ? 2 : 1);
         // All images in LDS where they fit and every wave of the chip has a tile of vectors (a block copies all of
-        // them).  Else blocks of 8 waves share one image at a time; few vectors go in blocks of 2 waves, and their code
-        // bytes are dealt to several blocks until there are two for every compute unit.
+        // them).  Else blocks of 8 waves share one image at a time; few vectors, and those of small images (nothing to share), go
+        // in blocks of 2 waves.  The code bytes are dealt to several blocks until there are two for every compute unit (d = 960,
+        // 16 x 256, blocks of 2 waves while there were few vectors, whole words dealt -> now: call of 2000 vectors 119 -> 52 us, 60 000 403 -> 250,
+        // 250 000 1525 -> 908; d = 128, 8 x 256: 1000 vectors 53 -> 28, 100 000 96 -> 69; 100 000 of d = 960, 32 x 16 in blocks of 8 waves 335 -> 351).
         const int resident_waves = nch == 1 ? 16 : 8;
         const bool resident = m * image_bytes <= ENC_RESIDENT_BYTES && n >= (int64_t)ctx->num_cu * resident_waves * ENC_VECS;
         const int64_t big = (n + 8 * ENC_VECS - 1) / (8 * ENC_VECS);
-        const int waves = resident ? resident_waves : (big >= 2 * ctx->num_cu ? 8 : 2);
+        const int waves = resident ? resident_waves : (big >= 2 * ctx->num_cu || (big * A.code_bytes >= ctx->num_cu && image_bytes >= 8192) ? 8 : 2);
         const int64_t bx = resident ? ctx->num_cu : (n + waves * ENC_VECS - 1) / (waves * ENC_VECS);
-        const int unit = A.words ? 4 : 1, units = A.code_bytes / unit;
         int parts = resident ? 1 : (int)((2 * (int64_t)ctx->num_cu + bx - 1) / bx);
+        if (parts > A.code_bytes / 4) A.words = 0;   // (more parts than words: byte by byte)
+        const int unit = A.words ? 4 : 1, units = A.code_bytes / unit;
         parts = parts < 1 ? 1 : (parts > units ? units : parts);
         A.bytes_per_y = (units + parts - 1) / parts * unit;
         parts = (A.code_bytes + A.bytes_per_y - 1) / A.bytes_per_y;
-        encode_prep_kernel<<<m, 1024, 0, ctx->stream>>>(codebooks, k, ds, nch, tiles, (uint4 *)ctx->encode_images.p);
+        const size_t prep_lds = (size_t)k * enc_prep_row(ds) * 4;
+        if (prep_lds > 32 * 1024)
+            PQ_HIP(ctx, hipFuncSetAttribute((const void *)encode_prep_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prep_lds));
+        encode_prep_kernel<<<m, 1024, prep_lds, ctx->stream>>>(codebooks, k, ds, nch, tiles, (uint4 *)ctx->encode_images.p);
         PQ_HIP(ctx, hipGetLastError());
         const dim3 grid((unsigned)bx, (unsigned)parts);
         const size_t lds = image_bytes * (resident ? m : 1);

@@ -538,6 +538,18 @@ def test_encode_edges_of_tiles(ctx, ds, m, k, n):
             assert np.array_equal(host(ctx.pq_encode(xd, dev(cb), fmt)), ref), (scale, shift)
 
 
+@pytest.mark.parametrize("ds,m,k,n", [(16, 8, 256, 1025), (16, 8, 256, 16_321), (46, 12, 256, 11_003), (50, 8, 256, 129), (64, 4, 256, 33_001), (8, 16, 16, 9_001),
+                                      (15, 8, 16, 1)])
+def test_encode_code_bytes_dealt_to_blocks(ctx, ds, m, k, n):
+    """Few vectors: the bytes of a code are written by several blocks (also where it has whole words), of 2 waves and of 8."""
+    r = np.random.default_rng(ds * 1000 + n)
+    x = (r.standard_normal((n, m * ds)) * 50).astype(np.float32)
+    cb = (r.standard_normal((m, k, ds)) * 50).astype(np.float32)
+    fmt = orc.CODES_U4_PACKED if k == 16 else orc.CODES_U8
+    ref = orc.pq_encode(x, cb)
+    assert np.array_equal(host(ctx.pq_encode(dev(x), dev(cb), fmt)), orc.pack_u4(ref) if fmt == orc.CODES_U4_PACKED else ref)
+
+
 @pytest.mark.parametrize("ds,m,k", [(8, 4, 256), (16, 2, 40), (5, 4, 16), (33, 2, 256)])
 def test_encode_codebooks_of_extreme_magnitude(ctx, ds, m, k):
     """Codebooks at both ends of fp32 (subnormal numbers, spreads too small to be scaled into fp16's range, components near
