@@ -158,11 +158,13 @@ int pq_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf
  *   out_val [nq][topk] f32 (float tables) or u32 (u8 tables, plain integer sums, no
  *   saturation); out_ids [nq][topk] i64.
  * Covered: (U8 codes, F32 tables, k = 256, m = 8 or 16), (U4 codes, U8 tables, k = 16,
- * m = 16; m = 32 from 1024 codes on, or from topk + 1 for topk above 128), and any (U8 | U4
- * codes, F32 | U8 tables) with m*k <= 8192 through a slower general kernel.  1 <= topk <= 1024, 0 <= n < 2^32; `codes` 16-byte aligned.
+ * m = 16; m = 32 from 1024 codes on, or from topk + 1 for topk above 128), (U8 codes, F32 tables,
+ * k = 256, m = 4) from 4096 codes on, and any (U8 | U4 codes, F32 | U8 tables) with m*k <= 8192
+ * through a slower general kernel.  1 <= topk <= 1024, 0 <= n < 2^32; `codes` 16-byte aligned.
  * Float sums add the m entries in fp32, in table order or in a rotation of it (the result
  * differs from the exact sum by at most (m-1) * 2^-24 relative either way).  For k = 256,
- * m = 8 or 16 and n >= 65536 the kernel first dismisses codes by integer lower bounds of their
+ * m = 8 or 16 and n >= 65536 (n >= 8192 for up to four queries, for topk >= 512 with 24 codes per
+ * result, and for m = 16 with 512 queries and more) the kernel first dismisses codes by integer lower bounds of their
  * distances (the pruning idea of Section 4.2: small quantised tables, exact distances only
  * for the codes they cannot rule out) and forms float sums only for the rest; the result is
  * that of the plain definition.  The bounds are 16-bit sums for 8 queries per pass over the
@@ -187,8 +189,8 @@ int pq_adc_scan_topk(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt c
  * Limit: the scratch the scan needs must fit.  That holds for the tuned shapes with topk <= 128 and
  * fewer than 249 queries, whatever n is (about 120 MiB on 256 compute units), and for calls of the
  * general kernel with few (chunk, query) blocks; a request that does not fit returns PQ_ENOMEM with a
- * message naming both sizes, and nothing has been enqueued.  32 x 4 codes whose lists do not fit go to the
- * general kernel before that.
+ * message naming both sizes, and nothing has been enqueued.  32 x 4 and 4 x 8 codes whose lists do not fit go
+ * to the general kernel before that.
  * Every call on a GPU shares that GPU's array (whatever the context or stream): calls that overlap
  * in time on one GPU race.  The array keeps the last call's contents; everything that must start
  * from a known value (work counter, bounds, histograms, candidate counters) is cleared by the call's

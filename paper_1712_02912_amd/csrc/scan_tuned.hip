@@ -151,7 +151,8 @@ constexpr int exact_bins(int tables) { return tables == 16 ? HIST_BINS - 1 : HIS
 constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bound of a float scan of many query groups
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
-constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan
+constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan (but see PRUNE_FEW_N)
+constexpr int64_t PRUNE_FEW_N = 1 << 13;   // from here on calls with few queries, long results or, with 16 tables, many queries are pruned too
 constexpr int64_t U4_SEED_MIN_N = 512;     // the integer scan takes a first bound from here on
 constexpr int PRUNE_INIT = 4096;           // codes looked at for the first bound of every query
 constexpr int PRUNE_MARGIN = 8;      // slack of the integer threshold, in table units
@@ -2232,7 +2233,15 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     const bool u4_m32 = kind == KIND_U4_M32, is_u4 = kind == KIND_U4_M16 || u4_m32;
     // The 8 x 256 float scan prunes with 16-bit lower bounds when the database is large enough to
     // pay for the preparation (a bound per query from the first PRUNE_INIT codes, then the tables).
-    const bool prune = (kind == KIND_F32_M8 || kind == KIND_F32_M16) && n >= PRUNE_MIN_N && opt_int(ctx, PQ_OPT_SCAN_PRUNE, 1) != 0;
+    // Between PRUNE_FEW_N and PRUNE_MIN_N codes the bound's slices take 6 us where the plain loop's bound takes 16 to 24, and the
+    // tables' preparation 10: it pays for up to four queries (plain loop -> this; 30 000 codes, 8 tables, one query, top-1 37 -> 31 us,
+    // top-100 50 -> 43; 60 000, four queries 55 -> 50; 16 tables 58 -> 46, 64 -> 54; eight queries 54 -> 56 and 62 -> 58), for long
+    // results (30 000 codes, top-1000, 100 queries 137 -> 85, 16 tables 141 -> 101; 9000 codes 80 -> 103, 20 000 codes, 300 queries,
+    // top-200 115 -> 126) and for many queries on 16 tables (30 000 codes, 700 queries, top-100 158 -> 126; 400 queries, 20 000 codes 93 -> 94;
+    // 8 tables 128 -> 129).  The fixed scratch keeps to the plain loop, whose lists are half as long.
+    const bool prune_small = n >= PRUNE_FEW_N && !ctx->ws_fixed &&
+                             (nq <= 4 || (topk >= 512 && n >= 24 * (int64_t)topk) || (kind == KIND_F32_M16 && nq >= 512));
+    const bool prune = (kind == KIND_F32_M8 || kind == KIND_F32_M16) && (n >= PRUNE_MIN_N || prune_small) && opt_int(ctx, PQ_OPT_SCAN_PRUNE, 1) != 0;
     const int tables = kind == KIND_F32_M16 ? 16 : 8;
     // eight tables and too many queries for the streaming shape (32 groups of 8 and more, i.e. 249 queries): 8-bit
     // lower bounds, 16 queries per pass (PQ_SCAN_Q8=0: 16-bit lower bounds, 8 queries per pass).  Measured on 25 M

@@ -1105,3 +1105,30 @@ def test_scan_f32_four_byte_codes(ctx, opts, n, nq, topk, kind):
         od, oi = orc.adc_scan_topk_f32(codes, orc.CODES_U8, luts, topk)
         for q in range(0, nq, 7):
             check_float_topk(got[0][q], got[1][q], od[q], oi[q], codes, orc.CODES_U8, luts[q], n)
+
+
+@pytest.mark.parametrize("n,nq,topk,m", [(8191, 1, 1, 8), (8192, 1, 1, 16), (8193, 4, 100, 8), (8200, 3, 1024, 16), (12_288, 5, 512, 8), (24_601, 30, 1000, 16),
+                                         (24_576, 600, 1024, 8), (9001, 513, 3, 16), (65_535, 2, 128, 8)])
+@pytest.mark.parametrize("kind", ["random", "few_values", "negative", "infinite"])
+def test_scan_f32_pruned_small_databases(ctx, opts, n, nq, topk, m, kind):
+    """Small databases that are pruned, and their neighbours: against the oracle and the plain loop."""
+    r = np.random.default_rng(n + nq)
+    codes = r.integers(0, 256, (n, m), dtype=np.uint8)
+    luts = (r.random((nq, m, 256)) * 100).astype(np.float32)
+    if kind == "few_values":
+        luts = np.round(luts / 30)
+    if kind == "negative":
+        luts -= 60.0
+    if kind == "infinite":
+        luts[:, 1, 9:200] = np.inf
+    got = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(luts), topk)]
+    opts.set("scan_prune", 0)
+    plain = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(luts), topk)]
+    # (entries of at most 100, m of them: two orders of the additions differ by less than 2 m roundings of 100 m)
+    np.testing.assert_allclose(got[0], plain[0], rtol=0, atol=2 * m * 100 * m * 2.0 ** -24)
+    if kind == "few_values":   # (whole numbers: no rounding, ids are decided)
+        assert np.array_equal(got[0], plain[0]) and np.array_equal(got[1], plain[1])
+    if kind == "random":
+        od, oi = orc.adc_scan_topk_f32(codes, orc.CODES_U8, luts, topk)
+        for q in range(0, nq, 97):
+            check_float_topk(got[0][q], got[1][q], od[q], oi[q], codes, orc.CODES_U8, luts[q], n)
