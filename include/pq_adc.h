@@ -162,7 +162,9 @@ int pq_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf
  * k = 256, m = 4) from 4096 codes on, and any (U8 | U4 codes, F32 | U8 tables) with m*k <= 8192
  * through a slower general kernel.  1 <= topk <= 1024, 0 <= n < 2^32; `codes` 16-byte aligned.
  * Float sums add the m entries in fp32, in table order or in a rotation of it (the result
- * differs from the exact sum by at most (m-1) * 2^-24 relative either way).  For k = 256,
+ * differs from the exact sum by at most (m-1) * 2^-24 relative either way): for k = 256, m = 8 or 16
+ * and n < 65536 from a table on that the row number gives, else in table order, so a query's
+ * result does not depend on the other queries of the call, on topk or on the entry point.  For k = 256,
  * m = 8 or 16 and n >= 65536 (n >= 8192 for up to four queries, for topk >= 512 with 24 codes per
  * result, and for m = 16 with 512 queries and more) the kernel first dismisses codes by integer lower bounds of their
  * distances (the pruning idea of Section 4.2: small quantised tables, exact distances only

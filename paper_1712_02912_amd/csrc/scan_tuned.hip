@@ -466,7 +466,10 @@ __device__ __forceinline__ void sums16_rotated(const __attribute__((address_spac
 // integer test against the current thresholds, and for every (code, query) that still passes adds
 // the eight float entries in table order -- the order of the plain definition, Eq. (adc1) -- tests the
 // result against the float bound and appends it to the wave's list of the query.
-template <class SM, int NT, int E, int QB = 8>
+// Databases below PRUNE_MIN_N are scanned by this loop or by the plain one, whichever is faster for the call: there the
+// entries are added in the plain loop's order, which starts at a table that the row number gives (chunks begin at
+// multiples of a sub-tile), so that a query's result does not depend on the loop that served it.
+template <class SM, int NT, int E, int QB, bool ROTATED>
 __device__ __noinline__ int scan_flush_pruned(LDS_PTR(SM) sm, uint64_t *wave_buf, int n) {
     constexpr int CPL = 16 / NT, CAP = 64 * E;
     constexpr bool Q8 = QB == 16;   // 8-bit entries, 16 queries per slot
@@ -585,23 +588,33 @@ __device__ __noinline__ int scan_flush_pruned(LDS_PTR(SM) sm, uint64_t *wave_buf
             const int q = b & (QB - 1), h = b / QB;
             const uint32_t w0 = h == 0 ? c.x : c.z, w1 = h == 0 ? c.y : c.w;
             const float *fl = (const float *)sm->slot_lut[q];   // the query's float tables [table][entry], in device memory
-            float d = fl[w0 & 255u];
-            d += fl[256 + ((w0 >> 8) & 255u)];
-            d += fl[512 + ((w0 >> 16) & 255u)];
-            d += fl[768 + (w0 >> 24)];
-            d += fl[1024 + (w1 & 255u)];
-            d += fl[1280 + ((w1 >> 8) & 255u)];
-            d += fl[1536 + ((w1 >> 16) & 255u)];
-            d += fl[1792 + (w1 >> 24)];
-            if constexpr (NT == 16) {   // one 16-byte code per lane: tables 8..15 index with c.z, c.w
-                d += fl[2048 + (c.z & 255u)];
-                d += fl[2304 + ((c.z >> 8) & 255u)];
-                d += fl[2560 + ((c.z >> 16) & 255u)];
-                d += fl[2816 + (c.z >> 24)];
-                d += fl[3072 + (c.w & 255u)];
-                d += fl[3328 + ((c.w >> 8) & 255u)];
-                d += fl[3584 + ((c.w >> 16) & 255u)];
-                d += fl[3840 + (c.w >> 24)];
+            float d;
+            if constexpr (ROTATED) {   // from table lw.rot on
+                uint32_t r[4] = {w0, w1, c.z, c.w};
+                if constexpr (NT == 8) rot8(r[0], r[1], (lw.rot & 4u) != 0u, lw.rot & 3u);
+                else rot16(r, lw.rot);
+                d = fl[lw.rot * 256u + (r[0] & 255u)];
+#pragma unroll
+                for (int s = 1; s < NT; ++s) d += fl[((lw.rot + s) & (NT - 1)) * 256u + ((r[s >> 2] >> (8 * (s & 3))) & 255u)];
+            } else {
+                d = fl[w0 & 255u];
+                d += fl[256 + ((w0 >> 8) & 255u)];
+                d += fl[512 + ((w0 >> 16) & 255u)];
+                d += fl[768 + (w0 >> 24)];
+                d += fl[1024 + (w1 & 255u)];
+                d += fl[1280 + ((w1 >> 8) & 255u)];
+                d += fl[1536 + ((w1 >> 16) & 255u)];
+                d += fl[1792 + (w1 >> 24)];
+                if constexpr (NT == 16) {   // one 16-byte code per lane: tables 8..15 index with c.z, c.w
+                    d += fl[2048 + (c.z & 255u)];
+                    d += fl[2304 + ((c.z >> 8) & 255u)];
+                    d += fl[2560 + ((c.z >> 16) & 255u)];
+                    d += fl[2816 + (c.z >> 24)];
+                    d += fl[3072 + (c.w & 255u)];
+                    d += fl[3328 + ((c.w >> 8) & 255u)];
+                    d += fl[3584 + ((c.w >> 16) & 255u)];
+                    d += fl[3840 + (c.w >> 24)];
+                }
             }
             const uint32_t ord = f32_to_ord(d);
             uint32_t eff;
@@ -1219,6 +1232,9 @@ void scan_tuned_kernel(TunedArgs a) {
         }
         __syncthreads();
 
+        auto flush_pruned = [&](int count) -> int {   // (a function for each order)
+            return a.rotated ? scan_flush_pruned<SM, NT, E, QB, true>(smp, wave_buf, count) : scan_flush_pruned<SM, NT, E, QB, false>(smp, wave_buf, count);
+        };
         PQ_TICK(TICK_SETUP);
         const int nvalid_q = sm.nvalid;
         int ring_cnt = 0;                  // positions parked in this wave's ring (uniform)
@@ -1361,7 +1377,7 @@ void scan_tuned_kernel(TunedArgs a) {
                 const int take = ring_cnt > RING_FLUSH ? (ring_cnt & ~63) : ring_cnt;
                 parked_total += (unsigned long long)take;
                 int appended;
-                if constexpr (PRUNED) appended = scan_flush_pruned<SM, NT, E, QB>(smp, wave_buf, take);
+                if constexpr (PRUNED) appended = flush_pruned(take);
                 else if constexpr (U4Q) appended = scan_flush_u4q<SM, E>(smp, wave_buf, take);
                 else appended = scan_flush<SM, KIND, E>(smp, wave_buf, take);
                 // 8-bit bounds park many codes that turn out to be none: there only the keys count
@@ -1435,7 +1451,7 @@ void scan_tuned_kernel(TunedArgs a) {
         PQ_TICK(TICK_LOOP);
         if (ring_cnt > 0) {
             parked_total += (unsigned long long)ring_cnt;
-            if constexpr (PRUNED) scan_flush_pruned<SM, NT, E, QB>(smp, wave_buf, ring_cnt);
+            if constexpr (PRUNED) flush_pruned(ring_cnt);
             else if constexpr (U4Q) scan_flush_u4q<SM, E>(smp, wave_buf, ring_cnt);
             else scan_flush<SM, KIND, E>(smp, wave_buf, ring_cnt);
         }
@@ -1747,8 +1763,8 @@ __global__ __launch_bounds__(64) void u4_seed_pick_kernel(const uint32_t *__rest
 // integer test dismisses): one block per four queries looks at the first `cnt` codes, counts the float distances at or
 // below the bound known so far (tau0 as handed in, or with self_ref the greatest distance of the first k codes)
 // in the bins the scan's histogram uses, and lowers tau0 to the smallest bin edge with at least k
-// distances at or below it, enlarged by 4e-6 of itself: the distances are summed from the lane's own first table on,
-// not in table order as in the scans (the tables' layout in LDS, see below).
+// distances at or below it: distances summed from the lane's own first table on, not in the order of the scans (the
+// tables' layout in LDS, see below), which prune_tables_kernel allows for.
 template <int M>
 __global__ __launch_bounds__(1024) void f32_seed_refine_kernel(const uint8_t *__restrict__ codes, int cnt,
                                                                const float *__restrict__ luts, int k, bool self_ref, int nq,
@@ -1858,11 +1874,8 @@ __global__ __launch_bounds__(1024) void f32_seed_refine_kernel(const uint8_t *__
     kth_bins();
     if (sub == 0 && q0 + myq < nq) {
         const int q = q0 + myq;
-        // (enlarged by a few units of fp32 rounding: the scans add a code's entries in table order, this kernel from
-        // the lane's own first table on)
-        auto enlarged = [](float x) { return x + fabsf(x) * 4e-6f; };
-        if (bin_s[myq] < HIST_BINS) tau0[q] = enlarged(ord_to_f32(edge_of(ref_s[myq], bin_s[myq])));
-        else if (self_ref) tau0[q] = cnt >= k ? enlarged(ord_to_f32(ref_s[myq])) : __builtin_inff();
+        if (bin_s[myq] < HIST_BINS) tau0[q] = ord_to_f32(edge_of(ref_s[myq], bin_s[myq]));
+        else if (self_ref) tau0[q] = cnt >= k ? ord_to_f32(ref_s[myq]) : __builtin_inff();
     }
 }
 
@@ -1957,16 +1970,19 @@ __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__r
 // L[j][b] = min(32767 / M, floor((D[j][b] - min_j) * scale)) for the M = 8 or 16 tables.  Output in
 // the slot order of the scan kernel: qtabs[group][b][j] holds entry b of table j for the 8 queries
 // of the group.
-// With seed_hist given, the kernel first reads every query's first bound off the bins of the sampling pass
-// (f32_seed_hist2_kernel; bins below seed_ref) and stores it as tau0, as the query's shared bound and as the reference
-// of its scan histogram: one launch instead of three.
+// tau0: every query's first bound; with seed_hist given, it is read off the bins of the sampling pass instead
+// (f32_seed_hist2_kernel; bins below seed_ref): one launch instead of three.  other_order: the bound's distances were added
+// up in another order than the scan's are.  Two orders of the M additions differ by less than 2 M roundings of the sum of
+// the entries' magnitudes, which is at most the distance and twice what the negative ones among the minima add up to, so
+// the bound is raised by 4e-6 of that (2^-24 * 32 = 1.9e-6).  The result is stored as the query's shared bound and as the
+// reference of its scan histogram.
 constexpr int PRUNE_TABLES_THREADS = 1024, PRUNE_TABLES_Y = 2;
 template <int M, int G = 8>   // G: queries per group (8 with 16-bit entries, 16 with 8-bit entries)
-__global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(const float *__restrict__ luts, float *tau0,
+__global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(const float *__restrict__ luts, const float *__restrict__ tau0, bool other_order,
+                                                           unsigned long long *tau_key_out, uint32_t *tau_ref_out,
                                                            int nq, uint4 *qtabs, float *off_out, float *scale_out, float range_q8,
                                                            uint4 *qtabs16, float *scale16_out, const uint32_t *seed_hist = nullptr,
-                                                           const float *seed_ref = nullptr, int seed_k = 0, int seed_shift = 0,
-                                                           unsigned long long *tau_key_out = nullptr, uint32_t *tau_ref_out = nullptr) {
+                                                           const float *seed_ref = nullptr, int seed_k = 0, int seed_shift = 0) {
     constexpr bool Q8 = G == 16;
     constexpr float ENTRY_MAX = Q8 ? PRUNE_ENTRY_MAX_Q8 : (float)(32767 / M);   // M entries must add up to less than 2^15 (2^7)
     const float RANGE = Q8 ? range_q8 : PRUNE_RANGE;
@@ -1974,6 +1990,7 @@ __global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(cons
     __shared__ float smin[G][M];
     __shared__ float sscale[G];
     __shared__ float sscale16[G];   // 8-bit entries: the scale of the 16-bit tables written beside them
+    __shared__ float sbound[G];     // first bounds read off the bins
     const int group = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // (with bins the first half of the waves read the queries' bounds off them while the others find the minima)
     constexpr int WAVES = PRUNE_TABLES_THREADS / 64;
@@ -1985,12 +2002,7 @@ __global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(cons
             const int b = hist_threshold(seed_hist + (size_t)gq * HIST_BINS, seed_k);
             if (lane == 0) {
                 const uint32_t ref = f32_to_ord(seed_ref[gq]);
-                const uint32_t edge = b < HIST_BINS ? ref - ((uint32_t)(HIST_BINS - 1 - b) << seed_shift) : f32_to_ord(__builtin_inff());   // (fewer than k counted: no bound)
-                tau0[gq] = ord_to_f32(edge);   // (every block of the group stores the same value)
-                if (blockIdx.y == 0) {
-                    tau_key_out[gq] = ((unsigned long long)edge << 32) | 0xffffffffull;
-                    tau_ref_out[gq] = b < HIST_BINS ? edge : TAU_REF_UNSET;
-                }
+                sbound[q] = b < HIST_BINS ? ord_to_f32(ref - ((uint32_t)(HIST_BINS - 1 - b) << seed_shift)) : __builtin_inff();   // (fewer than k counted: no bound)
             }
         }
     }
@@ -2019,13 +2031,20 @@ __global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(cons
         const int gq = group * G + tid;
         float scale = 0.f;
         if (gq < nq) {
-            float off = 0.f;
-            for (int j = 0; j < M; ++j) off += smin[tid][j];
+            float off = 0.f, negative = 0.f;
+            for (int j = 0; j < M; ++j) { off += smin[tid][j]; negative += fmaxf(-smin[tid][j], 0.f); }
+            float bound = seed_hist != nullptr ? sbound[tid] : tau0[gq];
+            if (other_order) bound += (fabsf(bound) + 2.f * negative) * 4e-6f;
+            if (blockIdx.y == 0) {
+                const bool bounded = bound < __builtin_inff();
+                tau_key_out[gq] = ((unsigned long long)(bounded ? f32_to_ord(bound) : f32_to_ord(__builtin_inff())) << 32) | 0xffffffffull;
+                tau_ref_out[gq] = bounded ? f32_to_ord(bound) : TAU_REF_UNSET;
+            }
             // RANGE units between the sum of the minima and the first bound, but never so many per unit of distance that
             // the threshold conversion loses a fraction of a table unit in fp32 (bound * scale stays below 10^6).  A bound
             // that leaves no range at all (k codes and more attain the minima: exact duplicates) takes that finest scale:
             // any entry above its table's minimum then counts several units and only the duplicates pass.
-            const float bound = tau0[gq], range = bound - off;
+            const float range = bound - off;
             const float finest = bound > 0.f && bound < 3.0e38f ? 0.99e6f / bound : 0.f;
             auto scale_for = [&](float units) {
                 float sc = range > 0.f ? units / range : finest;
@@ -2208,6 +2227,7 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
     a.nprobe = nprobe;
     a.qtabs = nullptr; a.prune_off = pair_off; a.prune_scale = pair_scale; a.pair_min = pair_min;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
+    a.rotated = 0;
     tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, nq,
                                                      0xff800000u, a.hist, L.nhist, tau0, nq, 1.f);
     PQ_HIP(ctx, hipGetLastError());
@@ -2238,7 +2258,8 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // top-100 50 -> 43; 60 000, four queries 55 -> 50; 16 tables 58 -> 46, 64 -> 54; eight queries 54 -> 56 and 62 -> 58), for long
     // results (30 000 codes, top-1000, 100 queries 137 -> 85, 16 tables 141 -> 101; 9000 codes 80 -> 103, 20 000 codes, 300 queries,
     // top-200 115 -> 126) and for many queries on 16 tables (30 000 codes, 700 queries, top-100 158 -> 126; 400 queries, 20 000 codes 93 -> 94;
-    // 8 tables 128 -> 129).  The fixed scratch keeps to the plain loop, whose lists are half as long.
+    // 8 tables 128 -> 129).  The fixed scratch keeps to the plain loop, whose lists are half as long.  Both loops give the same
+    // bits here (a.rotated).
     const bool prune_small = n >= PRUNE_FEW_N && !ctx->ws_fixed &&
                              (nq <= 4 || (topk >= 512 && n >= 24 * (int64_t)topk) || (kind == KIND_F32_M16 && nq >= 512));
     const bool prune = (kind == KIND_F32_M8 || kind == KIND_F32_M16) && (n >= PRUNE_MIN_N || prune_small) && opt_int(ctx, PQ_OPT_SCAN_PRUNE, 1) != 0;
@@ -2409,6 +2430,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
 
     a.qtabs = nullptr; a.prune_off = nullptr; a.prune_scale = nullptr; a.pair_min = nullptr;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
+    a.rotated = prune && n < PRUNE_MIN_N;
     float *tau0 = nullptr;
     if (prune) {
         tau0 = (float *)(ws + off_tau0);
@@ -2416,15 +2438,15 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         uint4 *qtabs = (uint4 *)(ws + off_qtabs);
         uint4 *qtabs16 = q8 ? (uint4 *)(ws + off_qtabs16) : nullptr;
         float *pscale16 = q8 ? (float *)(ws + off_pscale16) : nullptr;
+        uint32_t *const seed_hist = wide_seed ? (uint32_t *)(ws + off_seedhist) : nullptr;
+        tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
+                                                         0xff800000u, a.hist, L.nhist, nullptr, nq, 1.f, seed_hist, wide_seed ? (size_t)nq * HIST_BINS : 0);
         if (wide_seed) {
             // Few query groups over a large database: state cleared first, then one sampling pass whose bins every block
             // bounds for itself, then bound, shared state and tables of every group in one launch (three launches before the
             // scan; a pass over the first 4096 codes for the bins' reference, a launch to clear the bins, one to pick the
             // bounds and one to seed the state came on top before: 10^8 codes x 1 query 0.32 -> 0.27 ms per call)
-            uint32_t *seed_hist = (uint32_t *)(ws + off_seedhist);
             float *seed_ref = (float *)(ws + off_seedref);
-            tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
-                                                             0xff800000u, a.hist, L.nhist, nullptr, nq, 1.f, seed_hist, (size_t)nq * HIST_BINS);
             // (short slices while the launch stays under 2048 blocks, else the slices of the older pass)
             int slice = (seed_codes_f32 + SEED2_SLICE - 1) / SEED2_SLICE * nq <= 2048 ? SEED2_SLICE : SEED_SLICE;
             if (!seed_large) {   // two blocks per compute unit, slices of 1024 codes and more
@@ -2436,8 +2458,8 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             auto tables_of = tables == 8 ? prune_tables_kernel<8, 8> : prune_tables_kernel<16, 8>;
             auto seed_of = tables == 8 ? f32_seed_hist2_kernel<8> : f32_seed_hist2_kernel<16>;
             seed_of<<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_wide, slice, (const float *)luts, topk, seed_hist, seed_ref, shift);
-            tables_of<<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr,
-                                                                 seed_hist, seed_ref, topk, shift, a.tau_key, a.tau_ref);
+            tables_of<<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, nullptr, a.rotated != 0, a.tau_key, a.tau_ref, nq, qtabs, poff, pscale,
+                                                                 0.f, nullptr, nullptr, seed_hist, seed_ref, topk, shift);
             PQ_HIP(ctx, hipGetLastError());
         } else {
             // the first bound: smallest histogram edge with k distances among the first codes
@@ -2453,9 +2475,9 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             if (tables == 8) f32_seed_refine_kernel<8><<<(nq + SEED_QPB - 1) / SEED_QPB, 1024, 0, ctx->stream>>>(codes, first_codes, (const float *)luts, topk, true, nq, tau0);
             else f32_seed_refine_kernel<16><<<(nq + SEED_QPB - 1) / SEED_QPB, 1024, 0, ctx->stream>>>(codes, first_codes, (const float *)luts, topk, true, nq, tau0);
             PQ_HIP(ctx, hipGetLastError());
-            if (q8) prune_tables_kernel<8, 16><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, PRUNE_RANGE_Q8, qtabs16, pscale16);
-            else if (tables == 8) prune_tables_kernel<8><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
-            else prune_tables_kernel<16><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
+            if (q8) prune_tables_kernel<8, 16><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, true, a.tau_key, a.tau_ref, nq, qtabs, poff, pscale, PRUNE_RANGE_Q8, qtabs16, pscale16);
+            else if (tables == 8) prune_tables_kernel<8><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, true, a.tau_key, a.tau_ref, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
+            else prune_tables_kernel<16><<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, tau0, true, a.tau_key, a.tau_ref, nq, qtabs, poff, pscale, 0.f, nullptr, nullptr);
             PQ_HIP(ctx, hipGetLastError());
         }
         a.qtabs = qtabs; a.prune_off = poff; a.prune_scale = pscale; a.qtabs16 = qtabs16; a.prune_scale16 = pscale16;
@@ -2464,7 +2486,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         rc = launch_qmax_prescan(ctx, codes, n, PQ_CODES_U8, (const float *)luts, nq, cb, 256, PRUNE_INIT, topk, tau0);
         if (rc) return rc;
     }
-    if (!wide_seed) {   // (the wide first bound has cleared and seeded the state already)
+    if (!prune) {   // (the pruned scans' state has been cleared and seeded above)
         uint32_t *seed_hist_u4 = wide_seed_u4 ? (uint32_t *)(ws + off_seedhist) : nullptr;
         tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
                                                          is_u4 ? 0x7fffu : 0xff800000u, a.hist, L.nhist, tau0, nq,

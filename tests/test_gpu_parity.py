@@ -1132,3 +1132,36 @@ def test_scan_f32_pruned_small_databases(ctx, opts, n, nq, topk, m, kind):
         od, oi = orc.adc_scan_topk_f32(codes, orc.CODES_U8, luts, topk)
         for q in range(0, nq, 97):
             check_float_topk(got[0][q], got[1][q], od[q], oi[q], codes, orc.CODES_U8, luts[q], n)
+
+
+@pytest.mark.parametrize("kind", ["random", "far", "infinite", "negative"])
+@pytest.mark.parametrize("m", [8, 16])
+@pytest.mark.parametrize("n", [8192, 30_001, 65_535])
+def test_scan_f32_one_order_of_additions_whatever_the_batch(ctx, opts, m, n, kind):
+    """Databases below 65 536 codes are served by the pruned or by the plain loop: a query's distances and ids have the same bits
+    in either, alone, in a batch of any size, with any topk, and in the call that allocates nothing."""
+    r = np.random.default_rng(n + m)
+    codes = dev(r.integers(0, 256, (n, m), dtype=np.uint8))
+    tables = (r.random((600, m, 256)) * 100).astype(np.float32)
+    if kind == "far":
+        tables[:, 2, 7] = 3e20
+    if kind == "infinite":
+        tables[:, 1, 9:200] = np.inf
+    if kind == "negative":
+        tables -= 60.0
+    luts = dev(tables)
+
+    def scan(nq, topk, **kw):
+        out = ctx.pq_adc_scan_topk(codes, binding.CODES_U8, luts[:nq].contiguous(), topk, **kw)
+        return [host(t) for t in out]
+
+    opts.set("scan_prune", 0)
+    want_v, want_i = scan(600, 1024)
+    opts.set("scan_prune", 1)
+    for nq, topk in [(1, 1), (1, 100), (1, 511), (1, 1024), (4, 100), (5, 100), (5, 341), (5, 512), (40, 1000), (100, 512), (300, 512), (400, 800), (512, 100), (513, 100), (600, 1024)]:
+        v, i = scan(nq, topk)
+        assert np.array_equal(v, want_v[:nq, :topk]) and np.array_equal(i, want_i[:nq, :topk]), (nq, topk)
+    for nq, topk in [(1, 1), (1, 100), (4, 100), (5, 128)]:
+        out = (torch.empty((nq, topk), dtype=torch.float32, device="cuda"), torch.empty((nq, topk), dtype=torch.int64, device="cuda"))
+        v, i = scan(nq, topk, out=out, noalloc=True)
+        assert np.array_equal(v, want_v[:nq, :topk]) and np.array_equal(i, want_i[:nq, :topk]), (nq, topk)
