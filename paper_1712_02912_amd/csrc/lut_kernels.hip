@@ -1356,8 +1356,8 @@ int launch_quantize_luts(pq_ctx *ctx, const float *luts, int nq, int m, int k, c
 }
 
 // ------------------------------------------------------------------------------------------
-// Float ADC of one stored code with one query's tables (global memory), Eq. (adc1).
-__device__ __forceinline__ float adc_one(const uint8_t *code, int cf, const float *lut, int m, int k) {
+// Float ADC of one stored code with one query's tables (global memory), Eq. (adc1); added up from table `first` on.
+__device__ __forceinline__ float adc_one(const uint8_t *code, int cf, const float *lut, int m, int k, int first = 0) {
     const int cb = cf == PQ_CODES_U4_PACKED ? m / 2 : m;
     // codes of 8 or 16 bytes (every configured shape) aligned to their size come in one load
     uint32_t w[4] = {0, 0, 0, 0};
@@ -1370,7 +1370,8 @@ __device__ __forceinline__ float adc_one(const uint8_t *code, int cf, const floa
         w[0] = c.x; w[1] = c.y; w[2] = c.z; w[3] = c.w;
     }
     float dist = 0.f;
-    for (int j = 0; j < m; ++j) {
+    for (int s = 0; s < m; ++s) {
+        const int j = s + first < m ? s + first : s + first - m;
         const int pos = cf == PQ_CODES_U4_PACKED ? j >> 1 : j;
         const uint32_t byte = words ? (w[(pos >> 2) & 3] >> (8 * (pos & 3))) & 255u : code[pos];
         int idx;
@@ -1395,31 +1396,35 @@ static inline int staged_floats(int n2, int m, int k) {
 }
 
 // One block per query: distances of the first `cnt` codes (cnt <= 4096) as ordered 32-bit values in LDS,
-// then the kq-th smallest of them by radix selection (1 <= kq <= cnt).
+// then the kq-th smallest of them by radix selection (1 <= kq <= cnt).  row_order: 8 or 16 bytes per code added up in the
+// order of the plain float scan (scan_tuned.hip), which starts at a table that the row number gives.
 __global__ __launch_bounds__(1024) void qmax_prescan_kernel(const uint8_t *__restrict__ codes, int cnt, int cb,
                                                            int cf, const float *__restrict__ luts, int m, int k,
-                                                           int kq, int n2, int staged, float *qmax_out) {
+                                                           int kq, int n2, int staged, bool row_order, float *qmax_out) {
     extern __shared__ uint64_t skeys[];
     __shared__ uint32_t bins[256];
     __shared__ uint32_t state[2];
     const int q = blockIdx.x, tid = threadIdx.x;
     uint32_t *ords = reinterpret_cast<uint32_t *>(skeys);
     const float *lut = stage_tables(luts + (size_t)q * m * k, reinterpret_cast<float *>(skeys + n2), staged);
-    for (int i = tid; i < cnt; i += blockDim.x) ords[i] = f32_to_ord(adc_one(codes + (size_t)i * cb, cf, lut, m, k));
+    for (int i = tid; i < cnt; i += blockDim.x) {
+        const int first = !row_order ? 0 : m == 8 ? (i >> 2) & 7 : i & 15;
+        ords[i] = f32_to_ord(adc_one(codes + (size_t)i * cb, cf, lut, m, k, first));
+    }
     __syncthreads();
     const uint32_t kth = block_kth_smallest_u32(ords, cnt, (uint32_t)kq, bins, state);
     if (tid == 0) qmax_out[q] = ord_to_f32(kth);
 }
 
 int launch_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const float *luts, int nq, int m,
-                        int k, int init, int kq, float *qmax_out) {
+                        int k, int init, int kq, float *qmax_out, bool row_order) {
     const int cnt = (int)(init < n ? init : n);
     if (kq > cnt) kq = cnt;
     int n2 = 64;
     while (n2 < cnt) n2 <<= 1;
     const int cb = cf == PQ_CODES_U4_PACKED ? m / 2 : m;
     const int staged = staged_floats(n2, m, k);
-    qmax_prescan_kernel<<<nq, n2 >= 2048 ? 1024 : (n2 >= 1024 ? 512 : 256), (size_t)n2 * 8 + (size_t)staged * 4, ctx->stream>>>(codes, cnt, cb, cf, luts, m, k, kq, n2, staged, qmax_out);
+    qmax_prescan_kernel<<<nq, n2 >= 2048 ? 1024 : (n2 >= 1024 ? 512 : 256), (size_t)n2 * 8 + (size_t)staged * 4, ctx->stream>>>(codes, cnt, cb, cf, luts, m, k, kq, n2, staged, row_order, qmax_out);
     PQ_HIP(ctx, hipGetLastError());
     return PQ_OK;
 }

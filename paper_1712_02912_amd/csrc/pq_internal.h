@@ -86,7 +86,7 @@ int launch_build_luts(pq_ctx *ctx, const float *queries, const float *codebooks,
 int launch_quantize_luts(pq_ctx *ctx, const float *luts, int nq, int m, int k, const float *qmax,
                          uint8_t *qluts, float *qmin_out, float *scale_out, bool mark_nan = false);   // (16 x 16 tables: qmin_out NaN where an entry is)
 int launch_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const float *luts, int nq, int m,
-                        int k, int init, int kq, float *qmax_out);
+                        int k, int init, int kq, float *qmax_out, bool row_order = false);   // (see qmax_prescan_kernel)
 int launch_rerank(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const float *luts, int nq, int m, int k,
                   const int64_t *cand, int ncand, int topk, float *out_dist, int64_t *out_ids);
 int launch_scan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const void *luts, int lf, int nq, int m,

@@ -1511,7 +1511,7 @@ void scan_tuned_kernel(TunedArgs a) {
 __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *tau_key, uint32_t *ncand, uint32_t *mark,
                                   uint32_t *tau_ref, int ntau,
                                   uint32_t tau_value, uint32_t *hist, size_t nhist, const float *tau0, int nq,
-                                  float tau0_scale, uint32_t *also_zero = nullptr, size_t also_zero_n = 0) {
+                                  uint32_t *also_zero = nullptr, size_t also_zero_n = 0) {
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     if (i0 == 0) {
@@ -1520,10 +1520,8 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
     }
     for (size_t i = i0; i < (size_t)ntau; i += stride) {
         const bool seeded = tau0 != nullptr && i < (size_t)nq && tau0[i] < __builtin_inff();
-        // enlarged away from the value whatever its sign (tables handed in need not be distances)
-        const float bound = seeded ? tau0[i] + fabsf(tau0[i]) * (tau0_scale - 1.f) : 0.f;
-        tau_key[i] = ((unsigned long long)(seeded ? f32_to_ord(bound) : tau_value) << 32) | 0xffffffffull;   // (bounds on the value alone: last row)
-        tau_ref[i] = seeded ? f32_to_ord(bound) : TAU_REF_UNSET;
+        tau_key[i] = ((unsigned long long)(seeded ? f32_to_ord(tau0[i]) : tau_value) << 32) | 0xffffffffull;   // (bounds on the value alone: last row)
+        tau_ref[i] = seeded ? f32_to_ord(tau0[i]) : TAU_REF_UNSET;
         ncand[i] = 0;
         mark[i] = 0;
     }
@@ -2041,11 +2039,12 @@ __global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(cons
                 tau_ref_out[gq] = bounded ? f32_to_ord(bound) : TAU_REF_UNSET;
             }
             // RANGE units between the sum of the minima and the first bound, but never so many per unit of distance that
-            // the threshold conversion loses a fraction of a table unit in fp32 (bound * scale stays below 10^6).  A bound
+            // the threshold conversion or a distance's own roundings lose a fraction of a table unit in fp32 (bound * scale stays
+            // below 10^6, and so do the magnitudes that cancel in a distance).  A bound
             // that leaves no range at all (k codes and more attain the minima: exact duplicates) takes that finest scale:
             // any entry above its table's minimum then counts several units and only the duplicates pass.
             const float range = bound - off;
-            const float finest = bound > 0.f && bound < 3.0e38f ? 0.99e6f / bound : 0.f;
+            const float finest = bound > 0.f && bound < 3.0e38f ? 0.99e6f / (bound + 2.f * negative) : 0.f;
             auto scale_for = [&](float units) {
                 float sc = range > 0.f ? units / range : finest;
                 if (!(sc < finest)) sc = finest;
@@ -2229,7 +2228,7 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
     a.rotated = 0;
     tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, nq,
-                                                     0xff800000u, a.hist, L.nhist, tau0, nq, 1.f);
+                                                     0xff800000u, a.hist, L.nhist, tau0, nq);
     PQ_HIP(ctx, hipGetLastError());
     if (ctx->profiling) {
         a.stats = (unsigned long long *)(state + 8);
@@ -2358,8 +2357,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     const size_t off_poff = off_tau0 + align_up((size_t)ntau * 4, 256);
     const size_t off_pscale = off_poff + align_up((size_t)ntau * 4, 256);
     const size_t off_qtabs = off_pscale + align_up((size_t)ntau * 4, 256);
-    // the plain float loops get a first bound as well (enlarged by a few units of fp32 rounding: they
-    // add the table entries in a rotated order, the bound is computed in table order)
+    // the plain float loops get a first bound as well, from distances added up in their order
     const bool seed_plain = !is_u4 && !prune && n >= PRUNE_INIT;
     // Few query groups over a large database: the first bound comes from a larger part of the codes.
     // Measured optimum (10^7 .. 10^9 codes, 1 .. 200 queries): about 64 M code evaluations over all
@@ -2440,7 +2438,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         float *pscale16 = q8 ? (float *)(ws + off_pscale16) : nullptr;
         uint32_t *const seed_hist = wide_seed ? (uint32_t *)(ws + off_seedhist) : nullptr;
         tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
-                                                         0xff800000u, a.hist, L.nhist, nullptr, nq, 1.f, seed_hist, wide_seed ? (size_t)nq * HIST_BINS : 0);
+                                                         0xff800000u, a.hist, L.nhist, nullptr, nq, seed_hist, wide_seed ? (size_t)nq * HIST_BINS : 0);
         if (wide_seed) {
             // Few query groups over a large database: state cleared first, then one sampling pass whose bins every block
             // bounds for itself, then bound, shared state and tables of every group in one launch (three launches before the
@@ -2483,14 +2481,13 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         a.qtabs = qtabs; a.prune_off = poff; a.prune_scale = pscale; a.qtabs16 = qtabs16; a.prune_scale16 = pscale16;
     } else if (seed_plain) {
         tau0 = (float *)(ws + off_tau0);
-        rc = launch_qmax_prescan(ctx, codes, n, PQ_CODES_U8, (const float *)luts, nq, cb, 256, PRUNE_INIT, topk, tau0);
+        rc = launch_qmax_prescan(ctx, codes, n, PQ_CODES_U8, (const float *)luts, nq, cb, 256, PRUNE_INIT, topk, tau0, true);
         if (rc) return rc;
     }
     if (!prune) {   // (the pruned scans' state has been cleared and seeded above)
         uint32_t *seed_hist_u4 = wide_seed_u4 ? (uint32_t *)(ws + off_seedhist) : nullptr;
         tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
-                                                         is_u4 ? 0x7fffu : 0xff800000u, a.hist, L.nhist, tau0, nq,
-                                                         seed_plain ? 1.f + 4e-6f : 1.f, seed_hist_u4, wide_seed_u4 ? (size_t)nq * 4096 : 0);
+                                                         is_u4 ? 0x7fffu : 0xff800000u, a.hist, L.nhist, tau0, nq, seed_hist_u4, wide_seed_u4 ? (size_t)nq * 4096 : 0);
         PQ_HIP(ctx, hipGetLastError());
     }
     if (seed_u4) {

@@ -1134,7 +1134,7 @@ def test_scan_f32_pruned_small_databases(ctx, opts, n, nq, topk, m, kind):
             check_float_topk(got[0][q], got[1][q], od[q], oi[q], codes, orc.CODES_U8, luts[q], n)
 
 
-@pytest.mark.parametrize("kind", ["random", "far", "infinite", "negative"])
+@pytest.mark.parametrize("kind", ["random", "far", "infinite", "negative", "cancelling"])
 @pytest.mark.parametrize("m", [8, 16])
 @pytest.mark.parametrize("n", [8192, 30_001, 65_535])
 def test_scan_f32_one_order_of_additions_whatever_the_batch(ctx, opts, m, n, kind):
@@ -1149,6 +1149,9 @@ def test_scan_f32_one_order_of_additions_whatever_the_batch(ctx, opts, m, n, kin
         tables[:, 1, 9:200] = np.inf
     if kind == "negative":
         tables -= 60.0
+    if kind == "cancelling":
+        tables[:, 0] += 3e5
+        tables[:, 5] -= 3e5
     luts = dev(tables)
 
     def scan(nq, topk, **kw):
@@ -1165,3 +1168,27 @@ def test_scan_f32_one_order_of_additions_whatever_the_batch(ctx, opts, m, n, kin
         out = (torch.empty((nq, topk), dtype=torch.float32, device="cuda"), torch.empty((nq, topk), dtype=torch.int64, device="cuda"))
         v, i = scan(nq, topk, out=out, noalloc=True)
         assert np.array_equal(v, want_v[:nq, :topk]) and np.array_equal(i, want_i[:nq, :topk]), (nq, topk)
+
+
+@pytest.mark.parametrize("shift", [3e4, 1e6])
+@pytest.mark.parametrize("m", [8, 16])
+@pytest.mark.parametrize("n,nq,topk", [(4096, 7, 1), (4097, 3, 1000), (5000, 40, 100), (9001, 5, 10), (8192, 1, 100), (30_001, 600, 512), (30_001, 300, 1),
+                                       (65_536, 3, 1), (70_000, 300, 512), (70_000, 520, 1), (100_000, 20, 100), (150_000, 4, 1024)])
+def test_scan_f32_tables_that_cancel(ctx, m, n, nq, topk, shift):
+    """Tables of large entries that cancel (no distances): first bounds and lower bounds must allow for the roundings of the entries'
+    magnitudes, not of the distance, else results are lost.  Bit by bit against sums in the order of the scan."""
+    r = np.random.default_rng(n + nq)
+    codes = r.integers(0, 256, (n, m), dtype=np.uint8)
+    tables = (r.random((nq, m, 256)) * 100).astype(np.float32)
+    tables[:, 0] += np.float32(shift)
+    tables[:, m - 3] -= np.float32(shift)
+    v, i = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(tables), topk)]
+    rows = np.arange(n)
+    first = (0 if n >= 65_536 else rows >> 2 if m == 8 else rows) + np.zeros(n, np.int64)
+    for q in range(0, nq, 41):
+        want = np.zeros(n, np.float32)
+        for s in range(m):
+            j = (first + s) % m
+            want += tables[q, j, codes[rows, j]]
+        order = np.lexsort((rows, want))[:topk]
+        assert np.array_equal(v[q], want[order]) and np.array_equal(i[q], order), q
