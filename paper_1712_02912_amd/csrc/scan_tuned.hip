@@ -152,7 +152,7 @@ constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bou
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
 constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan (but see PRUNE_FEW_N)
-constexpr int64_t PRUNE_FEW_N = 1 << 13;   // from here on calls with few queries, long results or, with 16 tables, many queries are pruned too
+constexpr int64_t PRUNE_FEW_N = 1 << 13;   // from here on some calls are pruned too: few queries, long results, many queries on 16 tables
 constexpr int64_t U4_SEED_MIN_N = 512;     // the integer scan takes a first bound from here on
 constexpr int PRUNE_INIT = 4096;           // codes looked at for the first bound of every query
 constexpr int PRUNE_MARGIN = 8;      // slack of the integer threshold, in table units
@@ -2253,14 +2253,27 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // The 8 x 256 float scan prunes with 16-bit lower bounds when the database is large enough to
     // pay for the preparation (a bound per query from the first PRUNE_INIT codes, then the tables).
     // Between PRUNE_FEW_N and PRUNE_MIN_N codes the bound's slices take 6 us where the plain loop's bound takes 16 to 24, and the
-    // tables' preparation 10: it pays for up to four queries (plain loop -> this; 30 000 codes, 8 tables, one query, top-1 37 -> 31 us,
-    // top-100 50 -> 43; 60 000, four queries 55 -> 50; 16 tables 58 -> 46, 64 -> 54; eight queries 54 -> 56 and 62 -> 58), for long
-    // results (30 000 codes, top-1000, 100 queries 137 -> 85, 16 tables 141 -> 101; 9000 codes 80 -> 103, 20 000 codes, 300 queries,
-    // top-200 115 -> 126) and for many queries on 16 tables (30 000 codes, 700 queries, top-100 158 -> 126; 400 queries, 20 000 codes 93 -> 94;
-    // 8 tables 128 -> 129).  The fixed scratch keeps to the plain loop, whose lists are half as long.  Both loops give the same
-    // bits here (a.rotated).
-    const bool prune_small = n >= PRUNE_FEW_N && !ctx->ws_fixed &&
-                             (nq <= 4 || (topk >= 512 && n >= 24 * (int64_t)topk) || (kind == KIND_F32_M16 && nq >= 512));
+    // tables' preparation 10.  Times of the plain loop over those of the pruned one, codes of encoded vectors, 8192 to 65 535 of
+    // them (3231 calls; of the 1741 that the lines below let through 6 lose 5 % and more, and their mean is 1.23, that of the others 1.0):
+    //   up to 4 queries       0.98 to 1.76 (8192 codes 0.98 to 1.22; 30 000 codes, 8 tables, one query, top-100 45.5 -> 40.3 us)
+    //   8 tables, more        gains once the plain loop has more items than blocks, 2^22 pairs (100 queries, top-512: 36 000 codes 0.97,
+    //                         45 000 1.56; 248 queries: 16 000 0.86, 20 000 1.48), or results so long that the bound from its 4096
+    //                         codes lets most of a list through (16 queries, 30 000 codes: top-896 0.92, top-1000 1.29), and
+    //                         until the pruned loop has more items than blocks itself (248 queries: 45 000 codes 1.58, 55 000 0.86)
+    //   8 tables, 8-bit       (249 queries and more) 249: 0.54 to 1.15, 512: 0.72 to 1.49, 600 and top-768 on 0.92 to 1.49, 1000 1.04 to 1.35
+    //   16 tables             up to 128 queries: top-512 on 30 000 codes 0.91 to 1.11, 45 000 0.98 to 1.57; 129 to 383 queries 0.74 to 1.42;
+    //                         400 queries, top-768 on, 1.00 to 1.29
+    //   16 tables, many       512 queries 0.78 to 1.32; 520 and more 0.88 to 1.5 with 40 codes and more per result, nine in ten above 1.02 (400 results of
+    //                         10 000 codes 0.90)
+    // The fixed scratch keeps to the plain loop, whose lists are half as long.  Both loops give the same bits here (a.rotated).
+    const int64_t pairs = n * nq;
+    bool prune_small = nq <= 4;
+    if (!prune_small && kind == KIND_F32_M8)
+        prune_small = n >= 24 * (int64_t)topk && ((nq + 7) / 8 < STREAM_GROUPS ? pairs < 3 << 22 && (topk >= 1000 || (topk >= 512 && pairs >= 1 << 22)) : nq >= 600 && topk >= 768);
+    else if (!prune_small)
+        prune_small = nq > 512 ? n >= 40 * (int64_t)topk
+                               : topk >= 512 && (nq <= 128 ? n >= 40960 : nq >= 384 && topk >= 768 && n >= 24 * (int64_t)topk);
+    prune_small = prune_small && n >= PRUNE_FEW_N && !ctx->ws_fixed;
     const bool prune = (kind == KIND_F32_M8 || kind == KIND_F32_M16) && (n >= PRUNE_MIN_N || prune_small) && opt_int(ctx, PQ_OPT_SCAN_PRUNE, 1) != 0;
     const int tables = kind == KIND_F32_M16 ? 16 : 8;
     // eight tables and too many queries for the streaming shape (32 groups of 8 and more, i.e. 249 queries): 8-bit
