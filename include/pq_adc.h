@@ -99,6 +99,7 @@ const char *pq_version(void);
  *                             (unset: by the lengths of the candidate lists; same results)
  *   derived_code_copy (1)     0: Step 2 reads the candidates' codes from the database, not from copies beside the lists
  *   derived_sample (1)        0: the candidates of pq_derived_search always by two passes over the codes
+ *   alloc_limit_mib (0)       above 0: an allocation of more scratch memory than this fails as if the device had none
  *   ivf_quick_chunk_rows (1048576)  ivf_quick_adc_search: rows per work item at most (1024 ... 2^20); a list longer than
  *                             this is scanned in chunks, and a query's result lists (one per chunk of each of its
  *                             lists, at most nprobe + ntotal / this value) are part of the workspace */
@@ -238,9 +239,11 @@ int pq_rerank_f32(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf, 
  * no more), 1 KB per 512 candidates or more, and for long lists up to 256 MB of tables.
  * From 32 r2 codes and 84 M (code, query) pairs on, r2 >= 450, the counts come from a sample of
  * the codes, the lists hold the vectors up to a bucket that is sure enough to hold the r2-th
- * (about a fifth more memory), and the exact buckets and counts are taken from the lists, after
- * which the call waits for the stream once more; lists that turn out too short or too long send
- * the call to the two passes.  The results are the same.  With 640 queries and more the second pass
+ * (about a fifth more memory, and 8 bytes per code of the sample, one of every min(16, r2 / 150)
+ * codes), and the exact buckets and counts are taken from the lists, after
+ * which the call waits for the stream once more.  Where there is no memory for the sample or its lists, and
+ * where the lists turn out too short or too long, the call makes the two passes (in the latter case after
+ * the sample's pass, so that it takes half as long again).  The results are the same.  With 640 queries and more the second pass
  * takes 16 queries per pass over the codes (lower bounds of the integer sums in the loop, exact
  * sums for the codes that pass; option scan_q8 = 0: 8 queries per pass as for fewer queries).
  * Covered: m = 4, d % 4 == 0, d <= 4096, 256 <= k <= 65536, 1 <= topk <= 128, r2 >= 1,

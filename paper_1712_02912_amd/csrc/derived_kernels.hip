@@ -1297,7 +1297,9 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     // The sample holds 150 of the r2 vectors at least; below 84 M pairs the additional launches and the second wait cost what the
     // shorter count saves.  Call: 25 M codes, 1000 queries, r2 = 10 000 9.95 -> 6.75 ms, r2 = 1000 8.30 -> 5.88; 8 M, 100,
     // 10 000 0.73 -> 0.59; 25 M, 8, 10 000 0.556 -> 0.527; 1 M, 100, 1000 0.233 -> 0.218; but 2 M, 30, 10 000 0.272 -> 0.307
-    // and 8 M, 8, 10 000 0.307 -> 0.318.
+    // and 8 M, 8, 10 000 0.307 -> 0.318.  A call that its sample misleads pays for both ways: with a far code at half of the sample's
+    // rows, 25 M codes, 1000 queries, r2 = 10 000 9.97 -> 14.65 ms, 8 M, 100, 10 000 0.72 -> 1.07.  Rows that do not follow the hash
+    // mislead a query once in 300 000 (4.5 deviations), a call of 1000 queries once in 300.
     int sample_step = r2 / 150 < 16 ? r2 / 150 : 16;
     if (sample_step < 3 || n < (int64_t)r2 * 32 || n * nq < DQ_SAMPLE_PAIRS || opt_int(ctx, PQ_OPT_DERIVED_SAMPLE, 1) == 0) sample_step = 0;
     const int64_t nsample = sample_step > 0 ? n / sample_step : 0;
@@ -1333,8 +1335,11 @@ int launch_derived_search(pq_ctx *ctx, const uint16_t *codes16, int64_t n, const
     const size_t o_sbucket = take((size_t)nq * 4);
     const size_t o_room = take((size_t)nq * 4);
     const size_t o_sample = take((size_t)nsample * 8);
-    const size_t first_part_all = off;
-    int rc = ws_reserve(ctx, first_part_all);
+    int rc = ws_reserve(ctx, off);
+    if (rc == PQ_ENOMEM && sample_step > 0) {   // (the two passes do without)
+        sample_step = 0;
+        rc = ws_reserve(ctx, o_sample);
+    }
     if (rc) return rc;
     if (!ctx->host_pin) {   // a few words of pinned host memory, kept by the context
         void *p = nullptr;

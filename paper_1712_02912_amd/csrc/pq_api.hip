@@ -23,6 +23,12 @@ int hip_fail(pq_ctx *ctx, hipError_t e, const char *what) {
     return fail(ctx, PQ_EHIP, "HIP error %d (%s) in %s", (int)e, hipGetErrorString(e), what);
 }
 
+// hipMalloc, or its failure for want of memory where the option alloc_limit_mib says so
+static hipError_t scratch_malloc(pq_ctx *ctx, void **p, size_t bytes) {
+    const int limit = opt_int(ctx, PQ_OPT_ALLOC_LIMIT_MIB, 0);
+    return limit > 0 && bytes > (size_t)limit << 20 ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+}
+
 int ws_reserve(pq_ctx *ctx, size_t bytes) {
     if (bytes <= ctx->ws_bytes) return PQ_OK;
     if (ctx->ws_fixed)
@@ -37,7 +43,7 @@ int ws_reserve(pq_ctx *ctx, size_t bytes) {
     }
     const size_t want = align_up(bytes + bytes / 4, (size_t)1 << 20);
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, want);
+    hipError_t e = scratch_malloc(ctx, &p, want);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, PQ_ENOMEM, "workspace allocation of %zu bytes failed: %s", want, hipGetErrorString(e));
@@ -59,7 +65,7 @@ int buf_reserve(pq_ctx *ctx, pq_buf *buf, size_t bytes, const char *what) {
     for (const size_t spare : {bytes / 4, (size_t)0}) {   // with room to grow, or what is needed
         const size_t want = align_up(bytes + spare, (size_t)1 << 20);
         void *p = nullptr;
-        e = hipMalloc(&p, want);
+        e = scratch_malloc(ctx, &p, want);
         if (e == hipSuccess) {
             buf->p = p;
             buf->bytes = want;
@@ -77,7 +83,8 @@ static bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 static const char *const OPTION_NAMES[PQ_OPT_COUNT] = {"scan_prune", "scan_q8", "scan_force_general", "scan_blocks",
                                                        "scan_items_per_block", "scan_head", "lut_mfma", "ivf_prune",
                                                        "ivf_ws_gib", "ivf_block_waves", "scan_wide_seed", "ivf_short_max", "ivf_coarse_f32",
-                                                       "ivf_quick_chunk_rows", "ivf_coarse_f16", "encode_split16", "derived_tables", "derived_code_copy", "derived_sample"};
+                                                       "ivf_quick_chunk_rows", "ivf_coarse_f16", "encode_split16", "derived_tables", "derived_code_copy", "derived_sample",
+                                                       "alloc_limit_mib"};
 
 static void options_from_environment(pq_ctx *ctx) {
     for (int i = 0; i < PQ_OPT_COUNT; ++i) {

@@ -375,3 +375,22 @@ def test_derived_search_on_the_bounds_of_a_sample(ctx, opts, order, nq):
     if cap > 0:
         with pytest.raises(RuntimeError, match="cand_cap"):
             ctx.pq_derived_search(*args, cand_cap=cap - 1)
+
+
+def test_derived_search_without_memory_for_the_sample():
+    """The sample is a convenience: a call that cannot have its memory makes the two passes."""
+    ctx = binding.Context(0)
+    n, nq, r2 = 1_320_011, 64, 450   # 440 003 codes of 8 bytes in the sample
+    cb, cbar, codes, queries = make_problem(3, n, 512, 4, nq)
+    args = (dev(codes.view(np.int16)), dev(cbar), dev(cb), dev(queries), r2, 10)
+    ctx.pq_set_profiling(True)
+    ctx.pq_set_option("alloc_limit_mib", 3)
+    got = [t.cpu().numpy() for t in ctx.pq_derived_search(*args)[:4]]
+    assert "<count>" in ctx.pq_last_scan_info()["kernel"]
+    ctx.pq_set_option("alloc_limit_mib", None)
+    sampled = [t.cpu().numpy() for t in ctx.pq_derived_search(*args)[:4]]
+    assert "buckets of a sample" in ctx.pq_last_scan_info()["kernel"]
+    for a, b in zip(got, sampled):
+        assert np.array_equal(a, b)
+    torch.cuda.synchronize()
+    ctx.close()
