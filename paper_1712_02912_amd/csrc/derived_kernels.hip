@@ -108,8 +108,9 @@ struct DqPlaces {
         end = gq < a.nq ? a.cand_off[gq + 1] : 0;
     }
     __device__ __forceinline__ void reserve(const DqArgs &a, int gq, uint32_t count) { slot = count != 0u ? atomicAdd(&a.cand_cnt[gq], count) : 0u; }
-    // place `index` of query q's (the list holds exactly the vectors the first pass counted; the comparison only keeps a
-    // disagreement from writing past it)
+    // place `index` of query q's.  After a counting pass the list has room for exactly the vectors it counted.  Room estimated
+    // from a sample may be too small: the comparison is what keeps the keys beyond it out of the next query's list, cand_cnt still
+    // counts them, and derived_settle_kernel sees from that that the call has to make the two passes.
     __device__ __forceinline__ void store(const DqArgs &a, int q, bool pass, uint32_t index, uint32_t sum, uint32_t row, uint32_t w0, uint32_t w1) const {
         const uint64_t first = of_lane(begin, q) + (uint32_t)__builtin_amdgcn_readlane(slot, q);
         const uint64_t stop = of_lane(end, q);

@@ -368,7 +368,13 @@ def test_derived_search_on_the_bounds_of_a_sample(ctx, opts, order, nq):
         return [t.cpu().numpy() for t in out[:4]] + [h.sum(1).cpu().numpy(), (ids >= 0).sum(1).cpu().numpy()]
     ref = sets()
     opts.set("derived_sample", 1)
-    for got, want in zip(ctx.pq_derived_search(*args)[:4], two):
+    ctx.pq_set_profiling(True)
+    got = ctx.pq_derived_search(*args)[:4]
+    kernel = ctx.pq_last_scan_info()["kernel"]
+    ctx.pq_set_profiling(False)
+    # the last scan that was timed: the sampled call's collecting pass, or the counting pass of the call that went back to two
+    assert ("buckets of a sample" if order not in ("sample_nearer", "sample_farther") else "<count>") in kernel, kernel
+    for got, want in zip(got, two):
         assert np.array_equal(got.cpu().numpy(), want)
     for got, want in zip(sets(), ref):
         assert np.array_equal(got, want)
