@@ -23,6 +23,7 @@
 // below T (fewer than kprime) and, in row order, those equal to T.  Every float sum of this file is formed in
 // double in table order and rounded once, so that the bound, the 8-bit tables, the candidates and the distances are
 // those of the plain definition bit for bit.
+#include <stddef.h>
 #include <type_traits>
 #include "pq_internal.h"
 #include "scan_common.h"
@@ -119,8 +120,10 @@ __device__ __forceinline__ int quick_sum_cap(unsigned long long tau_key, float q
 }
 
 // ------------------------------------------------------------------------------------------
+// (256: slots are addressed by a bitwise or with their table's address, in sub-quantizers of 128 and of 256 bytes)
+constexpr int QK_SMEM_ALIGN = 256;
 template <int QK_WAVES, typename TieRow>
-struct __align__(16) QuickSmem {
+struct __align__(QK_SMEM_ALIGN) QuickSmem {
     uint2 lbtab[256];                            // slot j * 16 + i: 4-bit lower bounds of the entries (j, i) of the 8 pairs as bytes
     uint4 tab[256];                              // slot j * 16 + i: the 8-bit entries (j, i) of the 8 pairs as 16-bit values
     uint32_t hist[QK_QS][QK_BINS];
@@ -154,6 +157,8 @@ struct __align__(16) QuickSmem {
 typedef QuickSmem<4, uint16_t> QuickSmemShort;
 typedef QuickSmem<8, uint32_t> QuickSmemLong;
 static_assert(QK_LONG_MIN <= 65536, "rows of short items fit 16 bits");
+static_assert(offsetof(QuickSmemShort, lbtab) % 128 == 0 && offsetof(QuickSmemLong, lbtab) % 128 == 0, "sub-quantizers of 128 bytes");
+static_assert(offsetof(QuickSmemShort, tab) % 256 == 0 && offsetof(QuickSmemLong, tab) % 256 == 0, "sub-quantizers of 256 bytes");
 static_assert(sizeof(QuickSmemShort) <= 40 * 1024, "four blocks of 4 waves share the 160 KB of a compute unit");
 static_assert(sizeof(QuickSmemLong) <= 80 * 1024, "two blocks of 8 waves per compute unit");
 
@@ -193,7 +198,7 @@ __global__ __launch_bounds__(QK_WAVES * 64, LONG && !BOUNDS ? 2 : 4) void ivf_qu
                                                                        const float *__restrict__ luts, int nprobe, int topk,
                                                                        unsigned long long *tau_key, QuickBound qb) {
     constexpr int QK_THREADS = QK_WAVES * 64;
-    extern __shared__ __align__(16) unsigned char quick_smem[];
+    extern __shared__ __align__(QK_SMEM_ALIGN) unsigned char quick_smem[];
     typedef typename std::conditional<LONG, uint32_t, uint16_t>::type TieRow;
     QuickSmem<QK_WAVES, TieRow> &sm = *reinterpret_cast<QuickSmem<QK_WAVES, TieRow> *>(quick_smem);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
