@@ -607,3 +607,42 @@ def test_ivf_quick_bounds_across_lists(ctx, opts, kprime, topk, chunk_rows, spec
     od, oi = orc.ivf_quick_search(queries, coarse, offsets, packed, None, cb, orc.CODES_U4_PACKED, nprobe, 500, kprime, topk)
     gd, gi = ctx.ivf_quick_adc_search(dev(coarse), dev(offsets), dev(packed), None, dev(cb), dev(queries), nprobe, 500, kprime, topk)[:2]
     assert np.array_equal(gd.cpu().numpy(), od) and np.array_equal(gi.cpu().numpy(), oi)
+
+
+@pytest.mark.parametrize("kprime,topk,chunk_rows,special", [(128, 100, None, None), (100, 1, None, "ties"), (20, 128, 17_000, None), (128, 128, 17_000, "ties"),
+                                                            (64, 10, None, "huge"), (128, 50, None, "equal"), (128, 100, None, "near_last")])
+@pytest.mark.parametrize("long", [False, True])
+def test_ivf_quick_bounds_that_fall_within_an_item(ctx, opts, long, kprime, topk, chunk_rows, special):
+    """Items long enough to look at their queries' bounds again between segments, and more of them than there are blocks, so that these
+    bounds fall while an item is scanned: exact against the oracle (every 17th query), with tied and equal codes, infinite
+    distances, chunked lists, and near codes at the ends of the lists."""
+    r = np.random.default_rng(kprime + topk + long)
+    nlist, nprobe, d, nq = 20, 16, 32, 1000
+    # lists of 65 536 rows and more go to the blocks of 8 waves, two per compute unit, and are read in segments of 2048, 4096, 8192,
+    # 16 384 ... rows; the others to blocks of 4, four per compute unit, in segments of half of that.  The bounds are read after
+    # segments of 16 384 and of 8192 rows and more.
+    sizes = ([66_000 + 131 * i for i in range(10)] + [900] * 9 + [131_072]) if long else ([16_000 + 1201 * i for i in range(19)] + [8190])
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert nq * (nprobe - 9 if long else nprobe - 1) // 8 > (2 if long else 4) * cus
+    n = sum(sizes)
+    coarse = (r.normal(size=(nlist, d)) * 3).astype(np.float32)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    packed = r.integers(0, 256, (n, 8), dtype=np.uint8)
+    cb = (r.normal(size=(16, 16, d // 16)) * 2).astype(np.float32)
+    queries = (r.normal(size=(nq, d)) * 3).astype(np.float32)
+    if special == "ties":
+        packed = packed[r.integers(0, 50, n)]
+    if special == "huge":
+        cb[3, 5] = 1e30
+    if special == "equal":
+        packed[:] = packed[0]
+    if special == "near_last":   # the last 200 rows of a list decode to its centroid as well as the codebooks can: near to every query that probes it
+        best = np.abs(cb).sum(2).argmin(1).astype(np.uint8)
+        for end in offsets[1:]:
+            packed[end - 200:end] = orc.pack_u4(np.where(r.random((200, 16)) < 0.1, r.integers(0, 16, (200, 16)), best).astype(np.uint8))
+    if chunk_rows:
+        opts.set("ivf_quick_chunk_rows", chunk_rows)
+    some = slice(0, nq, 17)
+    od, oi = orc.ivf_quick_search(queries[some], coarse, offsets, packed, None, cb, orc.CODES_U4_PACKED, nprobe, 500, kprime, topk)
+    gd, gi = ctx.ivf_quick_adc_search(dev(coarse), dev(offsets), dev(packed), None, dev(cb), dev(queries), nprobe, 500, kprime, topk)[:2]
+    assert np.array_equal(gd.cpu().numpy()[some], od) and np.array_equal(gi.cpu().numpy()[some], oi)
