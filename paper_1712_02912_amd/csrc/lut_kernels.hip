@@ -1409,7 +1409,8 @@ __global__ __launch_bounds__(1024) void qmax_prescan_kernel(const uint8_t *__res
     const float *lut = stage_tables(luts + (size_t)q * m * k, reinterpret_cast<float *>(skeys + n2), staged);
     for (int i = tid; i < cnt; i += blockDim.x) {
         const int first = !row_order ? 0 : m == 8 ? (i >> 2) & 7 : i & 15;
-        ords[i] = f32_to_ord(adc_one(codes + (size_t)i * cb, cf, lut, m, k, first));
+        const float dist = adc_one(codes + (size_t)i * cb, cf, lut, m, k, first);
+        ords[i] = row_order ? f32_to_ord_nan_last(dist) : f32_to_ord(dist);
     }
     __syncthreads();
     const uint32_t kth = block_kth_smallest_u32(ords, cnt, (uint32_t)kq, bins, state);

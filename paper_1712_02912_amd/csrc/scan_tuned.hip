@@ -356,7 +356,7 @@ __device__ __noinline__ int scan_flush(LDS_PTR(SM) sm, uint64_t *wave_buf, int n
             for (int h = 0; h < CPL; ++h) {
                 uint32_t ord;
                 if constexpr (IS_U4) ord = (acc[h][q >> 1] >> (16 * (q & 1))) & 0xffffu;
-                else ord = f32_to_ord(__uint_as_float(acc[h][q]));
+                else ord = f32_to_ord_nan_last(__uint_as_float(acc[h][q]));
                 if (ok[h] && q < nvalid && ord < eff) m |= 1u << (h * QB + q);
             }
         }
@@ -616,7 +616,7 @@ __device__ __noinline__ int scan_flush_pruned(LDS_PTR(SM) sm, uint64_t *wave_buf
                     d += fl[3840 + (c.w >> 24)];
                 }
             }
-            const uint32_t ord = f32_to_ord(d);
+            const uint32_t ord = f32_to_ord_nan_last(d);
             uint32_t eff;
             if constexpr (Q8) {
                 eff = sm->eff_tmp[wave][q];
@@ -1809,7 +1809,7 @@ __global__ __launch_bounds__(1024) void f32_seed_refine_kernel(const uint8_t *__
             const float4 t = tab[((w[st >> 2] >> (8 * (st & 3))) & 255u) * M + ((rot + st) & (M - 1))];
             d.x += t.x; d.y += t.y; d.z += t.z; d.w += t.w;
         }
-        ord[0] = f32_to_ord(d.x); ord[1] = f32_to_ord(d.y); ord[2] = f32_to_ord(d.z); ord[3] = f32_to_ord(d.w);
+        ord[0] = f32_to_ord_nan_last(d.x); ord[1] = f32_to_ord_nan_last(d.y); ord[2] = f32_to_ord_nan_last(d.z); ord[3] = f32_to_ord_nan_last(d.w);
     };
     if (self_ref) {   // no bound yet: the greatest distance among the first k codes is one
         for (int i = tid; i < k && i < cnt; i += 1024) {
@@ -1936,7 +1936,7 @@ __global__ __launch_bounds__(1024) void f32_seed_hist2_kernel(const uint8_t *__r
                 float d = tab[c[u][0] & 255u];   // (table order, as the scans add a candidate's entries)
 #pragma unroll
                 for (int j = 1; j < M; ++j) d += tab[j * 256 + ((c[u][j >> 2] >> (8 * (j & 3))) & 255u)];
-                const uint32_t ord = f32_to_ord(d);
+                const uint32_t ord = f32_to_ord_nan_last(d);
                 if (ord <= limit) {
                     const uint32_t below = (ref - ord) >> shift;
                     atomicAdd(&hist[HIST_BINS - 1 - (below < HIST_BINS ? below : HIST_BINS - 1)], 1u);

@@ -16,6 +16,8 @@ __device__ __forceinline__ uint32_t f32_to_ord(float f) {
     uint32_t b = __float_as_uint(f);
     return b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
 }
+// The same with every NaN behind all numbers (above, one with its sign set comes first): a distance that is none is no result.
+__device__ __forceinline__ uint32_t f32_to_ord_nan_last(float f) { return f == f ? f32_to_ord(f) : 0xffffffffu; }
 __device__ __forceinline__ float ord_to_f32(uint32_t o) {
     uint32_t b = o ^ ((o >> 31) ? 0x80000000u : 0xffffffffu);
     return __uint_as_float(b);

@@ -1192,3 +1192,40 @@ def test_scan_f32_tables_that_cancel(ctx, m, n, nq, topk, shift):
             want += tables[q, j, codes[rows, j]]
         order = np.lexsort((rows, want))[:topk]
         assert np.array_equal(v[q], want[order]) and np.array_equal(i[q], order), q
+
+
+@pytest.mark.parametrize("kind", ["both_infinities", "minus_infinity", "nan_with_sign", "nan_rows"])
+@pytest.mark.parametrize("m", [4, 8, 16])
+@pytest.mark.parametrize("n,nq,topk", [(100, 3, 20), (4096, 5, 100), (4200, 2, 1000), (9001, 4, 1), (20_001, 600, 300), (33_000, 40, 1000), (66_000, 5, 1), (70_000, 300, 100), (300_001, 2, 1024)])
+def test_scan_f32_sums_that_are_no_numbers(ctx, m, n, nq, topk, kind):
+    """Tables with infinities of both signs and with NaN of either sign: the result holds the smallest sums that are numbers, minus
+    infinity among them, no NaN and nothing at plus infinity, and neither takes the place of a sum in a first bound."""
+    r = np.random.default_rng(n + m)
+    codes = r.integers(0, 256, (n, m), dtype=np.uint8)
+    tables = (r.random((nq, m, 256)) * 100).astype(np.float32)
+    if kind == "both_infinities":
+        tables[:, 0, :100] = np.inf
+        tables[:, 1, :100] = -np.inf
+    if kind == "minus_infinity":
+        tables[:, 1, 9] = -np.inf
+    if kind == "nan_with_sign":
+        tables[:, 2, :64] = np.copysign(np.float32(np.nan), np.float32(-1))
+        tables[:, 3, 7] = np.nan
+    if kind == "nan_rows":   # every sum but those of 50 codes
+        tables[:, 0, 1:] = np.copysign(np.float32(np.nan), np.float32(-1))
+        codes[:, 0] = np.maximum(codes[:, 0], 1)
+        codes[r.permutation(n)[:50], 0] = 0
+    v, i = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(tables), topk)]
+    rows = np.arange(n)
+    first = (0 if n >= 65_536 or m == 4 else rows >> 2 if m == 8 else rows) + np.zeros(n, np.int64)
+    for q in range(0, nq, 41):
+        sums = np.zeros(n, np.float32)
+        with np.errstate(invalid="ignore"):
+            for s in range(m):
+                j = (first + s) % m
+                sums += tables[q, j, codes[rows, j]]
+        number = rows[sums < np.inf]
+        order = number[np.lexsort((number, sums[number]))][:topk]
+        want_v, want_i = np.full(topk, np.inf, np.float32), np.full(topk, -1, np.int64)
+        want_v[:len(order)], want_i[:len(order)] = sums[order], order
+        assert np.array_equal(v[q], want_v) and np.array_equal(i[q], want_i), q
