@@ -149,9 +149,9 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_generic_kernel(ScanArgs a, 
 //
 // Row b of the tables in LDS (256 bytes) holds the entries of code byte b for the four queries as 16-byte slots, every table
 // in four copies; a lane reads slot (lane + 4 s) & 15 at step s, so the 16 lanes that the LDS serves together always read 16
-// different bank groups and a code costs four reads without conflicts for four queries.  What bounds the loop is these
-// reads: 32 cycles per 64 codes and four queries (4 M codes, 100 queries: 81 us for the chip, the kernel 204; set-up and end of
-// its 2000 items and the exact tests of tied codes take the rest).  The rotated order of the
+// different bank groups and a code costs four reads without conflicts for four queries.  What bounds the kernel is
+// vector instructions, 79 M for 4 M codes and 100 queries: their units are busy 76 % of its 197 us, the LDS 30 %; 10^6 codes and 6
+// queries (28 us) are bound by the latency of few short items, 24 and 10 %.  The rotated order of the
 // additions makes the sum a filter only, with a margin of its rounding; codes at or below the bound are added up again in table
 // order, so values and ids are those of the general kernel.
 // Bounds: a sample of the codes is counted first in the bins of a histogram per query (codes4_sample_kernel), the scan adds
