@@ -574,6 +574,16 @@ __device__ __noinline__ int scan_flush_pruned(LDS_PTR(SM) sm, uint64_t *wave_buf
                 m = m2;
             }
         }
+        if constexpr (ROTATED) {   // the bytes of the lane's codes, from that of its first table on
+            if constexpr (NT == 8) {
+                rot8(c.x, c.y, (lw.rot & 4u) != 0u, lw.rot & 3u);
+                rot8(c.z, c.w, (lw.rot & 4u) != 0u, lw.rot & 3u);
+            } else {
+                uint32_t r[4] = {c.x, c.y, c.z, c.w};
+                rot16(r, lw.rot);
+                c = make_uint4(r[0], r[1], r[2], r[3]);
+            }
+        }
         // the float bounds as scalars (a lane read inside the divergent loop below would miss
         // the lanes that have already left it)
         uint32_t eff_q[Q8 ? 1 : QB];   // (with 16 queries the bounds wait in LDS instead)
@@ -590,9 +600,7 @@ __device__ __noinline__ int scan_flush_pruned(LDS_PTR(SM) sm, uint64_t *wave_buf
             const float *fl = (const float *)sm->slot_lut[q];   // the query's float tables [table][entry], in device memory
             float d;
             if constexpr (ROTATED) {   // from table lw.rot on
-                uint32_t r[4] = {w0, w1, c.z, c.w};
-                if constexpr (NT == 8) rot8(r[0], r[1], (lw.rot & 4u) != 0u, lw.rot & 3u);
-                else rot16(r, lw.rot);
+                const uint32_t r[4] = {w0, w1, c.z, c.w};
                 d = fl[lw.rot * 256u + (r[0] & 255u)];
 #pragma unroll
                 for (int s = 1; s < NT; ++s) d += fl[((lw.rot + s) & (NT - 1)) * 256u + ((r[s >> 2] >> (8 * (s & 3))) & 255u)];
