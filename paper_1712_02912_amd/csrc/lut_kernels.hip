@@ -3,6 +3,7 @@
 // (Section 6.2.3, Alg. 5).
 #include "pq_internal.h"
 #include "topk_device.h"
+#include "lds_walk.h"
 
 namespace pq {
 
@@ -1356,8 +1357,8 @@ int launch_quantize_luts(pq_ctx *ctx, const float *luts, int nq, int m, int k, c
 }
 
 // ------------------------------------------------------------------------------------------
-// Float ADC of one stored code with one query's tables (global memory), Eq. (adc1); added up from table `first` on.
-__device__ __forceinline__ float adc_one(const uint8_t *code, int cf, const float *lut, int m, int k, int first = 0) {
+// Float ADC of one stored code with one query's tables (global memory), Eq. (adc1).
+__device__ __forceinline__ float adc_one(const uint8_t *code, int cf, const float *lut, int m, int k) {
     const int cb = cf == PQ_CODES_U4_PACKED ? m / 2 : m;
     // codes of 8 or 16 bytes (every configured shape) aligned to their size come in one load
     uint32_t w[4] = {0, 0, 0, 0};
@@ -1370,8 +1371,7 @@ __device__ __forceinline__ float adc_one(const uint8_t *code, int cf, const floa
         w[0] = c.x; w[1] = c.y; w[2] = c.z; w[3] = c.w;
     }
     float dist = 0.f;
-    for (int s = 0; s < m; ++s) {
-        const int j = s + first < m ? s + first : s + first - m;
+    for (int j = 0; j < m; ++j) {
         const int pos = cf == PQ_CODES_U4_PACKED ? j >> 1 : j;
         const uint32_t byte = words ? (w[(pos >> 2) & 3] >> (8 * (pos & 3))) & 255u : code[pos];
         int idx;
@@ -1379,6 +1379,25 @@ __device__ __forceinline__ float adc_one(const uint8_t *code, int cf, const floa
         else idx = byte;
         if (idx < k) dist += lut[(size_t)j * k + idx];
     }
+    return dist;
+}
+
+// The same of codes of M = 8 or 16 bytes (aligned to them) with tables of 256 entries, added up from table `first` on.
+template <int M>
+__device__ __forceinline__ float adc_bytes_from(const uint8_t *code, const float *lut, uint32_t first) {
+    uint32_t w[4];
+    if constexpr (M == 8) {
+        const uint2 c = *reinterpret_cast<const uint2 *>(code);
+        w[0] = c.x; w[1] = c.y;
+        rot8(w[0], w[1], (first & 4u) != 0u, first & 3u);
+    } else {
+        const uint4 c = *reinterpret_cast<const uint4 *>(code);
+        w[0] = c.x; w[1] = c.y; w[2] = c.z; w[3] = c.w;
+        rot16(w, first);
+    }
+    float dist = lut[first * 256u + (w[0] & 255u)];
+#pragma unroll
+    for (int s = 1; s < M; ++s) dist += lut[((first + s) & (M - 1)) * 256u + ((w[s >> 2] >> (8 * (s & 3))) & 255u)];
     return dist;
 }
 
@@ -1396,11 +1415,14 @@ static inline int staged_floats(int n2, int m, int k) {
 }
 
 // One block per query: distances of the first `cnt` codes (cnt <= 4096) as ordered 32-bit values in LDS,
-// then the kq-th smallest of them by radix selection (1 <= kq <= cnt).  row_order: 8 or 16 bytes per code added up in the
-// order of the plain float scan (scan_tuned.hip), which starts at a table that the row number gives.
+// then the kq-th smallest of them by radix selection (1 <= kq <= cnt).  ROW_ORDER: m = 8 or 16 bytes per code and k = 256, added up in the
+// order of the plain float scan (scan_tuned.hip), which starts at a table that the row number gives, NaN behind all numbers.
+// (An instance of its own: as an argument the order cost the pre-scan of 32 x 4 codes 2 us, and with M known the loads of a code are one and its
+// look-ups unrolled: 50 000 codes, 16 queries, top-1, 8 tables 47.8 -> 36.7 us, 16 tables 57 -> 43; 4200 codes, 1000 queries 92 -> 76, 121 -> 90.)
+template <bool ROW_ORDER>
 __global__ __launch_bounds__(1024) void qmax_prescan_kernel(const uint8_t *__restrict__ codes, int cnt, int cb,
                                                            int cf, const float *__restrict__ luts, int m, int k,
-                                                           int kq, int n2, int staged, bool row_order, float *qmax_out) {
+                                                           int kq, int n2, int staged, float *qmax_out) {
     extern __shared__ uint64_t skeys[];
     __shared__ uint32_t bins[256];
     __shared__ uint32_t state[2];
@@ -1408,9 +1430,9 @@ __global__ __launch_bounds__(1024) void qmax_prescan_kernel(const uint8_t *__res
     uint32_t *ords = reinterpret_cast<uint32_t *>(skeys);
     const float *lut = stage_tables(luts + (size_t)q * m * k, reinterpret_cast<float *>(skeys + n2), staged);
     for (int i = tid; i < cnt; i += blockDim.x) {
-        const int first = !row_order ? 0 : m == 8 ? (i >> 2) & 7 : i & 15;
-        const float dist = adc_one(codes + (size_t)i * cb, cf, lut, m, k, first);
-        ords[i] = row_order ? f32_to_ord_nan_last(dist) : f32_to_ord(dist);
+        const uint8_t *const code = codes + (size_t)i * cb;
+        if constexpr (ROW_ORDER) ords[i] = f32_to_ord_nan_last(m == 8 ? adc_bytes_from<8>(code, lut, (i >> 2) & 7) : adc_bytes_from<16>(code, lut, i & 15));
+        else ords[i] = f32_to_ord(adc_one(code, cf, lut, m, k));
     }
     __syncthreads();
     const uint32_t kth = block_kth_smallest_u32(ords, cnt, (uint32_t)kq, bins, state);
@@ -1425,7 +1447,8 @@ int launch_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, co
     while (n2 < cnt) n2 <<= 1;
     const int cb = cf == PQ_CODES_U4_PACKED ? m / 2 : m;
     const int staged = staged_floats(n2, m, k);
-    qmax_prescan_kernel<<<nq, n2 >= 2048 ? 1024 : (n2 >= 1024 ? 512 : 256), (size_t)n2 * 8 + (size_t)staged * 4, ctx->stream>>>(codes, cnt, cb, cf, luts, m, k, kq, n2, staged, row_order, qmax_out);
+    auto kernel = row_order ? qmax_prescan_kernel<true> : qmax_prescan_kernel<false>;
+    kernel<<<nq, n2 >= 2048 ? 1024 : (n2 >= 1024 ? 512 : 256), (size_t)n2 * 8 + (size_t)staged * 4, ctx->stream>>>(codes, cnt, cb, cf, luts, m, k, kq, n2, staged, qmax_out);
     PQ_HIP(ctx, hipGetLastError());
     return PQ_OK;
 }
