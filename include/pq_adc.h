@@ -167,8 +167,8 @@ int pq_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, pq_code_fmt cf
  * and n < 65536 from a table on that the row number gives, else in table order, so a query's
  * result does not depend on the other queries of the call, on topk or on the entry point.  Sums that
  * are NaN or plus infinity are no results (padding where fewer than topk others exist).  For k = 256,
- * m = 8 or 16 and n >= 65536 (n >= 8192 for up to four queries, and for some calls of long results or,
- * with m = 16, of many queries: where it is faster) the kernel first dismisses codes by integer lower bounds of their
+ * m = 8 or 16 and n >= 65536 (n >= 8192 for some calls of long results or, with m = 16, of many
+ * queries: where it is faster) the kernel first dismisses codes by integer lower bounds of their
  * distances (the pruning idea of Section 4.2: small quantised tables, exact distances only
  * for the codes they cannot rule out) and forms float sums only for the rest; the result is
  * that of the plain definition.  The bounds are 16-bit sums for 8 queries per pass over the

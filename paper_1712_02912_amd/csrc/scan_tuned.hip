@@ -151,8 +151,7 @@ constexpr int exact_bins(int tables) { return tables == 16 ? HIST_BINS - 1 : HIS
 constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bound of a float scan of many query groups
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
-constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan (but see PRUNE_FEW_N)
-constexpr int64_t PRUNE_FEW_N = 1 << 13;   // from here on some calls are pruned too: few queries, long results, many queries on 16 tables
+constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan, but for some calls (see launch_scan_tuned)
 constexpr int64_t U4_SEED_MIN_N = 512;     // the integer scan takes a first bound from here on
 constexpr int PRUNE_INIT = 4096;           // codes looked at for the first bound of every query
 constexpr int PRUNE_MARGIN = 8;      // slack of the integer threshold, in table units
@@ -1240,8 +1239,11 @@ void scan_tuned_kernel(TunedArgs a) {
         }
         __syncthreads();
 
-        auto flush_pruned = [&](int count) -> int {   // (a function for each order)
-            return a.rotated ? scan_flush_pruned<SM, NT, E, QB, true>(smp, wave_buf, count) : scan_flush_pruned<SM, NT, E, QB, false>(smp, wave_buf, count);
+        auto flush_pruned = [&](int count) -> int {
+            // (a function for each order; the forms that no smaller database takes have one: 8 tables with short lists, inverted lists)
+            if constexpr (!PQ_TUNED_ITEMS_ONLY && (NT == 16 || E == E_LARGE))
+                if (a.rotated) return scan_flush_pruned<SM, NT, E, QB, true>(smp, wave_buf, count);
+            return scan_flush_pruned<SM, NT, E, QB, false>(smp, wave_buf, count);
         };
         PQ_TICK(TICK_SETUP);
         const int nvalid_q = sm.nvalid;
@@ -2260,28 +2262,27 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     const bool u4_m32 = kind == KIND_U4_M32, is_u4 = kind == KIND_U4_M16 || u4_m32;
     // The 8 x 256 float scan prunes with 16-bit lower bounds when the database is large enough to
     // pay for the preparation (a bound per query from the first PRUNE_INIT codes, then the tables).
-    // Between PRUNE_FEW_N and PRUNE_MIN_N codes the bound's slices take 6 us where the plain loop's bound takes 16 to 24, and the
-    // tables' preparation 10.  Times of the plain loop over those of the pruned one, codes of encoded vectors, 8192 to 65 535 of
-    // them (3231 calls; of the 1741 that the lines below let through 6 lose 5 % and more, and their mean is 1.23, that of the others 1.0):
-    //   up to 4 queries       0.98 to 1.76 (8192 codes 0.98 to 1.22; 30 000 codes, 8 tables, one query, top-100 45.5 -> 40.3 us)
-    //   8 tables, more        gains once the plain loop has more items than blocks, 2^22 pairs (100 queries, top-512: 36 000 codes 0.97,
-    //                         45 000 1.56; 248 queries: 16 000 0.86, 20 000 1.48), or results so long that the bound from its 4096
-    //                         codes lets most of a list through (16 queries, 30 000 codes: top-896 0.92, top-1000 1.29), and
-    //                         until the pruned loop has more items than blocks itself (248 queries: 45 000 codes 1.58, 55 000 0.86)
-    //   8 tables, 8-bit       (249 queries and more) 249: 0.54 to 1.15, 512: 0.72 to 1.49, 600 and top-768 on 0.92 to 1.49, 1000 1.04 to 1.35
-    //   16 tables             up to 128 queries: top-512 on 30 000 codes 0.91 to 1.11, 45 000 0.98 to 1.57; 129 to 383 queries 0.74 to 1.42;
-    //                         400 queries, top-768 on, 1.00 to 1.29
-    //   16 tables, many       512 queries 0.78 to 1.32; 520 and more 0.88 to 1.5 with 40 codes and more per result, nine in ten above 1.02 (400 results of
-    //                         10 000 codes 0.90)
+    // Smaller databases: the plain loop needs no tables prepared (10 us), and its first bound comes from 4096 codes in one launch; it
+    // falls behind where its lists are long or where it has more items than blocks and the pruned loop has not.  Time of the
+    // plain loop over that of the pruned one, codes of encoded vectors, 4800 calls of 8192 to 65 535 codes and 1 to 1000 queries (the
+    // 659 that the lines let through 1.24 on average, six of them below 0.95; the others 0.86):
+    //   up to 4 queries, 512 results and more, 64 codes per result           0.97 to 1.91, mean 1.21 (top-100 0.85 to 1.05)
+    //   8 tables, below 249 queries, top-1000 on, up to 3 * 2^22 pairs       1.04 to 1.94, mean 1.40 (top-768 0.71 to 1.2; 248 queries, 55 000 codes 0.91)
+    //   8 tables, below 249 queries, top-512 on, 2^22 to 3 * 2^22 pairs      0.93 to 2.29, mean 1.43 (fewer pairs 0.65 to 1.05)
+    //   8 tables, 600 queries and more, top-1000 on                          0.95 to 1.37, mean 1.12 (top-512 0.67 to 1.28; 249 to 520 queries 0.45 to 1.46)
+    //   16 tables, below 249 queries, top-768 on, 2^22 to 3 * 2^21 pairs     1.16 to 1.45, mean 1.25 (30 000 codes, 248 queries 0.74)
+    //   16 tables, 600 queries and more, top-100 on, 24 576 codes and more   0.89 to 1.38, mean 1.11 (top-1 0.8 to 1.0, 20 000 codes 0.85 to 1.1)
     // The fixed scratch keeps to the plain loop, whose lists are half as long.  Both loops give the same bits here (a.rotated).
     const int64_t pairs = n * nq;
-    bool prune_small = nq <= 4;
-    if (!prune_small && kind == KIND_F32_M8)
-        prune_small = n >= 24 * (int64_t)topk && ((nq + 7) / 8 < STREAM_GROUPS ? pairs < 3 << 22 && (topk >= 1000 || (topk >= 512 && pairs >= 1 << 22)) : nq >= 600 && topk >= 768);
-    else if (!prune_small)
-        prune_small = nq > 512 ? n >= 40 * (int64_t)topk
-                               : topk >= 512 && (nq <= 128 ? n >= 40960 : nq >= 384 && topk >= 768 && n >= 24 * (int64_t)topk);
-    prune_small = prune_small && n >= PRUNE_FEW_N && !ctx->ws_fixed;
+    const bool few = (nq + 7) / 8 < STREAM_GROUPS;
+    bool prune_small = false;
+    if (kind == KIND_F32_M16 && nq >= 600) prune_small = topk >= 100 && n >= 3 << 13;
+    else if (topk < 512 || n < 16 * (int64_t)topk) prune_small = false;
+    else if (nq <= 4 && n >= 64 * (int64_t)topk) prune_small = true;
+    else if (!few) prune_small = nq >= 600 && topk >= 1000;
+    else if (kind == KIND_F32_M8) prune_small = pairs < 3 << 22 && (topk >= 1000 || pairs >= 1 << 22);
+    else prune_small = topk >= 768 && pairs >= 1 << 22 && pairs < 3 << 21;
+    prune_small = prune_small && !ctx->ws_fixed;
     const bool prune = (kind == KIND_F32_M8 || kind == KIND_F32_M16) && (n >= PRUNE_MIN_N || prune_small) && opt_int(ctx, PQ_OPT_SCAN_PRUNE, 1) != 0;
     const int tables = kind == KIND_F32_M16 ? 16 : 8;
     // eight tables and too many queries for the streaming shape (32 groups of 8 and more, i.e. 249 queries): 8-bit
@@ -2450,6 +2451,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     a.qtabs = nullptr; a.prune_off = nullptr; a.prune_scale = nullptr; a.pair_min = nullptr;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
     a.rotated = prune && n < PRUNE_MIN_N;
+    if (a.rotated && tables == 8 && small) return fail(ctx, PQ_EINVAL, "scan: no kernel of 8 tables with short lists adds in the plain loop's order");
     float *tau0 = nullptr;
     if (prune) {
         tau0 = (float *)(ws + off_tau0);

@@ -1161,7 +1161,7 @@ def test_scan_f32_one_order_of_additions_whatever_the_batch(ctx, opts, m, n, kin
     opts.set("scan_prune", 0)
     want_v, want_i = scan(600, 1024)
     opts.set("scan_prune", 1)
-    for nq, topk in [(1, 1), (1, 100), (1, 511), (1, 1024), (4, 100), (5, 100), (5, 341), (5, 512), (40, 1000), (100, 512), (300, 512), (400, 800), (512, 100), (513, 100), (600, 1024)]:
+    for nq, topk in [(1, 1), (1, 100), (1, 511), (1, 1024), (4, 100), (5, 100), (2, 512), (5, 341), (5, 512), (40, 1000), (100, 512), (150, 800), (300, 512), (400, 800), (512, 100), (600, 100), (600, 1024)]:
         v, i = scan(nq, topk)
         assert np.array_equal(v, want_v[:nq, :topk]) and np.array_equal(i, want_i[:nq, :topk]), (nq, topk)
     for nq, topk in [(1, 1), (1, 100), (4, 100), (5, 128)]:
