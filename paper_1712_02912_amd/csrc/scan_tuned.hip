@@ -1273,7 +1273,8 @@ void scan_tuned_kernel(TunedArgs a) {
                 const float t = floorf((ord_to_f32(eff) - sm.prune_off[ql]) * sc) + (float)(Q8 ? PRUNE_MARGIN_Q8 : PRUNE_MARGIN);
                 eff = ql < nvalid_q && sc >= 0.f ? (uint32_t)fmaxf(fminf(t, Q8 ? 127.f : 32767.f), 0.f) : 0u;
             } else {
-                eff = __float_as_uint(ord_to_f32(eff));
+                // (ordered as bits, minus zero comes before zero, compared as numbers it does not: a threshold of zero must let it pass)
+                eff = __float_as_uint(ord_to_f32(eff == f32_to_ord(0.f) ? eff + 1u : eff));
             }
 #pragma unroll
             for (int p = 0; p < 4; ++p) {

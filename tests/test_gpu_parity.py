@@ -1194,12 +1194,13 @@ def test_scan_f32_tables_that_cancel(ctx, m, n, nq, topk, shift):
         assert np.array_equal(v[q], want[order]) and np.array_equal(i[q], order), q
 
 
-@pytest.mark.parametrize("kind", ["both_infinities", "minus_infinity", "nan_with_sign", "nan_rows"])
+@pytest.mark.parametrize("kind", ["both_infinities", "minus_infinity", "nan_with_sign", "nan_rows", "minus_zero"])
 @pytest.mark.parametrize("m", [4, 8, 16])
 @pytest.mark.parametrize("n,nq,topk", [(100, 3, 20), (4096, 5, 100), (4200, 2, 1000), (9001, 4, 1), (20_001, 600, 300), (33_000, 40, 1000), (66_000, 5, 1), (70_000, 300, 100), (300_001, 2, 1024)])
 def test_scan_f32_sums_that_are_no_numbers(ctx, m, n, nq, topk, kind):
     """Tables with infinities of both signs and with NaN of either sign: the result holds the smallest sums that are numbers, minus
-    infinity among them, no NaN and nothing at plus infinity, and neither takes the place of a sum in a first bound."""
+    infinity among them, no NaN and nothing at plus infinity, and neither takes the place of a sum in a first bound.  Sums of minus
+    zero are results like others."""
     r = np.random.default_rng(n + m)
     codes = r.integers(0, 256, (n, m), dtype=np.uint8)
     tables = (r.random((nq, m, 256)) * 100).astype(np.float32)
@@ -1215,6 +1216,8 @@ def test_scan_f32_sums_that_are_no_numbers(ctx, m, n, nq, topk, kind):
         tables[:, 0, 1:] = np.copysign(np.float32(np.nan), np.float32(-1))
         codes[:, 0] = np.maximum(codes[:, 0], 1)
         codes[r.permutation(n)[:50], 0] = 0
+    if kind == "minus_zero":
+        tables[:] = -0.0
     v, i = [host(t) for t in ctx.pq_adc_scan_topk(dev(codes), binding.CODES_U8, dev(tables), topk)]
     rows = np.arange(n)
     first = (0 if n >= 65_536 or m == 4 else rows >> 2 if m == 8 else rows) + np.zeros(n, np.int64)
