@@ -105,7 +105,7 @@ struct TunedArgs {
     // (two 16-byte halves of 8 queries each), for the second test of the insert path, and their scale per query
     const uint4 *qtabs16;
     const float *prune_scale16;
-    int rotated;   // pruned flat scan: candidates are added up in the order of the plain loop (see scan_flush_pruned)
+    bool rotated;   // pruned flat scan: candidates are added up in the order of the plain loop (see scan_flush_pruned)
 };
 
 int launch_merge_topk(pq_ctx *ctx, const uint64_t *partial, int nchunks, int ngroups, int qb, int kpad, int nq,

@@ -939,7 +939,8 @@ __device__ __noinline__ void scan_merge_item(LDS_PTR(SM) sm, uint64_t *block_scr
 #endif
 enum { TICK_SETUP = 0, TICK_LOOP, TICK_FLUSH, TICK_REFRESH, TICK_EMIT, TICK_OVERFLOW, TICK_COUNT };
 
-template <int KIND, int E, int KPAD, int DEPTH>
+// ROTATED: the pruned scans of smaller databases (see scan_flush_pruned)
+template <int KIND, int E, int KPAD, int DEPTH, bool ROTATED = false>
 __global__ __launch_bounds__(TUNED_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void scan_tuned_kernel(TunedArgs a) {
     constexpr bool IS_U4 = KIND == KIND_U4_M16 || KIND == KIND_U4Q_M16 || KIND == KIND_U4_M32;   // values are integer sums
@@ -1239,12 +1240,6 @@ void scan_tuned_kernel(TunedArgs a) {
         }
         __syncthreads();
 
-        auto flush_pruned = [&](int count) -> int {
-            // (a function for each order; the forms that no smaller database takes have one: 8 tables with short lists, inverted lists)
-            if constexpr (!PQ_TUNED_ITEMS_ONLY && (NT == 16 || E == E_LARGE))
-                if (a.rotated) return scan_flush_pruned<SM, NT, E, QB, true>(smp, wave_buf, count);
-            return scan_flush_pruned<SM, NT, E, QB, false>(smp, wave_buf, count);
-        };
         PQ_TICK(TICK_SETUP);
         const int nvalid_q = sm.nvalid;
         int ring_cnt = 0;                  // positions parked in this wave's ring (uniform)
@@ -1388,7 +1383,7 @@ void scan_tuned_kernel(TunedArgs a) {
                 const int take = ring_cnt > RING_FLUSH ? (ring_cnt & ~63) : ring_cnt;
                 parked_total += (unsigned long long)take;
                 int appended;
-                if constexpr (PRUNED) appended = flush_pruned(take);
+                if constexpr (PRUNED) appended = scan_flush_pruned<SM, NT, E, QB, ROTATED>(smp, wave_buf, take);
                 else if constexpr (U4Q) appended = scan_flush_u4q<SM, E>(smp, wave_buf, take);
                 else appended = scan_flush<SM, KIND, E>(smp, wave_buf, take);
                 // 8-bit bounds park many codes that turn out to be none: there only the keys count
@@ -1462,7 +1457,7 @@ void scan_tuned_kernel(TunedArgs a) {
         PQ_TICK(TICK_LOOP);
         if (ring_cnt > 0) {
             parked_total += (unsigned long long)ring_cnt;
-            if constexpr (PRUNED) flush_pruned(ring_cnt);
+            if constexpr (PRUNED) scan_flush_pruned<SM, NT, E, QB, ROTATED>(smp, wave_buf, ring_cnt);
             else if constexpr (U4Q) scan_flush_u4q<SM, E>(smp, wave_buf, ring_cnt);
             else scan_flush<SM, KIND, E>(smp, wave_buf, ring_cnt);
         }
@@ -2114,7 +2109,15 @@ __global__ __launch_bounds__(PRUNE_TABLES_THREADS) void prune_tables_kernel(cons
 
 template <int KIND, int E, int KPAD, int DEPTH>
 static int launch_kind(pq_ctx *ctx, const TunedArgs &a, int nblocks) {
-    scan_tuned_kernel<KIND, E, KPAD, DEPTH><<<nblocks, TUNED_THREADS, 0, ctx->stream>>>(a);
+    // (kernels of their own for the other order: with both in one, the registers that the insert path needs made 86 724 codes of 16 bytes,
+    // 5 queries 54.5 -> 55.9 us)
+    constexpr bool ROTATED = !PQ_TUNED_ITEMS_ONLY && DEPTH == 2 && (KIND == KIND_F32P_M16 || (E == E_LARGE && (KIND == KIND_F32P_M8 || KIND == KIND_F32Q_M8)));
+    if (a.rotated) {
+        if constexpr (ROTATED) scan_tuned_kernel<KIND, E, KPAD, DEPTH, true><<<nblocks, TUNED_THREADS, 0, ctx->stream>>>(a);
+        else return fail(ctx, PQ_EINVAL, "scan: no kernel of this form adds in the plain loop's order");
+    } else {
+        scan_tuned_kernel<KIND, E, KPAD, DEPTH><<<nblocks, TUNED_THREADS, 0, ctx->stream>>>(a);
+    }
     PQ_HIP(ctx, hipGetLastError());
     return PQ_OK;
 }
@@ -2237,7 +2240,7 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
     a.nprobe = nprobe;
     a.qtabs = nullptr; a.prune_off = pair_off; a.prune_scale = pair_scale; a.pair_min = pair_min;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
-    a.rotated = 0;
+    a.rotated = false;
     tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, nq,
                                                      0xff800000u, a.hist, L.nhist, tau0, nq);
     PQ_HIP(ctx, hipGetLastError());
@@ -2285,6 +2288,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     else prune_small = topk >= 768 && pairs >= 1 << 22 && pairs < 3 << 21;
     prune_small = prune_small && !ctx->ws_fixed;
     const bool prune = (kind == KIND_F32_M8 || kind == KIND_F32_M16) && (n >= PRUNE_MIN_N || prune_small) && opt_int(ctx, PQ_OPT_SCAN_PRUNE, 1) != 0;
+    const bool rotated = prune && n < PRUNE_MIN_N;   // (fine tiles, and with 8 tables long lists: see launch_kind)
     const int tables = kind == KIND_F32_M16 ? 16 : 8;
     // eight tables and too many queries for the streaming shape (32 groups of 8 and more, i.e. 249 queries): 8-bit
     // lower bounds, 16 queries per pass (PQ_SCAN_Q8=0: 16-bit lower bounds, 8 queries per pass).  Measured on 25 M
@@ -2325,7 +2329,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // queries, are better off on all blocks.)
     const bool long_lists = spread && !small && few_groups && nq > 2 && ngroups <= 4 && n >= (int64_t)1 << (ngroups <= 2 ? 19 : 21) &&
                             n * cb < (int64_t)1 << (cb == 16 && !is_u4 ? 28 : 27);
-    const bool stream = few_groups && (!spread || n <= fine_tile || large || long_lists);   // (a single fine tile: nothing to spread)
+    const bool stream = few_groups && !rotated && (!spread || n <= fine_tile || large || long_lists);   // (a single fine tile: nothing to spread)
     const int tile = 64 * (16 / cb) * (stream ? 8 : 2);   // codes per wave group (DEPTH sub-tiles)
     const int64_t block_tile = (int64_t)tile * TUNED_WAVES;
 
@@ -2451,8 +2455,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
 
     a.qtabs = nullptr; a.prune_off = nullptr; a.prune_scale = nullptr; a.pair_min = nullptr;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
-    a.rotated = prune && n < PRUNE_MIN_N;
-    if (a.rotated && tables == 8 && small) return fail(ctx, PQ_EINVAL, "scan: no kernel of 8 tables with short lists adds in the plain loop's order");
+    a.rotated = rotated;
     float *tau0 = nullptr;
     if (prune) {
         tau0 = (float *)(ws + off_tau0);
@@ -2480,7 +2483,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             auto tables_of = tables == 8 ? prune_tables_kernel<8, 8> : prune_tables_kernel<16, 8>;
             auto seed_of = tables == 8 ? f32_seed_hist2_kernel<8> : f32_seed_hist2_kernel<16>;
             seed_of<<<sgrid, 1024, 0, ctx->stream>>>(codes, seed_codes_wide, slice, (const float *)luts, topk, seed_hist, seed_ref, shift);
-            tables_of<<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, nullptr, a.rotated != 0, a.tau_key, a.tau_ref, nq, qtabs, poff, pscale,
+            tables_of<<<dim3(ngroups, PRUNE_TABLES_Y), PRUNE_TABLES_THREADS, 0, ctx->stream>>>((const float *)luts, nullptr, a.rotated, a.tau_key, a.tau_ref, nq, qtabs, poff, pscale,
                                                                  0.f, nullptr, nullptr, seed_hist, seed_ref, topk, shift);
             PQ_HIP(ctx, hipGetLastError());
         } else {
