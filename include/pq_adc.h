@@ -87,6 +87,8 @@ const char *pq_version(void);
  *                             where short lists have their kernel, else the latter)
  *   ivf_ws_gib (24)           workspace limit of ivf_adc_search in GiB (1 ... 128)
  *   ivf_block_waves (8)       16: inverted lists scanned by blocks of 16 waves
+ *   scan_onehot               0: scans of packed 4-bit codes never on the matrix cores, 1: wherever they are served there (2^16 codes
+ *                             and 32 per result); unset: where that pays
  *   scan_wide_seed (1)        0: first bounds of flat scans of few queries from the small sample only
  *   ivf_short_max (12288)     inverted lists of fewer codes take the kernel for short lists (0: none)
  *   ivf_coarse_f32 (1)        0: Index step of ivf_adc_search from exact distances to every list (default: lists

@@ -523,18 +523,29 @@ __global__ __launch_bounds__(1024) void merge_topk_kernel(const uint64_t *partia
 // and 2048 keys (512 threads and 4096 keys for topk above 512), of which a compute unit holds several.
 constexpr int MERGE_COUNT = 256;   // as many kept keys find their ranks by counting, without a selection before
 constexpr int merge_lds_bytes(int cap) { return cap * 8 + cap * 4 + 1024 * 8; }   // kept keys, 32-bit values for the selection, the result's keys
-template <bool VAL_U32, int MERGE_CAP>
+enum { MERGE_LISTS, MERGE_COUNTED, MERGE_IF_FLAGGED };   // (kernels of their own: 1 us of a call that wants neither counts nor flag)
+template <bool VAL_U32, int MERGE_CAP, int MODE = MERGE_LISTS>
 __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__restrict__ partial,
                                                               const uint32_t *__restrict__ qlist_off, int nchunks,
                                                               int ngroups, int qb,
                                                               const unsigned long long *__restrict__ tau_key, int kpad, int topk,
                                                               const int64_t *__restrict__ ids, void *out_val,
                                                               int64_t *out_ids, const uint32_t *__restrict__ hist,
-                                                              const uint32_t *__restrict__ hist_ref, int hist_bins) {
+                                                              const uint32_t *__restrict__ hist_ref, int hist_bins,
+                                                              const uint32_t *__restrict__ counts, uint32_t cap, uint32_t *flag) {
     extern __shared__ uint64_t skeys[];
     __shared__ int s_count;
+    constexpr bool COUNTED = MODE == MERGE_COUNTED;
+    if (MODE == MERGE_IF_FLAGGED && *flag == 0u) return;
     const int gq = blockIdx.x, tid = threadIdx.x;
-    const size_t nlists = qlist_off ? (size_t)(qlist_off[gq + 1] - qlist_off[gq]) : (size_t)nchunks;
+    // (with counts a query has one list of up to cap keys, read as if it were lists of 64)
+    uint32_t listed = 0;
+    if constexpr (COUNTED) {
+        const uint32_t c = counts[(size_t)gq * COUNT_PITCH];
+        if ((c < (uint32_t)topk || c > cap) && tid == 0) *flag = 1u;
+        listed = c < cap ? c : cap;
+    }
+    const size_t nlists = COUNTED ? (size_t)((listed + 63u) / 64u) : qlist_off ? (size_t)(qlist_off[gq + 1] - qlist_off[gq]) : (size_t)nchunks;
     // Every list is packed (its keys first, KEY_EMPTY behind them; kpad is a multiple of 64): a wave
     // takes whole lists, 64 keys at a time, and leaves a list at the first empty slot it sees.
     const int wave = tid >> 6, lane = tid & 63, nwaves = (int)(blockDim.x >> 6);
@@ -542,6 +553,7 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
     // pieces at a time: otherwise a walk over a thousand short lists, or the 16 pieces of a full list of 1024 keys, is a chain of
     // memory round trips.  8 queries, 24 lists of up to 1024 keys each: 271 -> 79 us with the selections below.)
     auto list_ptr = [&](size_t l) {
+        if constexpr (COUNTED) return partial + (size_t)gq * cap + l * 64;
         const size_t list = qlist_off ? (size_t)qlist_off[gq] + l : (l * ngroups + gq / qb) * qb + gq % qb;
         return partial + list * kpad;
     };
@@ -550,7 +562,7 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
 #pragma unroll
         for (int u = 0; u < MLP; ++u) {
             const size_t l = l0 + (size_t)u * nwaves;
-            first[u] = l < nlists ? list_ptr(l)[lane] : KEY_EMPTY;
+            first[u] = l < nlists && (!COUNTED || (uint32_t)l * 64u + (uint32_t)lane < listed) ? list_ptr(l)[lane] : KEY_EMPTY;
         }
     };
     auto for_each_key = [&](auto &&f, uint64_t (&first)[MLP], bool loaded) {
@@ -741,18 +753,25 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
 
 int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *qlist_off, int nchunks, int ngroups, int qb,
                           const unsigned long long *tau_key, int kpad, int nq, int topk, const int64_t *ids, bool val_u32,
-                          void *out_val, int64_t *out_ids, const uint32_t *hist, const uint32_t *hist_ref, int hist_bins) {
+                          void *out_val, int64_t *out_ids, const uint32_t *hist, const uint32_t *hist_ref, int hist_bins,
+                          const uint32_t *counts, uint32_t list_cap, uint32_t *flag) {
     if (nq == 0) return PQ_OK;
     // (the histograms' bound: 16 KB read per query; with many queries the keys are fewer and the selection is the shorter way:
     // 1000 queries, top-100 34 us without, 44 with)
     auto launch = [&](auto kernel, int cap, int threads, const uint32_t *hist = nullptr) -> int {
         PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, merge_lds_bytes(cap)));
-        kernel<<<nq, threads, merge_lds_bytes(cap), ctx->stream>>>(partial, qlist_off, nchunks, ngroups, qb, tau_key, kpad, topk, ids, out_val, out_ids, hist, hist_ref, hist_bins);
+        kernel<<<nq, threads, merge_lds_bytes(cap), ctx->stream>>>(partial, qlist_off, nchunks, ngroups, qb, tau_key, kpad, topk, ids, out_val, out_ids, hist, hist_ref, hist_bins, counts, list_cap, flag);
         PQ_HIP(ctx, hipGetLastError());
         return PQ_OK;
     };
     // calls of many queries: several smaller blocks per compute unit (room for at least four times topk keys)
     const bool many = nq >= 2 * ctx->num_cu;
+    if (counts != nullptr) {   // (integer sums only)
+        if (many && topk <= 512) return launch(merge_filtered_kernel<true, 2048, MERGE_COUNTED>, 2048, 256);
+        if (many) return launch(merge_filtered_kernel<true, 4096, MERGE_COUNTED>, 4096, 512);
+        return launch(merge_filtered_kernel<true, 8192, MERGE_COUNTED>, 8192, 1024);
+    }
+    if (flag != nullptr) return launch(merge_filtered_kernel<true, 8192, MERGE_IF_FLAGGED>, 8192, 1024, hist);
     if (many && topk <= 512) {
         if (val_u32) return launch(merge_filtered_kernel<true, 2048>, 2048, 256);
         return launch(merge_filtered_kernel<false, 2048>, 2048, 256);

@@ -34,6 +34,7 @@
 
 #include "pq_internal.h"
 #include "scan_common.h"
+#include "scan_onehot.h"
 #include "topk_device.h"
 #include "lds_walk.h"
 
@@ -149,6 +150,7 @@ enum { KIND_F32_M8 = 0, KIND_F32_M16 = 1, KIND_U4_M16 = 2, KIND_F32P_M8 = 3, KIN
 // and a bound that falls into it is none.
 constexpr int exact_bins(int tables) { return tables == 16 ? HIST_BINS - 1 : HIST_BINS; }   // (tables after merging: 8 or 16)
 constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bound of a float scan of many query groups
+constexpr int ONEHOT_FLAG = 48;                // word of the state: some list of the scan on the matrix cores is too short or too long
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
 constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan, but for some calls (see launch_scan_tuned)
@@ -1517,12 +1519,13 @@ void scan_tuned_kernel(TunedArgs a) {
 __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *tau_key, uint32_t *ncand, uint32_t *mark,
                                   uint32_t *tau_ref, int ntau,
                                   uint32_t tau_value, uint32_t *hist, size_t nhist, const float *tau0, int nq,
-                                  uint32_t *also_zero = nullptr, size_t also_zero_n = 0) {
+                                  uint32_t *also_zero = nullptr, size_t also_zero_n = 0, uint32_t *zero_too = nullptr, size_t zero_too_n = 0) {
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     if (i0 == 0) {
         *work_counter = 0;
         for (int i = 2; i < 32; ++i) work_counter[i] = 0;   // the 64-bit statistics words behind it
+        work_counter[ONEHOT_FLAG] = 0;
     }
     for (size_t i = i0; i < (size_t)ntau; i += stride) {
         const bool seeded = tau0 != nullptr && i < (size_t)nq && tau0[i] < __builtin_inff();
@@ -1533,6 +1536,19 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
     }
     for (size_t i = i0; i < nhist; i += stride) hist[i] = 0;
     for (size_t i = i0; i < also_zero_n; i += stride) also_zero[i] = 0;   // (the bins of a first-bound pass that follows)
+    for (size_t i = i0; i < zero_too_n; i += stride) zero_too[i] = 0;
+}
+
+// The state of a scan on the matrix cores made ready for another scan, from those of its bounds that are, or for none (*only_if is 0).
+__global__ void rescan_reset_kernel(const uint32_t *only_if, uint32_t *work_counter, unsigned long long *tau_key, const uint32_t *cnt, uint32_t *ncand, int nq, int topk, int ntau, uint32_t *hist, size_t nhist) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    if (i0 == 0) *work_counter = *only_if == 0u ? 0x40000000u : 0u;   // (beyond any item: the scan has nothing to do)
+    if (*only_if == 0u) return;
+    for (size_t i = i0; i < (size_t)ntau; i += stride) {
+        if (i < (size_t)nq && cnt[i * COUNT_PITCH] < (uint32_t)topk) tau_key[i] = 0x7fffull << 32 | 0xffffffffull;   // (no bound then)
+        ncand[i] = 0;
+    }
+    for (size_t i = i0; i < nhist; i += stride) hist[i] = 0;
 }
 
 // First bound of the integer scan: one block per SEED_QPB queries adds up the 8-bit table entries of the
@@ -1542,8 +1558,9 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
 // entries of the block's queries for one code byte (both of its components added) are one 8-byte LDS
 // read, and their sums add up as four 16-bit fields of a 64-bit word.
 constexpr int SEED_QPB = 4;
-template <int NT>   // code bytes = pair-merged tables, 8 or 16
-__global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict__ codes, int cnt,
+// (STRIDED: the codes are taken in runs of 1024 bytes, of which only every stride-th counts)
+template <int NT, bool STRIDED>   // code bytes = pair-merged tables, 8 or 16
+__global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict__ codes, int cnt, int stride,
                                                        const uint8_t *__restrict__ qluts, int kq, int nq, unsigned long long *tau_key) {
     static_assert(HIST_BINS == 4096, "sums of 16 bytes index the bins");
     constexpr uint32_t BINS = (uint32_t)exact_bins(NT);   // cuts from there on are none
@@ -1574,7 +1591,10 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
         __syncthreads();
     };
     struct Code { uint32_t w[NT / 4]; };
-    auto load_code = [&](int i) {
+    constexpr int RUN = 1024 / NT;
+    auto row_of = [&](int i) -> uint32_t { return STRIDED ? (uint32_t)(i / RUN) * (uint32_t)(stride * RUN) + (uint32_t)(i % RUN) : (uint32_t)i; };
+    auto load_code = [&](int at) {
+        const size_t i = row_of(at);
         Code c;
         if constexpr (NT == 8) {
             const uint2 v = *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8);
@@ -1676,7 +1696,7 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
         const int nb = (cnt + 1023) / 1024;
         while (b < nb && cum + tie_cnt[myq][b] < need_s[myq]) cum += tie_cnt[myq][b++];
         if (b < nb) {
-            const uint32_t last_row = (uint32_t)((b + 1) * 1024 < cnt ? (b + 1) * 1024 : cnt) - 1u;
+            const uint32_t last_row = row_of(((b + 1) * 1024 < cnt ? (b + 1) * 1024 : cnt) - 1);
             tau_key[q0 + myq] = ((unsigned long long)cut_s[myq] << 32) | last_row;
         }
     }
@@ -2379,6 +2399,24 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
 
     const int ntau = ngroups * qb;
     const StateLayout L = state_layout(qb, ntau, cap, nblocks);
+    // (the lists of the scan on the matrix cores lie where the loops above have their waves' lists)
+    const size_t onehot_words = (size_t)nq * COUNT_PITCH + onehot_tie_words(nq), onehot_state = align_up(onehot_words * 4, 256);
+    int64_t onehot_cap = L.total - L.off_scratch > onehot_state ? (int64_t)((L.total - L.off_scratch - onehot_state) / ((size_t)nq * 8)) / 64 * 64 : 0;
+    if (onehot_cap > (small ? 16384 : 65536)) onehot_cap = small ? 16384 : 65536;
+    // It has a sample and a set-up of some 150 us to pay for, and it is twice as fast per (code, query) where the other loops serve 16
+    // queries per pass, three times where they serve 8.  Time of the other loop over its own, encoded codes of 0.1 to 25 M vectors, 16 to
+    // 1000 queries, top-10, -100 and -1000 (just above and below the lines; P: pairs, those of 32 tables counted twice):
+    //   249 queries and more, P from 2^28 on          0.95 to 2.1   (300 000 codes, 400 queries, top-10 and -100: 0.84)
+    //   the same, long results, 2^18 codes and more   1.4 to 2.9    (100 000 codes 0.9; short results 0.7 to 1.0)
+    //   24 to 248 queries, P from 11 * 2^26 on        1.0 to 1.75   (3 M codes, 128 queries 0.81 to 0.93; 10 M, 64 1.05 to 1.3)
+    //   16 to 248, long results, 2^23 codes, P 2^28   1.0 to 1.36   (3 M codes, 64 queries 0.98; 25 M, 8 queries 0.92)
+    const int64_t onehot_pairs = pairs * (cb / 8);
+    bool onehot = false;
+    if (is_u4 && n >= PRUNE_MIN_N && n >= 32 * (int64_t)topk && onehot_cap >= 4096 && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0) {
+        if (opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 0) > 0) onehot = true;
+        else if (nq >= 249) onehot = onehot_pairs >= (int64_t)1 << 28 || (!small && n >= 1 << 18);
+        else onehot = (nq >= 24 && onehot_pairs >= (int64_t)11 << 26) || (nq >= 16 && !small && n >= 1 << 23 && onehot_pairs >= (int64_t)1 << 28);
+    }
     const size_t off_partial = align_up(L.total, 256);
     const size_t off_tau0 = off_partial + align_up((size_t)nitems * qb * kpad * 8, 256);
     const size_t off_poff = off_tau0 + align_up((size_t)ntau * 4, 256);
@@ -2423,7 +2461,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     // sample: 1 M codes of 32 indexes, 100 queries 126 us of a call of 480 us; now 365).  Small databases take one as well: without a bound
     // every code is a candidate at first (10 000 codes of 16 indexes, 29 queries, top-100: two-pass call 282 -> 81 us).
     const bool seed_u4 = is_u4 && n >= U4_SEED_MIN_N && n >= 2 * (int64_t)topk;
-    bool wide_seed_u4 = wide_ok && seed_u4 && few_groups;
+    bool wide_seed_u4 = wide_ok && seed_u4 && few_groups && !onehot;
     const int64_t seed_codes_u4 = seed_codes_f32 > SEED_SLICE ? seed_codes_f32 : seed_codes_few;
     const int seed_slice_u4 = seed_codes_f32 > SEED_SLICE ? SEED_SLICE : SEED_SLICE / 8;
     if (wide_seed && ctx->ws_fixed && align_up(off_qtabs + (size_t)ngroups * 256 * tables * sizeof(uint4), 256) + (size_t)nq * (HIST_BINS + 1) * 4 + 1024 > ctx->ws_bytes)
@@ -2514,7 +2552,8 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     if (!prune) {   // (the pruned scans' state has been cleared and seeded above)
         uint32_t *seed_hist_u4 = wide_seed_u4 ? (uint32_t *)(ws + off_seedhist) : nullptr;
         tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
-                                                         is_u4 ? 0x7fffu : 0xff800000u, a.hist, L.nhist, tau0, nq, seed_hist_u4, wide_seed_u4 ? (size_t)nq * 4096 : 0);
+                                                         is_u4 ? 0x7fffu : 0xff800000u, a.hist, L.nhist, tau0, nq, seed_hist_u4, wide_seed_u4 ? (size_t)nq * 4096 : 0,
+                                                         (uint32_t *)a.scratch, onehot ? onehot_words : 0);
         PQ_HIP(ctx, hipGetLastError());
     }
     if (seed_u4) {
@@ -2537,8 +2576,17 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             }
             if ((int64_t)seed_codes > n) seed_codes = (int)n;
             const unsigned seed_blocks = (unsigned)((nq + SEED_QPB - 1) / SEED_QPB);
-            if (u4_m32) u4_seed_kernel<16><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, (const uint8_t *)luts, topk, nq, a.tau_key);
-            else u4_seed_kernel<8><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, (const uint8_t *)luts, topk, nq, a.tau_key);
+            if (onehot) {
+                // a part of the sample that the scan on the matrix cores begins with
+                const int run = 1024 / cb, rank = onehot_rank(n, topk);
+                const int64_t sample_runs = n / ((int64_t)run * onehot_stride(n));   // (whole ones)
+                int64_t runs = 16384 / run;
+                if (runs > sample_runs) runs = sample_runs;
+                const int every = (int)(sample_runs / runs) * onehot_stride(n);
+                if (u4_m32) u4_seed_kernel<16, true><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, (int)runs * run, every, (const uint8_t *)luts, rank, nq, a.tau_key);
+                else u4_seed_kernel<8, true><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, (int)runs * run, every, (const uint8_t *)luts, rank, nq, a.tau_key);
+            } else if (u4_m32) u4_seed_kernel<16, false><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, 1, (const uint8_t *)luts, topk, nq, a.tau_key);
+            else u4_seed_kernel<8, false><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, 1, (const uint8_t *)luts, topk, nq, a.tau_key);
         }
         PQ_HIP(ctx, hipGetLastError());
     }
@@ -2546,6 +2594,33 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         a.stats = (unsigned long long *)(ws + 8);
         note_scan(ctx, kind, qb, ngroups, a.stats, a.ncand, ntau);
         PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, ctx->stream));
+    }
+    if (onehot) {
+        uint32_t *const full = a.work_counter + ONEHOT_FLAG;
+        uint64_t *const lists = (uint64_t *)((uint8_t *)a.scratch + onehot_state);
+        uint32_t *const cnt = (uint32_t *)a.scratch;
+        rc = launch_scan_onehot(ctx, codes, n, cb, (const uint8_t *)luts, nq, topk, exact_bins(cb), a.tau_key, cnt, a.hist, lists,
+                                (uint32_t)onehot_cap, cnt + (size_t)nq * COUNT_PITCH, a.work_counter, a.stats);
+        if (rc) return rc;
+        if (ctx->profiling) {
+            const int width = onehot_queries_per_pass(cb, nq);
+            note_plain_scan(ctx, "scan_onehot_kernel (packed 4-bit codes on the matrix cores, 6-bit lower bounds; with its sample)", width, (nq + width - 1) / width);
+            ctx->stat_parked = a.stats;
+            ctx->stat_ncand = cnt;
+            ctx->stat_ncand_len = nq * COUNT_PITCH;   // (zeros between the counts)
+            PQ_HIP(ctx, hipEventRecord(ctx->ev_end, ctx->stream));
+            ctx->ev_valid = 1;
+        }
+        rc = launch_merge_filtered(ctx, lists, nullptr, 0, 1, 1, a.tau_key, 64, nq, topk, nullptr, true, out_val, out_ids, nullptr, nullptr, 0,
+                                   cnt, (uint32_t)onehot_cap, full);
+        if (rc) return rc;
+        // a list is too short or had no room for its keys: the whole call once more, from the bounds found so far
+        rescan_reset_kernel<<<64, 256, 0, ctx->stream>>>(full, a.work_counter, a.tau_key, cnt, a.ncand, nq, topk, ntau, a.hist, L.nhist);
+        PQ_HIP(ctx, hipGetLastError());
+        rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
+        if (rc) return rc;
+        return launch_merge_filtered(ctx, a.partial, nullptr, (int)nchunks, ngroups, qb, a.tau_key, kpad, nq, topk, nullptr, is_u4,
+                                     out_val, out_ids, a.hist, a.tau_ref, exact_bins(cb), nullptr, 0, full);
     }
     rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
     if (rc) return rc;

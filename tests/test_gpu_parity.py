@@ -743,6 +743,39 @@ def test_scan_u4_few_queries_large_database_wide_first_bound(ctx):
     run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts[:1], 100)
 
 
+# --------------------------------------------- packed 4-bit codes on the matrix cores
+# Sums are integers: results are bit-exact, ties by row.  Sizes around a load of codes (1024 bytes), the groups of 32 queries and the widths
+# of 32, 64 and 128 queries; tables of few values (ties by the thousand) beside ordinary ones, and queries whose codes all tie.
+@pytest.mark.parametrize("m", [16, 32])
+@pytest.mark.parametrize("n,nq,topk", [(65_536, 1, 1), (65_537, 31, 100), (66_001, 33, 129), (70_019, 65, 1000), (131_073, 129, 100), (65_664, 257, 10)])
+def test_scan_u4_on_matrix_cores_sizes(ctx, opts, m, n, nq, topk):
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(n + nq + m)
+    packed = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
+    qluts = np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * r.uniform(5, 60, (nq, m, 1))).astype(np.uint8)
+    qluts[::3] //= 32
+    qluts[0] = 255 if nq > 1 else qluts[0]
+    run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
+
+
+@pytest.mark.parametrize("m", [16, 32])
+@pytest.mark.parametrize("order", ["copies", "ascending", "descending"])
+def test_scan_u4_on_matrix_cores_misleading_samples(ctx, opts, m, order):
+    """Few distinct codes, and codes sorted by their distance: lists that are too short or too long take the other way."""
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(m)
+    qluts = np.repeat(r.integers(0, 256, (1, m, 16), dtype=np.uint8), 40, axis=0)
+    if order == "copies":
+        packed = r.integers(0, 256, (7, m // 2), dtype=np.uint8)[r.integers(0, 7, 150_001)]
+        qluts = r.integers(0, 256, (40, m, 16), dtype=np.uint8)
+    else:
+        packed = r.integers(0, 256, (150_001, m // 2), dtype=np.uint8)
+        nib = np.stack([packed & 15, packed >> 4], 2).reshape(len(packed), m)
+        sums = qluts[0][np.arange(m), nib].astype(np.int64).sum(1)
+        packed = packed[np.argsort(sums if order == "ascending" else -sums)]
+    run_int_scan(ctx, np.ascontiguousarray(packed), orc.CODES_U4_PACKED, qluts, 100)
+
+
 # --------------------------------------------- 8x8 float scan, 8-bit lower bounds, 16 queries per pass
 # 512 queries and more (enough groups of 16 to fill the GPU) take the loop on 8-bit lower bounds; these
 # cases aim at what is specific to it: ragged last group, saturating entries, degenerate ranges, ties.
