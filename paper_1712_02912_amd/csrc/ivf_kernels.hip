@@ -1091,14 +1091,18 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
             PQ_HIP(ctx, hipGetLastError());
         }
         unsigned long long *tau_key = nullptr;
+        // An item has one pair and more, a pair one chunk of its list and one more for every IVF_CHUNK_TARGET rows; the lists of a query
+        // are distinct, so that of short_max rows and more it has as many as fit the index.
+        const size_t long_lists = short_max > 0 && L->ntotal / short_max < nprobe ? (size_t)(L->ntotal / short_max) : (size_t)nprobe;
+        const size_t most_items = (size_t)nqb * (long_lists + (size_t)(L->ntotal / IVF_CHUNK_TARGET));
         rc = w8_blocks ? w8::launch_scan_items(ctx, kind, pmin, poff, pscale, L->codes, luts, nqb, nprobe, topk, items, nitems_dev,
-                                               pairs_by_list, pair_out, partial, ws + o_state, state_bytes, tau0, &tau_key)
+                                               pairs_by_list, pair_out, partial, ws + o_state, state_bytes, tau0, most_items, &tau_key)
                        : w16::launch_scan_items(ctx, kind, pmin, poff, pscale, L->codes, luts, nqb, nprobe, topk, items, nitems_dev,
-                                                pairs_by_list, pair_out, partial, ws + o_state, state_bytes, tau0, &tau_key);
+                                                pairs_by_list, pair_out, partial, ws + o_state, state_bytes, tau0, most_items, &tau_key);
         if (rc) return rc;
         // the short lists after the long ones: by then a query's bound has seen the lists that hold most of its codes
         if (short_max > 0) {
-            rc = launch_ivf_short_scan(ctx, L->codes, luts, short_items, nitems_dev + 1, pair_out, nprobe, topk, tau_key, partial);
+            rc = launch_ivf_short_scan(ctx, L->codes, luts, short_items, nitems_dev + 1, pair_out, nprobe, topk, tau_key, partial, (size_t)npairs);
             if (rc) return rc;
             if (ctx->profiling) {   // the measured "scan kernel" is both kernels
                 PQ_HIP(ctx, hipEventRecord(ctx->ev_end, s));

@@ -256,10 +256,11 @@ __global__ __launch_bounds__(SH_THREADS, 4) void ivf_short_scan_kernel(const uin
 
 int launch_ivf_short_scan(pq_ctx *ctx, const uint8_t *codes, const float *luts, const IvfShortItem *items,
                           const uint32_t *nitems_dev, const uint32_t *pair_out, int nprobe, int topk,
-                          unsigned long long *tau_key, uint64_t *partial) {
+                          unsigned long long *tau_key, uint64_t *partial, size_t most_items) {
     if (topk > SH_KPAD) return fail(ctx, PQ_EUNSUPPORTED, "ivf short scan: topk above %d", SH_KPAD);
     // four blocks per compute unit; items are dealt in a stride of the grid, longest lists first
-    ivf_short_scan_kernel<<<ctx->num_cu * 4, SH_THREADS, 0, ctx->stream>>>(codes, luts, items, nitems_dev, pair_out, nprobe,
+    const size_t full = (size_t)ctx->num_cu * 4;
+    ivf_short_scan_kernel<<<(unsigned)(most_items < full ? most_items : full), SH_THREADS, 0, ctx->stream>>>(codes, luts, items, nitems_dev, pair_out, nprobe,
                                                                           topk, tau_key, partial);
     PQ_HIP(ctx, hipGetLastError());
 #ifdef PQ_SCAN_TIMING

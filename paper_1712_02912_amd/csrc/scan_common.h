@@ -60,7 +60,7 @@ struct __align__(16) IvfShortItem {
 };
 int launch_ivf_short_scan(pq_ctx *ctx, const uint8_t *codes, const float *luts, const IvfShortItem *items,
                           const uint32_t *nitems_dev, const uint32_t *pair_out, int nprobe, int topk,
-                          unsigned long long *tau_key, uint64_t *partial);
+                          unsigned long long *tau_key, uint64_t *partial, size_t most_items);
 
 struct TunedArgs {
     const uint8_t *codes;
@@ -126,14 +126,14 @@ int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *
 // IVF: run the persistent scan kernel over a table of work items (see IvfItem).  `state` is a
 // caller-provided device region of tuned_state_bytes() bytes holding the per-query bounds,
 // histograms and the per-block candidate scratch; tau0 (optional, [nq]) seeds the per-query bounds
-// (+inf: none); *tau_key_out receives the per-query bounds.
+// (+inf: none); no more blocks are launched than the most_items that there can be; *tau_key_out receives the per-query bounds.
 namespace w16 {
 size_t tuned_state_bytes(int kind, int nq, int topk, int num_cu);
 int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float *pair_off, const float *pair_scale,
                       const uint8_t *codes, const float *luts, int nq, int nprobe, int topk,
                       const IvfItem *items, const uint32_t *nitems_dev, const int32_t *pairs_by_list,
                       const uint32_t *pair_out, uint64_t *partial, uint8_t *state, size_t state_bytes,
-                      const float *tau0, unsigned long long **tau_key_out);
+                      const float *tau0, size_t most_items, unsigned long long **tau_key_out);
 int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, const void *luts, int nq, int topk,
                       void *out_val, int64_t *out_ids);
 }  // namespace w16
@@ -143,7 +143,7 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
                       const uint8_t *codes, const float *luts, int nq, int nprobe, int topk,
                       const IvfItem *items, const uint32_t *nitems_dev, const int32_t *pairs_by_list,
                       const uint32_t *pair_out, uint64_t *partial, uint8_t *state, size_t state_bytes,
-                      const float *tau0, unsigned long long **tau_key_out);
+                      const float *tau0, size_t most_items, unsigned long long **tau_key_out);
 }  // namespace w8
 
 // ------------------------------------------------------------------------------------------

@@ -2241,7 +2241,7 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
                       const uint8_t *codes, const float *luts, int nq, int nprobe, int topk,
                       const IvfItem *items, const uint32_t *nitems_dev, const int32_t *pairs_by_list,
                       const uint32_t *pair_out, uint64_t *partial, uint8_t *state, size_t state_bytes,
-                      const float *tau0, unsigned long long **tau_key_out) {
+                      const float *tau0, size_t most_items, unsigned long long **tau_key_out) {
     const int qb = qb_of_kind(kind);
     if ((kind == KIND_F32P_M8 || kind == KIND_F32P_M16) && (!pair_min || !pair_off || !pair_scale))
         return fail(ctx, PQ_EINVAL, "scan_items: the pruned scan needs the pairs' minima, offsets and scales");
@@ -2261,15 +2261,18 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
     a.qtabs = nullptr; a.prune_off = pair_off; a.prune_scale = pair_scale; a.pair_min = pair_min;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
     a.rotated = false;
-    tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, nq,
-                                                     0xff800000u, a.hist, L.nhist, tau0, nq);
+    // (a block per query at least clears its 4096 bins)
+    tuned_init_kernel<<<nq < 64 ? 16 * nq : 1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, nq,
+                                                                         0xff800000u, a.hist, L.nhist, tau0, nq);
     PQ_HIP(ctx, hipGetLastError());
     if (ctx->profiling) {
         a.stats = (unsigned long long *)(state + 8);
         note_scan(ctx, kind, qb, 0, a.stats, a.ncand, nq);
         PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, ctx->stream));
     }
-    int rc = launch_by_kind(ctx, kind, small, true, a, nblocks);
+    // (blocks without an item each draw from the counter, one after the other: 1 M codes in 1024 lists, one query x 48 lists, 512 blocks
+    // 12.0 us for an empty table, 51 blocks 4.5)
+    int rc = launch_by_kind(ctx, kind, small, true, a, most_items < (size_t)nblocks ? (most_items > 0 ? (int)most_items : 1) : nblocks);
     if (rc) return rc;
     if (ctx->profiling) {
         PQ_HIP(ctx, hipEventRecord(ctx->ev_end, ctx->stream));
