@@ -994,7 +994,8 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
             ivf_select_probes_kernel<<<nqb, 256, 0, s>>>(dist, nlist, nprobe, probes, pout, flags);
             PQ_HIP(ctx, hipGetLastError());
         } else {
-            rc = launch_build_luts(ctx, qb, L->coarse_centroids, nqb, d, 1, nlist, dist);
+            rc = index_few_usable(qb, L->coarse_centroids, nqb, d) ? launch_index_few(ctx, qb, L->coarse_centroids, nqb, d, nlist, dist)
+                                                                   : launch_build_luts(ctx, qb, L->coarse_centroids, nqb, d, 1, nlist, dist);
             if (rc) return rc;
             ivf_select_probes_kernel<<<nqb, 256, 0, s>>>(dist, nlist, nprobe, probes, pout, nullptr);
             PQ_HIP(ctx, hipGetLastError());

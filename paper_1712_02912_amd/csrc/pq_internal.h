@@ -83,6 +83,9 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // ---- launchers implemented in the kernel files -------------------------------------
 int launch_build_luts(pq_ctx *ctx, const float *queries, const float *codebooks, int nq, int d, int m, int k,
                       float *luts);
+// Exact squared distances (plain definition in double, rounded once) of up to 8 vectors to k centroids of 4 i dimensions, 16-byte aligned.
+bool index_few_usable(const float *queries, const float *cents, int nq, int d);
+int launch_index_few(pq_ctx *ctx, const float *queries, const float *cents, int nq, int d, int k, float *out);
 int launch_quantize_luts(pq_ctx *ctx, const float *luts, int nq, int m, int k, const float *qmax,
                          uint8_t *qluts, float *qmin_out, float *scale_out, bool mark_nan = false);   // (16 x 16 tables: qmin_out NaN where an entry is)
 int launch_qmax_prescan(pq_ctx *ctx, const uint8_t *codes, int64_t n, int cf, const float *luts, int nq, int m,

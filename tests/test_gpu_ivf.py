@@ -71,6 +71,17 @@ def test_ivf_encoded_small(ctx, m):
     run_ivf(ctx, queries, coarse, offsets, codes, None, cb, 8, 50)
 
 
+# Up to eight queries take the Index step of few queries: every width of it, dimensions beside multiples of 32, lists beside multiples of
+# the 32 of a block, and a query that is one of the centroids.
+@pytest.mark.parametrize("nq", [1, 2, 3, 4, 5, 8, 9])
+@pytest.mark.parametrize("nlist,d", [(31, 32), (33, 72), (64, 128)])
+def test_ivf_index_step_of_few_queries(ctx, nq, nlist, d):
+    mix, coarse, cb, codes, order, offsets = make_index(4000, d, 8, nlist, seed=nlist + d)
+    queries = mix.sample(nq, 7)
+    queries[-1] = coarse[nlist - 1]
+    run_ivf(ctx, queries, coarse, offsets, codes, order, cb, min(nlist, 12), 10)
+
+
 def test_ivf_all_lists_equals_flat_scan_of_residual_tables(ctx):
     """nprobe = nlist: every code is scanned once with the tables of its own list."""
     mix, coarse, cb, codes, order, offsets = make_index(8000, 64, 8, 16, seed=31)
