@@ -254,31 +254,47 @@ __device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__re
     if (tid < 64) { cls_items[tid] = 0; cls_cursor[tid] = 0; }
     if (tid == 0) carry = 0;
     __syncthreads();
-    // PER consecutive lists per thread and round of the scan (one list each: 65 536 lists are 64 rounds of three barriers and
-    // a round trip to memory: one query over 65 536 lists, call 415 us; now 390)
+    // A round takes 8 * 64 consecutive lists per wave, 64 side by side at a time (one list per thread and round: 65 536 lists are 64 rounds
+    // of three barriers and a round trip to memory; eight consecutive lists per thread: loads of a wave touch 64 lines each).
     constexpr int PER = 8;
+    const int lane = tid & 63, wave = tid >> 6;
     for (int l0 = 0; l0 < nlist; l0 += PER * 1024) {
-        const int l = l0 + PER * tid;
-        uint32_t v[PER], sum = 0;
-        int64_t off[PER + 1];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) v[i] = l + i < nlist ? np[l + i] : 0u;
-#pragma unroll
-        for (int i = 0; i <= PER; ++i) off[i] = l + i <= nlist ? list_offsets[l + i] : 0;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) sum += v[i];
-        uint32_t before = block_scan_round(sum, wave_tot, &carry);
+        const int l = l0 + wave * (PER * 64) + lane;
+        uint32_t v[PER], before[PER], total = 0;
+        int64_t size[PER];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            if (l + i >= nlist) break;
-            pair_off[l + i] = before;
-            before += v[i];
-            const int64_t size = off[i + 1] - off[i];
-            const int nc = v[i] > 0 ? ivf_chunks_of(size, uncapped_rows) : 0;
-            nc_out[l + i] = (uint32_t)nc;
-            const bool is_short = size < short_max;
+            const int at = l + i * 64 < nlist ? l + i * 64 : nlist - 1;
+            v[i] = l + i * 64 < nlist ? np[at] : 0u;
+            size[i] = list_offsets[at + 1] - list_offsets[at];
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            uint32_t incl = v[i];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t up = __shfl_up(incl, o);
+                if (lane >= o) incl += up;
+            }
+            before[i] = total + incl - v[i];
+            total += (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+        }
+        if (lane == 0) wave_tot[wave] = total;
+        __syncthreads();
+        uint32_t base = carry;
+        for (int w = 0; w < wave; ++w) base += wave_tot[w];
+        __syncthreads();
+        if (tid == 1023) carry = base + total;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (l + i * 64 >= nlist) break;
+            pair_off[l + i * 64] = base + before[i];
+            const int nc = v[i] > 0 ? ivf_chunks_of(size[i], uncapped_rows) : 0;
+            nc_out[l + i * 64] = (uint32_t)nc;
+            const bool is_short = size[i] < short_max;
             const uint32_t items = is_short ? (nc > 0 ? (v[i] + short_qs - 1) / short_qs : 0u) : ((v[i] + qb - 1) / qb) * (uint32_t)nc;
-            if (items > 0) atomicAdd(&cls_items[(is_short ? 32 : 0) + 63 - __builtin_clzll((unsigned long long)size)], items);
+            if (items > 0) atomicAdd(&cls_items[(is_short ? 32 : 0) + 63 - __builtin_clzll((unsigned long long)size[i])], items);
         }
     }
     __syncthreads();
@@ -300,17 +316,34 @@ __device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__re
     // (every list the same way, touched or not: the waves then stay side by side and the items of a class stand in about the
     // order of their lists; untouched lists left out, or four lists of a thread at a time, mixed them and cost the
     // billion-code search 1 to 1.5 %)
-    for (int l = tid; l < nlist; l += 1024) {
-        const uint32_t v = np[l];
-        const int64_t size = list_offsets[l + 1] - list_offsets[l];
+    // (calls of up to 2^17 pairs: eight rounds' lists are read before any is placed; 65 536 lists are 64 round trips to memory
+    // otherwise, 65 us of this kernel)
+    auto place = [&](int l, uint32_t v, int64_t size, uint32_t nc) {
         const bool is_short = size < short_max;
-        const uint32_t items = is_short ? (nc_out[l] > 0 ? (v + short_qs - 1) / short_qs : 0u) : ((v + qb - 1) / qb) * nc_out[l];
+        const uint32_t items = is_short ? (nc > 0 ? (v + short_qs - 1) / short_qs : 0u) : ((v + qb - 1) / qb) * nc;
         if (items > 0) {
             const int c = (is_short ? 32 : 0) + 63 - __builtin_clzll((unsigned long long)size);
             item_off[l] = cls_base[c] + atomicAdd(&cls_cursor[c], items);
         } else {
             item_off[l] = 0;
         }
+    };
+    if (carry <= 1u << 17) {
+        for (int l0 = tid; l0 < nlist; l0 += PER * 1024) {
+            uint32_t v[PER], nc[PER];
+            int64_t size[PER];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int l = l0 + i * 1024 < nlist ? l0 + i * 1024 : nlist - 1;
+                v[i] = np[l]; nc[i] = nc_out[l];
+                size[i] = list_offsets[l + 1] - list_offsets[l];
+            }
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (l0 + i * 1024 < nlist) place(l0 + i * 1024, v[i], size[i], nc[i]);
+        }
+    } else {
+        for (int l = tid; l < nlist; l += 1024) place(l, np[l], list_offsets[l + 1] - list_offsets[l], nc_out[l]);
     }
 }
 __global__ __launch_bounds__(1024) void ivf_plan_kernel(const uint32_t *__restrict__ np, const int64_t *__restrict__ list_offsets, int nlist,
@@ -947,7 +980,12 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
         const float *qb = queries + (size_t)q0 * d;
         // Index step
         int32_t *pout = probe_out ? probe_out + (size_t)q0 * nprobe : nullptr;
-        if (opt_int(ctx, PQ_OPT_IVF_COARSE_F32, 1) != 0 && ncand <= IVF_REFINE_MAX && (int64_t)ncand * 8 <= nlist && d <= 8192 &&
+        if (index_few_usable(qb, L->coarse_centroids, nqb, d)) {   // (exact: nothing to be proved)
+            rc = launch_index_few(ctx, qb, L->coarse_centroids, nqb, d, nlist, dist);
+            if (rc) return rc;
+            ivf_select_probes_kernel<<<nqb, 256, 0, s>>>(dist, nlist, nprobe, probes, pout, nullptr);
+            PQ_HIP(ctx, hipGetLastError());
+        } else if (opt_int(ctx, PQ_OPT_IVF_COARSE_F32, 1) != 0 && ncand <= IVF_REFINE_MAX && (int64_t)ncand * 8 <= nlist && d <= 8192 &&
             coarse_f32_usable(ctx, qb, L->coarse_centroids, nqb, d, nlist, dist)) {
             int32_t *cand = (int32_t *)(ws + o_cand), *flags = (int32_t *)(ws + o_flags);
             unsigned int *maxnorm = (unsigned int *)(ws + o_maxnorm);
@@ -994,8 +1032,7 @@ int launch_ivf(pq_ctx *ctx, const ivf_lists *L, const float *codebooks, int m, i
             ivf_select_probes_kernel<<<nqb, 256, 0, s>>>(dist, nlist, nprobe, probes, pout, flags);
             PQ_HIP(ctx, hipGetLastError());
         } else {
-            rc = index_few_usable(qb, L->coarse_centroids, nqb, d) ? launch_index_few(ctx, qb, L->coarse_centroids, nqb, d, nlist, dist)
-                                                                   : launch_build_luts(ctx, qb, L->coarse_centroids, nqb, d, 1, nlist, dist);
+            rc = launch_build_luts(ctx, qb, L->coarse_centroids, nqb, d, 1, nlist, dist);
             if (rc) return rc;
             ivf_select_probes_kernel<<<nqb, 256, 0, s>>>(dist, nlist, nprobe, probes, pout, nullptr);
             PQ_HIP(ctx, hipGetLastError());
