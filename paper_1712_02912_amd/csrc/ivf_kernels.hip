@@ -257,9 +257,10 @@ __device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__re
     // A round takes 8 * 64 consecutive lists per wave, 64 side by side at a time (one list per thread and round: 65 536 lists are 64 rounds
     // of three barriers and a round trip to memory; eight consecutive lists per thread: loads of a wave touch 64 lines each).
     constexpr int PER = 8;
-    const int lane = tid & 63, wave = tid >> 6;
-    for (int l0 = 0; l0 < nlist; l0 += PER * 1024) {
-        const int l = l0 + wave * (PER * 64) + lane;
+    // (fewer lists: as few per wave as occupy all waves)
+    const int lane = tid & 63, wave = tid >> 6, per = nlist >= PER * 1024 ? PER : (nlist + 1023) / 1024;
+    for (int l0 = 0; l0 < nlist; l0 += per * 1024) {
+        const int l = l0 + wave * (per * 64) + lane;
         uint32_t v[PER], before[PER], total = 0;
         int64_t size[PER];
 #pragma unroll
@@ -270,6 +271,7 @@ __device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__re
         }
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
+            if (i >= per) break;
             uint32_t incl = v[i];
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -288,7 +290,7 @@ __device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__re
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            if (l + i * 64 >= nlist) break;
+            if (i >= per || l + i * 64 >= nlist) break;
             pair_off[l + i * 64] = base + before[i];
             const int nc = v[i] > 0 ? ivf_chunks_of(size[i], uncapped_rows) : 0;
             nc_out[l + i * 64] = (uint32_t)nc;
@@ -328,7 +330,7 @@ __device__ __forceinline__ void ivf_plan(const uint32_t *np, const int64_t *__re
             item_off[l] = 0;
         }
     };
-    if (carry <= 1u << 17) {
+    if (nlist > 1024 && carry <= 1u << 17) {
         for (int l0 = tid; l0 < nlist; l0 += PER * 1024) {
             uint32_t v[PER], nc[PER];
             int64_t size[PER];
