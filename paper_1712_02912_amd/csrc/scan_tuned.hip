@@ -150,6 +150,7 @@ enum { KIND_F32_M8 = 0, KIND_F32_M16 = 1, KIND_U4_M16 = 2, KIND_F32P_M8 = 3, KIN
 // and a bound that falls into it is none.
 constexpr int exact_bins(int tables) { return tables == 16 ? HIST_BINS - 1 : HIST_BINS; }   // (tables after merging: 8 or 16)
 constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bound of a float scan of many query groups
+constexpr int ONEHOT_SLICE = 2048;             // queries of a scan on the matrix cores
 constexpr int ONEHOT_FLAG = 48;                // word of the state: some list of the scan on the matrix cores is too short or too long
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
@@ -1594,7 +1595,7 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
     constexpr int RUN = 1024 / NT;
     auto row_of = [&](int i) -> uint32_t { return STRIDED ? (uint32_t)(i / RUN) * (uint32_t)(stride * RUN) + (uint32_t)(i % RUN) : (uint32_t)i; };
     auto load_code = [&](int at) {
-        const size_t i = row_of(at);
+        const size_t i = STRIDED ? (size_t)row_of(at) : (size_t)at;
         Code c;
         if constexpr (NT == 8) {
             const uint2 v = *reinterpret_cast<const uint2 *>(codes + (size_t)i * 8);
@@ -2287,6 +2288,17 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
                       void *out_val, int64_t *out_ids) {
     int rc;
     const bool u4_m32 = kind == KIND_U4_M32, is_u4 = kind == KIND_U4_M16 || u4_m32;
+    // Scans on the matrix cores (below) make a pass over the codes per 128 or 64 queries whatever their number: more queries than their lists
+    // have room for in the memory that the other loops take are served one slice after the other.
+    if (is_u4 && nq > ONEHOT_SLICE && n >= (u4_m32 ? 1 << 16 : 1 << 17) && n >= 32 * (int64_t)topk && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0 && !ctx->ws_fixed) {
+        for (int q0 = 0; q0 < nq; q0 += ONEHOT_SLICE) {
+            const int nqs = nq - q0 < ONEHOT_SLICE ? nq - q0 : ONEHOT_SLICE;
+            rc = launch_scan_tuned(ctx, kind, codes, n, (const uint8_t *)luts + (size_t)q0 * (u4_m32 ? 512 : 256), nqs, topk,
+                                   (uint32_t *)out_val + (size_t)q0 * topk, out_ids + (size_t)q0 * topk);
+            if (rc) return rc;
+        }
+        return PQ_OK;
+    }
     // The 8 x 256 float scan prunes with 16-bit lower bounds when the database is large enough to
     // pay for the preparation (a bound per query from the first PRUNE_INIT codes, then the tables).
     // Smaller databases: the plain loop needs no tables prepared (10 us), and its first bound comes from 4096 codes in one launch; it
@@ -2415,7 +2427,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     //   16 to 248, long results, 2^23 codes, P 2^28   1.0 to 1.36   (3 M codes, 64 queries 0.98; 25 M, 8 queries 0.92)
     const int64_t onehot_pairs = pairs * (cb / 8);
     bool onehot = false;
-    if (is_u4 && n >= PRUNE_MIN_N && n >= 32 * (int64_t)topk && onehot_cap >= 4096 && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0) {
+    if (is_u4 && n >= PRUNE_MIN_N && n >= 32 * (int64_t)topk && onehot_cap >= (small ? 8192 : 32768) && ((uintptr_t)luts & 15) == 0 && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0) {
         if (opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 0) > 0) onehot = true;
         else if (nq >= 249) onehot = onehot_pairs >= (int64_t)1 << 28 || (!small && n >= 1 << 18);
         else onehot = (nq >= 24 && onehot_pairs >= (int64_t)11 << 26) || (nq >= 16 && !small && n >= 1 << 23 && onehot_pairs >= (int64_t)1 << 28);

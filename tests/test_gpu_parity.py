@@ -758,6 +758,13 @@ def test_scan_u4_on_matrix_cores_sizes(ctx, opts, m, n, nq, topk):
     run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
 
 
+def test_scan_u4_on_matrix_cores_in_slices_of_queries(ctx):
+    r = np.random.default_rng(77)
+    packed = r.integers(0, 256, (131_072, 8), dtype=np.uint8)
+    qluts = np.minimum(255, r.standard_normal((2050, 16, 16)) ** 2 * 40).astype(np.uint8)
+    run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, 3)
+
+
 @pytest.mark.parametrize("m", [16, 32])
 @pytest.mark.parametrize("order", ["copies", "ascending", "descending"])
 def test_scan_u4_on_matrix_cores_misleading_samples(ctx, opts, m, order):
