@@ -230,7 +230,12 @@ int pq_last_scan_info(pq_ctx *ctx, char *name, size_t name_bytes, int *queries_p
     if (!ctx) return PQ_EINVAL;
     if (!ctx->ev_valid) return fail(ctx, PQ_EINVAL, "no profiled scan kernel recorded");
     PQ_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    if (name && name_bytes > 0) snprintf(name, name_bytes, "%s", ctx->last_scan_name);
+    if (name && name_bytes > 0) {
+        uint32_t again = 0;
+        if (ctx->stat_again) PQ_HIP(ctx, hipMemcpy(&again, ctx->stat_again, sizeof(again), hipMemcpyDeviceToHost));
+        if (again != 0) snprintf(name, name_bytes, "%s; %u queries again by the other loops", ctx->last_scan_name, again);
+        else snprintf(name, name_bytes, "%s", ctx->last_scan_name);
+    }
     if (queries_per_pass) *queries_per_pass = ctx->last_scan_qpp;
     if (passes) *passes = ctx->last_scan_passes;
     if (parked_lanes) {

@@ -46,6 +46,7 @@ struct pq_ctx {
     const unsigned long long *stat_parked;
     const uint32_t *stat_ncand;
     int stat_ncand_len;
+    const uint32_t *stat_again;   // queries that a scan on the matrix cores left to the other loops
     char err[512];
 };
 
@@ -76,6 +77,7 @@ static inline void note_plain_scan(pq_ctx *ctx, const char *name, int queries_pe
     ctx->stat_parked = nullptr;
     ctx->stat_ncand = nullptr;
     ctx->stat_ncand_len = 0;
+    ctx->stat_again = nullptr;
 }
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

@@ -106,7 +106,26 @@ struct TunedArgs {
     const uint4 *qtabs16;
     const float *prune_scale16;
     bool rotated;   // pruned flat scan: candidates are added up in the order of the plain loop (see scan_flush_pruned)
+    // integer scan of *again_count queries only, number again_query[slot] in slot `slot` (state by query, result lists by slot)
+    const uint32_t *again_count, *again_query;
 };
+
+// Items of the scan of `count` queries that are known on the device, where all queries of the call would be `nitems` items in
+// `nchunks` chunks: the call's chunks, or as many as give every block an item.
+struct AgainPlan {
+    int ngroups, nchunks;
+    int64_t chunk_codes;
+};
+__device__ inline AgainPlan again_plan(int count, int qb, int64_t n, int nchunks, int nitems, int nblocks, int64_t block_tile) {
+    AgainPlan p;
+    p.ngroups = (count + qb - 1) / qb;
+    if (p.ngroups == 0) return AgainPlan{0, 0, 0};
+    int64_t chunks = nblocks / p.ngroups > nchunks ? nblocks / p.ngroups : nchunks;
+    if (chunks > nitems / p.ngroups) chunks = nitems / p.ngroups;   // (as many result lists as there is memory for)
+    p.chunk_codes = ((n + chunks - 1) / chunks + block_tile - 1) / block_tile * block_tile;
+    p.nchunks = (int)((n + p.chunk_codes - 1) / p.chunk_codes);
+    return p;
+}
 
 // Counters of queries that many waves add to lie 128 bytes apart: additions to one line are made one after the other, 8 ns each
 // (25 M codes, 1000 queries, 2300 keys each: 0.6 ms with the counters side by side).
@@ -116,13 +135,24 @@ int launch_merge_topk(pq_ctx *ctx, const uint64_t *partial, int nchunks, int ngr
                       int topk, bool val_u32, void *out_val, int64_t *out_ids);
 // merge of the per-query result lists of a scan that leaves a final bound per query in tau_key
 // (see merge_filtered_kernel); any number of lists.  hist (optional): the scan's histograms [nq][HIST_BINS] of the keys in
-// the lists, of which the first hist_bins bins say something; float values: below hist_ref[q].  counts (optional): query q has
-// one list instead, the min(c, cap) keys at partial[q][cap] with c = counts[q * COUNT_PITCH], kpad 64, and *flag is set if it is not between topk and cap keys
-// long; with a flag and no counts nothing is done if *flag is 0 (integer sums both).
+// the lists, of which the first hist_bins bins say something; float values: below hist_ref[q].
 int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *qlist_off, int nchunks, int ngroups, int qb,
                           const unsigned long long *tau_key, int kpad, int nq, int topk, const int64_t *ids, bool val_u32,
-                          void *out_val, int64_t *out_ids, const uint32_t *hist = nullptr, const uint32_t *hist_ref = nullptr, int hist_bins = 0,
-                          const uint32_t *counts = nullptr, uint32_t cap = 0, uint32_t *flag = nullptr);
+                          void *out_val, int64_t *out_ids, const uint32_t *hist = nullptr, const uint32_t *hist_ref = nullptr, int hist_bins = 0);
+// A scan on the matrix cores leaves one list per query, the first min(c, cap) keys of lists[q][cap] with c = counts[q * COUNT_PITCH].
+// Queries whose list is not between topk and cap keys long are entered in query[*count] instead (and their state made ready: hist
+// clear, tau_key a bound from the hist of the sample where the list is short, *work_counter 0) to be scanned once more and merged from `partial`.
+struct AgainArgs {
+    uint32_t *count, *query;
+    uint32_t *work_counter, *hist;
+    unsigned long long *tau_key;
+    int64_t n, block_tile;      // of that scan (see again_plan)
+    int nchunks, nitems, nblocks, qb;
+};
+int launch_merge_counted(pq_ctx *ctx, const uint64_t *lists, const uint32_t *counts, uint32_t cap, const AgainArgs &again, int nq, int topk,
+                         void *out_val, int64_t *out_ids, int hist_bins);
+int launch_merge_again(pq_ctx *ctx, const uint64_t *partial, const AgainArgs &again, int kpad, int nq, int topk, void *out_val, int64_t *out_ids,
+                       int hist_bins);
 // IVF: run the persistent scan kernel over a table of work items (see IvfItem).  `state` is a
 // caller-provided device region of tuned_state_bytes() bytes holding the per-query bounds,
 // histograms and the per-block candidate scratch; tau0 (optional, [nq]) seeds the per-query bounds

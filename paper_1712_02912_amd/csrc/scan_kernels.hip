@@ -523,7 +523,7 @@ __global__ __launch_bounds__(1024) void merge_topk_kernel(const uint64_t *partia
 // and 2048 keys (512 threads and 4096 keys for topk above 512), of which a compute unit holds several.
 constexpr int MERGE_COUNT = 256;   // as many kept keys find their ranks by counting, without a selection before
 constexpr int merge_lds_bytes(int cap) { return cap * 8 + cap * 4 + 1024 * 8; }   // kept keys, 32-bit values for the selection, the result's keys
-enum { MERGE_LISTS, MERGE_COUNTED, MERGE_IF_FLAGGED };   // (kernels of their own: 1 us of a call that wants neither counts nor flag)
+enum { MERGE_LISTS, MERGE_COUNTED, MERGE_AGAIN };   // (the latter two: see AgainArgs; kernels of their own: 1 us of a call that wants neither)
 template <bool VAL_U32, int MERGE_CAP, int MODE = MERGE_LISTS>
 __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__restrict__ partial,
                                                               const uint32_t *__restrict__ qlist_off, int nchunks,
@@ -532,18 +532,37 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
                                                               const int64_t *__restrict__ ids, void *out_val,
                                                               int64_t *out_ids, const uint32_t *__restrict__ hist,
                                                               const uint32_t *__restrict__ hist_ref, int hist_bins,
-                                                              const uint32_t *__restrict__ counts, uint32_t cap, uint32_t *flag) {
+                                                              const uint32_t *__restrict__ counts, uint32_t cap, AgainArgs again) {
     extern __shared__ uint64_t skeys[];
     __shared__ int s_count;
     constexpr bool COUNTED = MODE == MERGE_COUNTED;
-    if (MODE == MERGE_IF_FLAGGED && *flag == 0u) return;
-    const int gq = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x, slot = blockIdx.x;
+    int gq = slot;
+    if constexpr (MODE == MERGE_AGAIN) {
+        const int count = (int)*again.count;
+        if (slot >= count) return;
+        const AgainPlan plan = again_plan(count, qb, again.n, again.nchunks, again.nitems, again.nblocks, again.block_tile);
+        gq = (int)again.query[slot];
+        nchunks = plan.nchunks;
+        ngroups = plan.ngroups;
+    }
     // (with counts a query has one list of up to cap keys, read as if it were lists of 64)
     uint32_t listed = 0;
     if constexpr (COUNTED) {
-        const uint32_t c = counts[(size_t)gq * COUNT_PITCH];
-        if ((c < (uint32_t)topk || c > cap) && tid == 0) *flag = 1u;
-        listed = c < cap ? c : cap;
+        listed = counts[(size_t)gq * COUNT_PITCH];
+        if (gq == 0 && tid == 0) *again.work_counter = 0u;
+        if (listed < (uint32_t)topk || listed > cap) {
+            // (the bound of a short list is none, but the sample's topk-th key is one, if it has counted as many)
+            uint32_t *const bins = again.hist + (size_t)gq * HIST_BINS;
+            if (tid < 64 && listed < (uint32_t)topk) {
+                const int bin = hist_threshold(bins, topk);
+                if (tid == 0) again.tau_key[gq] = (uint64_t)(bin < hist_bins ? (uint32_t)bin : 0x7fffu) << 32 | 0xffffffffull;
+            }
+            __syncthreads();
+            for (int i = tid; i < HIST_BINS; i += blockDim.x) bins[i] = 0u;
+            if (tid == 0) again.query[atomicAdd(again.count, 1u)] = (uint32_t)gq;
+            return;
+        }
     }
     const size_t nlists = COUNTED ? (size_t)((listed + 63u) / 64u) : qlist_off ? (size_t)(qlist_off[gq + 1] - qlist_off[gq]) : (size_t)nchunks;
     // Every list is packed (its keys first, KEY_EMPTY behind them; kpad is a multiple of 64): a wave
@@ -554,7 +573,7 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
     // memory round trips.  8 queries, 24 lists of up to 1024 keys each: 271 -> 79 us with the selections below.)
     auto list_ptr = [&](size_t l) {
         if constexpr (COUNTED) return partial + (size_t)gq * cap + l * 64;
-        const size_t list = qlist_off ? (size_t)qlist_off[gq] + l : (l * ngroups + gq / qb) * qb + gq % qb;
+        const size_t list = qlist_off ? (size_t)qlist_off[gq] + l : (l * ngroups + slot / qb) * qb + slot % qb;
         return partial + list * kpad;
     };
     constexpr int MLP = 4, REST = 5;
@@ -753,25 +772,18 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
 
 int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *qlist_off, int nchunks, int ngroups, int qb,
                           const unsigned long long *tau_key, int kpad, int nq, int topk, const int64_t *ids, bool val_u32,
-                          void *out_val, int64_t *out_ids, const uint32_t *hist, const uint32_t *hist_ref, int hist_bins,
-                          const uint32_t *counts, uint32_t list_cap, uint32_t *flag) {
+                          void *out_val, int64_t *out_ids, const uint32_t *hist, const uint32_t *hist_ref, int hist_bins) {
     if (nq == 0) return PQ_OK;
     // (the histograms' bound: 16 KB read per query; with many queries the keys are fewer and the selection is the shorter way:
     // 1000 queries, top-100 34 us without, 44 with)
     auto launch = [&](auto kernel, int cap, int threads, const uint32_t *hist = nullptr) -> int {
         PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, merge_lds_bytes(cap)));
-        kernel<<<nq, threads, merge_lds_bytes(cap), ctx->stream>>>(partial, qlist_off, nchunks, ngroups, qb, tau_key, kpad, topk, ids, out_val, out_ids, hist, hist_ref, hist_bins, counts, list_cap, flag);
+        kernel<<<nq, threads, merge_lds_bytes(cap), ctx->stream>>>(partial, qlist_off, nchunks, ngroups, qb, tau_key, kpad, topk, ids, out_val, out_ids, hist, hist_ref, hist_bins, nullptr, 0u, AgainArgs{});
         PQ_HIP(ctx, hipGetLastError());
         return PQ_OK;
     };
     // calls of many queries: several smaller blocks per compute unit (room for at least four times topk keys)
     const bool many = nq >= 2 * ctx->num_cu;
-    if (counts != nullptr) {   // (integer sums only)
-        if (many && topk <= 512) return launch(merge_filtered_kernel<true, 2048, MERGE_COUNTED>, 2048, 256);
-        if (many) return launch(merge_filtered_kernel<true, 4096, MERGE_COUNTED>, 4096, 512);
-        return launch(merge_filtered_kernel<true, 8192, MERGE_COUNTED>, 8192, 1024);
-    }
-    if (flag != nullptr) return launch(merge_filtered_kernel<true, 8192, MERGE_IF_FLAGGED>, 8192, 1024, hist);
     if (many && topk <= 512) {
         if (val_u32) return launch(merge_filtered_kernel<true, 2048>, 2048, 256);
         return launch(merge_filtered_kernel<false, 2048>, 2048, 256);
@@ -784,6 +796,29 @@ int launch_merge_filtered(pq_ctx *ctx, const uint64_t *partial, const uint32_t *
     if ((int64_t)nchunks * kpad <= 8192) hist = nullptr;
     if (val_u32) return launch(merge_filtered_kernel<true, 8192>, 8192, 1024, hist);
     return launch(merge_filtered_kernel<false, 8192>, 8192, 1024, hist);
+}
+
+int launch_merge_counted(pq_ctx *ctx, const uint64_t *lists, const uint32_t *counts, uint32_t cap, const AgainArgs &again, int nq, int topk,
+                         void *out_val, int64_t *out_ids, int hist_bins) {
+    auto launch = [&](auto kernel, int room, int threads) -> int {   // (sized as above)
+        PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, merge_lds_bytes(room)));
+        kernel<<<nq, threads, merge_lds_bytes(room), ctx->stream>>>(lists, nullptr, 0, 1, 1, again.tau_key, 64, topk, nullptr, out_val, out_ids, nullptr, nullptr, hist_bins, counts, cap, again);
+        PQ_HIP(ctx, hipGetLastError());
+        return PQ_OK;
+    };
+    const bool many = nq >= 2 * ctx->num_cu;
+    if (many && topk <= 512) return launch(merge_filtered_kernel<true, 2048, MERGE_COUNTED>, 2048, 256);
+    if (many) return launch(merge_filtered_kernel<true, 4096, MERGE_COUNTED>, 4096, 512);
+    return launch(merge_filtered_kernel<true, 8192, MERGE_COUNTED>, 8192, 1024);
+}
+
+int launch_merge_again(pq_ctx *ctx, const uint64_t *partial, const AgainArgs &again, int kpad, int nq, int topk, void *out_val, int64_t *out_ids,
+                       int hist_bins) {
+    auto kernel = merge_filtered_kernel<true, 8192, MERGE_AGAIN>;
+    PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, merge_lds_bytes(8192)));
+    kernel<<<nq, 1024, merge_lds_bytes(8192), ctx->stream>>>(partial, nullptr, 0, 1, again.qb, again.tau_key, kpad, topk, nullptr, out_val, out_ids, again.hist, nullptr, hist_bins, nullptr, 0u, again);
+    PQ_HIP(ctx, hipGetLastError());
+    return PQ_OK;
 }
 
 // ------------------------------------------------------------------------------------------

@@ -151,7 +151,7 @@ enum { KIND_F32_M8 = 0, KIND_F32_M16 = 1, KIND_U4_M16 = 2, KIND_F32P_M8 = 3, KIN
 constexpr int exact_bins(int tables) { return tables == 16 ? HIST_BINS - 1 : HIST_BINS; }   // (tables after merging: 8 or 16)
 constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bound of a float scan of many query groups
 constexpr int ONEHOT_SLICE = 2048;             // queries of a scan on the matrix cores
-constexpr int ONEHOT_FLAG = 48;                // word of the state: some list of the scan on the matrix cores is too short or too long
+constexpr int ONEHOT_AGAIN = 48;               // word of the state: queries whose list of the scan on the matrix cores is too short or too long
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
 constexpr int64_t PRUNE_MIN_N = 1 << 16;   // smaller databases take the plain float scan, but for some calls (see launch_scan_tuned)
@@ -942,8 +942,8 @@ __device__ __noinline__ void scan_merge_item(LDS_PTR(SM) sm, uint64_t *block_scr
 #endif
 enum { TICK_SETUP = 0, TICK_LOOP, TICK_FLUSH, TICK_REFRESH, TICK_EMIT, TICK_OVERFLOW, TICK_COUNT };
 
-// ROTATED: the pruned scans of smaller databases (see scan_flush_pruned)
-template <int KIND, int E, int KPAD, int DEPTH, bool ROTATED = false>
+// ROTATED: the pruned scans of smaller databases (see scan_flush_pruned); LISTED: integer scans of queries listed on the device
+template <int KIND, int E, int KPAD, int DEPTH, bool ROTATED = false, bool LISTED = false>
 __global__ __launch_bounds__(TUNED_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void scan_tuned_kernel(TunedArgs a) {
     constexpr bool IS_U4 = KIND == KIND_U4_M16 || KIND == KIND_U4Q_M16 || KIND == KIND_U4_M32;   // values are integer sums
@@ -974,7 +974,15 @@ void scan_tuned_kernel(TunedArgs a) {
     uint64_t *block_scratch = a.scratch + (size_t)blockIdx.x * TUNED_WAVES * QB * CAP;
     uint64_t *wave_buf = block_scratch + (size_t)wave * QB * CAP;
 
-    const int nitems = a.item_tab ? (int)*a.nitems_dev : a.nitems;
+    int nitems = a.item_tab ? (int)*a.nitems_dev : a.nitems;
+    [[maybe_unused]] int listed = 0;
+    [[maybe_unused]] AgainPlan plan;
+    if constexpr (LISTED) {
+        listed = (int)*a.again_count;
+        plan = again_plan(listed, QB, a.n, a.nchunks, a.nitems, (int)gridDim.x, (int64_t)SUB * DEPTH * TUNED_WAVES);
+        nitems = plan.ngroups * plan.nchunks;
+        if (nitems == 0) return;
+    }
     int gstep = 0;   // steps of this wave over all its items: paces the periodic bound refresh
     unsigned long long parked_total = 0;   // positions this wave has handed to the insert path (uniform; reported when profiling)
     if (threadIdx.x == 0) sm.stat_parked = 0ull;
@@ -1031,9 +1039,11 @@ void scan_tuned_kernel(TunedArgs a) {
                     sm.nvalid = nslots;
                 }
             } else {
-                const int group = item % a.ngroups, chunk = item / a.ngroups;
-                const int gq = group * QB + s;
-                if (gq < a.nq) {
+                const int ngroups = LISTED ? plan.ngroups : a.ngroups, nq = LISTED ? listed : a.nq;
+                const int group = item % ngroups, chunk = item / ngroups;
+                int gq = group * QB + s;
+                if (gq < nq) {
+                    if constexpr (LISTED) gq = (int)a.again_query[gq];
                     qid = gq;
                     lut = IS_U4 ? (const void *)((const uint8_t *)a.luts + (size_t)gq * (NT * 32))
                                 : (const void *)((const float *)a.luts + (size_t)gq * (NT * 256));
@@ -1045,17 +1055,18 @@ void scan_tuned_kernel(TunedArgs a) {
                 }
                 out = a.partial + ((size_t)item * QB + s) * KPAD;
                 if (s == 0) {
-                    const bool head = chunk < a.head_chunks;
-                    const int64_t cbeg = head ? (int64_t)chunk * a.head_codes
-                                              : (int64_t)a.head_chunks * a.head_codes + (int64_t)(chunk - a.head_chunks) * a.chunk_codes;
-                    const int64_t clen = head ? a.head_codes : a.chunk_codes;
+                    const bool head = !LISTED && chunk < a.head_chunks;
+                    const int64_t cbeg = LISTED ? (int64_t)chunk * plan.chunk_codes
+                                         : head ? (int64_t)chunk * a.head_codes
+                                                : (int64_t)a.head_chunks * a.head_codes + (int64_t)(chunk - a.head_chunks) * a.chunk_codes;
+                    const int64_t clen = LISTED ? plan.chunk_codes : head ? a.head_codes : a.chunk_codes;
                     const int64_t cend = cbeg + clen < a.n ? cbeg + clen : a.n;
                     sm.code_begin = cbeg;
                     sm.chunk_ptr = a.codes + cbeg * CB;
                     sm.ncodes = cend > cbeg ? (int)(cend - cbeg) : 0;
                     sm.skip = 0;
                     sm.group = group;
-                    sm.nvalid = a.nq - group * QB < QB ? a.nq - group * QB : QB;
+                    sm.nvalid = nq - group * QB < QB ? nq - group * QB : QB;
                 }
             }
             const int sq = qid < 0 ? 0 : qid;
@@ -1526,7 +1537,7 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
     if (i0 == 0) {
         *work_counter = 0;
         for (int i = 2; i < 32; ++i) work_counter[i] = 0;   // the 64-bit statistics words behind it
-        work_counter[ONEHOT_FLAG] = 0;
+        work_counter[ONEHOT_AGAIN] = 0;
     }
     for (size_t i = i0; i < (size_t)ntau; i += stride) {
         const bool seeded = tau0 != nullptr && i < (size_t)nq && tau0[i] < __builtin_inff();
@@ -1538,18 +1549,6 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
     for (size_t i = i0; i < nhist; i += stride) hist[i] = 0;
     for (size_t i = i0; i < also_zero_n; i += stride) also_zero[i] = 0;   // (the bins of a first-bound pass that follows)
     for (size_t i = i0; i < zero_too_n; i += stride) zero_too[i] = 0;
-}
-
-// The state of a scan on the matrix cores made ready for another scan, from those of its bounds that are, or for none (*only_if is 0).
-__global__ void rescan_reset_kernel(const uint32_t *only_if, uint32_t *work_counter, unsigned long long *tau_key, const uint32_t *cnt, uint32_t *ncand, int nq, int topk, int ntau, uint32_t *hist, size_t nhist) {
-    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
-    if (i0 == 0) *work_counter = *only_if == 0u ? 0x40000000u : 0u;   // (beyond any item: the scan has nothing to do)
-    if (*only_if == 0u) return;
-    for (size_t i = i0; i < (size_t)ntau; i += stride) {
-        if (i < (size_t)nq && cnt[i * COUNT_PITCH] < (uint32_t)topk) tau_key[i] = 0x7fffull << 32 | 0xffffffffull;   // (no bound then)
-        ncand[i] = 0;
-    }
-    for (size_t i = i0; i < nhist; i += stride) hist[i] = 0;
 }
 
 // First bound of the integer scan: one block per SEED_QPB queries adds up the 8-bit table entries of the
@@ -2133,7 +2132,11 @@ static int launch_kind(pq_ctx *ctx, const TunedArgs &a, int nblocks) {
     // (kernels of their own for the other order: with both in one, the registers that the insert path needs made 86 724 codes of 16 bytes,
     // 5 queries 54.5 -> 55.9 us)
     constexpr bool ROTATED = !PQ_TUNED_ITEMS_ONLY && DEPTH == 2 && (KIND == KIND_F32P_M16 || (E == E_LARGE && (KIND == KIND_F32P_M8 || KIND == KIND_F32Q_M8)));
-    if (a.rotated) {
+    constexpr bool LISTED = !PQ_TUNED_ITEMS_ONLY && (KIND == KIND_U4_M16 || KIND == KIND_U4Q_M16 || KIND == KIND_U4_M32);
+    if (a.again_count != nullptr) {
+        if constexpr (LISTED) scan_tuned_kernel<KIND, E, KPAD, DEPTH, false, true><<<nblocks, TUNED_THREADS, 0, ctx->stream>>>(a);
+        else return fail(ctx, PQ_EINVAL, "scan: no kernel of this form serves listed queries");
+    } else if (a.rotated) {
         if constexpr (ROTATED) scan_tuned_kernel<KIND, E, KPAD, DEPTH, true><<<nblocks, TUNED_THREADS, 0, ctx->stream>>>(a);
         else return fail(ctx, PQ_EINVAL, "scan: no kernel of this form adds in the plain loop's order");
     } else {
@@ -2223,6 +2226,7 @@ static void note_scan(pq_ctx *ctx, int kind, int qb, int passes, const unsigned 
     ctx->stat_parked = parked;
     ctx->stat_ncand = ncand;
     ctx->stat_ncand_len = ncand_len;
+    ctx->stat_again = nullptr;
 }
 
 static int qb_of_kind(int kind) {
@@ -2262,6 +2266,7 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
     a.qtabs = nullptr; a.prune_off = pair_off; a.prune_scale = pair_scale; a.pair_min = pair_min;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
     a.rotated = false;
+    a.again_count = nullptr; a.again_query = nullptr;
     // (a block per query at least clears its 4096 bins)
     tuned_init_kernel<<<nq < 64 ? 16 * nq : 1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, nq,
                                                                          0xff800000u, a.hist, L.nhist, tau0, nq);
@@ -2432,8 +2437,10 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         else if (nq >= 249) onehot = onehot_pairs >= (int64_t)1 << 28 || (!small && n >= 1 << 18);
         else onehot = (nq >= 24 && onehot_pairs >= (int64_t)11 << 26) || (nq >= 16 && !small && n >= 1 << 23 && onehot_pairs >= (int64_t)1 << 28);
     }
-    const size_t off_partial = align_up(L.total, 256);
-    const size_t off_tau0 = off_partial + align_up((size_t)nitems * qb * kpad * 8, 256);
+    const size_t partial_bytes = align_up((size_t)nitems * qb * kpad * 8, 256), off_again = align_up(L.total, 256);
+    if (onehot && ctx->ws_fixed && align_up(off_again + (size_t)nq * 4, 256) + partial_bytes > ctx->ws_bytes) onehot = false;
+    const size_t off_partial = onehot ? align_up(off_again + (size_t)nq * 4, 256) : off_again;
+    const size_t off_tau0 = off_partial + partial_bytes;
     const size_t off_poff = off_tau0 + align_up((size_t)ntau * 4, 256);
     const size_t off_pscale = off_poff + align_up((size_t)ntau * 4, 256);
     const size_t off_qtabs = off_pscale + align_up((size_t)ntau * 4, 256);
@@ -2509,6 +2516,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     a.qtabs = nullptr; a.prune_off = nullptr; a.prune_scale = nullptr; a.pair_min = nullptr;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
     a.rotated = rotated;
+    a.again_count = nullptr; a.again_query = nullptr;
     float *tau0 = nullptr;
     if (prune) {
         tau0 = (float *)(ws + off_tau0);
@@ -2611,7 +2619,6 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, ctx->stream));
     }
     if (onehot) {
-        uint32_t *const full = a.work_counter + ONEHOT_FLAG;
         uint64_t *const lists = (uint64_t *)((uint8_t *)a.scratch + onehot_state);
         uint32_t *const cnt = (uint32_t *)a.scratch;
         rc = launch_scan_onehot(ctx, codes, n, cb, (const uint8_t *)luts, nq, topk, exact_bins(cb), a.tau_key, cnt, a.hist, lists,
@@ -2623,19 +2630,18 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             ctx->stat_parked = a.stats;
             ctx->stat_ncand = cnt;
             ctx->stat_ncand_len = nq * COUNT_PITCH;   // (zeros between the counts)
+            ctx->stat_again = a.work_counter + ONEHOT_AGAIN;
             PQ_HIP(ctx, hipEventRecord(ctx->ev_end, ctx->stream));
             ctx->ev_valid = 1;
         }
-        rc = launch_merge_filtered(ctx, lists, nullptr, 0, 1, 1, a.tau_key, 64, nq, topk, nullptr, true, out_val, out_ids, nullptr, nullptr, 0,
-                                   cnt, (uint32_t)onehot_cap, full);
+        AgainArgs again{a.work_counter + ONEHOT_AGAIN, (uint32_t *)(ws + off_again), a.work_counter, a.hist, a.tau_key, n, block_tile, (int)nchunks, (int)nitems, nblocks, qb};
+        rc = launch_merge_counted(ctx, lists, cnt, (uint32_t)onehot_cap, again, nq, topk, out_val, out_ids, exact_bins(cb));
         if (rc) return rc;
-        // a list is too short or had no room for its keys: the whole call once more, from the bounds found so far
-        rescan_reset_kernel<<<64, 256, 0, ctx->stream>>>(full, a.work_counter, a.tau_key, cnt, a.ncand, nq, topk, ntau, a.hist, L.nhist);
-        PQ_HIP(ctx, hipGetLastError());
+        // the queries whose list is too short or had no room for its keys once more, from the bounds found so far
+        a.again_count = again.count; a.again_query = again.query;
         rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
         if (rc) return rc;
-        return launch_merge_filtered(ctx, a.partial, nullptr, (int)nchunks, ngroups, qb, a.tau_key, kpad, nq, topk, nullptr, is_u4,
-                                     out_val, out_ids, a.hist, a.tau_ref, exact_bins(cb), nullptr, 0, full);
+        return launch_merge_again(ctx, a.partial, again, kpad, nq, topk, out_val, out_ids, exact_bins(cb));
     }
     rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
     if (rc) return rc;

@@ -783,6 +783,31 @@ def test_scan_u4_on_matrix_cores_misleading_samples(ctx, opts, m, order):
     run_int_scan(ctx, np.ascontiguousarray(packed), orc.CODES_U4_PACKED, qluts, 100)
 
 
+def run_on_matrix_cores(ctx, packed, qluts, topk, again):
+    """run_int_scan of a call that takes the matrix cores and scans `again` of its queries once more."""
+    ctx.pq_set_profiling(True)
+    try:
+        run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
+        kernel = ctx.pq_last_scan_info()["kernel"]
+    finally:
+        ctx.pq_set_profiling(False)
+    assert kernel.startswith("scan_onehot_kernel"), kernel
+    assert kernel.endswith(f"; {again} queries again by the other loops") == (again > 0) and ("again" in kernel) == (again > 0), kernel
+
+
+# With 32 tables a query whose sums all lie beyond the bins that are counted gets no bound, and so no list of its own: it alone is scanned
+# again.  Forms of that scan: short and long results, coarse and fine tiles (many codes per block or few), one group of queries and several.
+@pytest.mark.parametrize("n,nq,topk,bad", [(70_001, 40, 100, [7]), (263_000, 300, 1000, [0, 7, 299]), (530_000, 16, 129, [3]), (1_100_003, 64, 10, list(range(1, 64, 5))),
+                                           (66_000, 33, 128, list(range(33)))])
+def test_scan_u4_on_matrix_cores_scans_only_queries_without_bound_again(ctx, opts, n, nq, topk, bad):
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(n + nq)
+    packed = r.integers(0, 256, (n, 16), dtype=np.uint8)
+    qluts = np.minimum(255, r.standard_normal((nq, 32, 16)) ** 2 * r.uniform(5, 40, (nq, 32, 1))).astype(np.uint8)
+    qluts[bad] = 255
+    run_on_matrix_cores(ctx, packed, qluts, topk, len(bad))
+
+
 # --------------------------------------------- 8x8 float scan, 8-bit lower bounds, 16 queries per pass
 # 512 queries and more (enough groups of 16 to fill the GPU) take the loop on 8-bit lower bounds; these
 # cases aim at what is specific to it: ragged last group, saturating entries, degenerate ranges, ties.
