@@ -106,26 +106,11 @@ struct TunedArgs {
     const uint4 *qtabs16;
     const float *prune_scale16;
     bool rotated;   // pruned flat scan: candidates are added up in the order of the plain loop (see scan_flush_pruned)
-    // integer scan of *again_count queries only, number again_query[slot] in slot `slot` (state by query, result lists by slot)
+    // integer scan of *again_count queries only, number again_query[slot] in slot `slot` (state by query, result lists by slot), in the chunks
+    // that all queries would take: a query whose bound is loose costs most at the start of a chunk (50 of 1000 queries without a bound, 32
+    // tables, 1 M codes, top-1000: 8.9 ms; in as many chunks as give every block an item 13.6)
     const uint32_t *again_count, *again_query;
 };
-
-// Items of the scan of `count` queries that are known on the device, where all queries of the call would be `nitems` items in
-// `nchunks` chunks: the call's chunks, or as many as give every block an item.
-struct AgainPlan {
-    int ngroups, nchunks;
-    int64_t chunk_codes;
-};
-__device__ inline AgainPlan again_plan(int count, int qb, int64_t n, int nchunks, int nitems, int nblocks, int64_t block_tile) {
-    AgainPlan p;
-    p.ngroups = (count + qb - 1) / qb;
-    if (p.ngroups == 0) return AgainPlan{0, 0, 0};
-    int64_t chunks = nblocks / p.ngroups > nchunks ? nblocks / p.ngroups : nchunks;
-    if (chunks > nitems / p.ngroups) chunks = nitems / p.ngroups;   // (as many result lists as there is memory for)
-    p.chunk_codes = ((n + chunks - 1) / chunks + block_tile - 1) / block_tile * block_tile;
-    p.nchunks = (int)((n + p.chunk_codes - 1) / p.chunk_codes);
-    return p;
-}
 
 // Counters of queries that many waves add to lie 128 bytes apart: additions to one line are made one after the other, 8 ns each
 // (25 M codes, 1000 queries, 2300 keys each: 0.6 ms with the counters side by side).
@@ -146,8 +131,7 @@ struct AgainArgs {
     uint32_t *count, *query;
     uint32_t *work_counter, *hist;
     unsigned long long *tau_key;
-    int64_t n, block_tile;      // of that scan (see again_plan)
-    int nchunks, nitems, nblocks, qb;
+    int nchunks, qb;            // of that scan
 };
 int launch_merge_counted(pq_ctx *ctx, const uint64_t *lists, const uint32_t *counts, uint32_t cap, const AgainArgs &again, int nq, int topk,
                          void *out_val, int64_t *out_ids, int hist_bins);

@@ -541,10 +541,8 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
     if constexpr (MODE == MERGE_AGAIN) {
         const int count = (int)*again.count;
         if (slot >= count) return;
-        const AgainPlan plan = again_plan(count, qb, again.n, again.nchunks, again.nitems, again.nblocks, again.block_tile);
         gq = (int)again.query[slot];
-        nchunks = plan.nchunks;
-        ngroups = plan.ngroups;
+        ngroups = (count + qb - 1) / qb;
     }
     // (with counts a query has one list of up to cap keys, read as if it were lists of 64)
     uint32_t listed = 0;
@@ -816,7 +814,7 @@ int launch_merge_again(pq_ctx *ctx, const uint64_t *partial, const AgainArgs &ag
                        int hist_bins) {
     auto kernel = merge_filtered_kernel<true, 8192, MERGE_AGAIN>;
     PQ_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, merge_lds_bytes(8192)));
-    kernel<<<nq, 1024, merge_lds_bytes(8192), ctx->stream>>>(partial, nullptr, 0, 1, again.qb, again.tau_key, kpad, topk, nullptr, out_val, out_ids, again.hist, nullptr, hist_bins, nullptr, 0u, again);
+    kernel<<<nq, 1024, merge_lds_bytes(8192), ctx->stream>>>(partial, nullptr, again.nchunks, 1, again.qb, again.tau_key, kpad, topk, nullptr, out_val, out_ids, again.hist, nullptr, hist_bins, nullptr, 0u, again);
     PQ_HIP(ctx, hipGetLastError());
     return PQ_OK;
 }

@@ -289,7 +289,8 @@ __device__ __noinline__ void onehot_image(lds_ptr<OnehotSmem<NB, G>> sm, uint32_
     const unsigned long long key = sm->key[q];
     // sums below `below` can still be candidates; at the bound's own sum its row decides
     const int64_t below = (int64_t)(key >> 32) + ((uint32_t)key >= row_lo ? 1 : 0) - (int64_t)sm->off[q];
-    const bool none = q0 + q >= nq || below <= 0;
+    // (a query that the first codes gave no bound is left to the other loops)
+    const bool none = q0 + q >= nq || below <= 0 || (uint32_t)(key >> 32) >= 0x7fffu;
     const float scale = none ? 0.f : below <= RANGE ? 1.f : (float)RANGE / (float)below;
     const uint32_t short_of = !none && below <= RANGE ? RANGE - (uint32_t)below : 0u;   // what the tables' c add up to
 #pragma unroll 1

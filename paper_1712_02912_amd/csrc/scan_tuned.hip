@@ -976,11 +976,9 @@ void scan_tuned_kernel(TunedArgs a) {
 
     int nitems = a.item_tab ? (int)*a.nitems_dev : a.nitems;
     [[maybe_unused]] int listed = 0;
-    [[maybe_unused]] AgainPlan plan;
     if constexpr (LISTED) {
         listed = (int)*a.again_count;
-        plan = again_plan(listed, QB, a.n, a.nchunks, a.nitems, (int)gridDim.x, (int64_t)SUB * DEPTH * TUNED_WAVES);
-        nitems = plan.ngroups * plan.nchunks;
+        nitems = a.nchunks * ((listed + QB - 1) / QB);
         if (nitems == 0) return;
     }
     int gstep = 0;   // steps of this wave over all its items: paces the periodic bound refresh
@@ -1039,7 +1037,7 @@ void scan_tuned_kernel(TunedArgs a) {
                     sm.nvalid = nslots;
                 }
             } else {
-                const int ngroups = LISTED ? plan.ngroups : a.ngroups, nq = LISTED ? listed : a.nq;
+                const int ngroups = LISTED ? (listed + QB - 1) / QB : a.ngroups, nq = LISTED ? listed : a.nq;
                 const int group = item % ngroups, chunk = item / ngroups;
                 int gq = group * QB + s;
                 if (gq < nq) {
@@ -1055,11 +1053,10 @@ void scan_tuned_kernel(TunedArgs a) {
                 }
                 out = a.partial + ((size_t)item * QB + s) * KPAD;
                 if (s == 0) {
-                    const bool head = !LISTED && chunk < a.head_chunks;
-                    const int64_t cbeg = LISTED ? (int64_t)chunk * plan.chunk_codes
-                                         : head ? (int64_t)chunk * a.head_codes
-                                                : (int64_t)a.head_chunks * a.head_codes + (int64_t)(chunk - a.head_chunks) * a.chunk_codes;
-                    const int64_t clen = LISTED ? plan.chunk_codes : head ? a.head_codes : a.chunk_codes;
+                    const bool head = chunk < a.head_chunks;
+                    const int64_t cbeg = head ? (int64_t)chunk * a.head_codes
+                                              : (int64_t)a.head_chunks * a.head_codes + (int64_t)(chunk - a.head_chunks) * a.chunk_codes;
+                    const int64_t clen = head ? a.head_codes : a.chunk_codes;
                     const int64_t cend = cbeg + clen < a.n ? cbeg + clen : a.n;
                     sm.code_begin = cbeg;
                     sm.chunk_ptr = a.codes + cbeg * CB;
@@ -2634,7 +2631,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             PQ_HIP(ctx, hipEventRecord(ctx->ev_end, ctx->stream));
             ctx->ev_valid = 1;
         }
-        AgainArgs again{a.work_counter + ONEHOT_AGAIN, (uint32_t *)(ws + off_again), a.work_counter, a.hist, a.tau_key, n, block_tile, (int)nchunks, (int)nitems, nblocks, qb};
+        AgainArgs again{a.work_counter + ONEHOT_AGAIN, (uint32_t *)(ws + off_again), a.work_counter, a.hist, a.tau_key, (int)nchunks, qb};
         rc = launch_merge_counted(ctx, lists, cnt, (uint32_t)onehot_cap, again, nq, topk, out_val, out_ids, exact_bins(cb));
         if (rc) return rc;
         // the queries whose list is too short or had no room for its keys once more, from the bounds found so far
