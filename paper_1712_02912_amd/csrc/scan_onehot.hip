@@ -13,12 +13,17 @@
 //
 // Keys (sum, row) within the bound cost an atomic addition in device memory each, and a bound that falls while the scan goes on
 // lets topk (1 + ln(n / codes of the first bound)) of them through per query: 25 M encoded codes, 1000 queries, top-1000 took 7.4 M
-// additions to lists and as many to histograms, 1.8 of 3.6 ms.  The bounds are therefore found first, from every onehot_stride-th
-// load of codes, by the same loop, whose keys are only counted: a quarter of the sample with a bound from a few thousand of its
+// additions to lists and as many to histograms, 1.8 of 3.6 ms.  The bounds are therefore found first, from a sample of the codes,
+// by the same loop, whose keys are only counted: a quarter of the sample with a bound from a few thousand of its
 // codes, the rest with the bound that the quarter gives.  Of the whole sample the r-th key is taken, r = mu + 4.5 sqrt(mu) + 4,
-// which is so far above the number mu = topk / stride of the results that such a sample holds that fewer than topk codes of all at
-// or below it are one query in a million (if it is a sample).  Some 1.5 topk codes per query pass in the scan itself; their keys go to
-// the query's list.  A list of fewer than topk keys, or of more than it has room for, sends the call the way it went before.
+// which is so far above the number mu = topk / 2^shift of the results that such a sample holds that fewer than topk codes of all at
+// or below it are one query in a million.  The sample has one row of every 2^shift, each in a place of its own, so that the results in it
+// are as many as of independent rows, or closer to mu, whatever the order that the rows are stored in.  (Every 2^shift-th load of 1024
+// bytes, as it was, is no such sample where neighbours lie together: 25 M codes in groups of 64 neighbours x 1000 queries, top-1000,
+// left hundreds of queries short lists.)  It is gathered first: half of the lines of memory are touched, 22 us for 25 M codes (16
+// if they are in the last cache).  Some 1.5 topk codes per query pass in the scan itself; their keys go to the query's list.  Queries whose
+// list has fewer than topk keys, or more than it has room for, are left to the other loops.  25 M codes x 1000 queries, top-1000, before and after:
+// in no order 2.64 and 2.61 ms, in groups of 64 neighbours 9.8 and 2.2, in the order of 8192 lists 11.3 and 2.9 (16-query loop 5.2, 3.9 and 8.0).
 //
 // What bounds it: v_mfma_f32_32x32x64_f8f6f4 on these types forms 1024 sums of 16 tables in 4 instructions of 32 cycles, 19.6 T
 // sums/s at the nominal clock; under this load the device holds 13.3 T/s without any tests, 12.9 T/s with them in the shadow of the
@@ -42,10 +47,11 @@ constexpr int OH_WAVES = 4, OH_THREADS = OH_WAVES * 64;
 constexpr int OH_QUEUE = 512;                  // (row, query) pairs of a wave that wait for their exact sums
 constexpr int OH_CENTRE = 15;                  // e is stored as e - 15, and a table's share of R is 15
 constexpr int OH_MOST = 75;
+constexpr int OH_PICK_THREADS = 512;            // of the last look at the counts (see onehot_pick_kernel)
 enum { OH_FIRST, OH_REST, OH_LIST };           // a quarter of the sample, the rest of it, all codes
 
 struct OnehotArgs {
-    const uint8_t *codes;
+    const uint8_t *codes;          // (of the sample: gathered)
     int64_t n;
     // Chunks: nhead ones of head_codes rows, then ones of chunk_codes (both multiples of a block's load of codes, below 2^25).  Where
     // sums tie by the ten thousand, the rows that are listed are the first ones: those come in small items.
@@ -54,7 +60,7 @@ struct OnehotArgs {
     int ntiles, nitems;    // item = chunk * ntiles + tile of queries
     const uint8_t *qluts;
     int nq, topk, hist_bins;       // (sample: the rank looked for in place of topk)
-    int stride;                    // every stride-th load of codes is looked at
+    int shift;                     // (sample: its i-th code is that of row onehot_sample_row(i, shift))
     unsigned long long *tau_key;   // [nq] whole key at or below which the query has topk codes
     uint32_t *cnt;                 // [nq][COUNT_PITCH] keys handed to the query's list
     uint32_t *hist;                // [nq][HIST_BINS]
@@ -127,9 +133,9 @@ __device__ __noinline__ void onehot_flush(lds_ptr<OnehotSmem<NB, G>> sm, int wav
     const int lane = lane_id();
     const uint8_t *chunk_ptr = sm->chunk_ptr;
     const uint32_t ncodes = (uint32_t)sm->ncodes, row0 = (uint32_t)sm->begin;
-    const int q0 = sm->q0;
+    const int q0 = sm->q0, shift = sm->a.shift;
     for (int i0 = 0; i0 < qn; i0 += 64 * U) {
-        uint32_t q[U], row[U], w[U][NB / 4];
+        uint32_t q[U], row[U], id[U], w[U][NB / 4];   // (id: the row in the database)
         bool in[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -138,6 +144,10 @@ __device__ __noinline__ void onehot_flush(lds_ptr<OnehotSmem<NB, G>> sm, int wav
             q[u] = e & 127u;
             row[u] = e >> 7;
             in[u] = i < qn && row[u] < ncodes;
+            id[u] = SAMPLE ? onehot_sample_row(row0 + row[u], shift) : row0 + row[u];
+            // (codes of the least sum that the tables allow: behind the bound's row nothing can qualify)
+            const unsigned long long bound = sm->key[q[u]];
+            in[u] = in[u] && !((uint32_t)(bound >> 32) == sm->off[q[u]] && id[u] > (uint32_t)bound);
 #pragma unroll
             for (int x = 0; x < NB / 4; ++x) w[u][x] = 0u;
             if (in[u]) {
@@ -150,46 +160,53 @@ __device__ __noinline__ void onehot_flush(lds_ptr<OnehotSmem<NB, G>> sm, int wav
                 }
             }
         }
-        uint32_t sum[U], at[U];   // (at: place in the list)
+        uint32_t sum[U], base[U], rank[U];   // (places in the list: that of the lane named `leader`, and from there)
+        int leader[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             sum[u] = sm->off[q[u]];
             lds_ptr<uint8_t> t = &sm->tab[q[u]][0];
 #pragma unroll
             for (int j = 0; j < NB * 2; ++j) sum[u] += t[j * 16 + ((w[u][j >> 3] >> (4 * (j & 7))) & 15u)];
-            const unsigned long long key = (unsigned long long)sum[u] << 32 | (row0 + row[u]);
+            const unsigned long long key = (unsigned long long)sum[u] << 32 | id[u];
             in[u] = in[u] && key <= sm->key[q[u]];
         }
-        // Additions to one address are made one after the other, 8 ns each.  Ties by the ten thousand crowd in few queries: lanes that
-        // share what the first of them adds to add together, three times over.
+        // Additions to one address are made one after the other, 8 ns each.  Ties by the ten thousand crowd in few queries, and so do
+        // the candidates where neighbours are stored together: lanes that share what the first of them adds to add together, three times over
+        // (all additions of the lanes in one instruction, whose answer takes a microsecond: 4 M codes in the order of 8192 lists, 1000 queries,
+        // top-1000, 1750 -> 1265 us against an instruction a turn).
         auto add = [](uint32_t *at, uint32_t by) { return __hip_atomic_fetch_add(at, by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             uint64_t todo = __ballot(in[u]);
             if constexpr (!SAMPLE) {
+                uint32_t by = 1u;
+                leader[u] = lane;
+                rank[u] = base[u] = 0u;
                 for (int turn = 0; turn < 3 && todo != 0ull; ++turn) {
                     const int first = __builtin_ctzll(todo);
                     const uint64_t same = __ballot(in[u] && q[u] == (uint32_t)__builtin_amdgcn_readlane(q[u], first)) & todo;
                     if (__popcll(same) < 6) break;
-                    uint32_t base = 0;
-                    if (lane == first) base = add(sm->a.cnt + (size_t)(q0 + q[u]) * COUNT_PITCH, (uint32_t)__popcll(same));
-                    base = __builtin_amdgcn_readlane(base, first);
-                    if ((same >> lane) & 1ull) at[u] = base + (uint32_t)mask_prefix(same);
+                    if ((same >> lane) & 1ull) {
+                        leader[u] = first;
+                        rank[u] = (uint32_t)mask_prefix(same);
+                        by = (uint32_t)__popcll(same);
+                    }
                     todo &= ~same;
                 }
-                if ((todo >> lane) & 1ull) at[u] = add(sm->a.cnt + (size_t)(q0 + q[u]) * COUNT_PITCH, 1u);
+                if (in[u] && leader[u] == lane) base[u] = add(sm->a.cnt + (size_t)(q0 + q[u]) * COUNT_PITCH, by);
             } else {
                 uint32_t *const bin = sm->a.hist + (size_t)(q0 + q[u]) * HIST_BINS + (sum[u] < HIST_BINS ? sum[u] : HIST_BINS - 1);
                 uint32_t *tie = nullptr;
 #pragma unroll
                 for (int s = 0; s < ONEHOT_TIES; ++s)
                     if (in[u] && sum[u] + 1u == sm->tie_val[q[u]][s])
-                        tie = sm->a.tie_rows + ((size_t)(q0 + q[u]) * ONEHOT_TIES + s) * ONEHOT_TIE_BINS + tie_bin(row0 + row[u]);
+                        tie = sm->a.tie_rows + ((size_t)(q0 + q[u]) * ONEHOT_TIES + s) * ONEHOT_TIE_BINS + tie_bin(id[u]);
                 for (int turn = 0; turn < 3 && todo != 0ull; ++turn) {
                     const int first = __builtin_ctzll(todo);
                     const uint64_t same = __ballot(in[u] && q[u] == (uint32_t)__builtin_amdgcn_readlane(q[u], first) && sum[u] == (uint32_t)__builtin_amdgcn_readlane(sum[u], first)) & todo;
                     if (__popcll(same) < 6) break;
-                    const uint32_t bucket = tie_bin(row0 + row[u]);
+                    const uint32_t bucket = tie_bin(id[u]);
                     const uint64_t near = __ballot(bucket == (uint32_t)__builtin_amdgcn_readlane(bucket, first)) & same;
                     if (lane == first) {
                         add(bin, (uint32_t)__popcll(same));
@@ -204,41 +221,60 @@ __device__ __noinline__ void onehot_flush(lds_ptr<OnehotSmem<NB, G>> sm, int wav
         }
         if constexpr (!SAMPLE) {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (in[u] && at[u] < sm->a.cap) sm->a.lists[(size_t)(q0 + q[u]) * sm->a.cap + at[u]] = (uint64_t)sum[u] << 32 | (row0 + row[u]);
+            for (int u = 0; u < U; ++u) {
+                const uint32_t at = (uint32_t)__shfl((int)base[u], leader[u]) + rank[u];
+                if (in[u] && at < sm->a.cap) sm->a.lists[(size_t)(q0 + q[u]) * sm->a.cap + at] = (uint64_t)sum[u] << 32 | id[u];
+            }
         }
     }
 }
 
+// The place of the counts by rows of the sum `bin`, -1 if there are none: they are kept from now on if there is a place left.
+__device__ __forceinline__ int onehot_tie_slot(uint32_t *tie_val, uint32_t bin) {
+    for (int s = 0; s < ONEHOT_TIES; ++s) {
+        const uint32_t v = __builtin_amdgcn_readfirstlane(__hip_atomic_load(tie_val + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (v == bin + 1u) return s;
+        if (v == 0u) {
+            if (lane_id() == 0) __hip_atomic_store(tie_val + s, bin + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return -1;
+        }
+    }
+    return -1;
+}
+
+// A bound, and where a better one is to be looked for: the need-th sampled row (0: nowhere) of its sum among those in tie bin `bin` (-1: all).
+struct OnehotCut {
+    uint64_t key;
+    uint32_t need;
+    int bin;
+};
+
 // For one wave: the key at or below which `topk` of the counted keys are (KEY_EMPTY: fewer, or beyond the bins that say something).
 // Sums tie, in clustered data by the hundred thousand, and rows tell them apart: the first bound on a sum that far more than topk
 // keys reach has the rows of that sum counted from then on (the least sum that the tables allow is counted from the start), later ones
-// end at the last row of the bin in which the last tie that is needed falls.  Counts may lag behind, never run ahead.
-__device__ __forceinline__ uint64_t onehot_bound(const uint32_t *hist, uint32_t *tie_val, const uint32_t *tie_rows, int topk, int hist_bins) {
+// end at the last row of the bin in which the last tie that is needed falls.  Counts may lag behind, never run ahead.  Equal codes that are
+// stored side by side all fall in one bin: where more than `most` beyond those needed do, the rows themselves are worth a look.
+template <bool LAST>
+__device__ __forceinline__ OnehotCut onehot_bound(const uint32_t *hist, uint32_t *tie_val, const uint32_t *tie_rows, int topk, int hist_bins, uint32_t most) {
     const int lane = lane_id();
     const int bin = hist_threshold(hist, topk);
-    if (bin >= hist_bins) return KEY_EMPTY;
+    if (bin >= hist_bins) return {KEY_EMPTY, 0u, -1};
     uint32_t below = 0;
     for (int i = lane; i < bin; i += 64) below += hist[i];
     for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o);
     below = __builtin_amdgcn_readfirstlane(below);
     uint64_t key = (uint64_t)(uint32_t)bin << 32 | 0xffffffffull;
     // (the counts grow while they are read: more than topk below the bin bounds the sums by bin - 1)
-    if (below >= (uint32_t)topk) return bin > 0 ? key - (1ull << 32) : key;
-    if (below + hist[bin] < 2u * (uint32_t)topk + 64u) return key;
-    int slot = -1;
-#pragma unroll 1
-    for (int s = 0; s < ONEHOT_TIES && slot < 0; ++s) {
-        uint32_t v = 0;
-        if (lane == 0) {
-            v = __hip_atomic_load(tie_val + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (v == 0u) __hip_atomic_compare_exchange_strong(tie_val + s, &v, (uint32_t)bin + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        v = __builtin_amdgcn_readfirstlane(v);
-        if (v == 0u) return key;   // counted from now on
-        if (v == (uint32_t)bin + 1u) slot = s;
+    if (below >= (uint32_t)topk) return {bin > 0 ? key - (1ull << 32) : key, 0u, -1};
+    const uint32_t ties = __builtin_amdgcn_readfirstlane(hist[bin]), need = (uint32_t)topk - below;
+    if (below + ties < 2u * (uint32_t)topk + 64u) return {key, 0u, -1};
+    if constexpr (!LAST) {   // a quarter of the sample: the whole will likely end at an earlier sum
+        const int likely = hist_threshold(hist, (topk + 3) / 4);
+        if (likely < bin && hist[likely] > most / 8) (void)onehot_tie_slot(tie_val, (uint32_t)likely);
     }
-    if (slot < 0) return key;
+    const OnehotCut by_sum = {key, LAST && ties > need && ties - need > most ? need : 0u, -1};
+    const int slot = onehot_tie_slot(tie_val, (uint32_t)bin);
+    if (slot < 0) return by_sum;
     uint32_t c[ONEHOT_TIE_BINS / 64], incl = 0;
 #pragma unroll
     for (int i = 0; i < ONEHOT_TIE_BINS / 64; ++i) {
@@ -251,18 +287,77 @@ __device__ __forceinline__ uint64_t onehot_bound(const uint32_t *hist, uint32_t 
         const uint32_t up = __shfl_up(incl, o);
         if (lane >= o) incl += up;
     }
-    const uint32_t need = (uint32_t)topk - below;
     const uint64_t reach = __ballot(incl >= need);
-    if (reach == 0ull) return key;
+    if (reach == 0ull) return by_sum;
     const int l = __builtin_ctzll(reach);
-    uint32_t cum = incl - mine, last = 0;   // (of lane l)
+    uint32_t cum = incl - mine, last = 0, wanted = 0, there = 0;   // (of lane l; of the bin's ties: needed, counted)
 #pragma unroll
     for (int i = 0; i < ONEHOT_TIE_BINS / 64; ++i) {
-        if (cum < need) last = (uint32_t)i;
+        if (cum < need) { last = (uint32_t)i; wanted = need - cum; there = c[i]; }
         cum += c[i];
     }
     const uint32_t last_bin = (uint32_t)l * (ONEHOT_TIE_BINS / 64) + (uint32_t)__builtin_amdgcn_readlane(last, l);
-    return (uint64_t)(uint32_t)bin << 32 | tie_bin_last_row(last_bin);
+    wanted = (uint32_t)__builtin_amdgcn_readlane(wanted, l);
+    there = (uint32_t)__builtin_amdgcn_readlane(there, l);
+    return {(uint64_t)(uint32_t)bin << 32 | tie_bin_last_row(last_bin), LAST && there - wanted > most ? wanted : 0u, (int)last_bin};
+}
+
+// Whole block: the row of the cut's need-th tie in the sample (0xffffffff: there are fewer).
+template <int NB>
+__device__ __forceinline__ uint32_t onehot_tied_row(const OnehotArgs &a, int q, const OnehotCut cut) {
+    constexpr int U = 4, WAVES = OH_PICK_THREADS / 64;
+    __shared__ uint16_t pair[NB][256];
+    __shared__ uint32_t got[2][U][WAVES], found;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint8_t *const tab = a.qluts + (size_t)q * (NB * 32);
+    for (int i = tid; i < NB * 256; i += OH_PICK_THREADS) {
+        const int r = i >> 8, byte = i & 255;
+        pair[r][byte] = (uint16_t)(tab[r * 32 + (byte & 15)] + tab[r * 32 + 16 + (byte >> 4)]);
+    }
+    if (tid == 0) found = 0xffffffffu;
+    __syncthreads();
+    const uint32_t sum = (uint32_t)(cut.key >> 32), ns = (uint32_t)a.n;
+    const uint32_t first = cut.bin <= 0 ? 0u : (tie_bin_last_row((uint32_t)cut.bin - 1u) + 1u) >> a.shift;
+    const uint64_t last = cut.bin < 0 ? ns - 1u : tie_bin_last_row((uint32_t)cut.bin) >> a.shift;   // (in the sample)
+    const uint32_t end = last < ns ? (uint32_t)last + 1u : ns;
+    uint32_t seen = 0;
+    for (uint32_t at = first, turn = 0; at < end; at += U * OH_PICK_THREADS, turn ^= 1u) {
+        uint64_t tied[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = at + u * OH_PICK_THREADS + tid;
+            uint32_t w[NB / 4] = {};
+            if (i < end) {
+                if constexpr (NB == 8) {
+                    const uint2 v = reinterpret_cast<const uint2 *>(a.codes)[i];
+                    w[0] = v.x; w[1] = v.y;
+                } else {
+                    const uint4 v = reinterpret_cast<const uint4 *>(a.codes)[i];
+                    w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+                }
+            }
+            uint32_t s = 0;
+#pragma unroll
+            for (int r = 0; r < NB; ++r) s += pair[r][(w[r >> 2] >> (8 * (r & 3))) & 255u];
+            tied[u] = __ballot(i < end && s == sum && (cut.bin < 0 || tie_bin(onehot_sample_row(i, a.shift)) == (uint32_t)cut.bin));
+            if (lane == 0) got[turn][u][wave] = (uint32_t)__popcll(tied[u]);
+        }
+        __syncthreads();   // (one per turn: the next one's counts go to the other half)
+        uint32_t before = seen;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            for (int w = 0; w < WAVES; ++w) {
+                const uint32_t c = got[turn][u][w];
+                if (w == wave && before < cut.need && before + c >= cut.need) {
+                    if (((tied[u] >> lane) & 1ull) && (uint32_t)mask_prefix(tied[u]) == cut.need - 1u - before) found = onehot_sample_row(at + u * OH_PICK_THREADS + tid, a.shift);
+                }
+                before += c;
+            }
+        seen = before;
+        if (seen >= cut.need) break;
+    }
+    __syncthreads();
+    return found;
 }
 
 // Whole block: the queries' bounds and the tables' image for the rows from row_lo on.
@@ -370,10 +465,10 @@ __global__ __launch_bounds__(OH_THREADS, onehot_blocks_per_cu(NB, G)) void scan_
             if (least != 0u) atomicAdd(&sm.off[q], least);
         }
         // the loads that this pass looks at, and the one that is its x-th
-        const int runs = SAMPLE ? (ncodes + a.stride * LOAD - 1) / (a.stride * LOAD) : (ncodes + LOAD - 1) / LOAD;
+        const int runs = (ncodes + LOAD - 1) / LOAD;
         const int nloads = PASS == OH_FIRST ? (runs + 3) / 4 : PASS == OH_REST ? runs - (runs + 3) / 4 : runs;
         auto row_of = [&](int x) -> int {   // (x beyond nloads by up to two rounds of the waves: below 2^25 all the same)
-            return PASS == OH_LIST ? x * LOAD : (PASS == OH_FIRST ? 4 * x : x + x / 3 + 1) * (a.stride * LOAD);
+            return (PASS == OH_LIST ? x : PASS == OH_FIRST ? 4 * x : x + x / 3 + 1) * LOAD;
         };
         const int per_wave = (nloads + OH_WAVES - 1) / OH_WAVES;
         // 16 bytes per lane, rows beyond the item read as zeros
@@ -391,7 +486,7 @@ __global__ __launch_bounds__(OH_THREADS, onehot_blocks_per_cu(NB, G)) void scan_
         };
         uint4 code_a = load(wave), code_b = load(wave + OH_WAVES);   // (two loads on their way: one's products take 1 us, memory sometimes longer)
         __syncthreads();
-        onehot_image<NB, G, SAMPLE>(smp, (uint32_t)begin);
+        onehot_image<NB, G, SAMPLE>(smp, SAMPLE ? onehot_sample_row((uint32_t)begin, a.shift) : (uint32_t)begin);
         {
             v8i A[G][NS];
 #pragma unroll
@@ -494,34 +589,62 @@ __global__ __launch_bounds__(OH_THREADS, onehot_blocks_per_cu(NB, G)) void scan_
     }
 }
 
-// The bounds that the counts give: one wave per query.
-__global__ __launch_bounds__(64) void onehot_pick_kernel(OnehotArgs a) {
+// The bounds that the counts give: one wave per query, and behind the whole sample (LAST) a block that looks through it for the row at which
+// ties end (only where a list might have no room for them).
+template <int NB, bool LAST>
+__global__ __launch_bounds__(LAST ? OH_PICK_THREADS : 64) void onehot_pick_kernel(OnehotArgs a) {
     const int q = blockIdx.x;
-    const unsigned long long key = onehot_bound(a.hist + (size_t)q * HIST_BINS, a.tie_val + (size_t)q * ONEHOT_TIES,
-                                                a.tie_rows + (size_t)q * (ONEHOT_TIES * ONEHOT_TIE_BINS), a.topk, a.hist_bins);
-    if (threadIdx.x == 0 && key < a.tau_key[q]) a.tau_key[q] = key;
-    if (q == 0 && threadIdx.x == 0) *a.work_counter = 0u;
+    __shared__ OnehotCut s_cut;
+    const uint32_t most = (a.cap - a.cap / 4 >> a.shift) - (uint32_t)a.topk;   // (of a list's room three quarters; cap is far above the topk of both)
+    if (threadIdx.x < 64) {
+        const uint32_t *const hist = a.hist + (size_t)q * HIST_BINS;
+        uint32_t *const tie_val = a.tie_val + (size_t)q * ONEHOT_TIES;
+        const OnehotCut cut = onehot_bound<LAST>(hist, tie_val, a.tie_rows + (size_t)q * (ONEHOT_TIES * ONEHOT_TIE_BINS), a.topk, a.hist_bins, most);
+        const unsigned long long before = a.tau_key[q];
+        if (cut.key < before && threadIdx.x == 0) a.tau_key[q] = cut.key;
+        if (LAST && threadIdx.x == 0) s_cut = cut;
+        if (q == 0 && threadIdx.x == 0) *a.work_counter = 0u;
+    }
+    if constexpr (LAST) {
+        __syncthreads();
+        const OnehotCut cut = s_cut;
+        if (cut.need == 0u) return;
+        const uint32_t row = onehot_tied_row<NB>(a, q, cut);
+        const unsigned long long key = cut.key >> 32 << 32 | row;
+        if (threadIdx.x == 0 && key < a.tau_key[q]) a.tau_key[q] = key;
+    }
 }
 
-// (before the sample) the least sum that a query's tables allow is the first whose rows are counted
-__global__ __launch_bounds__(64) void onehot_least_kernel(OnehotArgs a, int tables) {
-    const int q = blockIdx.x, lane = threadIdx.x;
+// The sample gathered, and the least sum that a query's tables allow: the first whose rows are counted.  Bound by the lines of memory that the
+// sample touches.
+template <class CODE>
+__global__ __launch_bounds__(256) void onehot_sample_kernel(const CODE *__restrict__ codes, uint32_t ns, int shift, CODE *__restrict__ sample,
+                                                            const uint8_t *__restrict__ qluts, int nq, int tables, uint32_t *__restrict__ tie_val) {
+    const int least_blocks = (nq + 3) / 4;   // (a wave per query)
+    if ((int)blockIdx.x >= least_blocks) {
+        const uint32_t i = (blockIdx.x - (uint32_t)least_blocks) * 256u + threadIdx.x;
+        if (i < ns) sample[i] = codes[onehot_sample_row(i, shift)];
+        return;
+    }
+    const int q = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (q >= nq) return;
     uint32_t least = 0;
     if (lane < tables) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(a.qluts + ((size_t)q * tables + lane) * 16);
+        const uint4 v = *reinterpret_cast<const uint4 *>(qluts + ((size_t)q * tables + lane) * 16);
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
         least = 255u;
 #pragma unroll
         for (int x = 0; x < 16; ++x) least = min(least, (w[x >> 2] >> (8 * (x & 3))) & 255u);
     }
     for (int o = 32; o > 0; o >>= 1) least += __shfl_xor(least, o);
-    if (lane == 0) a.tie_val[(size_t)q * ONEHOT_TIES] = least + 1u;
+    if (lane == 0) tie_val[(size_t)q * ONEHOT_TIES] = least + 1u;
 }
 
 template <int NB, int G, int PASS>
 static int launch_tiles(pq_ctx *ctx, OnehotArgs &a) {
     constexpr int QT = 32 * G, LOAD = 1024 / NB;
-    const int64_t step = (int64_t)LOAD * (PASS == OH_LIST ? OH_WAVES : 4 * a.stride);
+    constexpr int64_t step = (int64_t)LOAD * OH_WAVES;   // (and a round of the sample's four quarters)
+    static_assert(OH_WAVES == 4, "a quarter of a chunk's loads of the sample is every fourth");
     const int most = onehot_blocks_per_cu(NB, G) * ctx->num_cu;
     a.ntiles = (a.nq + QT - 1) / QT;
     // As many items per block as have 64 loads of a wave and more (their set-up takes the time of 10), up to six: of the two blocks of a
@@ -548,39 +671,52 @@ static int launch_tiles(pq_ctx *ctx, OnehotArgs &a) {
 }
 
 template <int NB, int G>
-static int launch_passes(pq_ctx *ctx, OnehotArgs &a, int topk) {
-    onehot_least_kernel<<<a.nq, 64, 0, ctx->stream>>>(a, 2 * NB);
-    PQ_HIP(ctx, hipGetLastError());
+static int launch_passes(pq_ctx *ctx, OnehotArgs &a, const uint8_t *codes, int64_t n, int topk) {
     int rc = launch_tiles<NB, G, OH_FIRST>(ctx, a);
     if (rc) return rc;
-    onehot_pick_kernel<<<a.nq, 64, 0, ctx->stream>>>(a);
+    onehot_pick_kernel<NB, false><<<a.nq, 64, 0, ctx->stream>>>(a);
     PQ_HIP(ctx, hipGetLastError());
     rc = launch_tiles<NB, G, OH_REST>(ctx, a);
     if (rc) return rc;
-    onehot_pick_kernel<<<a.nq, 64, 0, ctx->stream>>>(a);
+    onehot_pick_kernel<NB, true><<<a.nq, OH_PICK_THREADS, 0, ctx->stream>>>(a);
     PQ_HIP(ctx, hipGetLastError());
     a.topk = topk;
+    a.codes = codes;
+    a.n = n;
     return launch_tiles<NB, G, OH_LIST>(ctx, a);
 }
 
 int onehot_queries_per_pass(int code_bytes, int nq) { return nq <= 32 ? 32 : nq <= 64 || code_bytes == 16 ? 64 : 128; }
 
-// (a 32nd of 25 M codes costs the sample's passes 0.25 ms for 1000 queries and lets 1.9 topk codes through, a 16th 0.4 and 1.6)
-int onehot_stride(int64_t n) { return n >= 1 << 23 ? 32 : n >= 1 << 21 ? 16 : 8; }
+// (a 32nd of 25 M codes costs the sample's passes 0.25 ms for 1000 queries and lets 1.9 topk codes through, a 16th 0.4 and 1.6; less where it has no room)
+int onehot_shift(int64_t n, int code_bytes, size_t room) {
+    int shift = n >= 1 << 23 ? 5 : n >= 1 << 21 ? 4 : 3;
+    while (shift <= 8 && (size_t)(n >> shift) * code_bytes > room) ++shift;
+    return shift <= 8 ? shift : 0;
+}
 
-int onehot_rank(int64_t n, int topk) {
-    const double mu = (double)topk / onehot_stride(n);
+int onehot_rank(int shift, int topk) {
+    const double mu = (double)topk / (1 << shift);
     return (int)(mu + 4.5 * sqrt(mu) + 4.0);
 }
 
-int launch_scan_onehot(pq_ctx *ctx, const uint8_t *codes, int64_t n, int code_bytes, const uint8_t *qluts, int nq, int topk, int hist_bins,
+int launch_onehot_sample(pq_ctx *ctx, const uint8_t *codes, int64_t n, int code_bytes, int shift, uint8_t *sample, const uint8_t *qluts, int nq, uint32_t *ties) {
+    const uint32_t ns = (uint32_t)(n >> shift);
+    const unsigned blocks = (unsigned)((nq + 3) / 4) + (ns + 255) / 256;
+    if (code_bytes == 8) onehot_sample_kernel<uint2><<<blocks, 256, 0, ctx->stream>>>((const uint2 *)codes, ns, shift, (uint2 *)sample, qluts, nq, 16, ties);
+    else onehot_sample_kernel<uint4><<<blocks, 256, 0, ctx->stream>>>((const uint4 *)codes, ns, shift, (uint4 *)sample, qluts, nq, 32, ties);
+    PQ_HIP(ctx, hipGetLastError());
+    return PQ_OK;
+}
+
+int launch_scan_onehot(pq_ctx *ctx, const uint8_t *codes, int64_t n, int code_bytes, const uint8_t *sample, int shift, const uint8_t *qluts, int nq, int topk, int hist_bins,
                        unsigned long long *tau_key, uint32_t *cnt, uint32_t *hist, uint64_t *lists, uint32_t cap,
                        uint32_t *ties, uint32_t *work_counter, unsigned long long *stats) {
-    OnehotArgs a{codes, n, 0, 0, 0, 0, 0, qluts, nq, onehot_rank(n, topk), hist_bins, onehot_stride(n), tau_key, cnt, hist, lists, cap,
+    OnehotArgs a{sample, n >> shift, 0, 0, 0, 0, 0, qluts, nq, onehot_rank(shift, topk), hist_bins, shift, tau_key, cnt, hist, lists, cap,
                  ties, ties + (size_t)nq * ONEHOT_TIES, work_counter, stats};
     const int width = onehot_queries_per_pass(code_bytes, nq);
-    if (code_bytes == 8) return width == 32 ? launch_passes<8, 1>(ctx, a, topk) : width == 64 ? launch_passes<8, 2>(ctx, a, topk) : launch_passes<8, 4>(ctx, a, topk);
-    return width == 32 ? launch_passes<16, 1>(ctx, a, topk) : launch_passes<16, 2>(ctx, a, topk);
+    if (code_bytes == 8) return width == 32 ? launch_passes<8, 1>(ctx, a, codes, n, topk) : width == 64 ? launch_passes<8, 2>(ctx, a, codes, n, topk) : launch_passes<8, 4>(ctx, a, codes, n, topk);
+    return width == 32 ? launch_passes<16, 1>(ctx, a, codes, n, topk) : launch_passes<16, 2>(ctx, a, codes, n, topk);
 }
 
 }  // namespace pq

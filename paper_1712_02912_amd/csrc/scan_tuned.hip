@@ -1555,9 +1555,9 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
 // entries of the block's queries for one code byte (both of its components added) are one 8-byte LDS
 // read, and their sums add up as four 16-bit fields of a 64-bit word.
 constexpr int SEED_QPB = 4;
-// (STRIDED: the codes are taken in runs of 1024 bytes, of which only every stride-th counts)
+// (STRIDED: the codes are those of a sample, see onehot_sample_row, and taken in runs of 1024 bytes, of which only every stride-th counts)
 template <int NT, bool STRIDED>   // code bytes = pair-merged tables, 8 or 16
-__global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict__ codes, int cnt, int stride,
+__global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict__ codes, int cnt, int stride, int shift,
                                                        const uint8_t *__restrict__ qluts, int kq, int nq, unsigned long long *tau_key) {
     static_assert(HIST_BINS == 4096, "sums of 16 bytes index the bins");
     constexpr uint32_t BINS = (uint32_t)exact_bins(NT);   // cuts from there on are none
@@ -1693,7 +1693,8 @@ __global__ __launch_bounds__(1024) void u4_seed_kernel(const uint8_t *__restrict
         const int nb = (cnt + 1023) / 1024;
         while (b < nb && cum + tie_cnt[myq][b] < need_s[myq]) cum += tie_cnt[myq][b++];
         if (b < nb) {
-            const uint32_t last_row = row_of(((b + 1) * 1024 < cnt ? (b + 1) * 1024 : cnt) - 1);
+            uint32_t last_row = row_of(((b + 1) * 1024 < cnt ? (b + 1) * 1024 : cnt) - 1);
+            if constexpr (STRIDED) last_row = onehot_sample_row(last_row, shift);
             tau_key[q0 + myq] = ((unsigned long long)cut_s[myq] << 32) | last_row;
         }
     }
@@ -2420,6 +2421,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     const size_t onehot_words = (size_t)nq * COUNT_PITCH + onehot_tie_words(nq), onehot_state = align_up(onehot_words * 4, 256);
     int64_t onehot_cap = L.total - L.off_scratch > onehot_state ? (int64_t)((L.total - L.off_scratch - onehot_state) / ((size_t)nq * 8)) / 64 * 64 : 0;
     if (onehot_cap > (small ? 16384 : 65536)) onehot_cap = small ? 16384 : 65536;
+    const int sample_shift = onehot_cap > 0 ? onehot_shift(n, cb, L.total - L.off_scratch - onehot_state) : 0;   // (and before them its sample)
     // It has a sample and a set-up of some 150 us to pay for, and it is twice as fast per (code, query) where the other loops serve 16
     // queries per pass, three times where they serve 8.  Time of the other loop over its own, encoded codes of 0.1 to 25 M vectors, 16 to
     // 1000 queries, top-10, -100 and -1000 (just above and below the lines; P: pairs, those of 32 tables counted twice):
@@ -2429,7 +2431,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     //   16 to 248, long results, 2^23 codes, P 2^28   1.0 to 1.36   (3 M codes, 64 queries 0.98; 25 M, 8 queries 0.92)
     const int64_t onehot_pairs = pairs * (cb / 8);
     bool onehot = false;
-    if (is_u4 && n >= PRUNE_MIN_N && n >= 32 * (int64_t)topk && onehot_cap >= (small ? 8192 : 32768) && ((uintptr_t)luts & 15) == 0 && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0) {
+    if (is_u4 && n >= PRUNE_MIN_N && n >= 32 * (int64_t)topk && sample_shift > 0 && onehot_cap >= (small ? 8192 : 32768) && ((uintptr_t)luts & 15) == 0 && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0) {
         if (opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 0) > 0) onehot = true;
         else if (nq >= 249) onehot = onehot_pairs >= (int64_t)1 << 28 || (!small && n >= 1 << 18);
         else onehot = (nq >= 24 && onehot_pairs >= (int64_t)11 << 26) || (nq >= 16 && !small && n >= 1 << 23 && onehot_pairs >= (int64_t)1 << 28);
@@ -2598,15 +2600,18 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             const unsigned seed_blocks = (unsigned)((nq + SEED_QPB - 1) / SEED_QPB);
             if (onehot) {
                 // a part of the sample that the scan on the matrix cores begins with
-                const int run = 1024 / cb, rank = onehot_rank(n, topk);
-                const int64_t sample_runs = n / ((int64_t)run * onehot_stride(n));   // (whole ones)
+                uint8_t *const sample = (uint8_t *)a.scratch + onehot_state;
+                rc = launch_onehot_sample(ctx, codes, n, cb, sample_shift, sample, (const uint8_t *)luts, nq, (uint32_t *)a.scratch + (size_t)nq * COUNT_PITCH);
+                if (rc) return rc;
+                const int run = 1024 / cb, rank = onehot_rank(sample_shift, topk);
+                const int64_t sample_runs = (n >> sample_shift) / run;   // (whole ones)
                 int64_t runs = 16384 / run;
                 if (runs > sample_runs) runs = sample_runs;
-                const int every = (int)(sample_runs / runs) * onehot_stride(n);
-                if (u4_m32) u4_seed_kernel<16, true><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, (int)runs * run, every, (const uint8_t *)luts, rank, nq, a.tau_key);
-                else u4_seed_kernel<8, true><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, (int)runs * run, every, (const uint8_t *)luts, rank, nq, a.tau_key);
-            } else if (u4_m32) u4_seed_kernel<16, false><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, 1, (const uint8_t *)luts, topk, nq, a.tau_key);
-            else u4_seed_kernel<8, false><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, 1, (const uint8_t *)luts, topk, nq, a.tau_key);
+                const int every = (int)(sample_runs / runs);
+                if (u4_m32) u4_seed_kernel<16, true><<<seed_blocks, 1024, 0, ctx->stream>>>(sample, (int)runs * run, every, sample_shift, (const uint8_t *)luts, rank, nq, a.tau_key);
+                else u4_seed_kernel<8, true><<<seed_blocks, 1024, 0, ctx->stream>>>(sample, (int)runs * run, every, sample_shift, (const uint8_t *)luts, rank, nq, a.tau_key);
+            } else if (u4_m32) u4_seed_kernel<16, false><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, 1, 0, (const uint8_t *)luts, topk, nq, a.tau_key);
+            else u4_seed_kernel<8, false><<<seed_blocks, 1024, 0, ctx->stream>>>(codes, seed_codes, 1, 0, (const uint8_t *)luts, topk, nq, a.tau_key);
         }
         PQ_HIP(ctx, hipGetLastError());
     }
@@ -2618,7 +2623,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     if (onehot) {
         uint64_t *const lists = (uint64_t *)((uint8_t *)a.scratch + onehot_state);
         uint32_t *const cnt = (uint32_t *)a.scratch;
-        rc = launch_scan_onehot(ctx, codes, n, cb, (const uint8_t *)luts, nq, topk, exact_bins(cb), a.tau_key, cnt, a.hist, lists,
+        rc = launch_scan_onehot(ctx, codes, n, cb, (const uint8_t *)a.scratch + onehot_state, sample_shift, (const uint8_t *)luts, nq, topk, exact_bins(cb), a.tau_key, cnt, a.hist, lists,
                                 (uint32_t)onehot_cap, cnt + (size_t)nq * COUNT_PITCH, a.work_counter, a.stats);
         if (rc) return rc;
         if (ctx->profiling) {

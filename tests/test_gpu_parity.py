@@ -808,6 +808,69 @@ def test_scan_u4_on_matrix_cores_scans_only_queries_without_bound_again(ctx, opt
     run_on_matrix_cores(ctx, packed, qluts, topk, len(bad))
 
 
+def sampled_rows(n, shift):
+    """The rows that bound a scan on the matrix cores (onehot_sample_row)."""
+    i = np.arange(n >> shift, dtype=np.uint64)
+    mix = np.uint64(0x9e3779b9)
+    x = ((i ^ (i >> np.uint64(15))) * mix) & np.uint64(0xffffffff)
+    x = ((x ^ (x >> np.uint64(15))) * mix) & np.uint64(0xffffffff)
+    return (i << np.uint64(shift) | x >> np.uint64(32 - shift)).astype(np.int64)
+
+
+def int_sums(packed, m, qlut):
+    nib = np.stack([packed & 15, packed >> 4], 2).reshape(len(packed), m)
+    return sum(qlut[j].astype(np.int32)[nib[:, j]] for j in range(m))
+
+
+# The sample is made to mislead: all results of some queries lie in it, so that it bounds too few.  Every form of the other loops that these
+# queries are left to (8 and 16 queries per pass, 32 tables, short and long results, coarse and fine tiles).
+@pytest.mark.parametrize("m,n,nq,topk,bad", [(16, 263_001, 300, 1000, [0, 7, 299]), (16, 263_000, 300, 100, list(range(2, 40, 2))), (16, 70_001, 40, 100, [39]),
+                                             (16, 1_100_003, 64, 128, [5, 60]), (16, 530_000, 9, 200, [8]), (32, 263_000, 300, 129, [1]), (32, 70_001, 100, 64, [3, 90])])
+def test_scan_u4_on_matrix_cores_scans_misled_queries_again(ctx, opts, m, n, nq, topk, bad):
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(n + nq + m)
+    packed = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
+    qluts = np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * r.uniform(5, 40, (nq, m, 1))).astype(np.uint8)
+    places = r.permutation(sampled_rows(n, 3))
+    for b, q in enumerate(bad):
+        best = np.argpartition(int_sums(packed, m, qluts[q]), topk)[:topk]
+        best = best[~np.isin(best, places[:(b + 1) * topk])]
+        to = places[b * topk:b * topk + len(best)]
+        packed[best], packed[to] = packed[to].copy(), packed[best].copy()
+    run_on_matrix_cores(ctx, packed, qluts, topk, len(bad))
+
+
+# Neighbours stored side by side: the sample bounds every query as it does for rows in any other order.
+@pytest.mark.parametrize("m,n,nq,topk,group", [(16, 300_000, 300, 1000, 64), (16, 300_032, 300, 100, 1024), (16, 2_200_000, 60, 100, 64), (32, 300_000, 100, 1000, 64), (16, 131_072, 100, 10, 16)])
+def test_scan_u4_on_matrix_cores_neighbours_side_by_side(ctx, opts, m, n, nq, topk, group):
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(n + nq + m)
+    nib = np.repeat(r.integers(0, 16, (n // group, m), dtype=np.uint8), group, 0)
+    moved = r.random(nib.shape) < 0.15
+    nib[moved] = r.integers(0, 16, int(moved.sum()), dtype=np.uint8)
+    packed = np.ascontiguousarray(nib[:, 0::2] | nib[:, 1::2] << 4)
+    qluts = np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * r.uniform(5, 40, (nq, m, 1))).astype(np.uint8)
+    run_on_matrix_cores(ctx, packed, qluts, topk, 0)
+
+
+# Equal codes stored side by side, far from the start: their rows, not their sum, end the results.  They are the nearest codes of half of the queries: of the
+# least sum that the tables allow, or of a greater one.
+@pytest.mark.parametrize("m,nq,topk,least", [(16, 40, 100, True), (16, 40, 1000, False), (32, 20, 1000, True), (32, 20, 50, False)])
+def test_scan_u4_on_matrix_cores_equal_codes_side_by_side(ctx, opts, m, nq, topk, least):
+    opts.set("scan_onehot", 1)
+    n, r = 2_200_003, np.random.default_rng(nq + m + topk)
+    packed = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
+    code = r.integers(0, 16, m, dtype=np.uint8)
+    packed[2_000_000:2_090_000] = code[0::2] | code[1::2] << 4
+    qluts = (1 + np.minimum(254, r.standard_normal((nq, m, 16)) ** 2 * r.uniform(5, 40, (nq, m, 1)))).astype(np.uint8)
+    qluts[::2, np.arange(m), code] = 0
+    if not least:
+        qluts[::2, 0, (code[0] + 1) % 16] = qluts[::2, 1, (code[1] + 1) % 16] = 0
+        qluts[::2, 0, code[0]] = 1
+        packed[:, 0] = np.where((packed[:, 0] & 15) == (code[0] + 1) % 16, packed[:, 0] & 0xf0 | code[0], packed[:, 0])
+    run_on_matrix_cores(ctx, packed, qluts, topk, 0)
+
+
 # --------------------------------------------- 8x8 float scan, 8-bit lower bounds, 16 queries per pass
 # 512 queries and more (enough groups of 16 to fill the GPU) take the loop on 8-bit lower bounds; these
 # cases aim at what is specific to it: ragged last group, saturating entries, degenerate ranges, ties.
