@@ -821,7 +821,7 @@ int launch_ivf_quick(pq_ctx *ctx, const uint8_t *codes, const int64_t *list_offs
         ctx->stat_parked = nullptr;
         ctx->stat_ncand = nullptr;
         ctx->stat_ncand_len = 0;
-        ctx->stat_again = nullptr;
+        ctx->stat_onehot = nullptr;
     }
     {
         auto long_kernel = bounds ? ivf_quick_scan_kernel<8, true, true> : ivf_quick_scan_kernel<8, true, false>;

@@ -192,8 +192,8 @@ int pq_destroy(pq_ctx *ctx) {
         (void)hipEventDestroy(ctx->aux_fork);
         (void)hipEventDestroy(ctx->aux_join);
     }
-    if (ctx->ev_begin) (void)hipEventDestroy(ctx->ev_begin);
-    if (ctx->ev_end) (void)hipEventDestroy(ctx->ev_end);
+    for (hipEvent_t e : {ctx->ev_begin, ctx->ev_end, ctx->ev_again_begin, ctx->ev_again_end})
+        if (e) (void)hipEventDestroy(e);
     free(ctx);
     return PQ_OK;
 }
@@ -201,16 +201,20 @@ int pq_destroy(pq_ctx *ctx) {
 int pq_set_profiling(pq_ctx *ctx, int enable) {
     if (!ctx) return PQ_EINVAL;
     if (enable && !(ctx->ev_begin && ctx->ev_end)) {
-        // both events or none: a failure must not leave half of the pair behind
-        hipEvent_t b = nullptr, e = nullptr;
-        hipError_t rc = hipEventCreate(&b);
-        if (rc == hipSuccess) rc = hipEventCreate(&e);
-        if (rc != hipSuccess) {
-            if (b) (void)hipEventDestroy(b);
+        // all events or none: a failure must not leave some of them behind
+        hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+        for (hipEvent_t &e : ev) {
+            const hipError_t rc = hipEventCreate(&e);
+            if (rc == hipSuccess) continue;
+            e = nullptr;
+            for (hipEvent_t made : ev)
+                if (made) (void)hipEventDestroy(made);
             return hip_fail(ctx, rc, "hipEventCreate");
         }
-        ctx->ev_begin = b;
-        ctx->ev_end = e;
+        ctx->ev_begin = ev[0];
+        ctx->ev_end = ev[1];
+        ctx->ev_again_begin = ev[2];
+        ctx->ev_again_end = ev[3];
     }
     ctx->profiling = enable ? 1 : 0;
     ctx->ev_valid = 0;
@@ -222,6 +226,12 @@ int pq_last_scan_kernel_ms(pq_ctx *ctx, float *ms) {
     if (!ctx->ev_valid) return fail(ctx, PQ_EINVAL, "no profiled scan kernel recorded");
     PQ_HIP(ctx, hipEventSynchronize(ctx->ev_end));
     PQ_HIP(ctx, hipEventElapsedTime(ms, ctx->ev_begin, ctx->ev_end));
+    if (ctx->ev_valid & 2) {
+        float again = 0.f;
+        PQ_HIP(ctx, hipEventSynchronize(ctx->ev_again_end));
+        PQ_HIP(ctx, hipEventElapsedTime(&again, ctx->ev_again_begin, ctx->ev_again_end));
+        *ms += again;
+    }
     return PQ_OK;
 }
 
@@ -230,10 +240,10 @@ int pq_last_scan_info(pq_ctx *ctx, char *name, size_t name_bytes, int *queries_p
     if (!ctx) return PQ_EINVAL;
     if (!ctx->ev_valid) return fail(ctx, PQ_EINVAL, "no profiled scan kernel recorded");
     PQ_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    unsigned long long onehot[2] = {0, 0};
+    if (ctx->stat_onehot) PQ_HIP(ctx, hipMemcpy(onehot, ctx->stat_onehot, sizeof(onehot), hipMemcpyDeviceToHost));
     if (name && name_bytes > 0) {
-        uint32_t again = 0;
-        if (ctx->stat_again) PQ_HIP(ctx, hipMemcpy(&again, ctx->stat_again, sizeof(again), hipMemcpyDeviceToHost));
-        if (again != 0) snprintf(name, name_bytes, "%s; %u queries again by the other loops", ctx->last_scan_name, again);
+        if (onehot[1] != 0) snprintf(name, name_bytes, "%s; %llu queries again by the other loops", ctx->last_scan_name, onehot[1]);
         else snprintf(name, name_bytes, "%s", ctx->last_scan_name);
     }
     if (queries_per_pass) *queries_per_pass = ctx->last_scan_qpp;
@@ -249,7 +259,7 @@ int pq_last_scan_info(pq_ctx *ctx, char *name, size_t name_bytes, int *queries_p
 #endif
     }
     if (inserted_keys) {
-        uint64_t total = 0;
+        uint64_t total = onehot[0];
         uint32_t buf[1024];
         for (int at = 0; ctx->stat_ncand && at < ctx->stat_ncand_len; at += 1024) {
             const int take = ctx->stat_ncand_len - at < 1024 ? ctx->stat_ncand_len - at : 1024;

@@ -39,14 +39,15 @@ struct pq_ctx {
     int num_cu;
     int profiling;              // bracket the scan kernel with events
     hipEvent_t ev_begin, ev_end;
-    int ev_valid;
+    hipEvent_t ev_again_begin, ev_again_end;   // around a second kernel that belongs to the scan
+    int ev_valid;               // bit 0: ev_begin, ev_end; bit 1: the other two
     // measurement aids (valid while profiling): the scan kernel last launched, and where its counters live in the workspace
     char last_scan_name[320];
     int last_scan_qpp, last_scan_passes;
     const unsigned long long *stat_parked;
     const uint32_t *stat_ncand;
     int stat_ncand_len;
-    const uint32_t *stat_again;   // queries that a scan on the matrix cores left to the other loops
+    const unsigned long long *stat_onehot;   // scans on the matrix cores: keys inserted, queries left to the other loops
     char err[512];
 };
 
@@ -77,7 +78,7 @@ static inline void note_plain_scan(pq_ctx *ctx, const char *name, int queries_pe
     ctx->stat_parked = nullptr;
     ctx->stat_ncand = nullptr;
     ctx->stat_ncand_len = 0;
-    ctx->stat_again = nullptr;
+    ctx->stat_onehot = nullptr;
 }
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

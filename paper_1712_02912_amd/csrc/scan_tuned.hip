@@ -1528,12 +1528,12 @@ void scan_tuned_kernel(TunedArgs a) {
 __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *tau_key, uint32_t *ncand, uint32_t *mark,
                                   uint32_t *tau_ref, int ntau,
                                   uint32_t tau_value, uint32_t *hist, size_t nhist, const float *tau0, int nq,
-                                  uint32_t *also_zero = nullptr, size_t also_zero_n = 0, uint32_t *zero_too = nullptr, size_t zero_too_n = 0) {
+                                  uint32_t *also_zero = nullptr, size_t also_zero_n = 0, uint32_t *zero_too = nullptr, size_t zero_too_n = 0, bool keep_stats = false) {
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     if (i0 == 0) {
         *work_counter = 0;
-        for (int i = 2; i < 32; ++i) work_counter[i] = 0;   // the 64-bit statistics words behind it
+        for (int i = 2; i < 32 && !keep_stats; ++i) work_counter[i] = 0;   // the 64-bit statistics words behind it
         work_counter[ONEHOT_AGAIN] = 0;
     }
     for (size_t i = i0; i < (size_t)ntau; i += stride) {
@@ -1546,6 +1546,14 @@ __global__ void tuned_init_kernel(uint32_t *work_counter, unsigned long long *ta
     for (size_t i = i0; i < nhist; i += stride) hist[i] = 0;
     for (size_t i = i0; i < also_zero_n; i += stride) also_zero[i] = 0;   // (the bins of a first-bound pass that follows)
     for (size_t i = i0; i < zero_too_n; i += stride) zero_too[i] = 0;
+}
+
+// measurement aid: stats[0] += the counts (of more than `most` keys no more were kept), stats[1] += *again
+__global__ __launch_bounds__(256) void note_counts_kernel(const uint32_t *counts, int n, int pitch, uint32_t most, const uint32_t *again, unsigned long long *stats) {
+    unsigned long long sum = 0;
+    for (int i = threadIdx.x; i < n; i += 256) sum += counts[(size_t)i * pitch] < most ? counts[(size_t)i * pitch] : most;
+    if (sum != 0) atomicAdd(stats, sum);
+    if (threadIdx.x == 0 && again != nullptr) stats[1] += *again;
 }
 
 // First bound of the integer scan: one block per SEED_QPB queries adds up the 8-bit table entries of the
@@ -2224,7 +2232,7 @@ static void note_scan(pq_ctx *ctx, int kind, int qb, int passes, const unsigned 
     ctx->stat_parked = parked;
     ctx->stat_ncand = ncand;
     ctx->stat_ncand_len = ncand_len;
-    ctx->stat_again = nullptr;
+    ctx->stat_onehot = nullptr;
 }
 
 static int qb_of_kind(int kind) {
@@ -2287,17 +2295,18 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
 }
 
 #if !PQ_TUNED_ITEMS_ONLY
-int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, const void *luts, int nq, int topk,
-                      void *out_val, int64_t *out_ids) {
+// (one of `nslices` calls that serve a batch)
+static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, const void *luts, int nq, int topk, void *out_val, int64_t *out_ids,
+                      int slice, int nslices) {
     int rc;
     const bool u4_m32 = kind == KIND_U4_M32, is_u4 = kind == KIND_U4_M16 || u4_m32;
     // Scans on the matrix cores (below) make a pass over the codes per 128 or 64 queries whatever their number: more queries than their lists
     // have room for in the memory that the other loops take are served one slice after the other.
-    if (is_u4 && nq > ONEHOT_SLICE && n >= (u4_m32 ? 1 << 16 : 1 << 17) && n >= 32 * (int64_t)topk && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0 && !ctx->ws_fixed) {
+    if (is_u4 && nslices == 1 && nq > ONEHOT_SLICE && n >= (u4_m32 ? 1 << 16 : 1 << 17) && n >= 32 * (int64_t)topk && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0 && !ctx->ws_fixed) {
         for (int q0 = 0; q0 < nq; q0 += ONEHOT_SLICE) {
             const int nqs = nq - q0 < ONEHOT_SLICE ? nq - q0 : ONEHOT_SLICE;
-            rc = launch_scan_tuned(ctx, kind, codes, n, (const uint8_t *)luts + (size_t)q0 * (u4_m32 ? 512 : 256), nqs, topk,
-                                   (uint32_t *)out_val + (size_t)q0 * topk, out_ids + (size_t)q0 * topk);
+            rc = scan_slice(ctx, kind, codes, n, (const uint8_t *)luts + (size_t)q0 * (u4_m32 ? 512 : 256), nqs, topk,
+                            (uint32_t *)out_val + (size_t)q0 * topk, out_ids + (size_t)q0 * topk, q0 / ONEHOT_SLICE, (nq + ONEHOT_SLICE - 1) / ONEHOT_SLICE);
             if (rc) return rc;
         }
         return PQ_OK;
@@ -2575,7 +2584,7 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         uint32_t *seed_hist_u4 = wide_seed_u4 ? (uint32_t *)(ws + off_seedhist) : nullptr;
         tuned_init_kernel<<<1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, ntau,
                                                          is_u4 ? 0x7fffu : 0xff800000u, a.hist, L.nhist, tau0, nq, seed_hist_u4, wide_seed_u4 ? (size_t)nq * 4096 : 0,
-                                                         (uint32_t *)a.scratch, onehot ? onehot_words : 0);
+                                                         (uint32_t *)a.scratch, onehot ? onehot_words : 0, ctx->profiling && slice > 0);
         PQ_HIP(ctx, hipGetLastError());
     }
     if (seed_u4) {
@@ -2617,8 +2626,10 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     }
     if (ctx->profiling) {
         a.stats = (unsigned long long *)(ws + 8);
-        note_scan(ctx, kind, qb, ngroups, a.stats, a.ncand, ntau);
-        PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, ctx->stream));
+        if (slice == 0) {
+            note_scan(ctx, kind, qb, ngroups, a.stats, a.ncand, ntau);
+            PQ_HIP(ctx, hipEventRecord(ctx->ev_begin, ctx->stream));
+        }
     }
     if (onehot) {
         uint64_t *const lists = (uint64_t *)((uint8_t *)a.scratch + onehot_state);
@@ -2627,22 +2638,31 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
                                 (uint32_t)onehot_cap, cnt + (size_t)nq * COUNT_PITCH, a.work_counter, a.stats);
         if (rc) return rc;
         if (ctx->profiling) {
-            const int width = onehot_queries_per_pass(cb, nq);
-            note_plain_scan(ctx, "scan_onehot_kernel (packed 4-bit codes on the matrix cores, 6-bit lower bounds; with its sample)", width, (nq + width - 1) / width);
+            const int width = onehot_queries_per_pass(cb, nq), passes = (nq + width - 1) / width;
+            if (slice == 0) note_plain_scan(ctx, "", width, 0);
+            ctx->last_scan_passes += passes;
+            snprintf(ctx->last_scan_name, sizeof(ctx->last_scan_name), "scan_onehot_kernel (packed 4-bit codes on the matrix cores, 6-bit lower bounds; with its sample%s)",
+                     nslices > 1 ? "; slices of queries, with the merges between them" : "");
             ctx->stat_parked = a.stats;
-            ctx->stat_ncand = cnt;
-            ctx->stat_ncand_len = nq * COUNT_PITCH;   // (zeros between the counts)
-            ctx->stat_again = a.work_counter + ONEHOT_AGAIN;
-            PQ_HIP(ctx, hipEventRecord(ctx->ev_end, ctx->stream));
-            ctx->ev_valid = 1;
+            ctx->stat_onehot = a.stats + 12;
+            if (nslices == 1) PQ_HIP(ctx, hipEventRecord(ctx->ev_end, ctx->stream));
+            note_counts_kernel<<<1, 256, 0, ctx->stream>>>(cnt, nq, COUNT_PITCH, (uint32_t)onehot_cap, nullptr, a.stats + 12);   // (the scan below writes where the counts are)
+            PQ_HIP(ctx, hipGetLastError());
         }
         AgainArgs again{a.work_counter + ONEHOT_AGAIN, (uint32_t *)(ws + off_again), a.work_counter, a.hist, a.tau_key, (int)nchunks, qb};
         rc = launch_merge_counted(ctx, lists, cnt, (uint32_t)onehot_cap, again, nq, topk, out_val, out_ids, exact_bins(cb));
         if (rc) return rc;
         // the queries whose list is too short or had no room for its keys once more, from the bounds found so far
         a.again_count = again.count; a.again_query = again.query;
+        if (ctx->profiling && nslices == 1) PQ_HIP(ctx, hipEventRecord(ctx->ev_again_begin, ctx->stream));
         rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
         if (rc) return rc;
+        if (ctx->profiling) {
+            PQ_HIP(ctx, hipEventRecord(nslices == 1 ? ctx->ev_again_end : ctx->ev_end, ctx->stream));
+            ctx->ev_valid = nslices == 1 ? 3 : 1;
+            note_counts_kernel<<<1, 256, 0, ctx->stream>>>(a.ncand, nq, 1, 0xffffffffu, again.count, a.stats + 12);
+            PQ_HIP(ctx, hipGetLastError());
+        }
         return launch_merge_again(ctx, a.partial, again, kpad, nq, topk, out_val, out_ids, exact_bins(cb));
     }
     rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
@@ -2653,6 +2673,11 @@ int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     }
     return launch_merge_filtered(ctx, a.partial, nullptr, (int)nchunks, ngroups, qb, a.tau_key, kpad, nq, topk, nullptr, is_u4,
                                  out_val, out_ids, a.hist, a.tau_ref, is_u4 ? exact_bins(cb) : HIST_BINS);
+}
+
+int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, const void *luts, int nq, int topk,
+                      void *out_val, int64_t *out_ids) {
+    return scan_slice(ctx, kind, codes, n, luts, nq, topk, out_val, out_ids, 0, 1);
 }
 
 #endif   // !PQ_TUNED_ITEMS_ONLY

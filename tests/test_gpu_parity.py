@@ -3,6 +3,8 @@
 Float distances: 1e-5 relative, top-k sets identical up to ties inside that band.
 Integer sums, quantised tables and ids: bit-exact.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -788,11 +790,16 @@ def run_on_matrix_cores(ctx, packed, qluts, topk, again):
     ctx.pq_set_profiling(True)
     try:
         run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
-        kernel = ctx.pq_last_scan_info()["kernel"]
+        info = ctx.pq_last_scan_info()
     finally:
         ctx.pq_set_profiling(False)
+    kernel, nq = info["kernel"], len(qluts)
     assert kernel.startswith("scan_onehot_kernel"), kernel
     assert kernel.endswith(f"; {again} queries again by the other loops") == (again > 0) and ("again" in kernel) == (again > 0), kernel
+    # every query's results are among the keys inserted, which are at most a full list (and, again, every code)
+    room = 16384 if topk <= 128 else 65536
+    assert nq * topk <= info["inserted_keys"] <= nq * room + again * len(packed)
+    assert info["passes"] == math.ceil(nq / info["queries_per_pass"])
 
 
 # With 32 tables a query whose sums all lie beyond the bins that are counted gets no bound, and so no list of its own: it alone is scanned
