@@ -150,7 +150,6 @@ enum { KIND_F32_M8 = 0, KIND_F32_M16 = 1, KIND_U4_M16 = 2, KIND_F32P_M8 = 3, KIN
 // and a bound that falls into it is none.
 constexpr int exact_bins(int tables) { return tables == 16 ? HIST_BINS - 1 : HIST_BINS; }   // (tables after merging: 8 or 16)
 constexpr int SEED_CODES_BATCH = 1 << 15;   // codes looked at for the first bound of a float scan of many query groups
-constexpr int ONEHOT_SLICE = 2048;             // queries of a scan on the matrix cores
 constexpr int ONEHOT_AGAIN = 48;               // word of the state: queries whose list of the scan on the matrix cores is too short or too long
 constexpr int SEED_CODES_STREAM = 1 << 16;  // codes looked at for the first bound when few groups share the GPU (<= PRUNE_MIN_N)
 constexpr int STREAM_GROUPS = 32;          // flat scans of fewer query groups fetch like streaming scans
@@ -2295,22 +2294,43 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
 }
 
 #if !PQ_TUNED_ITEMS_ONLY
+// Integer scans on the matrix cores (scan_onehot.hip) have a sample and a set-up of some 150 us to pay for, and are twice as fast per (code, query)
+// where the other loops serve 16 queries per pass, three times where they serve 8.  Time of the other loop over their own, encoded codes of
+// 0.1 to 25 M vectors, 16 to 1000 queries, top-10, -100 and -1000 (just above and below the lines; P: pairs, those of 32 tables counted twice):
+//   249 queries and more, P from 2^28 on          0.95 to 2.1   (300 000 codes, 400 queries, top-10 and -100: 0.84)
+//   the same, long results, 2^18 codes and more   1.4 to 2.9    (100 000 codes 0.9; short results 0.7 to 1.0)
+//   24 to 248 queries, P from 11 * 2^26 on        1.0 to 1.75   (3 M codes, 128 queries 0.81 to 0.93; 10 M, 64 1.05 to 1.3)
+//   16 to 248, long results, 2^23 codes, P 2^28   1.0 to 1.36   (3 M codes, 64 queries 0.98; 25 M, 8 queries 0.92)
+static bool onehot_pays(int64_t n, int nq, int topk, bool wide) {
+    const int64_t pairs = n * nq * (wide ? 2 : 1);
+    if (nq >= 249) return pairs >= (int64_t)1 << 28 || (topk > 128 && n >= 1 << 18);
+    return (nq >= 24 && pairs >= (int64_t)11 << 26) || (nq >= 16 && topk > 128 && n >= 1 << 23 && pairs >= (int64_t)1 << 28);
+}
+static bool onehot_serves(const pq_ctx *ctx, int64_t n, int nq, int topk, bool wide, const void *luts) {
+    const int option = opt_int(ctx, PQ_OPT_SCAN_ONEHOT, -1);
+    return option != 0 && n >= PRUNE_MIN_N && n >= 32 * (int64_t)topk && ((uintptr_t)luts & 15) == 0 && (option > 0 || onehot_pays(n, nq, topk, wide));
+}
+// keys that a query's list has room for at least
+static int onehot_least_room(int topk) { return topk <= 128 ? 8192 : 32768; }
+
+// Queries of one call: all, or equal parts of more queries than there is room for.  The lists of a scan on the matrix cores lie in the memory that the waves'
+// lists of the other loops take, whatever the number of queries, and it makes a pass over the codes per 128 or 64 of them.
+static int queries_per_slice(const pq_ctx *ctx, int kind, int64_t n, const void *luts, int nq, int topk) {
+    if ((kind != KIND_U4_M16 && kind != KIND_U4_M32) || ctx->ws_fixed || nq < 2 * 249) return nq;
+    const bool wide = kind == KIND_U4_M32;
+    const int blocks = opt_int(ctx, PQ_OPT_SCAN_BLOCKS, ctx->num_cu);
+    const size_t scratch = (size_t)(blocks < 1 ? 1 : blocks < ctx->num_cu ? blocks : ctx->num_cu) * TUNED_WAVES * (!wide && opt_int(ctx, PQ_OPT_SCAN_Q8, 1) != 0 ? 16 : 8) * 64 * (topk <= 128 ? E_SMALL : E_LARGE) * 8;
+    const int most = (int)(scratch / (onehot_least_room(topk) * 8 + COUNT_PITCH * 4 + onehot_tie_words(1) * 4 + 2));   // (2: the words end on a multiple of 256 bytes)
+    if (nq <= most || most < 249) return nq;
+    const int parts = (nq + most - 1) / most, each = (nq + parts - 1) / parts;
+    return each >= 249 && onehot_serves(ctx, n, nq - (parts - 1) * each, topk, wide, luts) ? each : nq;
+}
+
 // (one of `nslices` calls that serve a batch)
 static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, const void *luts, int nq, int topk, void *out_val, int64_t *out_ids,
                       int slice, int nslices) {
     int rc;
     const bool u4_m32 = kind == KIND_U4_M32, is_u4 = kind == KIND_U4_M16 || u4_m32;
-    // Scans on the matrix cores (below) make a pass over the codes per 128 or 64 queries whatever their number: more queries than their lists
-    // have room for in the memory that the other loops take are served one slice after the other.
-    if (is_u4 && nslices == 1 && nq > ONEHOT_SLICE && n >= (u4_m32 ? 1 << 16 : 1 << 17) && n >= 32 * (int64_t)topk && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0 && !ctx->ws_fixed) {
-        for (int q0 = 0; q0 < nq; q0 += ONEHOT_SLICE) {
-            const int nqs = nq - q0 < ONEHOT_SLICE ? nq - q0 : ONEHOT_SLICE;
-            rc = scan_slice(ctx, kind, codes, n, (const uint8_t *)luts + (size_t)q0 * (u4_m32 ? 512 : 256), nqs, topk,
-                            (uint32_t *)out_val + (size_t)q0 * topk, out_ids + (size_t)q0 * topk, q0 / ONEHOT_SLICE, (nq + ONEHOT_SLICE - 1) / ONEHOT_SLICE);
-            if (rc) return rc;
-        }
-        return PQ_OK;
-    }
     // The 8 x 256 float scan prunes with 16-bit lower bounds when the database is large enough to
     // pay for the preparation (a bound per query from the first PRUNE_INIT codes, then the tables).
     // Smaller databases: the plain loop needs no tables prepared (10 us), and its first bound comes from 4096 codes in one launch; it
@@ -2431,20 +2451,7 @@ static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     int64_t onehot_cap = L.total - L.off_scratch > onehot_state ? (int64_t)((L.total - L.off_scratch - onehot_state) / ((size_t)nq * 8)) / 64 * 64 : 0;
     if (onehot_cap > (small ? 16384 : 65536)) onehot_cap = small ? 16384 : 65536;
     const int sample_shift = onehot_cap > 0 ? onehot_shift(n, cb, L.total - L.off_scratch - onehot_state) : 0;   // (and before them its sample)
-    // It has a sample and a set-up of some 150 us to pay for, and it is twice as fast per (code, query) where the other loops serve 16
-    // queries per pass, three times where they serve 8.  Time of the other loop over its own, encoded codes of 0.1 to 25 M vectors, 16 to
-    // 1000 queries, top-10, -100 and -1000 (just above and below the lines; P: pairs, those of 32 tables counted twice):
-    //   249 queries and more, P from 2^28 on          0.95 to 2.1   (300 000 codes, 400 queries, top-10 and -100: 0.84)
-    //   the same, long results, 2^18 codes and more   1.4 to 2.9    (100 000 codes 0.9; short results 0.7 to 1.0)
-    //   24 to 248 queries, P from 11 * 2^26 on        1.0 to 1.75   (3 M codes, 128 queries 0.81 to 0.93; 10 M, 64 1.05 to 1.3)
-    //   16 to 248, long results, 2^23 codes, P 2^28   1.0 to 1.36   (3 M codes, 64 queries 0.98; 25 M, 8 queries 0.92)
-    const int64_t onehot_pairs = pairs * (cb / 8);
-    bool onehot = false;
-    if (is_u4 && n >= PRUNE_MIN_N && n >= 32 * (int64_t)topk && sample_shift > 0 && onehot_cap >= (small ? 8192 : 32768) && ((uintptr_t)luts & 15) == 0 && opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 1) != 0) {
-        if (opt_int(ctx, PQ_OPT_SCAN_ONEHOT, 0) > 0) onehot = true;
-        else if (nq >= 249) onehot = onehot_pairs >= (int64_t)1 << 28 || (!small && n >= 1 << 18);
-        else onehot = (nq >= 24 && onehot_pairs >= (int64_t)11 << 26) || (nq >= 16 && !small && n >= 1 << 23 && onehot_pairs >= (int64_t)1 << 28);
-    }
+    bool onehot = is_u4 && onehot_serves(ctx, n, nq, topk, u4_m32, luts) && sample_shift > 0 && onehot_cap >= onehot_least_room(topk);
     const size_t partial_bytes = align_up((size_t)nitems * qb * kpad * 8, 256), off_again = align_up(L.total, 256);
     if (onehot && ctx->ws_fixed && align_up(off_again + (size_t)nq * 4, 256) + partial_bytes > ctx->ws_bytes) onehot = false;
     const size_t off_partial = onehot ? align_up(off_again + (size_t)nq * 4, 256) : off_again;
@@ -2677,7 +2684,17 @@ static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
 
 int launch_scan_tuned(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, const void *luts, int nq, int topk,
                       void *out_val, int64_t *out_ids) {
-    return scan_slice(ctx, kind, codes, n, luts, nq, topk, out_val, out_ids, 0, 1);
+    const int each = queries_per_slice(ctx, kind, n, luts, nq, topk);
+    const int nslices = each > 0 ? (nq + each - 1) / each : 1;
+    for (int i = 0; i < nslices; ++i) {
+        const size_t q0 = (size_t)i * each;
+        const int nqs = nq - (int)q0 < each ? nq - (int)q0 : each;
+        // (values of all kinds have 32 bits; more than one slice: tables of 4-bit codes only)
+        const int rc = scan_slice(ctx, kind, codes, n, (const uint8_t *)luts + q0 * (kind == KIND_U4_M32 ? 512 : 256), nqs, topk,
+                                  (uint32_t *)out_val + q0 * topk, out_ids + q0 * topk, i, nslices);
+        if (rc) return rc;
+    }
+    return PQ_OK;
 }
 
 #endif   // !PQ_TUNED_ITEMS_ONLY

@@ -760,13 +760,6 @@ def test_scan_u4_on_matrix_cores_sizes(ctx, opts, m, n, nq, topk):
     run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
 
 
-def test_scan_u4_on_matrix_cores_in_slices_of_queries(ctx):
-    r = np.random.default_rng(77)
-    packed = r.integers(0, 256, (131_072, 8), dtype=np.uint8)
-    qluts = np.minimum(255, r.standard_normal((2050, 16, 16)) ** 2 * 40).astype(np.uint8)
-    run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, 3)
-
-
 @pytest.mark.parametrize("m", [16, 32])
 @pytest.mark.parametrize("order", ["copies", "ascending", "descending"])
 def test_scan_u4_on_matrix_cores_misleading_samples(ctx, opts, m, order):
@@ -785,7 +778,7 @@ def test_scan_u4_on_matrix_cores_misleading_samples(ctx, opts, m, order):
     run_int_scan(ctx, np.ascontiguousarray(packed), orc.CODES_U4_PACKED, qluts, 100)
 
 
-def run_on_matrix_cores(ctx, packed, qluts, topk, again):
+def run_on_matrix_cores(ctx, packed, qluts, topk, again, passes=None):
     """run_int_scan of a call that takes the matrix cores and scans `again` of its queries once more."""
     ctx.pq_set_profiling(True)
     try:
@@ -799,7 +792,7 @@ def run_on_matrix_cores(ctx, packed, qluts, topk, again):
     # every query's results are among the keys inserted, which are at most a full list (and, again, every code)
     room = 16384 if topk <= 128 else 65536
     assert nq * topk <= info["inserted_keys"] <= nq * room + again * len(packed)
-    assert info["passes"] == math.ceil(nq / info["queries_per_pass"])
+    assert info["passes"] == (passes or math.ceil(nq / info["queries_per_pass"]))
 
 
 # With 32 tables a query whose sums all lie beyond the bins that are counted gets no bound, and so no list of its own: it alone is scanned
@@ -876,6 +869,37 @@ def test_scan_u4_on_matrix_cores_equal_codes_side_by_side(ctx, opts, m, nq, topk
         qluts[::2, 0, code[0]] = 1
         packed[:, 0] = np.where((packed[:, 0] & 15) == (code[0] + 1) % 16, packed[:, 0] & 0xf0 | code[0], packed[:, 0])
     run_on_matrix_cores(ctx, packed, qluts, topk, 0)
+
+
+# More queries than their lists have room for: equal slices of them, all of which take the matrix cores (32 tables: room for half as many).
+@pytest.mark.parametrize("m,n,nq,topk,passes", [(16, 65_600, 3000, 3, 2 * 12), (32, 65_536, 1501, 100, 2 * 12), (32, 65_536, 2100, 130, 2 * 17)])
+def test_scan_u4_on_matrix_cores_in_slices_of_queries(ctx, opts, m, n, nq, topk, passes):
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(77 + nq)
+    packed = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
+    qluts = np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * 20).astype(np.uint8)
+    if m == 32:
+        qluts[700], qluts[-1] = 255, 255          # (no bound: scanned again, one of each slice)
+    run_on_matrix_cores(ctx, packed, qluts, topk, 2 if m == 32 else 0, passes)
+
+
+def test_scan_u4_batches_that_the_matrix_cores_do_not_serve_stay_whole(ctx, opts):
+    """Tables that are not on 16 bytes: the other loops take the batch in one go, whatever its size."""
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(5)
+    n, nq = 65_600, 3000
+    packed = r.integers(0, 256, (n, 8), dtype=np.uint8)
+    qluts = np.minimum(255, r.standard_normal((nq, 16, 16)) ** 2 * 20).astype(np.uint8)
+    moved = torch.empty(qluts.size + 4, dtype=torch.uint8, device="cuda")[4:].view(nq, 16, 16)
+    moved.copy_(dev(qluts))
+    ctx.pq_set_profiling(True)
+    try:
+        s, i = ctx.pq_adc_scan_topk(dev(packed), orc.CODES_U4_PACKED, moved, 3)
+        info = ctx.pq_last_scan_info()
+    finally:
+        ctx.pq_set_profiling(False)
+    check_exact_topk(host(s), host(i), *orc.adc_scan_topk_u8(packed, orc.CODES_U4_PACKED, qluts, 3))
+    assert info["kernel"].startswith("scan_tuned_kernel<U4Q_M16") and info["passes"] == math.ceil(nq / 16), info
 
 
 # --------------------------------------------- 8x8 float scan, 8-bit lower bounds, 16 queries per pass
