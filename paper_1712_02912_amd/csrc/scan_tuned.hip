@@ -2295,16 +2295,25 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
 
 #if !PQ_TUNED_ITEMS_ONLY
 // Integer scans on the matrix cores (scan_onehot.hip) have a sample and a set-up of some 150 us to pay for, and are twice as fast per (code, query)
-// where the other loops serve 16 queries per pass, three times where they serve 8.  Time of the other loop over their own, encoded codes of
-// 0.1 to 25 M vectors, 16 to 1000 queries, top-10, -100 and -1000 (just above and below the lines; P: pairs, those of 32 tables counted twice):
-//   249 queries and more, P from 2^28 on          0.95 to 2.1   (300 000 codes, 400 queries, top-10 and -100: 0.84)
-//   the same, long results, 2^18 codes and more   1.4 to 2.9    (100 000 codes 0.9; short results 0.7 to 1.0)
-//   24 to 248 queries, P from 11 * 2^26 on        1.0 to 1.75   (3 M codes, 128 queries 0.81 to 0.93; 10 M, 64 1.05 to 1.3)
-//   16 to 248, long results, 2^23 codes, P 2^28   1.0 to 1.36   (3 M codes, 64 queries 0.98; 25 M, 8 queries 0.92)
+// where the other loops serve 16 queries per pass, three times where they serve 8; long results cost the other loops more, short ones
+// less.  Time of the other loop over theirs, 4990 calls over encoded codes in no order, 65 536 to 25 M (9 M with 32 tables), 16 to 2000
+// queries, top-1 to top-1024; served there are 2085 of them (P: pairs, those of 32 tables counted twice):
+//   249 queries and more, P from 2^28 on      16 tables 0.99 to 2.4, mean 1.58 (top-1 to -32 of 262 144 codes and fewer 0.84 to 1.03)
+//                                             32 tables 0.96 to 2.8, 1.66 (top-1 to -32 of fewer codes or pairs 0.82 to 1.08)
+//   the same, fewer pairs, long results       16 tables 0.98 to 1.9, 1.33 (top-129 to -300 of up to 700 000 codes 0.77 to 1.02)
+//                                             32 tables 1.02 to 2.9, 1.83
+//   16 to 248 queries                         16 tables 0.98 to 2.8, 1.55 (top-1000, 16 queries, 25 M codes 0.88; 180, 4 M 0.92)
+//                                             32 tables 0.98 to 1.7, 1.30 (48 queries, top-10 to -200, 8 M codes 0.80 to 0.94)
 static bool onehot_pays(int64_t n, int nq, int topk, bool wide) {
-    const int64_t pairs = n * nq * (wide ? 2 : 1);
-    if (nq >= 249) return pairs >= (int64_t)1 << 28 || (topk > 128 && n >= 1 << 18);
-    return (nq >= 24 && pairs >= (int64_t)11 << 26) || (nq >= 16 && topk > 128 && n >= 1 << 23 && pairs >= (int64_t)1 << 28);
+    const int64_t pairs = n * nq * (wide ? 2 : 1), p26 = (int64_t)1 << 26;
+    if (nq >= 249) {
+        if (pairs < 4 * p26) return topk > 128 && n >= 1 << 18 && (wide || topk >= 480 || n >= 11 << 16);
+        if (topk >= 100) return true;
+        return wide && topk >= 32 ? n >= 5 << 15 : n >= 5 << 16 && (!wide || pairs >= 8 * p26 || (topk >= 10 && n >= 1 << 19));
+    }
+    const bool longest = topk >= 900 && !wide;
+    if (wide && nq > 32 && nq < 64) return topk >= 256 && n >= 1 << 23 && pairs >= 4 * p26;   // (a pass serves 64)
+    return (nq >= 24 && pairs >= (longest ? 15 : 11) * p26) || (nq >= (longest ? 24 : 16) && topk > 128 && n >= 1 << 23 && pairs >= 4 * p26);
 }
 static bool onehot_serves(const pq_ctx *ctx, int64_t n, int nq, int topk, bool wide, const void *luts) {
     const int option = opt_int(ctx, PQ_OPT_SCAN_ONEHOT, -1);
@@ -2323,7 +2332,10 @@ static int queries_per_slice(const pq_ctx *ctx, int kind, int64_t n, const void 
     const int most = (int)(scratch / (onehot_least_room(topk) * 8 + COUNT_PITCH * 4 + onehot_tie_words(1) * 4 + 2));   // (2: the words end on a multiple of 256 bytes)
     if (nq <= most || most < 249) return nq;
     const int parts = (nq + most - 1) / most, each = (nq + parts - 1) / parts;
-    return each >= 249 && onehot_serves(ctx, n, nq - (parts - 1) * each, topk, wide, luts) ? each : nq;
+    // (the other loops take a batch in one go: time of theirs over that of the slices, 1470 to 8000 queries, just above and below the lines: top-1 to -32 1 M codes
+    // 0.99 to 1.31, 740 000 codes 0.91 to 1.18; top-100, 16 tables 524 288 codes 1.06 to 1.13, 370 000 0.89 to 0.95; top-300 1.09 to 1.27; top-1000 1.1 to 2.7)
+    const bool pays = topk >= 900 || n >= (topk >= 300 || (topk >= 100 && !wide) ? 1 << 19 : 1 << 20) || opt_int(ctx, PQ_OPT_SCAN_ONEHOT, -1) > 0;
+    return pays && each >= 249 && onehot_serves(ctx, n, nq - (parts - 1) * each, topk, wide, luts) ? each : nq;
 }
 
 // (one of `nslices` calls that serve a batch)
