@@ -1253,20 +1253,22 @@ int launch_build_luts(pq_ctx *ctx, const float *queries, const float *codebooks,
     return PQ_OK;
 }
 
-// Index step of few queries: squared distances to all centroids by the plain definition, in double, rounded once.  Eight lanes
-// per centroid, every fourth dimension four at a time, up to QN queries side by side.  Bound by the latency of its loads for small
-// indexes and by reading the centroids for large ones; the tiles of 64 queries of build_luts_mfma_kernel are empty here, and each walks
+// Index step of few queries: squared distances to all centroids by the plain definition, in double, rounded once.  PARTS lanes
+// per centroid, four dimensions at a time each, up to QN queries side by side.  Bound by the latency of its loads for small
+// indexes (hence 32 lanes where 8 would be fewer blocks than compute units: 1024 lists of 960 dimensions, eight queries 73 -> 29 us, of 128 dimensions
+// 13.5 -> 5.9; the tiles 63 and 10)
+// and by reading the centroids for large ones; the tiles of 64 queries of build_luts_mfma_kernel are empty here, and each walks
 // its dimensions in eight dependent steps (one query, 1024 lists of 128 dimensions 13 -> 2.9 us).
-template <int QN>
+template <int QN, int PARTS>
 __global__ __launch_bounds__(256) void index_few_kernel(const float4 *__restrict__ queries, const float4 *__restrict__ cents, int nq, int d4, int k,
                                                         float *__restrict__ out) {
-    const int c = (int)blockIdx.x * 32 + (threadIdx.x >> 3), part = threadIdx.x & 7;
+    const int c = (int)blockIdx.x * (256 / PARTS) + (int)threadIdx.x / PARTS, part = threadIdx.x % PARTS;
     const float4 *const x = cents + (size_t)(c < k ? c : k - 1) * d4;
     double acc[QN];
 #pragma unroll
     for (int q = 0; q < QN; ++q) acc[q] = 0.0;
 #pragma unroll 4
-    for (int i = part; i < d4; i += 8) {
+    for (int i = part; i < d4; i += PARTS) {
         const float4 v = x[i];
 #pragma unroll
         for (int q = 0; q < QN; ++q) {
@@ -1279,7 +1281,7 @@ __global__ __launch_bounds__(256) void index_few_kernel(const float4 *__restrict
     for (int q = 0; q < QN; ++q) {
         double s = acc[q];
 #pragma unroll
-        for (int o = 1; o < 8; o <<= 1) s += __shfl_xor(s, o);
+        for (int o = 1; o < PARTS; o <<= 1) s += __shfl_xor(s, o);
         if (part == q && c < k && q < nq) out[(size_t)q * k + c] = (float)s;
     }
 }
@@ -1288,8 +1290,11 @@ bool index_few_usable(const float *queries, const float *cents, int nq, int d) {
     return nq >= 1 && nq <= 8 && d % 4 == 0 && (((uintptr_t)queries | (uintptr_t)cents) & 15) == 0;
 }
 int launch_index_few(pq_ctx *ctx, const float *queries, const float *cents, int nq, int d, int k, float *out) {
-    auto kernel = nq == 1 ? index_few_kernel<1> : nq == 2 ? index_few_kernel<2> : nq <= 4 ? index_few_kernel<4> : index_few_kernel<8>;
-    kernel<<<(k + 31) / 32, 256, 0, ctx->stream>>>((const float4 *)queries, (const float4 *)cents, nq, d / 4, k, out);
+    const bool wide = (k + 31) / 32 < ctx->num_cu;
+    auto kernel = wide ? (nq == 1 ? index_few_kernel<1, 32> : nq == 2 ? index_few_kernel<2, 32> : nq <= 4 ? index_few_kernel<4, 32> : index_few_kernel<8, 32>)
+                       : (nq == 1 ? index_few_kernel<1, 8> : nq == 2 ? index_few_kernel<2, 8> : nq <= 4 ? index_few_kernel<4, 8> : index_few_kernel<8, 8>);
+    const int per_block = wide ? 8 : 32;
+    kernel<<<(k + per_block - 1) / per_block, 256, 0, ctx->stream>>>((const float4 *)queries, (const float4 *)cents, nq, d / 4, k, out);
     PQ_HIP(ctx, hipGetLastError());
     return PQ_OK;
 }

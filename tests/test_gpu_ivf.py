@@ -82,6 +82,16 @@ def test_ivf_index_step_of_few_queries(ctx, nq, nlist, d):
     run_ivf(ctx, queries, coarse, offsets, codes, order, cb, min(nlist, 12), 10)
 
 
+# So many lists that eight lanes per centroid fill the chip (32 lanes below), one beside a block, and more dimensions than 32 lanes take at once.
+@pytest.mark.parametrize("nq", [1, 2, 4, 7])
+@pytest.mark.parametrize("nlist,d", [(8193, 40), (300, 200)])
+def test_ivf_index_step_of_few_queries_many_lists(ctx, nq, nlist, d):
+    mix, coarse, cb, codes, order, offsets = make_index(9000, d, 8, nlist, seed=nlist + nq)
+    queries = mix.sample(nq, 11)
+    queries[0] = coarse[nlist - 1]
+    run_ivf(ctx, queries, coarse, offsets, codes, order, cb, 12, 10)
+
+
 def test_ivf_all_lists_equals_flat_scan_of_residual_tables(ctx):
     """nprobe = nlist: every code is scanned once with the tables of its own list."""
     mix, coarse, cb, codes, order, offsets = make_index(8000, 64, 8, 16, seed=31)
