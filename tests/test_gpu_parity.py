@@ -746,38 +746,6 @@ def test_scan_u4_few_queries_large_database_wide_first_bound(ctx):
 
 
 # --------------------------------------------- packed 4-bit codes on the matrix cores
-# Sums are integers: results are bit-exact, ties by row.  Sizes around a load of codes (1024 bytes), the groups of 32 queries and the widths
-# of 32, 64 and 128 queries; tables of few values (ties by the thousand) beside ordinary ones, and queries whose codes all tie.
-@pytest.mark.parametrize("m", [16, 32])
-@pytest.mark.parametrize("n,nq,topk", [(65_536, 1, 1), (65_537, 31, 100), (66_001, 33, 129), (70_019, 65, 1000), (131_073, 129, 100), (65_664, 257, 10)])
-def test_scan_u4_on_matrix_cores_sizes(ctx, opts, m, n, nq, topk):
-    opts.set("scan_onehot", 1)
-    r = np.random.default_rng(n + nq + m)
-    packed = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
-    qluts = np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * r.uniform(5, 60, (nq, m, 1))).astype(np.uint8)
-    qluts[::3] //= 32
-    qluts[0] = 255 if nq > 1 else qluts[0]
-    run_int_scan(ctx, packed, orc.CODES_U4_PACKED, qluts, topk)
-
-
-@pytest.mark.parametrize("m", [16, 32])
-@pytest.mark.parametrize("order", ["copies", "ascending", "descending"])
-def test_scan_u4_on_matrix_cores_misleading_samples(ctx, opts, m, order):
-    """Few distinct codes, and codes sorted by their distance: lists that are too short or too long take the other way."""
-    opts.set("scan_onehot", 1)
-    r = np.random.default_rng(m)
-    qluts = np.repeat(r.integers(0, 256, (1, m, 16), dtype=np.uint8), 40, axis=0)
-    if order == "copies":
-        packed = r.integers(0, 256, (7, m // 2), dtype=np.uint8)[r.integers(0, 7, 150_001)]
-        qluts = r.integers(0, 256, (40, m, 16), dtype=np.uint8)
-    else:
-        packed = r.integers(0, 256, (150_001, m // 2), dtype=np.uint8)
-        nib = np.stack([packed & 15, packed >> 4], 2).reshape(len(packed), m)
-        sums = qluts[0][np.arange(m), nib].astype(np.int64).sum(1)
-        packed = packed[np.argsort(sums if order == "ascending" else -sums)]
-    run_int_scan(ctx, np.ascontiguousarray(packed), orc.CODES_U4_PACKED, qluts, 100)
-
-
 def run_on_matrix_cores(ctx, packed, qluts, topk, again, passes=None):
     """run_int_scan of a call that takes the matrix cores and scans `again` of its queries once more."""
     ctx.pq_set_profiling(True)
@@ -793,6 +761,48 @@ def run_on_matrix_cores(ctx, packed, qluts, topk, again, passes=None):
     room = 16384 if topk <= 128 else 65536
     assert nq * topk <= info["inserted_keys"] <= nq * room + again * len(packed)
     assert info["passes"] == (passes or math.ceil(nq / info["queries_per_pass"]))
+
+
+# Sums are integers: results are bit-exact, ties by row.  Sizes around a load of codes (1024 bytes), the groups of 32 queries and the widths
+# of 32, 64 and 128 queries; tables of few values (ties by the thousand) beside ordinary ones.
+@pytest.mark.parametrize("m", [16, 32])
+@pytest.mark.parametrize("n,nq,topk", [(65_536, 1, 1), (65_537, 31, 100), (66_001, 33, 129), (70_019, 65, 1000), (131_073, 129, 100), (65_664, 257, 10)])
+def test_scan_u4_on_matrix_cores_sizes(ctx, opts, m, n, nq, topk):
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(n + nq + m)
+    packed = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
+    qluts = np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * r.uniform(5, 60, (nq, m, 1))).astype(np.uint8)
+    qluts[::3] //= 32
+    run_on_matrix_cores(ctx, packed, qluts, topk, 0)
+
+
+@pytest.mark.parametrize("value", [0, 1, 255])
+def test_scan_u4_on_matrix_cores_constant_tables(ctx, opts, value):
+    """All codes tie: rows decide, within the sums that are counted."""
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(value)
+    packed = r.integers(0, 256, (131_073, 8), dtype=np.uint8)
+    qluts = r.integers(0, 256, (40, 16, 16), dtype=np.uint8)
+    qluts[::9] = value
+    run_on_matrix_cores(ctx, packed, qluts, 100, 0)
+
+
+@pytest.mark.parametrize("m", [16, 32])
+@pytest.mark.parametrize("order", ["copies", "ascending", "descending"])
+def test_scan_u4_on_matrix_cores_misleading_samples(ctx, opts, m, order):
+    """Few distinct codes, and codes sorted by their distance: the sample bounds them all the same."""
+    opts.set("scan_onehot", 1)
+    r = np.random.default_rng(m)
+    qluts = np.repeat(r.integers(0, 256, (1, m, 16), dtype=np.uint8), 40, axis=0)
+    if order == "copies":
+        packed = r.integers(0, 256, (7, m // 2), dtype=np.uint8)[r.integers(0, 7, 150_001)]
+        qluts = r.integers(0, 256, (40, m, 16), dtype=np.uint8)
+    else:
+        packed = r.integers(0, 256, (150_001, m // 2), dtype=np.uint8)
+        nib = np.stack([packed & 15, packed >> 4], 2).reshape(len(packed), m)
+        sums = qluts[0][np.arange(m), nib].astype(np.int64).sum(1)
+        packed = packed[np.argsort(sums if order == "ascending" else -sums)]
+    run_on_matrix_cores(ctx, np.ascontiguousarray(packed), qluts, 100, 0)
 
 
 # With 32 tables a query whose sums all lie beyond the bins that are counted gets no bound, and so no list of its own: it alone is scanned
@@ -1410,3 +1420,30 @@ def test_scan_f32_sums_that_are_no_numbers(ctx, m, n, nq, topk, kind):
         want_v, want_i = np.full(topk, np.inf, np.float32), np.full(topk, -1, np.int64)
         want_v[:len(order)], want_i[:len(order)] = sums[order], order
         assert np.array_equal(v[q], want_v) and np.array_equal(i[q], want_i), q
+
+
+@pytest.mark.parametrize("order", ["none", "sorted"])
+@pytest.mark.parametrize("topk", [100, 1000])
+def test_scan_u4_full_size_both_loops(ctx, opts, order, topk):
+    """Config 2's scan on the matrix cores (the default) and by the 16-query loop: the same keys for every query, also where equal
+    codes and neighbours are stored side by side."""
+    mix = datagen.sift_like()
+    cb = dev(datagen.sampled_codebooks(mix, 16, 16))
+    codes = torch.cat([ctx.pq_encode(mix.sample_device(1 << 20, 900 + i), cb, orc.CODES_U4_PACKED) for i in range(24)])
+    if order == "sorted":
+        codes = codes.view(torch.int64).view(-1).sort()[0].view(torch.uint8).view(-1, 8)
+    luts = ctx.pq_build_luts(dev(mix.sample(1000, datagen.SEED_QUERIES)), cb)
+    qluts, _, _ = ctx.pq_quantize_luts(luts, luts.amin(2).sum(1) * 1.5 + 1.0)
+    got = {}
+    for option, kernel in ((None, "scan_onehot_kernel"), (0, "scan_tuned_kernel<U4Q_M16")):
+        if option is not None:
+            opts.set("scan_onehot", option)
+        ctx.pq_set_profiling(True)
+        try:
+            got[kernel] = ctx.pq_adc_scan_topk(codes, orc.CODES_U4_PACKED, qluts, topk)
+            name = ctx.pq_last_scan_info()["kernel"]
+        finally:
+            ctx.pq_set_profiling(False)
+        assert name.startswith(kernel) and "again" not in name, name
+    (sa, ia), (sb, ib) = got.values()
+    assert torch.equal(sa, sb) and torch.equal(ia, ib)

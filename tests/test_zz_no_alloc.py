@@ -86,3 +86,23 @@ def test_noalloc_scan_rejects_what_does_not_fit():
     torch.cuda.synchronize()
     assert torch.equal(i, ri) and torch.equal(v, rv)
     ctx.close()
+
+
+@pytest.mark.parametrize("m,n,nq,topk", [(16, 250_001, 33, 128), (32, 131_075, 40, 10)])
+def test_noalloc_scan_on_matrix_cores(m, n, nq, topk):
+    """Scans on the matrix cores keep their lists, sample and counters within the fixed scratch."""
+    ctx = binding.Context(0)
+    ctx.pq_set_option("scan_onehot", 1)
+    r = np.random.default_rng(m)
+    packed = dev(r.integers(0, 256, (n, m // 2), dtype=np.uint8))
+    qluts = dev(np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * 30).astype(np.uint8))
+    qluts[3] = 255                  # 32 tables: scanned again by the other loops
+    rv, ri, v, i = both(ctx, packed, binding.CODES_U4_PACKED, qluts, topk)
+    assert np.array_equal(rv, v) and np.array_equal(ri, i)
+    ctx.pq_set_profiling(True)
+    out = (torch.empty((nq, topk), dtype=torch.int32, device="cuda"), torch.empty((nq, topk), dtype=torch.int64, device="cuda"))
+    ctx.pq_adc_scan_topk(packed, binding.CODES_U4_PACKED, qluts, topk, out=out, noalloc=True)
+    kernel = ctx.pq_last_scan_info()["kernel"]
+    assert kernel.startswith("scan_onehot_kernel") and ("again" in kernel) == (m == 32), kernel
+    assert np.array_equal(rv, out[0].cpu().numpy()) and np.array_equal(ri, out[1].cpu().numpy())
+    ctx.close()
