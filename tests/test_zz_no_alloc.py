@@ -1,5 +1,7 @@
 """The scan entry point that allocates nothing (fixed scratch array inside the library) against
 pq_adc_scan_topk, through the C ABI: two calls in a row, the second on a smaller input."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -97,6 +99,7 @@ def test_noalloc_scan_on_matrix_cores(m, n, nq, topk):
     packed = dev(r.integers(0, 256, (n, m // 2), dtype=np.uint8))
     qluts = dev(np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * 30).astype(np.uint8))
     qluts[3] = 255                  # 32 tables: scanned again by the other loops
+    gc.collect()                    # (tensors of earlier tests that the collector would free while the call's memory is counted)
     rv, ri, v, i = both(ctx, packed, binding.CODES_U4_PACKED, qluts, topk)
     assert np.array_equal(rv, v) and np.array_equal(ri, i)
     ctx.pq_set_profiling(True)
