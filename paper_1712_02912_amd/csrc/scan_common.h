@@ -106,10 +106,9 @@ struct TunedArgs {
     const uint4 *qtabs16;
     const float *prune_scale16;
     bool rotated;   // pruned flat scan: candidates are added up in the order of the plain loop (see scan_flush_pruned)
-    // integer scan of *again_count queries only, number again_query[slot] in slot `slot` (state by query, result lists by slot), in the chunks
-    // that all queries would take: a query whose bound is loose costs most at the start of a chunk (50 of 1000 queries without a bound, 32
-    // tables, 1 M codes, top-1000: 8.9 ms; in as many chunks as give every block an item 13.6)
-    const uint32_t *again_count, *again_query;
+    // Integer scan of listed queries only (item_tab == nullptr, nitems_dev != nullptr): *nitems_dev of them, number pair_out[slot] in slot `slot` (state
+    // by query, result lists by slot), in the chunks that all queries would take: a query whose bound is loose costs most at the start of a chunk (50 of
+    // 1000 queries without a bound, 32 tables, 1 M codes, top-1000: 8.9 ms; in as many chunks as give every block an item 13.6).
 };
 
 // Counters of queries that many waves add to lie 128 bytes apart: additions to one line are made one after the other, 8 ns each

@@ -18,7 +18,7 @@ __device__ __forceinline__ uint32_t onehot_sample_row(uint32_t i, int shift) {
     return (i << shift) | (x >> (32 - shift));
 }
 // shift of a sample that fits `room` bytes (0: none), and the rank in it that bounds the scan
-int onehot_shift(int64_t n, int code_bytes, size_t room);
+int onehot_shift(int64_t n, int code_bytes, int nq, int topk, size_t room);
 int onehot_rank(int shift, int topk);
 // The sample's codes side by side, and the queries' least sums, whose rows are the first to be counted (`ties` as below).
 int launch_onehot_sample(pq_ctx *ctx, const uint8_t *codes, int64_t n, int code_bytes, int shift, uint8_t *sample, const uint8_t *qluts, int nq, uint32_t *ties);

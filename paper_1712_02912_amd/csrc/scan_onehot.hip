@@ -20,10 +20,10 @@
 // or below it are one query in a million.  The sample has one row of every 2^shift, each in a place of its own, so that the results in it
 // are as many as of independent rows, or closer to mu, whatever the order that the rows are stored in.  (Every 2^shift-th load of 1024
 // bytes, as it was, is no such sample where neighbours lie together: 25 M codes in groups of 64 neighbours x 1000 queries, top-1000,
-// left hundreds of queries short lists.)  It is gathered first: half of the lines of memory are touched, 22 us for 25 M codes (16
-// if they are in the last cache).  Some 1.5 topk codes per query pass in the scan itself; their keys go to the query's list.  Queries whose
+// left hundreds of queries short lists.)  It is gathered first: a line of memory
+// per code, 12 us for 25 M codes (22 with twice as many).  Some 1.5 topk codes per query pass in the scan itself; their keys go to the query's list.  Queries whose
 // list has fewer than topk keys, or more than it has room for, are left to the other loops.  25 M codes x 1000 queries, top-1000, before and after:
-// in no order 2.64 and 2.61 ms, in groups of 64 neighbours 9.8 and 2.2, in the order of 8192 lists 11.3 and 2.9 (16-query loop 5.2, 3.9 and 8.0).
+// in no order 2.64 and 2.50 ms, in groups of 64 neighbours 9.8 and 2.1, in the order of 8192 lists 11.3 and 2.7 (16-query loop 5.2, 3.9 and 8.0).
 //
 // What bounds it: v_mfma_f32_32x32x64_f8f6f4 on these types forms 1024 sums of 16 tables in 4 instructions of 32 cycles, 19.6 T
 // sums/s at the nominal clock; under this load the device holds 13.3 T/s without any tests, 12.9 T/s with them in the shadow of the
@@ -146,8 +146,10 @@ __device__ __noinline__ void onehot_flush(lds_ptr<OnehotSmem<NB, G>> sm, int wav
             in[u] = i < qn && row[u] < ncodes;
             id[u] = SAMPLE ? onehot_sample_row(row0 + row[u], shift) : row0 + row[u];
             // (codes of the least sum that the tables allow: behind the bound's row nothing can qualify)
-            const unsigned long long bound = sm->key[q[u]];
-            in[u] = in[u] && !((uint32_t)(bound >> 32) == sm->off[q[u]] && id[u] > (uint32_t)bound);
+            if constexpr (!SAMPLE) {
+                const unsigned long long bound = sm->key[q[u]];
+                in[u] = in[u] && !((uint32_t)(bound >> 32) == sm->off[q[u]] && id[u] > (uint32_t)bound);
+            }
 #pragma unroll
             for (int x = 0; x < NB / 4; ++x) w[u][x] = 0u;
             if (in[u]) {
@@ -268,10 +270,6 @@ __device__ __forceinline__ OnehotCut onehot_bound(const uint32_t *hist, uint32_t
     if (below >= (uint32_t)topk) return {bin > 0 ? key - (1ull << 32) : key, 0u, -1};
     const uint32_t ties = __builtin_amdgcn_readfirstlane(hist[bin]), need = (uint32_t)topk - below;
     if (below + ties < 2u * (uint32_t)topk + 64u) return {key, 0u, -1};
-    if constexpr (!LAST) {   // a quarter of the sample: the whole will likely end at an earlier sum
-        const int likely = hist_threshold(hist, (topk + 3) / 4);
-        if (likely < bin && hist[likely] > most / 8) (void)onehot_tie_slot(tie_val, (uint32_t)likely);
-    }
     const OnehotCut by_sum = {key, LAST && ties > need && ties - need > most ? need : 0u, -1};
     const int slot = onehot_tie_slot(tie_val, (uint32_t)bin);
     if (slot < 0) return by_sum;
@@ -689,9 +687,11 @@ static int launch_passes(pq_ctx *ctx, OnehotArgs &a, const uint8_t *codes, int64
 
 int onehot_queries_per_pass(int code_bytes, int nq) { return nq <= 32 ? 32 : nq <= 64 || code_bytes == 16 ? 64 : 128; }
 
-// (a 32nd of 25 M codes costs the sample's passes 0.25 ms for 1000 queries and lets 1.9 topk codes through, a 16th 0.4 and 1.6; less where it has no room)
-int onehot_shift(int64_t n, int code_bytes, size_t room) {
-    int shift = n >= 1 << 23 ? 5 : n >= 1 << 21 ? 4 : 3;
+// A greater shift makes the sample's gathering and passes cheaper and lets more keys through: 25 M codes, 1000 queries, top-100 and -1000, ms with shift 4 2.35
+// and 2.74, 5 2.16 and 2.58, 6 2.08 and 2.48, 7 2.09 and 2.53; 8.4 M 0.96 and 1.32 with 5, 0.97 and 1.34 with 6; 256 queries, top-1000, 16 M 0.74 with 5, 0.80
+// with 6; 4 M 0.66 and 0.93 with 4, 0.67 and 0.92 with 5; 1 M 0.38 and 0.61 with 3, 0.37 and 0.57 with 4.  (More where it has no room.)
+int onehot_shift(int64_t n, int code_bytes, int nq, int topk, size_t room) {
+    int shift = n >= 3 << 22 && (topk <= 512 || nq >= 512) ? 6 : n >= 1 << 23 ? 5 : n >= 1 << 21 ? 4 : 3;
     while (shift <= 8 && (size_t)(n >> shift) * code_bytes > room) ++shift;
     return shift <= 8 ? shift : 0;
 }

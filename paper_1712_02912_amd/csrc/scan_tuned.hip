@@ -976,7 +976,7 @@ void scan_tuned_kernel(TunedArgs a) {
     int nitems = a.item_tab ? (int)*a.nitems_dev : a.nitems;
     [[maybe_unused]] int listed = 0;
     if constexpr (LISTED) {
-        listed = (int)*a.again_count;
+        listed = (int)*a.nitems_dev;
         nitems = a.nchunks * ((listed + QB - 1) / QB);
         if (nitems == 0) return;
     }
@@ -1040,7 +1040,7 @@ void scan_tuned_kernel(TunedArgs a) {
                 const int group = item % ngroups, chunk = item / ngroups;
                 int gq = group * QB + s;
                 if (gq < nq) {
-                    if constexpr (LISTED) gq = (int)a.again_query[gq];
+                    if constexpr (LISTED) gq = (int)a.pair_out[gq];
                     qid = gq;
                     lut = IS_U4 ? (const void *)((const uint8_t *)a.luts + (size_t)gq * (NT * 32))
                                 : (const void *)((const float *)a.luts + (size_t)gq * (NT * 256));
@@ -2138,7 +2138,7 @@ static int launch_kind(pq_ctx *ctx, const TunedArgs &a, int nblocks) {
     // 5 queries 54.5 -> 55.9 us)
     constexpr bool ROTATED = !PQ_TUNED_ITEMS_ONLY && DEPTH == 2 && (KIND == KIND_F32P_M16 || (E == E_LARGE && (KIND == KIND_F32P_M8 || KIND == KIND_F32Q_M8)));
     constexpr bool LISTED = !PQ_TUNED_ITEMS_ONLY && (KIND == KIND_U4_M16 || KIND == KIND_U4Q_M16 || KIND == KIND_U4_M32);
-    if (a.again_count != nullptr) {
+    if (a.item_tab == nullptr && a.nitems_dev != nullptr) {
         if constexpr (LISTED) scan_tuned_kernel<KIND, E, KPAD, DEPTH, false, true><<<nblocks, TUNED_THREADS, 0, ctx->stream>>>(a);
         else return fail(ctx, PQ_EINVAL, "scan: no kernel of this form serves listed queries");
     } else if (a.rotated) {
@@ -2271,7 +2271,6 @@ int launch_scan_items(pq_ctx *ctx, int kind, const float *pair_min, const float 
     a.qtabs = nullptr; a.prune_off = pair_off; a.prune_scale = pair_scale; a.pair_min = pair_min;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
     a.rotated = false;
-    a.again_count = nullptr; a.again_query = nullptr;
     // (a block per query at least clears its 4096 bins)
     tuned_init_kernel<<<nq < 64 ? 16 * nq : 1024, 256, 0, ctx->stream>>>(a.work_counter, a.tau_key, a.ncand, a.refresh_mark, a.tau_ref, nq,
                                                                          0xff800000u, a.hist, L.nhist, tau0, nq);
@@ -2462,7 +2461,7 @@ static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     const size_t onehot_words = (size_t)nq * COUNT_PITCH + onehot_tie_words(nq), onehot_state = align_up(onehot_words * 4, 256);
     int64_t onehot_cap = L.total - L.off_scratch > onehot_state ? (int64_t)((L.total - L.off_scratch - onehot_state) / ((size_t)nq * 8)) / 64 * 64 : 0;
     if (onehot_cap > (small ? 16384 : 65536)) onehot_cap = small ? 16384 : 65536;
-    const int sample_shift = onehot_cap > 0 ? onehot_shift(n, cb, L.total - L.off_scratch - onehot_state) : 0;   // (and before them its sample)
+    const int sample_shift = onehot_cap > 0 ? onehot_shift(n, cb, nq, topk, L.total - L.off_scratch - onehot_state) : 0;   // (and before them its sample)
     bool onehot = is_u4 && onehot_serves(ctx, n, nq, topk, u4_m32, luts) && sample_shift > 0 && onehot_cap >= onehot_least_room(topk);
     const size_t partial_bytes = align_up((size_t)nitems * qb * kpad * 8, 256), off_again = align_up(L.total, 256);
     if (onehot && ctx->ws_fixed && align_up(off_again + (size_t)nq * 4, 256) + partial_bytes > ctx->ws_bytes) onehot = false;
@@ -2543,7 +2542,6 @@ static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
     a.qtabs = nullptr; a.prune_off = nullptr; a.prune_scale = nullptr; a.pair_min = nullptr;
     a.qtabs16 = nullptr; a.prune_scale16 = nullptr;
     a.rotated = rotated;
-    a.again_count = nullptr; a.again_query = nullptr;
     float *tau0 = nullptr;
     if (prune) {
         tau0 = (float *)(ws + off_tau0);
@@ -2672,7 +2670,7 @@ static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
         rc = launch_merge_counted(ctx, lists, cnt, (uint32_t)onehot_cap, again, nq, topk, out_val, out_ids, exact_bins(cb));
         if (rc) return rc;
         // the queries whose list is too short or had no room for its keys once more, from the bounds found so far
-        a.again_count = again.count; a.again_query = again.query;
+        a.nitems_dev = again.count; a.pair_out = again.query;
         if (ctx->profiling && nslices == 1) PQ_HIP(ctx, hipEventRecord(ctx->ev_again_begin, ctx->stream));
         rc = launch_by_kind(ctx, kind, small, stream, a, nblocks);
         if (rc) return rc;
