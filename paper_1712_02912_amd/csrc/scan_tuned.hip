@@ -65,7 +65,9 @@ constexpr int RING_PERIOD = 256;  // and, if anything is parked, every this many
 // RING: ring entries per wave
 // WIDE16: room for a second set of tables (16-bit entries of 16 queries, 64 KB) beside the scan's own
 // STAGE: bytes of one query's 8-bit tables
-template <int RING, bool WIDE16 = false, int STAGE = 256>
+// (LISTED: a type of its own, and with it the out-of-line functions, for the scans of listed queries: with a second caller those of the plain
+// scans were compiled another way, and 25 M 16 x 4 codes, 8 queries, top-1000 scanned in 225 us, not 221)
+template <int RING, bool WIDE16 = false, int STAGE = 256, bool LISTED = false>
 struct __align__(16) TunedSmemT {
     uint4 lut[4096];
     uint4 lut16[WIDE16 ? 4096 : 1];   // entry (byte b, table j): two 16-byte halves at (b * 8 + j) * 2
@@ -961,7 +963,7 @@ void scan_tuned_kernel(TunedArgs a) {
     constexpr int CAP = 64 * E;
     typedef typename std::conditional<IS_U4, U32Val, F32Val>::type V;
     // ring: two tiles fit behind a ring that was not flushed
-    typedef TunedSmemT<RING_FLUSH + 64 * DEPTH, Q8, KIND == KIND_U4_M32 ? 512 : 256> SM;   // a group of sub-tiles fits behind a ring that was not flushed
+    typedef TunedSmemT<RING_FLUSH + 64 * DEPTH, Q8, KIND == KIND_U4_M32 ? 512 : 256, LISTED> SM;   // a group of sub-tiles fits behind a ring that was not flushed
     static_assert(TUNED_WAVES != 8 || sizeof(SM) <= 80 * 1024, "two blocks of 8 waves share the 160 KB of a CU");
     __shared__ SM sm;
     LDS_PTR(SM) smp = (LDS_PTR(SM))&sm;

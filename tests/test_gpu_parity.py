@@ -1447,3 +1447,32 @@ def test_scan_u4_full_size_both_loops(ctx, opts, order, topk):
         assert name.startswith(kernel) and "again" not in name, name
     (sa, ia), (sb, ib) = got.values()
     assert torch.equal(sa, sb) and torch.equal(ia, ib)
+
+
+@pytest.mark.parametrize("m", [16, 32])
+def test_scan_u4_on_matrix_cores_in_a_captured_graph(m):
+    """Every replay gives the results of the tables that it finds, those of queries that are scanned again (32 tables) among them."""
+    stream = torch.cuda.Stream()
+    g_ctx = binding.Context(0, stream)
+    g_ctx.pq_set_option("scan_onehot", 1)
+    r = np.random.default_rng(m)
+    n, nq, topk = 70_001, 40, 100
+    with torch.cuda.stream(stream):
+        packed_h = r.integers(0, 256, (n, m // 2), dtype=np.uint8)
+        packed, qluts = dev(packed_h), torch.zeros((nq, m, 16), dtype=torch.uint8, device="cuda")
+        g_ctx.pq_adc_scan_topk(packed, orc.CODES_U4_PACKED, qluts, topk)   # (the workspace)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            s, i = g_ctx.pq_adc_scan_topk(packed, orc.CODES_U4_PACKED, qluts, topk)
+        for turn in range(4):
+            tables = np.minimum(255, r.standard_normal((nq, m, 16)) ** 2 * r.uniform(5, 40, (nq, m, 1))).astype(np.uint8)
+            tables[::7 + turn] = 255
+            qluts.copy_(torch.from_numpy(tables))
+            graph.replay()
+            gs, gi = host(s), host(i)
+            check_exact_topk(gs, gi, *orc.adc_scan_topk_u8(packed_h, orc.CODES_U4_PACKED, tables, topk))
+            # eager work on the same workspace between the replays
+            es, ei = g_ctx.pq_adc_scan_topk(packed, orc.CODES_U4_PACKED, qluts[: 3 + turn].contiguous(), topk)
+            assert np.array_equal(host(es), gs[: 3 + turn]) and np.array_equal(host(ei), gi[: 3 + turn])
+    g_ctx.close()
