@@ -87,12 +87,16 @@ const char *pq_version(void);
  *                             where short lists have their kernel, else the latter)
  *   ivf_ws_gib (24)           workspace limit of ivf_adc_search in GiB (1 ... 128)
  *   ivf_block_waves (8)       16: inverted lists scanned by blocks of 16 waves
- *   scan_onehot               0: scans of packed 4-bit codes never on the matrix cores, 1: wherever they are served there (2^16 codes
- *                             and 32 per result); unset: where that pays
+ *   scan_onehot               0: scans of packed 4-bit codes never on the matrix cores, 1: wherever they are served there (2^16
+ *                             codes and 32 per result, tables on 16 bytes, and room for 8192 keys per query, 32 768 above
+ *                             top-128: batches of more queries than the scratch memory holds such lists for go in
+ *                             slices, calls that allocate nothing take the other loops then); unset: where that pays
  *   scan_wide_seed (1)        0: first bounds of flat scans of few queries from the small sample only
  *   ivf_short_max (12288)     inverted lists of fewer codes take the kernel for short lists (0: none)
  *   ivf_coarse_f32 (1)        0: Index step of ivf_adc_search from exact distances to every list (default: lists
- *                             ranked by matrix-core distances, the nearest measured exactly; same lists)
+ *                             ranked by matrix-core distances, the nearest measured exactly; same lists).  Without effect,
+ *                             like ivf_coarse_f16, for up to eight queries whose dimensions are a multiple of four, on
+ *                             16-byte addresses: those are measured exactly against every list
  *   ivf_coarse_f16 (1)        0: the ranking pass over all lists on the fp32 matrix cores (default: on the fp16 ones,
  *                             every operand as the sum of two halves: the accuracy of fp32, a third of the time)
  *   encode_split16 (1)        0: pq_encode measures every centroid in double (default: centroids of up to 64 dimensions per

@@ -2334,8 +2334,8 @@ static int queries_per_slice(const pq_ctx *ctx, int kind, int64_t n, const void 
     if (nq <= most || most < 249) return nq;
     const int parts = (nq + most - 1) / most, each = (nq + parts - 1) / parts;
     // (the other loops take a batch in one go: time of theirs over that of the slices, 1470 to 8000 queries, just above and below the lines: top-1 to -32 1 M codes
-    // 0.99 to 1.31, 740 000 codes 0.91 to 1.18; top-100, 16 tables 524 288 codes 1.06 to 1.13, 370 000 0.89 to 0.95; top-300 1.09 to 1.27; top-1000 1.1 to 2.7)
-    const bool pays = topk >= 900 || n >= (topk >= 300 || (topk >= 100 && !wide) ? 1 << 19 : 1 << 20) || opt_int(ctx, PQ_OPT_SCAN_ONEHOT, -1) > 0;
+    // 0.99 to 1.31 (32 tables, top-100 1.09 to 1.31), 740 000 codes 0.91 to 1.18; top-100, 16 tables 524 288 codes 1.06 to 1.13, 370 000 0.89 to 0.95; top-300 1.09 to 1.27; top-1000 1.1 to 2.7)
+    const bool pays = topk >= 900 || n >= (topk >= 300 || (topk >= 100 && !wide) ? 1 << 19 : 15 << 16) || opt_int(ctx, PQ_OPT_SCAN_ONEHOT, -1) > 0;
     return pays && each >= 249 && onehot_serves(ctx, n, nq - (parts - 1) * each, topk, wide, luts) ? each : nq;
 }
 

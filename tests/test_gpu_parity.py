@@ -898,7 +898,7 @@ def test_scan_u4_on_matrix_cores_in_slices_of_queries(ctx, opts, m, n, nq, topk,
     (16, 262_144, 249, 129, False), (16, 262_144, 249, 480, True), (16, 720_896, 249, 129, True), (16, 327_680, 1000, 1, True), (16, 262_144, 1100, 1, False),
     (16, 262_144, 1100, 100, True), (16, 1 << 20, 248, 100, False), (16, 1 << 23, 88, 100, True), (16, 1 << 23, 88, 1000, True), (16, 1 << 22, 180, 1000, False),
     (32, 262_144, 249, 129, True), (32, 262_144, 600, 31, False), (32, 262_144, 600, 32, True), (32, 1 << 23, 48, 100, False), (32, 1 << 23, 48, 300, True),
-    (32, 1 << 19, 1500, 100, False), (32, 1 << 20, 1500, 100, True), (16, 1 << 19, 3000, 99, False), (16, 1 << 19, 3000, 100, True)])
+    (32, 1 << 19, 1500, 100, False), (32, 983_040, 1500, 100, True), (16, 1 << 19, 3000, 99, False), (16, 1 << 19, 3000, 100, True)])
 def test_scan_u4_calls_that_take_the_matrix_cores(ctx, m, n, nq, topk, served):
     codes = datagen.random_codes_device(n, m // 2, seed=n + m)
     qluts = torch.randint(0, 40, (nq, m, 16), dtype=torch.uint8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(nq))
