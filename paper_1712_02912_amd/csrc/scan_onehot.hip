@@ -150,6 +150,15 @@ __device__ __noinline__ void onehot_flush(lds_ptr<OnehotSmem<NB, G>> sm, int wav
                 const unsigned long long bound = sm->key[q[u]];
                 in[u] = in[u] && !((uint32_t)(bound >> 32) == sm->off[q[u]] && id[u] > (uint32_t)bound);
             }
+        }
+        if constexpr (!SAMPLE) {   // (they come by the thousand where they are stored side by side: 4 M codes in the order of 8192 lists, top-100, 929 -> 736 us)
+            bool any = false;
+#pragma unroll
+            for (int u = 0; u < U; ++u) any = any || in[u];
+            if (__ballot(any) == 0ull) continue;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int x = 0; x < NB / 4; ++x) w[u][x] = 0u;
             if (in[u]) {
