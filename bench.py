@@ -64,16 +64,16 @@ def scan_roofline(n, code_bytes, lookups_per_code, kernel_ms, info, profile):
             "hbm_traffic_frac": (traffic / sec / 1e9 / HBM_PEAK_GBS) if traffic else None,
             "kernel": info["kernel"], "kernel_ms": kernel_ms, "queries_per_pass": info["queries_per_pass"],
             "passes_over_the_codes": passes, "algorithmic_bytes": alg,
-            "lds": {"bound": "lds", "achieved": lds_bytes / sec / 1e9, "peak": LDS_PEAK_GBS, "unit": "GB/s",
+            "lds": None if "scan_onehot" in info["kernel"] else {"bound": "lds", "achieved": lds_bytes / sec / 1e9, "peak": LDS_PEAK_GBS, "unit": "GB/s",
                     "frac": lds_bytes / sec / 1e9 / LDS_PEAK_GBS,
                     "note": "table lookups of the scan loop only: %d reads of 16 bytes per code and pass" % lookups_per_code},
             "note": "algorithmic bytes = code bytes x passes over the codes; when the codes fit the 256 MB Infinity Cache "
                     "(25 M codes = 200 MB) later passes are served from it and the HBM bytes really moved are `traffic`; "
-                    "what binds the many-query kernel is LDS reads and vector issue (see `lds`)"}
+                    "what binds the many-query kernel is LDS reads and vector issue (see `lds`), on the matrix cores their products"}
 
 
 def pruning_stats(info, n, nq, codes_per_lane=2):
-    lanes = float(info["passes"]) * n / codes_per_lane
+    lanes = float(n) * nq if "scan_onehot" in info["kernel"] else float(info["passes"]) * n / codes_per_lane   # (there: pairs)
     return {"parked_lanes": info["parked_lanes"], "share_of_lanes_parked": info["parked_lanes"] / lanes if lanes else None,
             "inserted_keys": info["inserted_keys"], "share_of_pairs_inserted": info["inserted_keys"] / (float(n) * nq)}
 

@@ -23,7 +23,7 @@ int pq_last_scan_kernel_ms(pq_ctx *ctx, float *ms);
  * queries_per_pass: queries one pass over a chunk of codes serves; passes: passes over the whole code
  * array the launch makes (= groups of queries; 0 for inverted lists, where it varies per list);
  * parked_lanes: lanes (16 code bytes each) whose lower bounds let at least one (code, query) pair through
- * to the insert path; inserted_keys: (code, query) pairs that passed every test and were appended to a
+ * to the insert path (scans on the matrix cores: such pairs); inserted_keys: (code, query) pairs that passed every test and were appended to a
  * candidate list, once more for queries that were scanned again, whose number ends the name (both 0 for kernels without these counters).  Any pointer may be NULL.  Valid until the
  * next call on the context. */
 int pq_last_scan_info(pq_ctx *ctx, char *name, size_t name_bytes, int *queries_per_pass, int *passes,
