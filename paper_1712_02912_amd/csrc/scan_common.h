@@ -107,9 +107,12 @@ struct TunedArgs {
     const float *prune_scale16;
     bool rotated;   // pruned flat scan: candidates are added up in the order of the plain loop (see scan_flush_pruned)
     // Integer scan of listed queries only (item_tab == nullptr, nitems_dev != nullptr): *nitems_dev of them, number pair_out[slot] in slot `slot` (state
-    // by query, result lists by slot), in the chunks that all queries would take: a query whose bound is loose costs most at the start of a chunk (50 of
-    // 1000 queries without a bound, 32 tables, 1 M codes, top-1000: 8.9 ms; in as many chunks as give every block an item 13.6).
+    // by query, result lists by slot), in the chunks that all queries would take and in groups of again_per_group queries.
 };
+// Queries per group of a scan of `count` listed queries: as many as a group takes, but where queries may have no bound at all (`spread`: 32 tables) as
+// few as make no more groups than all queries of the call would: such a query costs an item that scans for it more than the pass over the codes (50 of 1000
+// queries without a bound, 32 tables, 1 M codes, top-1000: 3.6 ms, in groups of eight 8.9, in as many chunks as give every block an item 13.6).
+__device__ __forceinline__ int again_per_group(int count, int qb, int most_groups, bool spread) { return spread ? (count + most_groups - 1) / most_groups : qb; }
 
 // Counters of queries that many waves add to lie 128 bytes apart: additions to one line are made one after the other, 8 ns each
 // (25 M codes, 1000 queries, 2300 keys each: 0.6 ms with the counters side by side).
@@ -130,7 +133,8 @@ struct AgainArgs {
     uint32_t *count, *query;
     uint32_t *work_counter, *hist;
     unsigned long long *tau_key;
-    int nchunks, qb;            // of that scan
+    int nchunks, qb, ngroups;   // of that scan
+    bool spread;                // (see again_per_group)
 };
 int launch_merge_counted(pq_ctx *ctx, const uint64_t *lists, const uint32_t *counts, uint32_t cap, const AgainArgs &again, int nq, int topk,
                          void *out_val, int64_t *out_ids, int hist_bins);

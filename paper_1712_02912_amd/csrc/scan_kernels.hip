@@ -537,12 +537,13 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
     __shared__ int s_count;
     constexpr bool COUNTED = MODE == MERGE_COUNTED;
     const int tid = threadIdx.x, slot = blockIdx.x;
-    int gq = slot;
+    int gq = slot, per = qb;   // (per: queries per group)
     if constexpr (MODE == MERGE_AGAIN) {
         const int count = (int)*again.count;
         if (slot >= count) return;
         gq = (int)again.query[slot];
-        ngroups = (count + qb - 1) / qb;
+        per = again_per_group(count, qb, again.ngroups, again.spread);
+        ngroups = (count + per - 1) / per;
     }
     // (with counts a query has one list of up to cap keys, read as if it were lists of 64)
     uint32_t listed = 0;
@@ -571,7 +572,7 @@ __global__ __launch_bounds__(1024) void merge_filtered_kernel(const uint64_t *__
     // memory round trips.  8 queries, 24 lists of up to 1024 keys each: 271 -> 79 us with the selections below.)
     auto list_ptr = [&](size_t l) {
         if constexpr (COUNTED) return partial + (size_t)gq * cap + l * 64;
-        const size_t list = qlist_off ? (size_t)qlist_off[gq] + l : (l * ngroups + slot / qb) * qb + slot % qb;
+        const size_t list = qlist_off ? (size_t)qlist_off[gq] + l : (l * ngroups + slot / per) * qb + slot % per;
         return partial + list * kpad;
     };
     constexpr int MLP = 4, REST = 5;

@@ -976,11 +976,12 @@ void scan_tuned_kernel(TunedArgs a) {
     uint64_t *wave_buf = block_scratch + (size_t)wave * QB * CAP;
 
     int nitems = a.item_tab ? (int)*a.nitems_dev : a.nitems;
-    [[maybe_unused]] int listed = 0;
+    [[maybe_unused]] int listed = 0, per = QB;   // (queries; per group)
     if constexpr (LISTED) {
         listed = (int)*a.nitems_dev;
-        nitems = a.nchunks * ((listed + QB - 1) / QB);
-        if (nitems == 0) return;
+        if (listed == 0) return;
+        per = again_per_group(listed, QB, a.ngroups, KIND == KIND_U4_M32);
+        nitems = a.nchunks * ((listed + per - 1) / per);
     }
     int gstep = 0;   // steps of this wave over all its items: paces the periodic bound refresh
     unsigned long long parked_total = 0;   // positions this wave has handed to the insert path (uniform; reported when profiling)
@@ -1038,10 +1039,10 @@ void scan_tuned_kernel(TunedArgs a) {
                     sm.nvalid = nslots;
                 }
             } else {
-                const int ngroups = LISTED ? (listed + QB - 1) / QB : a.ngroups, nq = LISTED ? listed : a.nq;
+                const int ngroups = LISTED ? (listed + per - 1) / per : a.ngroups, nq = LISTED ? listed : a.nq;
                 const int group = item % ngroups, chunk = item / ngroups;
-                int gq = group * QB + s;
-                if (gq < nq) {
+                int gq = LISTED ? group * per + s : group * QB + s;
+                if (gq < nq && (!LISTED || s < per)) {
                     if constexpr (LISTED) gq = (int)a.pair_out[gq];
                     qid = gq;
                     lut = IS_U4 ? (const void *)((const uint8_t *)a.luts + (size_t)gq * (NT * 32))
@@ -1064,7 +1065,8 @@ void scan_tuned_kernel(TunedArgs a) {
                     sm.ncodes = cend > cbeg ? (int)(cend - cbeg) : 0;
                     sm.skip = 0;
                     sm.group = group;
-                    sm.nvalid = nq - group * QB < QB ? nq - group * QB : QB;
+                    if constexpr (LISTED) sm.nvalid = nq - group * per < per ? nq - group * per : per;
+                    else sm.nvalid = nq - group * QB < QB ? nq - group * QB : QB;
                 }
             }
             const int sq = qid < 0 ? 0 : qid;
@@ -2668,7 +2670,7 @@ static int scan_slice(pq_ctx *ctx, int kind, const uint8_t *codes, int64_t n, co
             note_counts_kernel<<<1, 256, 0, ctx->stream>>>(cnt, nq, COUNT_PITCH, (uint32_t)onehot_cap, nullptr, a.stats + 12);   // (the scan below writes where the counts are)
             PQ_HIP(ctx, hipGetLastError());
         }
-        AgainArgs again{a.work_counter + ONEHOT_AGAIN, (uint32_t *)(ws + off_again), a.work_counter, a.hist, a.tau_key, (int)nchunks, qb};
+        AgainArgs again{a.work_counter + ONEHOT_AGAIN, (uint32_t *)(ws + off_again), a.work_counter, a.hist, a.tau_key, (int)nchunks, qb, ngroups, u4_m32};
         rc = launch_merge_counted(ctx, lists, cnt, (uint32_t)onehot_cap, again, nq, topk, out_val, out_ids, exact_bins(cb));
         if (rc) return rc;
         // the queries whose list is too short or had no room for its keys once more, from the bounds found so far
